@@ -21,6 +21,8 @@
 
 #include "alphacx.h"
 #include "kernels.hpp"
+#include "simplices.hpp"
+#include "emit.hpp"
 #include "measure.hpp"
 #include "sweep.hpp"
 #include "partition.hpp"
@@ -310,17 +312,23 @@ static T read_one(const T *d, hipStream_t s) {
     return h;
 }
 
-// Exact 64-bit sum of n int32 counts (synchronises the stream). The
-// counted-fill fallbacks check their totals with it before 32-bit scans.
+// Exact 64-bit sum of n int32 counts, to *out on the device (the counted
+// passes check their totals with it before 32-bit scans).
+static void sum_i64(const int *x, long long n, long long *out, hipStream_t s, Scope &sc) {
+    long long b = (n + BLOCK - 1) / BLOCK;
+    b = b < 1 ? 1 : (b > 1024 ? 1024 : b);
+    long long *part = sc.get<long long>(b);
+    k_sum_i64<<<(unsigned)b, BLOCK, 0, s>>>(x, n, part);
+    k_fold_i64<<<1, BLOCK, 0, s>>>(part, (int)b, out);
+    LAUNCH_CHECK();
+}
+
+// The same, read back (synchronises the stream).
 static long long total_i64(const int *x, long long n, hipStream_t s, Scope &sc) {
     if (n <= 0) return 0;
-    long long b = (n + BLOCK - 1) / BLOCK;
-    if (b > 1024) b = 1024;
-    long long *part = sc.get<long long>(b + 1);
-    k_sum_i64<<<(unsigned)b, BLOCK, 0, s>>>(x, n, part);
-    k_fold_i64<<<1, 1, 0, s>>>(part, (int)b, part + b);
-    LAUNCH_CHECK();
-    return read_one(part + b, s);
+    long long *t = sc.get<long long>(1);
+    sum_i64(x, n, t, s, sc);
+    return read_one(t, s);
 }
 
 static void check_total(long long t, const char *what) {
@@ -336,18 +344,13 @@ static long long isqrt_ceil(long long v) {
     return r;
 }
 
-// Candidate arrays of one call, used by the emit stage.
-struct Cands {
-    const int *up, *edge_i, *tri_k, *tri_e, *tet_t, *tet_l, *perm;
-};
-
 // Stable LSD radix sort of (key, payload) on bits [lo, hi) of key, 8 bits per
 // pass. key / pay are set to the buffers that hold the result (the inputs' or
 // scratch of the scope); *spare_key / *spare_pay (if given) to two other
 // buffers of n entries.
 template <class P>
 static void radix_sort(unsigned *&key, P *&pay, int n, int lo, int hi, hipStream_t s, Scope &sc,
-                       unsigned **spare_key = nullptr, P **spare_pay = nullptr, const int *live = nullptr) {
+                       unsigned **spare_key = nullptr, P **spare_pay = nullptr) {
     unsigned *k2 = sc.get<unsigned>(n > 0 ? n : 1);
     P *p2 = sc.get<P>(n > 0 ? n : 1);
     unsigned *kin = key, *kout = k2;
@@ -357,9 +360,9 @@ static void radix_sort(unsigned *&key, P *&pay, int n, int lo, int hi, hipStream
         int *hist = sc.get<int>((size_t)RS_BINS * tiles);
         int *totals = sc.get<int>(RS_BINS);
         for (int shift = lo; shift < hi; shift += RS_BITS) {
-            k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, shift, hist, tiles, live);
+            k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, shift, hist, tiles);
             k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
-            k_rs_scatter<P><<<tiles, RS_BLOCK, 0, s>>>(kin, pin, kout, pout, n, shift, hist, totals, tiles, live);
+            k_rs_scatter<P><<<tiles, RS_BLOCK, 0, s>>>(kin, pin, kout, pout, n, shift, hist, totals, tiles);
             LAUNCH_CHECK();
             std::swap(kin, kout);
             std::swap(pin, pout);
@@ -382,14 +385,13 @@ static int bits_for(long long n) {
     return b;
 }
 
-// Emit keys of dimension K - 1 for n balls and M candidates: rows are keyed
-// by their least input id (< n); a bucket is 2^shift ids, at most EK_KEYS,
-// at least 256 buckets where n allows (so that small inputs still spread over
+// Merge keys of dimension K - 1 for n balls and M rows: rows are keyed by
+// their least input id (< n); a bucket is 2^shift ids, at most EK_KEYS, at
+// least 256 buckets where n allows (so that small inputs still spread over
 // many blocks), and small enough that the expected largest bucket, 2^shift K
-// M / n rows, stays within 95% of what a block orders in LDS; dropped
-// candidates get `drop`, the first key of the bucket after those of every id,
-// which fits in `bits` key bits. The radix sort orders bits [shift, bits).
-// The pruning kernel that writes the keys and emit_dim take the same M.
+// M / n rows, stays within 95% of what a block orders in LDS; `drop` is the
+// first key of the bucket after those of every id, and keys up to it fit in
+// `bits` bits. The radix sort orders bits [shift, bits).
 struct EmitKeys {
     int bits, shift;
     unsigned drop;
@@ -407,25 +409,21 @@ static EmitKeys emit_keys(int n, long long M) {
 }
 
 // start[0..nb] of the ranges of key >> shift in m sorted keys (k_key_starts).
-static void key_starts(const unsigned *key, long long m, int shift, int nb, int *start, hipStream_t s,
-                       const int *live = nullptr) {
+static void key_starts(const unsigned *key, long long m, int shift, int nb, int *start, hipStream_t s) {
     const long long threads = m / KS_PT + 1;  // rows 0..m
-    k_key_starts<<<(unsigned)((threads + KS_BLOCK - 1) / KS_BLOCK), KS_BLOCK, 0, s>>>(key, (int)m, shift, nb, start,
-                                                                                    live);
+    k_key_starts<<<(unsigned)((threads + KS_BLOCK - 1) / KS_BLOCK), KS_BLOCK, 0, s>>>(key, (int)m, shift, nb, start);
     LAUNCH_CHECK();
 }
 
-// Emit dimension d = K - 1 from the candidates' keys (least input id; not
-// kept: the drop key) and payloads: a radix sort over the key bits above the
-// bucket (2^shift ids, emit_keys) makes each bucket contiguous, k_key_starts
-// finds the buckets' starts and k_emit_block orders each bucket and writes
-// its rows; up to EK_KEYS balls one block takes every row, unsorted. The
-// output arrays have room for all M candidates; the kept count goes to
-// *m_out on the device. live: the count is read on the device (at most M).
+// Merge of dimension d = K - 1 from the rows' keys (least input id) and
+// payloads: a radix sort over the key bits above the bucket (2^shift ids,
+// emit_keys) makes each bucket contiguous, k_key_starts finds the buckets'
+// starts and k_emit_block orders each bucket and writes its rows; up to
+// EK_KEYS balls one block takes every row, unsorted. The row count goes to
+// *m_out on the device. Sizes are copied (they are A^2 already).
 template <int K>
 static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double *size_in, int M, int n,
-                     hipStream_t s, Scope &sc, ac_complex *res, int d, int *m_out, bool to_A2 = true,
-                     const int *live = nullptr) {
+                     hipStream_t s, Scope &sc, ac_complex *res, int d, int *m_out) {
     typedef typename EmitPay<K>::type P;
     res->d_simp[d] = static_cast<int32_t *>(dev_alloc((size_t)(M > 0 ? M : 1) * K * sizeof(int32_t)));
     res->d_size[d] = static_cast<double *>(dev_alloc((size_t)(M > 0 ? M : 1) * sizeof(double)));
@@ -435,69 +433,30 @@ static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double
     }
     if (n <= EK_KEYS && M <= ek_rows<K>()) {
         // a few hundred balls: one block orders every row, no radix sort
-        k_emit_block<K><<<1, EK_BLOCK, 0, s>>>(key, pay, nullptr, EK_SHIFT, 1, nullptr, nullptr, size_in, to_A2 ? 1 : 0,
-                                              res->d_simp[d], res->d_size[d], m_out, n, M, live);
+        k_emit_block<K><<<1, EK_BLOCK, 0, s>>>(key, pay, nullptr, EK_SHIFT, 1, nullptr, nullptr, size_in,
+                                              res->d_simp[d], res->d_size[d], m_out, n, M);
         LAUNCH_CHECK();
         return;
     }
     const EmitKeys ek = emit_keys<K>(n, M);
     unsigned *gkey = nullptr;
     P *gpay = nullptr;
-    radix_sort<P>(key, pay, M, ek.shift, ek.bits, s, sc, &gkey, &gpay, live);
+    radix_sort<P>(key, pay, M, ek.shift, ek.bits, s, sc, &gkey, &gpay);
     const int nb = (int)(ek.drop >> ek.shift);
     int *start = sc.get<int>((size_t)nb + 1);
-    key_starts(key, M, ek.shift, nb, start, s, live);
+    key_starts(key, M, ek.shift, nb, start, s);
     LAUNCH_CHECK();
     k_emit_block<K><<<(unsigned)nb, EK_BLOCK, 0, s>>>(key, pay, start, ek.shift, nb, gkey, gpay, size_in,
-                                                     to_A2 ? 1 : 0, res->d_simp[d], res->d_size[d], m_out);
+                                                     res->d_simp[d], res->d_size[d], m_out);
     LAUNCH_CHECK();
 }
 
-// Second stream of the calling thread on the current device, with events for
-// its fork from and join into the caller's stream: the emit of triangles,
-// tetrahedra and vertices runs there beside the pruning kernels and the edge
-// emit. Non-blocking (no implicit order with the null stream), default
-// priority; created on first use and kept until the process ends.
-struct AuxStream {
-    hipStream_t s = nullptr;
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-};
-static AuxStream &aux_stream() {
-    thread_local std::map<int, AuxStream> per_dev;
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    AuxStream &a = per_dev[dev];
-    if (!a.s) {
-        HIP_TRY(hipStreamCreateWithFlags(&a.s, hipStreamNonBlocking));
-        // order between two streams of one device: a device-scope release
-        // suffices (no system-scope fence, no timing)
-        for (hipEvent_t &e : a.ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence));
-    }
-    return a;
-}
-
-// `to` waits for the work enqueued on `from` so far (through event e).
-static void stream_after(hipStream_t to, hipStream_t from, hipEvent_t e) {
-    HIP_TRY(hipEventRecord(e, from));
-    HIP_TRY(hipStreamWaitEvent(to, e, 0));
-}
-
-// Output order of every candidate of dimension K - 1 (for a sweep): the
-// rows sorted as emit_dim sorts them (rows_s) and each candidate's place in
-// that order (spos).
-template <int K>
-static void order_dim(int M, const Cands &cd, int n, hipStream_t s, Scope &sc, int *rows_s, int *spos) {
-    typedef typename OrderPay<K>::type P;
-    if (M == 0) return;
-    unsigned *key = sc.get<unsigned>(M);
-    P *pay = sc.get<P>(M);
-    k_order_keys<K><<<grid_for(M), BLOCK, 0, s>>>(M, cd.up, cd.edge_i, cd.tri_k, cd.tri_e, cd.tet_t, cd.tet_l, cd.perm,
-                                                  key, pay);
-    LAUNCH_CHECK();
-    radix_sort<P>(key, pay, M, bits_for((long long)n), s, sc);
-    k_order_rank<K><<<grid_for(M), BLOCK, 0, s>>>(key, pay, M, rows_s, spos);
-    LAUNCH_CHECK();
-}
+// Pairs of upper entries a build makes room for (25 bytes each); past it the
+// candidate triangles are counted first.
+constexpr long long PAIR_ROOM = 1LL << 28;
+// Bytes of output rows a build allocates for candidates that may not be kept
+// (see run_pipeline).
+constexpr long long OUT_ROOM = 64LL << 20;
 
 struct Options {
     int cell_mA = 0;
@@ -624,11 +583,11 @@ struct Fixed {
     std::vector<long long> cells;  // per molecule: grid cells
     PredParams pp{};
     int wmax = 0, slot = 0;
-    long long E = 0, T = 0, Q = 0;
-    bool two_pass = false;  // a stage needed the counted fill
+    long long E = 0, P = 0, T = 0, Q = 0;  // candidate edges, pairs, candidate triangles, kept tetrahedra
+    bool two_pass = false;  // a stage needed a counted pass
     // given to a fixed run (device arrays uploaded before it)
     long long ncell = 0;  // cells of all molecules' capacities
-    int E_cap = 1, T_cap = 1, Q_cap = 1;
+    int E_cap = 1, P_cap = 1, T_cap = 1, Q_cap = 1;
     const int2 *d_tiles = nullptr;
     const int *d_tile_first = nullptr;
     const Grid *d_tmpl = nullptr;       // recorded grids with each molecule's first cell
@@ -673,7 +632,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         return r;
     };
     ac_complex *res = nullptr;
-    hipStream_t s_aux = nullptr;  // the second stream, once work was put on it
     try {
         for (int k = 0; k < n_alpha; k++) rs[k] = new_result();
         res = rs[0];
@@ -725,6 +683,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         pp.bmax = 2.0 * (double)sgc;
         pp.gmax = 4.0 * (double)pp.sg2 + (double)wmax;
         pp.force_exact = o.force_exact;
+        pp.fast = pp.sg2 < (1LL << 25);
         if (fx && fx->learn) {
             fx->pp = pp;
             fx->wmax = wmax;
@@ -813,8 +772,16 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const long long nb_slab = (long long)BLOCK * slot;
         int *nslab = sc.get<int>((size_t)nbN * nb_slab + NBR_PAD);
         unsigned *upmask = sc.get<unsigned>(n);
-        int *nbtot = sc.get<int>(2 * (size_t)nbN);
-        int *nboff = sc.get<int>(nbN + 1), *uboff = sc.get<int>(nbN + 1);
+        const int nbs = (int)(nbN + 3) & ~3;
+        int *nbtot = sc.get<int>(3 * (size_t)nbs);
+        int *uoff = sc.get<int>(nbN), *poff = sc.get<int>(nbN);
+        // balls of a group: enough groups to fill the GPU, else as many balls as
+        // a block's steps serve well (fewer waits per ball)
+        const int gshift = n >= (1 << 18) ? 8 : (n >= (1 << 17) ? 7 : 6);
+        const int groups = ((n - 1) >> gshift) + 1;
+        unsigned char *eng = sc.get<unsigned char>(n);
+        int *pair_base = sc.get<int>((size_t)groups + 1);
+        const int *stop = fixed ? &cnt->stop : nullptr;  // kernels of a stopped recorded build return at once
         // the fast exact pair test applies when every scanned offset stays
         // below 26 A per axis, s_g^2 < 2^25 and alpha >= 0 (see k_neighbours)
         bool nb_fast = pp.aq >= 0 && pp.sg2 < (1LL << 25);
@@ -840,234 +807,208 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                                                                    nullptr, nullptr, nullptr, vgab, vert_min, cnt);
         LAUNCH_CHECK();
         tm.mark(ST_NBR_SCAN);
-        scan_i32(nbtot, nboff, nbN, s, sc, &cnt->Nn);
-        scan_i32(nbtot + nbN, uboff, nbN, s, sc, &cnt->E);
+        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbN, nbs, uoff, poff, cnt);
         LAUNCH_CHECK();
         Counters c0{};
         if (fixed) {
-            k_plan_guard<<<1, WAVE, 0, s>>>(cnt, 0, fx->E_cap);
+            k_plan_guard<<<1, WAVE, 0, s>>>(cnt, fx->E_cap, fx->P_cap);
             LAUNCH_CHECK();
             c0.E = fx->E_cap;
+            c0.P = fx->P_cap;
         } else {
             c0 = read_one(cnt, s);
         }
         if (c0.dup) throw HipError{AC_E_DUPLICATE, "two balls have equal quantised centres"};
         const bool nbr_two_pass = c0.overflow != 0;
-        if (fx && fx->learn) fx->two_pass |= nbr_two_pass;
-        if (!fixed && (nbr_two_pass || (long long)nbN * nb_slab >= (long long)INT_MAX)) {
-            // past this size the slab bound no longer keeps the total in 32 bits
-            check_total(total_i64(deg_n, n, s, sc), "neighbour entries");
-        }
+        int *pairs = nullptr;
         if (nbr_two_pass) {
-            scan_i32(deg_n, nbr_start, n, s, sc, &cnt->Nn);
-            scan_i32(deg_up, up_start, n, s, sc, &cnt->E);
+            // exact totals: neighbour entries, candidate edges, pairs
+            pairs = sc.get<int>(groups);
+            k_group_pairs<<<(groups + NWAVE - 1) / NWAVE, BLOCK, 0, s>>>(deg_up, n, gshift, groups, pairs, eng);
             LAUNCH_CHECK();
+            sum_i64(deg_n, n, &cnt->Nn, s, sc);
+            sum_i64(deg_up, n, &cnt->E, s, sc);
+            sum_i64(pairs, groups, &cnt->P, s, sc);
+            fill<int>(&cnt->overflow, 0, 1, s);
             c0 = read_one(cnt, s);
         }
-        const int E = c0.E, Nn = c0.Nn;
-        if (fx && fx->learn) fx->E = E;
-        const int *E_live = fixed ? &cnt->El : nullptr;  // fixed: the launches below read the count
+        check_total(c0.Nn, "neighbour entries");
+        check_total(c0.E, "candidate edges");
+        // room for every pair, or (too many pairs) the counted triangles
+        const bool counted = c0.P > PAIR_ROOM;
+        const int E = (int)c0.E;
+        const long long Nn = c0.Nn;
+        if (fx && fx->learn) {
+            fx->E = E;
+            fx->P = c0.P;
+            fx->two_pass |= nbr_two_pass || counted;
+        }
         // neighbour rows: in the slabs after the one-pass search, else in CSR
+        const size_t E1 = E > 0 ? E : 1;
         int *nbr = nbr_two_pass ? sc.get<int>((size_t)(Nn > 0 ? Nn : 1) + NBR_PAD) : nslab;
-        int *up = sc.get<int>(E > 0 ? E : 1);
-        int *edge_i = sc.get<int>(E > 0 ? E : 1);
+        int *up = sc.get<int>(E1), *up_id = sc.get<int>(E1), *edge_i = sc.get<int>(E1);
         tm.mark(ST_NBR_FILL);
         if (!nbr_two_pass) {
             if (slot == NB_SLOT_WIDE)
-                k_nbr_compact<NB_SLOT_WIDE><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uboff, nbr_start,
-                                                                 up_start, up, edge_i, fixed ? &cnt->stop : nullptr);
+                k_nbr_compact<NB_SLOT_WIDE><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uoff, poff, perm,
+                                                                 nbr_start, up_start, up, up_id, edge_i, pair_base, gshift,
+                                                                 eng, stop);
             else
-                k_nbr_compact<NB_SLOT><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uboff, nbr_start, up_start,
-                                                            up, edge_i, fixed ? &cnt->stop : nullptr);
-        } else if (nb_fast) {
-            k_neighbours<NB_FILL, NB_SLOT, true><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp,
-                                                                      nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                                      nbr_start, up_start, nbr, up, edge_i, vgab,
-                                                                      vert_min, cnt);
+                k_nbr_compact<NB_SLOT><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uoff, poff, perm, nbr_start,
+                                                            up_start, up, up_id, edge_i, pair_base, gshift, eng, stop);
+            LAUNCH_CHECK();
         } else {
-            k_neighbours<NB_FILL, NB_SLOT><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp, nullptr,
-                                                                nullptr, nullptr, nullptr, nullptr, nbr_start, up_start,
-                                                                nbr, up, edge_i, vgab, vert_min, cnt);
-        }
-        LAUNCH_CHECK();
-        const int *nbr_cnt = deg_n;
-        unsigned char *egab = sc.get<unsigned char>(E > 0 ? E : 1);
-        long long *edge_min = sc.get<long long>(E > 0 ? E : 1);
-        if (split && E > 0) {
-            tm.mark(ST_EDGE_AC2);
-            k_edge_ac2<<<grid_for(E), BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up, edge_i, E, pp, egab,
-                                                    edge_min);
+            scan_i32(deg_n, nbr_start, n, s, sc);
+            scan_i32(deg_up, up_start, n, s, sc);
+            if (!counted) scan_i32(pairs, pair_base, groups, s, sc);
+            int *up_scan = sc.get<int>(E1), *id_scan = sc.get<int>(E1);
+            if (nb_fast)
+                k_neighbours<NB_FILL, NB_SLOT, true><<<nbN, BLOCK, 0, s>>>(
+                    atom, perm, n, d_grids, n_mol, cell_start, pp, nullptr, nullptr, nullptr, nullptr, nullptr, nbr_start,
+                    up_start, nbr, up_scan, edge_i, vgab, vert_min, cnt);
+            else
+                k_neighbours<NB_FILL, NB_SLOT><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp, nullptr,
+                                                                    nullptr, nullptr, nullptr, nullptr, nbr_start,
+                                                                    up_start, nbr, up_scan, edge_i, vgab, vert_min, cnt);
+            k_up_ids<<<grid_for(E), BLOCK, 0, s>>>(up_scan, E, perm, id_scan);
+            k_up_rank<<<grid_for(E), BLOCK, 0, s>>>(up_scan, id_scan, E, edge_i, up_start, up, up_id);
             LAUNCH_CHECK();
         }
+        unsigned char *egab = sc.get<unsigned char>(E1);
+        long long *edge_min = sc.get<long long>(E1);
 
-        // ---- candidate triangles (with AC2 of the edges): one pass into
-        // per-block slabs, then compaction; two passes if a slab overflows ----
-        int *tri_cnt = sc.get<int>(E > 0 ? E : 1);
-        int *tri_start = sc.get<int>(E + 1);
-        const unsigned nbE = grid_for(E);
-        int *tslab = sc.get<int>((size_t)nbE * TRI_SLAB);
-        int *tbtot = sc.get<int>(nbE);
-        int *tboff = sc.get<int>(nbE + 1);
-        tm.mark(ST_TRI_COUNT);
-        fill<int>(&cnt->overflow, 0, 1, s);
+        // ---- AC2 of the candidate edges, candidate triangles of every group ----
+        Cands cd{};
+        cd.atom = atom;
+        cd.perm = perm;
+        cd.nbr_start = nbr_start;
+        cd.nbr_cnt = deg_n;
+        cd.nbr = nbr;
+        cd.up_start = up_start;
+        cd.up = up;
+        cd.up_id = up_id;
+        cd.edge_i = edge_i;
+        cd.tri_base = pair_base;
+        cd.tri_cnt = sc.get<int>(groups);
+        cd.n = n;
+        cd.gshift = gshift;
+        // the edge count on the device (a recorded build's launch is sized for its capacity)
+        const int *E_dev = up_start + n;
+        if (split) tm.mark(ST_EDGE_AC2); else tm.mark(ST_TRI_COUNT);
         if (E > 0) {
-            if (split)
-                k_triangles<TRI_ONEPASS, false><<<nbE, BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up,
-                                                                     edge_i, E, pp, tri_cnt, egab, edge_min, tslab,
-                                                                     tbtot, nullptr, nullptr, nullptr, cnt);
-            else
-                k_triangles<TRI_ONEPASS><<<nbE, BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i,
-                                                              E, pp, tri_cnt, egab, edge_min, tslab, tbtot, nullptr,
-                                                              nullptr, nullptr, cnt, E_live);
+            k_edge_ac2<<<grid_for(E), BLOCK, 0, s>>>(cd, E_dev, pp, egab, edge_min, eng, stop);
             LAUNCH_CHECK();
-            tm.mark(ST_TRI_SCAN);
-            scan_i32(tbtot, tboff, nbE, s, sc, &cnt->T);
+        }
+        if (split) tm.mark(ST_TRI_COUNT);
+        long long room = c0.P;
+        if (counted) {
+            k_triangles<true><<<groups, BLOCK, 0, s>>>(cd, pp, nullptr, cnt, stop);
             LAUNCH_CHECK();
-        } else {
-            tm.mark(ST_TRI_SCAN);
-            fill<int>(&cnt->T, 0, 1, s);
+            room = total_i64(cd.tri_cnt, groups, s, sc);
+            check_total(room, "candidate triangles");
+            scan_i32(cd.tri_cnt, pair_base, groups, s, sc);
         }
-        Counters ct{};
-        if (fixed) {
-            k_plan_guard<<<1, WAVE, 0, s>>>(cnt, 1, fx->T_cap);
-            LAUNCH_CHECK();
-            ct.T = fx->T_cap;
-        } else {
-            ct = read_one(cnt, s);
-        }
-        const bool tri_two_pass = ct.overflow != 0;
-        if (fx && fx->learn) fx->two_pass |= tri_two_pass;
-        if (!fixed && (tri_two_pass || (long long)nbE * TRI_SLAB >= (long long)INT_MAX)) {
-            // past this size the slab bound no longer keeps the total in 32 bits
-            check_total(total_i64(tri_cnt, E, s, sc), "candidate triangles");
-        }
-        if (tri_two_pass) {
-            scan_i32(tri_cnt, tri_start, E, s, sc, &cnt->T);
-            LAUNCH_CHECK();
-            ct = read_one(cnt, s);
-        }
-        const int T = ct.T;
-        if (fx && fx->learn) fx->T = T;
-        const int *T_live = fixed ? &cnt->Tl : nullptr;
-        int *tri_k = sc.get<int>(T > 0 ? T : 1);
-        int *tri_e = sc.get<int>(T > 0 ? T : 1);
-        unsigned char *tgab = sc.get<unsigned char>(T > 0 ? T : 1);
-        double *tsize = sc.get<double>(T > 0 ? T : 1);
-        long long *tri_min = sc.get<long long>(T > 0 ? T : 1);
-        int *tet_cnt = sc.get<int>(T > 0 ? T : 1);
-        int *tet_start = sc.get<int>(T + 1);
+        const size_t T1 = room > 0 ? (size_t)room : 1;
+        cd.tri_e = sc.get<int>(T1);
+        cd.tri_f = sc.get<int>(T1);
+        cd.tri_first = sc.get<int>(E1);
+        long long *tri_min = sc.get<long long>(T1);
+        unsigned char *tgab = sc.get<unsigned char>(T1);
+        double *tsize = sc.get<double>(T1);
+        k_triangles<false><<<groups, BLOCK, 0, s>>>(cd, pp, tri_min, cnt, stop);
+        LAUNCH_CHECK();
+        tm.mark(ST_TRI_SCAN);  // the triangles are in place: no scan, no fill
         tm.mark(ST_TRI_FILL);
-        if (fixed) fill<int>(tri_start, 0, 1, s);  // no edge at run time leaves tri_start[0] unwritten
-        if (E > 0 && !tri_two_pass) {
-            k_tri_compact<<<(nbE + TRI_CB - 1) / TRI_CB, BLOCK, 0, s>>>(tri_cnt, E, tslab, tboff, tri_start, tri_k,
-                                                                       tri_e, E_live);
-            LAUNCH_CHECK();
-        } else if (T > 0) {
-            k_triangles<TRI_FILL><<<nbE, BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i, E, pp,
-                                                       nullptr, nullptr, nullptr, nullptr, nullptr, tri_start, tri_k,
-                                                       tri_e, cnt);
-            LAUNCH_CHECK();
-        }
-        if (E == 0) fill<int>(tri_start, 0, 1, s);
-        // ---- AC2 of triangles and candidate tetrahedra: one pass into
-        // per-block slabs, then compaction; two passes if a slab overflows ----
-        const unsigned nbT = grid_for(T);
-        int *qslab = sc.get<int>((size_t)nbT * TET_SLAB);
-        int *qbtot = sc.get<int>(nbT);
-        int *qboff = sc.get<int>(nbT + 1);
-        if (split && T > 0) {
-            tm.mark(ST_TRI_AC2);
-            k_tri_ac2<<<grid_for(T), BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up, edge_i, tri_k, tri_e, T, pp,
-                                                   tgab, tsize, tri_min, cnt);
-            LAUNCH_CHECK();
-        }
-        tm.mark(ST_TRI_GABRIEL);
-        fill<int>(&cnt->overflow, 0, 1, s);
-        if (T > 0) {
-            if (split)
-                k_tet_candidates<TET_ONEPASS, false><<<nbT, BLOCK, 0, s>>>(
-                    atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i, tri_k, tri_e, T, pp, tgab, tsize, tri_min,
-                    tet_cnt, qslab, qbtot, nullptr, nullptr, nullptr, cnt);
-            else
-                k_tet_candidates<TET_ONEPASS><<<nbT, BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up,
-                                                                   edge_i, tri_k, tri_e, T, pp, tgab, tsize, tri_min,
-                                                                   tet_cnt, qslab, qbtot, nullptr, nullptr, nullptr, cnt,
-                                                                   T_live);
-            LAUNCH_CHECK();
-        }
-        tm.mark(ST_TET_COUNT);
-        if (T > 0) {
-            scan_i32(qbtot, qboff, nbT, s, sc, &cnt->Q);
-            LAUNCH_CHECK();
-        } else {
-            fill<int>(&cnt->Q, 0, 1, s);
-        }
-        Counters cq{};
-        if (fixed) {
-            k_plan_guard<<<1, WAVE, 0, s>>>(cnt, 2, fx->Q_cap);
-            LAUNCH_CHECK();
-            cq.Q = fx->Q_cap;
-        } else {
-            cq = read_one(cnt, s);
-        }
-        const bool tet_two_pass = cq.overflow != 0;
-        if (fx && fx->learn) fx->two_pass |= tet_two_pass;
-        if (tet_two_pass) {
-            check_total(total_i64(tet_cnt, T, s, sc), "candidate tetrahedra");
-            scan_i32(tet_cnt, tet_start, T, s, sc, &cnt->Q);
-            LAUNCH_CHECK();
-            cq = read_one(cnt, s);
-        }
-        const int Q = cq.Q;
-        if (fx && fx->learn) fx->Q = Q;
-        const int *Q_live = fixed ? &cnt->Ql : nullptr;
-        int *tet_t = sc.get<int>(Q > 0 ? Q : 1);
-        int *tet_l = sc.get<int>(Q > 0 ? Q : 1);
-        double *qsize = sc.get<double>(Q > 0 ? Q : 1);
-        tm.mark(ST_TET_FILL);
-        if (T > 0 && !tet_two_pass) {
-            k_tet_compact<<<nbT, BLOCK, 0, s>>>(tet_cnt, T, qslab, qboff, tet_t, tet_l, T_live);
-            LAUNCH_CHECK();
-        } else if (Q > 0) {
-            k_tet_candidates<TET_FILL><<<nbT, BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i,
-                                                            tri_k, tri_e, T, pp, nullptr, nullptr, nullptr, nullptr,
-                                                            nullptr, nullptr, tet_start, tet_t, tet_l, cnt);
-            LAUNCH_CHECK();
-        }
 
-        // ---- pruning: tetrahedra, then triangles, edges, vertices ----
-        int *tri_att = nullptr, *edge_att = nullptr, *vert_att = nullptr;  // sweep only
-        double *vsize_in = sc.get<double>(n);
-        int *vflag = sc.get<int>(n);
-        int *vpos = sc.get<int>(n + 1);
-        auto prune_init = [&]() {
-            const long long mx = std::max<long long>(std::max<long long>(T, E), n);
-            const long long nb = std::min<long long>((mx + BLOCK - 1) / BLOCK, 65536);
-            k_prune_init<<<(unsigned)nb, BLOCK, 0, s>>>(T, E, n, tri_att, tri_min, edge_att, edge_min, vert_att, vert_min);
+        // ---- AC2 of the triangles, candidate tetrahedra and Step 2.
+        // Kept tetrahedra are those of the regular triangulation, about 6.8 a
+        // ball at most where the radii are large, far fewer at alpha = 0 with
+        // van der Waals radii; a group past its slab is counted and run again
+        if (split) tm.mark(ST_TRI_AC2); else tm.mark(ST_TRI_GABRIEL);
+        // grown radii beyond the wide slots: some 170 candidate tetrahedra a
+        // ball, of which 6 are kept; each triangle's apex balls rule out the rest
+        const bool use_apex = pp.sgc > 2600;
+        int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
+        if (use_apex)
+            k_tri_ac2<true><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tsize, apex, cnt, stop);
+        else
+            k_tri_ac2<false><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tsize, apex, cnt, stop);
+        LAUNCH_CHECK();
+        Tets tt{};
+        tt.cap = (pp.sgc > 2000 ? 16 : 8) << gshift;
+        tt.num = sc.get<int>(groups);
+        tt.kept = sc.get<int>(groups);
+        tt.cand = sc.get<int>(groups);
+        auto tet_room = [&](size_t rows) {
+            if (rows < 1) rows = 1;
+            tt.t = sc.get<int>(rows);
+            tt.t2 = sc.get<int>(rows);
+            tt.size = sc.get<double>(rows);
+            if (n_alpha > 1) tt.face = sc.get<int4>(rows);
+        };
+        tet_room((size_t)groups * tt.cap);
+        auto tetrahedra = [&]() {
+            if (use_apex)
+                k_tetrahedra<true><<<groups, BLOCK, 0, s>>>(cd, pp, apex, tt, cnt, stop);
+            else
+                k_tetrahedra<false><<<groups, BLOCK, 0, s>>>(cd, pp, apex, tt, cnt, stop);
             LAUNCH_CHECK();
         };
-        // vertices of one alpha (Step 5), then their output in input order
-        auto vert_final = [&](const PredParams &pa) {
-            k_vert_final<<<grid_for(n), BLOCK, 0, s>>>(atom, perm, n, pa, o.vertex_shortcut, vgab, vert_min, vsize_in);
+        auto tet_ac2 = [&]() {
+            const bool few = pp.sgc <= 2000;  // below one candidate a ball
+            if (n_alpha > 1 && few)
+                k_tet_ac2<true, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+            else if (n_alpha > 1)
+                k_tet_ac2<true, BLOCK><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+            else if (few)
+                k_tet_ac2<false, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+            else
+                k_tet_ac2<false, BLOCK><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
             LAUNCH_CHECK();
         };
-        auto vert_emit = [&](ac_complex *r, int *m_out, hipStream_t se) {
-            k_vert_flags<<<grid_for(n), BLOCK, 0, se>>>(vsize_in, n, vflag);
-            LAUNCH_CHECK();
-            scan_i32(vflag, vpos, n, se, sc, m_out);
-            r->d_simp[0] = static_cast<int32_t *>(dev_alloc((size_t)n * sizeof(int32_t)));
-            r->d_size[0] = static_cast<double *>(dev_alloc((size_t)n * sizeof(double)));
-            k_vert_emit<<<grid_for(n), BLOCK, 0, se>>>(vsize_in, vpos, n, r->d_simp[0], r->d_size[0]);
+        // counted ranges for every group's tetrahedra, after an overflow: both
+        // kernels again (marks of the first run stand: minima, each of a kept
+        // tetrahedron)
+        auto tet_counted = [&]() {
+            const long long q = total_i64(tt.num, groups, s, sc);
+            check_total(q, "candidate tetrahedra");
+            int *base = sc.get<int>((size_t)groups + 1);
+            scan_i32(tt.num, base, groups, s, sc);
+            tt.tet_base = base;
+            tet_room((size_t)q);
+            fill<int>(&cnt->overflow, 0, 1, s);
+            if (fx && fx->learn) fx->two_pass = true;
+            tetrahedra();
+            tet_ac2();
+        };
+        if (split) tm.mark(ST_TRI_GABRIEL);
+        tetrahedra();
+        tm.mark(ST_TET_COUNT);  // in place: no scan, no fill
+        tm.mark(ST_TET_FILL);
+        tm.mark(ST_TETRA);
+        tet_ac2();
+
+        // ---- pruning and output ----
+        int4 *rec = sc.get<int4>((size_t)n + 1);
+        const int rec_tiles = (n + REC_TILE - 1) / REC_TILE;
+        int4 *tile_sum = rec_tiles > 1 ? sc.get<int4>(rec_tiles) : nullptr;
+        OutCap out_cap{INT_MAX, INT_MAX, INT_MAX};
+        if (fixed) out_cap = {fx->E_cap, fx->T_cap, fx->Q_cap};
+        // the records scanned, and the vertices (out0 / size0; a sweep's records hold none)
+        auto scan_records = [&](int *out0, double *size0) {
+            if (rec_tiles > 1) {
+                k_rec_sums<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, stop);
+                k_rec_prefix<<<1, 1024, 0, s>>>(tile_sum, rec_tiles, cd.tri_cnt, tt.cand, groups, cnt, fixed, out_cap,
+                                               STOP_CAPACITY);
+            }
+            k_rec_apply<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, out0, size0, cd.tri_cnt, tt.cand,
+                                                       groups, cnt, fixed, out_cap, STOP_CAPACITY);
             LAUNCH_CHECK();
         };
-        // rows of each molecule of a batch in the sorted outputs of r (device)
-        auto mol_rows = [&](ac_complex *r, Counters *cm, long long *d_rows, const long long *d_bound) {
-            const unsigned nb = (unsigned)((n_mol + 1 + BLOCK - 1) / BLOCK);
-            k_row_lower_bound<1><<<nb, BLOCK, 0, s>>>(r->d_simp[0], &cm->m0, d_bound, n_mol + 1, d_rows);
-            k_row_lower_bound<2><<<nb, BLOCK, 0, s>>>(r->d_simp[1], &cm->m1, d_bound, n_mol + 1, d_rows + (n_mol + 1));
-            k_row_lower_bound<3><<<nb, BLOCK, 0, s>>>(r->d_simp[2], &cm->m2, d_bound, n_mol + 1, d_rows + 2 * (n_mol + 1));
-            k_row_lower_bound<4><<<nb, BLOCK, 0, s>>>(r->d_simp[3], &cm->m3, d_bound, n_mol + 1, d_rows + 3 * (n_mol + 1));
-            LAUNCH_CHECK();
+        auto dev_rows = [&](ac_complex *r, int d, long long rows) {
+            const size_t m = rows > 0 ? (size_t)rows : 1;
+            r->d_simp[d] = static_cast<int32_t *>(dev_alloc(m * (d + 1) * sizeof(int32_t)));
+            r->d_size[d] = static_cast<double *>(dev_alloc(m * sizeof(double)));
         };
         long long *d_bound = nullptr;
         if (n_mol > 1 && fixed) {
@@ -1076,117 +1017,114 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             d_bound = sc.get<long long>(n_mol + 1);
             HIP_TRY(hipMemcpyAsync(d_bound, bt.off.data(), (n_mol + 1) * sizeof(long long), hipMemcpyHostToDevice, s));
         }
-        // per-alpha kept counts (m0..m3 of cs[k]); the main counters keep the
-        // fallback count and the lookup flag
-        Counters *cs = cnt;
-        if (n_alpha > 1) {
-            cs = sc.get<Counters>(n_alpha);
-            HIP_TRY(hipMemsetAsync(cs, 0, n_alpha * sizeof(Counters), s));
-        }
         long long *d_rows = n_mol > 1 ? sc.get<long long>((size_t)n_alpha * 4 * (n_mol + 1)) : nullptr;
+        Counters cf{};
+        std::vector<Counters> cm(n_alpha);
 
         if (n_alpha == 1) {
-            // every candidate leaves its pruning kernel with its emit key
-            // (least input id, n if not kept) and payload
-            unsigned *qkey = sc.get<unsigned>(Q > 0 ? Q : 1), *tkey = sc.get<unsigned>(T > 0 ? T : 1);
-            unsigned *ekey = sc.get<unsigned>(E > 0 ? E : 1);
-            EmitPay<4>::type *qpay = sc.get<EmitPay<4>::type>(Q > 0 ? Q : 1);
-            EmitPay<3>::type *tpay = sc.get<EmitPay<3>::type>(T > 0 ? T : 1);
-            EmitPay<2>::type *epay = sc.get<EmitPay<2>::type>(E > 0 ? E : 1);
-            // Each dimension's emit needs only its own pruning kernel: the
-            // emit of the tetrahedra, the triangles and the vertices runs on a
-            // second stream beside the later pruning kernels and the edge emit
-            // (the longest); the streams join before the counts are read.
-            // Measured on the 3M-atom shell: 2.470 ms per build against 2.508
-            // on one stream (a kernel on either stream mostly fills the GPU,
-            // so the other stream's kernels run in its gaps). Small builds
-            // keep one stream (the waits between streams cost more than the
-            // overlap gains: 260 atoms, 0.36 ms against 0.31), and so do a
-            // profile that times these stages and a build on fixed scratch
-            // (which creates no stream or event).
-            const bool one_stream =
-                n < (1 << 20) || (tm.on && (tm.only < 0 || tm.only >= ST_TETRA)) || t_arena;
-            AuxStream *ax = one_stream ? nullptr : &aux_stream();
-            hipStream_t s2 = ax ? ax->s : s;
-            s_aux = ax ? ax->s : nullptr;
-            tm.mark(ST_TETRA);
-            if (Q > 0) {
-                k_tet_ac2<false><<<grid_for(Q), BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i,
-                                                              tri_start, tri_k, tri_e, tet_t, tet_l, Q, pp, tgab, tri_min,
-                                                              nullptr, qsize, nullptr, emit_keys<4>(n, Q).drop, qkey, qpay, cnt,
-                                                              Q_live);
+            int2 *ball_cnt = sc.get<int2>(n);
+            dev_rows(res, 0, n);
+            auto prune = [&]() {
+                k_tri_final<<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, tri_min, egab, eng, edge_min, tt, ball_cnt, cnt, stop);
                 LAUNCH_CHECK();
-            }
-            auto emit_tets = [&]() { emit_dim<4>(qkey, qpay, qsize, Q, n, s2, sc, res, 3, &cnt->m3, true, Q_live); };
-            auto emit_tris = [&]() { emit_dim<3>(tkey, tpay, nullptr, T, n, s2, sc, res, 2, &cnt->m2, true, T_live); };
-            if (ax) {
-                stream_after(s2, s, ax->ev[0]);
-                emit_tets();
-            }
+                tm.mark(ST_EDGE_FINAL);
+                k_edge_final<<<grid_for(n), BLOCK, 0, s>>>(cd, pp, o.vertex_shortcut, egab, edge_min, vgab, eng, vert_min,
+                                                          ball_cnt, rec, cnt, stop);
+                LAUNCH_CHECK();
+                tm.mark(ST_VERT_FINAL);
+                scan_records(res->d_simp[0], res->d_size[0]);
+                if (n_mol > 1) {
+                    k_mol_rows<<<(unsigned)((n_mol + 256) / 256), 256, 0, s>>>(rec, d_bound, n_mol, d_rows, stop);
+                    LAUNCH_CHECK();
+                }
+            };
+            auto write_rows = [&]() {
+                k_rows<<<groups, BLOCK, 0, s>>>(cd, pp, rec, egab, edge_min, tgab, tsize, tri_min, tt, res->d_simp[1], res->d_size[1], res->d_simp[2],
+                                               res->d_size[2], res->d_simp[3], res->d_size[3], stop);
+                LAUNCH_CHECK();
+            };
             tm.mark(ST_TRI_FINAL);
-            if (T > 0) {
-                k_tri_final<<<grid_for(T), BLOCK, 0, s>>>(up_start, up, edge_i, tri_k, tri_e, T, tgab, tsize, tri_min, egab,
-                                                         edge_min, perm, emit_keys<3>(n, T).drop, tkey, tpay, cnt, T_live);
-                LAUNCH_CHECK();
+            prune();
+            // Outputs sized for every candidate where that is little memory: the
+            // rows are then written before the counts are read, one wait in
+            // all. Else the counts are read first.
+            const long long q_room = (long long)groups * tt.cap;
+            const bool roomy = fixed || E * 16LL + room * 20LL + q_room * 24LL <= OUT_ROOM;
+            if (roomy) {
+                dev_rows(res, 1, fixed ? fx->E_cap : E);
+                dev_rows(res, 2, fixed ? fx->T_cap : room);
+                dev_rows(res, 3, fixed ? fx->Q_cap : q_room);
+                tm.mark(ST_EMIT);
+                write_rows();
+                tm.mark(ST_COUNT);
             }
-            if (ax) {
-                stream_after(s2, s, ax->ev[1]);
-                emit_tris();
+            if (fixed) {
+                // nothing is read back: the plan reads the counters after a replay
+                fx->cnt = cnt;
+                fx->d_rows = d_rows;
+                outs[0] = res;
+                return AC_OK;
             }
-            tm.mark(ST_EDGE_FINAL);
-            if (E > 0) {
-                k_edge_final<<<grid_for(E), BLOCK, 0, s>>>(atom, up, edge_i, E, egab, edge_min, vgab, vert_min, perm,
-                                                          emit_keys<2>(n, E).drop, ekey, epay, E_live);
-                LAUNCH_CHECK();
+            cf = read_one(cnt, s);
+            const bool again = cf.overflow != 0;  // a group kept more tetrahedra than its slab holds
+            if (again) {
+                tet_counted();
+                prune();
+                cf = read_one(cnt, s);
             }
-            tm.mark(ST_VERT_FINAL);
-            vert_final(pp);
-            if (ax) {
-                stream_after(s2, s, ax->ev[2]);
-                vert_emit(res, &cnt->m0, s2);
+            if (cf.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
+            if (again && roomy) {
+                dev_free(res->d_simp[3]);
+                dev_free(res->d_size[3]);
+                res->d_simp[3] = nullptr;
+                res->d_size[3] = nullptr;
+                dev_rows(res, 3, cf.m3);
             }
-            // ---- emit ----
-            tm.mark(ST_EMIT);
-            if (!ax) vert_emit(res, &cnt->m0, s);
-            emit_dim<2>(ekey, epay, nullptr, E, n, s, sc, res, 1, &cnt->m1, true, E_live);
-            if (ax) {
-                stream_after(s, s2, ax->ev[3]);
-            } else {
-                emit_tris();
-                emit_tets();
+            if (!roomy) {
+                dev_rows(res, 1, cf.m1);
+                dev_rows(res, 2, cf.m2);
+                dev_rows(res, 3, cf.m3);
             }
-            if (n_mol > 1) mol_rows(res, cnt, d_rows, d_bound);
+            if (again || !roomy) {
+                tm.mark(ST_EMIT);
+                write_rows();
+                tm.mark(ST_COUNT);
+                // the scratch goes back to the pool: its last reader has to end
+                HIP_TRY(hipStreamSynchronize(s));
+            }
+            cm[0] = cf;
+            if (fx && fx->learn) {
+                fx->T = cf.T;
+                fx->Q = cf.m3;
+            }
         } else {
-            // ---- sweep: AC2 of the tetrahedra, the output order of every
-            // candidate and each candidate's AC3 threshold once; then per
-            // alpha, comparisons, pruning and compaction in output order ----
-            tm.mark(ST_TETRA);
-            tri_att = sc.get<int>(T > 0 ? T : 1);
-            edge_att = sc.get<int>(E > 0 ? E : 1);
-            vert_att = sc.get<int>(n);
-            unsigned char *qin = sc.get<unsigned char>(Q > 0 ? Q : 1);
-            int4 *tface = sc.get<int4>(Q > 0 ? Q : 1);
-            if (Q > 0) {
-                k_tet_ac2<true><<<grid_for(Q), BLOCK, 0, s>>>(atom, perm, nbr_start, nbr_cnt, nbr, up_start, up, edge_i,
-                                                             tri_start, tri_k, tri_e, tet_t, tet_l, Q, pp, tgab, nullptr,
-                                                             qin, qsize, tface, emit_keys<4>(n, Q).drop, nullptr, nullptr, cnt);
+            // ---- sweep: the output order of every candidate and each
+            // candidate's AC3 threshold once; then per alpha, comparisons,
+            // pruning and compaction in output order ----
+            auto places = [&]() {
+                k_sweep_counts<<<groups, BLOCK, 0, s>>>(cd, tt, rec);
                 LAUNCH_CHECK();
+                scan_records(nullptr, nullptr);
+                return read_one(cnt, s);
+            };
+            Counters cp = places();
+            if (cp.overflow) {
+                tet_counted();
+                cp = places();
             }
-            int2 *tedge = sc.get<int2>(T > 0 ? T : 1);
-            if (T > 0) {
-                k_tri_edges<<<grid_for(T), BLOCK, 0, s>>>(up_start, up, edge_i, tri_k, tri_e, T, tedge);
-                LAUNCH_CHECK();
-            }
-            const Cands cd{up, edge_i, tri_k, tri_e, tet_t, tet_l, perm};
-            const int M[4] = {n, E, T, Q};
-            int *rows_s[4] = {}, *spos[4] = {}, *thr[4] = {}, *tsum[4] = {}, *toff[4] = {};
+            const int M[4] = {n, cp.m1, cp.m2, cp.m3};
+            const int T = M[2], Q = M[3];
+            const size_t T1s = T > 0 ? T : 1, Q1 = Q > 0 ? Q : 1;
+            int *tri_att = sc.get<int>(T1s), *edge_att = sc.get<int>(E1), *vert_att = sc.get<int>(n);
+            long long *stri_min = sc.get<long long>(T1s);
+            long long *svert_min = sc.get<long long>(n);
+            int *rows_s[4] = {}, *thr[4] = {}, *tsum[4] = {}, *toff[4] = {};
             unsigned char *in_s[4] = {};
             double *sz_s[4] = {}, *szp[4] = {};
             for (int d = 1; d <= 3; d++) {
                 const int m = M[d] > 0 ? M[d] : 1;
                 const unsigned nb = grid_for(m);
                 rows_s[d] = sc.get<int>((size_t)m * (d + 1));
-                spos[d] = sc.get<int>(m);
                 in_s[d] = sc.get<unsigned char>(m);
                 tsum[d] = sc.get<int>(nb);
                 toff[d] = sc.get<int>((size_t)nb + 1);
@@ -1194,55 +1132,60 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 thr[d] = sc.get<int>(m);
                 szp[d] = sc.get<double>(m);
             }
-            int2 *ends = sc.get<int2>(E > 0 ? E : 1);
-            int4 *face2 = sc.get<int4>(T > 0 ? T : 1);
-            int4 *face3 = sc.get<int4>(Q > 0 ? Q : 1);
-            order_dim<2>(E, cd, n, s, sc, rows_s[1], spos[1]);
-            order_dim<3>(T, cd, n, s, sc, rows_s[2], spos[2]);
-            order_dim<4>(Q, cd, n, s, sc, rows_s[3], spos[3]);
-            if (E > 0) {
-                k_sweep_prep_edge<<<grid_for(E), BLOCK, 0, s>>>(atom, up, edge_i, E, egab, spos[1], aq, thr[1], szp[1],
-                                                               ends);
-                LAUNCH_CHECK();
-            }
-            if (T > 0) {
-                k_sweep_prep_tri<<<grid_for(T), BLOCK, 0, s>>>(atom, up, edge_i, tri_k, tri_e, T, tgab, tsize, tedge,
-                                                              spos[2], spos[1], pp, thr[2], szp[2], face2, cnt);
-                LAUNCH_CHECK();
-            }
-            if (Q > 0) {
-                k_sweep_prep_tet<<<grid_for(Q), BLOCK, 0, s>>>(atom, up, edge_i, tri_k, tri_e, tet_t, tet_l, Q, qin, qsize,
-                                                              tface, spos[3], spos[2], pp, thr[3], szp[3], face3, cnt);
-                LAUNCH_CHECK();
-            }
+            int2 *ends = sc.get<int2>(E1);
+            int4 *face2 = sc.get<int4>(T1s);
+            int4 *face3 = sc.get<int4>(Q1);
+            int4 *adj = sc.get<int4>(n);
+            k_sweep_adj<<<groups, BLOCK, 0, s>>>(cd, tt, rec, adj);
+            if (E > 0)
+                k_sweep_prep_edge<<<grid_for(E), BLOCK, 0, s>>>(cd, E, egab, adj, aq, thr[1], szp[1], rows_s[1], ends);
+            k_sweep_prep_tri<<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, adj, pp, thr[2], szp[2], rows_s[2], face2, cnt);
+            k_sweep_prep_tet<<<groups, BLOCK, 0, s>>>(cd, tt, adj, pp, thr[3], szp[3], rows_s[3], face3, cnt);
+            LAUNCH_CHECK();
+            double *vsize_in = sc.get<double>(n);
+            int *vflag = sc.get<int>(n);
+            int *vpos = sc.get<int>((size_t)n + 1);
+            // per-alpha kept counts (m0..m3 of cs[k]); the main counters keep
+            // the candidate totals, the fallback count and the lookup flag
+            Counters *cs = sc.get<Counters>(n_alpha);
+            HIP_TRY(hipMemsetAsync(cs, 0, n_alpha * sizeof(Counters), s));
+            tm.mark(ST_TRI_FINAL);
+            tm.mark(ST_EDGE_FINAL);
+            tm.mark(ST_VERT_FINAL);
             tm.mark(ST_EMIT);
             for (int k = 0; k < n_alpha; k++) {
                 PredParams pa = pp;
                 pa.aq = aqs[k];
                 ac_complex *r = rs[k];
-                prune_init();
+                const long long mx = std::max<long long>(std::max<long long>(T, E), n);
+                k_prune_init<<<(unsigned)std::min<long long>((mx + BLOCK - 1) / BLOCK, 65536), BLOCK, 0, s>>>(
+                    T, E, n, tri_att, stri_min, edge_att, edge_min, vert_att, svert_min);
+                LAUNCH_CHECK();
                 if (Q > 0) {
-                    k_sweep_tets<<<grid_for(Q), BLOCK, 0, s>>>(Q, pa.aq, thr[3], szp[3], face3, thr[2], tri_att, tri_min,
+                    k_sweep_tets<<<grid_for(Q), BLOCK, 0, s>>>(Q, pa.aq, thr[3], szp[3], face3, thr[2], tri_att, stri_min,
                                                               in_s[3], sz_s[3], tsum[3], cnt);
                     LAUNCH_CHECK();
                 }
                 if (T > 0) {
-                    k_sweep_tris<<<grid_for(T), BLOCK, 0, s>>>(T, pa.aq, thr[2], szp[2], face2, tri_att, tri_min, thr[1],
+                    k_sweep_tris<<<grid_for(T), BLOCK, 0, s>>>(T, pa.aq, thr[2], szp[2], face2, tri_att, stri_min, thr[1],
                                                               edge_att, edge_min, in_s[2], sz_s[2], tsum[2], cnt);
                     LAUNCH_CHECK();
                 }
                 if (E > 0) {
                     k_sweep_edges<<<grid_for(E), BLOCK, 0, s>>>(E, pa.aq, thr[1], szp[1], ends, edge_att, edge_min, vgab,
-                                                               vert_att, vert_min, in_s[1], sz_s[1], tsum[1]);
+                                                               vert_att, svert_min, in_s[1], sz_s[1], tsum[1]);
                     LAUNCH_CHECK();
                 }
-                vert_final(pa);
-                vert_emit(r, &cs[k].m0, s);
+                k_vert_final<<<grid_for(n), BLOCK, 0, s>>>(atom, perm, n, pa, o.vertex_shortcut, vgab, svert_min, vsize_in);
+                k_vert_flags<<<grid_for(n), BLOCK, 0, s>>>(vsize_in, n, vflag);
+                LAUNCH_CHECK();
+                scan_i32(vflag, vpos, n, s, sc, &cs[k].m0);
+                dev_rows(r, 0, n);
+                k_vert_emit<<<grid_for(n), BLOCK, 0, s>>>(vsize_in, vpos, n, r->d_simp[0], r->d_size[0]);
+                LAUNCH_CHECK();
                 int *m_out[4] = {&cs[k].m0, &cs[k].m1, &cs[k].m2, &cs[k].m3};
                 for (int d = 1; d <= 3; d++) {
-                    const int K = d + 1;
-                    r->d_simp[d] = static_cast<int32_t *>(dev_alloc((size_t)(M[d] > 0 ? M[d] : 1) * K * sizeof(int32_t)));
-                    r->d_size[d] = static_cast<double *>(dev_alloc((size_t)(M[d] > 0 ? M[d] : 1) * sizeof(double)));
+                    dev_rows(r, d, M[d]);
                     if (M[d] == 0) {
                         fill<int>(m_out[d], 0, 1, s);
                         continue;
@@ -1260,16 +1203,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                                                              r->d_size[d]);
                     LAUNCH_CHECK();
                 }
-                if (n_mol > 1) mol_rows(r, &cs[k], d_rows + (size_t)k * 4 * (n_mol + 1), d_bound);
             }
-        }
-        tm.mark(ST_COUNT);
-        if (fixed) {
-            // nothing is read back: the plan reads the counters after a replay
-            fx->cnt = cnt;
-            fx->d_rows = d_rows;
-            outs[0] = res;
-            return AC_OK;
+            tm.mark(ST_COUNT);
+            read_back(cm.data(), cs, (size_t)n_alpha, s);
+            cf = read_one(cnt, s);
+            if (cf.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
         }
 
         // ---- results ----
@@ -1278,11 +1216,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             rows.resize((size_t)n_alpha * 4 * (n_mol + 1));
             read_back(rows.data(), (const int64_t *)d_rows, rows.size(), s);
         }
-        std::vector<Counters> cm(n_alpha);
-        if (n_alpha > 1) read_back(cm.data(), cs, (size_t)n_alpha, s);
-        const Counters cf = read_one(cnt, s);
-        if (n_alpha == 1) cm[0] = cf;
-        if (cf.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
         tm.collect(res->stage_ms);
         for (int k = 0; k < n_alpha; k++) {
             ac_complex *r = rs[k];
@@ -1291,8 +1224,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             r->alpha_q = aqs[k];
             r->cand[0] = n;
             r->cand[1] = E;
-            r->cand[2] = T;
-            r->cand[3] = Q;
+            r->cand[2] = cf.T;
+            r->cand[3] = cf.Q;
             r->fallbacks = (int64_t)cf.exact_fallbacks;
             r->work[0] = ncell;
             r->work[1] = Nn;
@@ -1312,7 +1245,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         }
     } catch (const HipError &e) {
         (void)hipStreamSynchronize(s);
-        if (s_aux) (void)hipStreamSynchronize(s_aux);
         for (ac_complex *r : rs) free_complex(r);
         return set_error(e.st, e.msg);
     }
@@ -1389,7 +1321,7 @@ static void merge_rows(OwnedRows &own, int n, hipStream_t s, Scope &sc, ac_compl
         if (size) HIP_TRY(hipMemcpyAsync(size + off, own.size[j], c * sizeof(double), hipMemcpyDeviceToDevice, s));
         off += (long long)c;
     }
-    emit_dim<K>(key, pay, size, m, n, s, sc, r, K - 1, m_out, false);
+    emit_dim<K>(key, pay, size, m, n, s, sc, r, K - 1, m_out);
 }
 
 static ac_status run_partitioned(const double *d_xyz, const double *d_r, int64_t n64, double alpha, int parts,
@@ -2034,6 +1966,7 @@ static ac_status plan_create(const double *d_xyz, const double *d_r, const Batch
             return (int)c;
         };
         fx.E_cap = grow(fx.E);
+        fx.P_cap = grow(fx.P);
         fx.T_cap = grow(fx.T);
         fx.Q_cap = grow(fx.Q);
         std::vector<long long> cap(n_mol);
@@ -2142,9 +2075,9 @@ static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
         r->alpha_q = (int64_t)std::nearbyint(p->alpha * 1e6);
         const int m[4] = {c.m0, c.m1, c.m2, c.m3};
         r->cand[0] = p->n;
-        r->cand[1] = c.El;
-        r->cand[2] = c.Tl;
-        r->cand[3] = c.Ql;
+        r->cand[1] = c.E;
+        r->cand[2] = c.T;
+        r->cand[3] = c.Q;
         r->fallbacks = (int64_t)c.exact_fallbacks;
         r->work[0] = p->fx.ncell;
         r->work[1] = c.Nn;

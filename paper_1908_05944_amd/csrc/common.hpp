@@ -20,6 +20,13 @@ __device__ __forceinline__ double double_from_ordered(long long k) {
 }
 constexpr long long ORDERED_POS_INF = 0x7ff0000000000000LL;  // +inf encoded
 
+// x, as a value the optimiser knows nothing about: what is computed from it is
+// computed there and not kept in registers from an earlier use.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
 // MI355X dispatches consecutive workgroups round-robin over its 8 XCDs, each
@@ -34,35 +41,18 @@ __device__ __forceinline__ int xcd_block() {
     return x * q + min(x, r) + k;
 }
 
-// The same for a launch sized for a capacity of which only the first `live`
-// blocks have work (counts known on the device only): those blocks are
-// spread evenly over the XCDs, each XCD taking one contiguous range of them,
-// and the idle blocks map onto [live, gridDim.x). Still a bijection on
-// [0, gridDim.x); with live = gridDim.x it is xcd_block().
-__device__ __forceinline__ int xcd_block(int live) {
-    const int nb = gridDim.x, b = blockIdx.x;
-    live = min(max(live, 0), nb);
-    const int x = b % NUM_XCD, k = b / NUM_XCD;
-    const int q = live / NUM_XCD, r = live % NUM_XCD;  // live blocks per XCD
-    const int len = q + (x < r);
-    if (k < len) return x * q + min(x, r) + k;
-    const int Q = nb / NUM_XCD, R = nb % NUM_XCD;  // blocks per XCD
-    return live + (x * Q + min(x, R)) - (x * q + min(x, r)) + (k - len);
-}
-
-// Item count of a launch: `cap`, the count it was sized for, or, when `live`
-// is given, the smaller count an earlier kernel on the stream wrote there
-// (launches recorded before their counts are known, as in a captured graph).
-__device__ __forceinline__ int live_count(int cap, const int *live) { return live ? min(cap, *live) : cap; }
-
-// Inclusive prefix sum over the 64 lanes of a wave.
+// Inclusive prefix sum over the 64 lanes of a wave: data-parallel-primitive
+// moves inside the vector ALU (shifts by 1, 2, 4, 8 inside each row of 16
+// lanes, then the rows' last lanes broadcast to the later rows). A lane whose
+// source lies outside adds 0. No LDS round trips: a chain of six shuffles
+// costs a wave several hundred cycles, these six adds some tens.
 __device__ __forceinline__ int wave_inclusive_scan(int v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) {
-        int t = __shfl_up(v, off, WAVE);
-        if (lane >= off) v += t;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
     return v;
 }
 
@@ -98,6 +88,34 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *total) {
     __syncthreads();  // wsum may be reused by the next call
     *total = tot;
     return off + incl - v;
+}
+
+// Three of them at once (one pair of barriers).
+template <int NT>
+__device__ __forceinline__ void block_exclusive_scan3(int a, int b, int c, int (&off)[3], int (&tot)[3]) {
+    __shared__ int wsum[3][NT / WAVE];
+    const int ia = wave_inclusive_scan(a), ib = wave_inclusive_scan(b), ic = wave_inclusive_scan(c);
+    const int w = threadIdx.x / WAVE;
+    if (lane_id() == WAVE - 1) {
+        wsum[0][w] = ia;
+        wsum[1][w] = ib;
+        wsum[2][w] = ic;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        off[d] = 0;
+        tot[d] = 0;
+#pragma unroll
+        for (int k = 0; k < NT / WAVE; k++) {
+            off[d] += k < w ? wsum[d][k] : 0;
+            tot[d] += wsum[d][k];
+        }
+    }
+    __syncthreads();  // wsum may be reused by the next call
+    off[0] += ia - a;
+    off[1] += ib - b;
+    off[2] += ic - c;
 }
 
 // ---------------------------------------------------------------------------

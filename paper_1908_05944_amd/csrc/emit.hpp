@@ -2,23 +2,31 @@
 // in lexicographic order, each with its Size (Sec. 2.3; the paper outputs
 // membership only).
 //
-// The pruning kernels key every candidate by the least input id of its row
-// with the remaining ids and its Size (for a tetrahedron: its candidate
-// index) as payload; a candidate that is not kept gets the drop key, the
-// first key of the bucket after every input id's. A bucket is 2^shift
-// consecutive ids (at most EK_KEYS; smaller for small inputs, so that there
-// are some hundred buckets). A stable LSD radix sort over the key bits above
-// the bucket (8-bit passes) makes every bucket's rows contiguous, the dropped
-// rows last; k_key_starts finds where each
-// bucket starts, and k_emit_block finishes one bucket per block in LDS: it
-// loads the bucket's rows, counts the rows of each id with LDS atomics, scans
-// the counts, orders the rows by id, ranks each row in its id's group by the
-// remaining ids and writes it to its final place. Every global access is a
-// contiguous range; no global atomics, no scattered writes (a bucket with more
-// rows than LDS holds is finished through global scratch instead).
+// Every simplex belongs to its least input id, and the pruning kernels hold
+// each ball's simplices in output order already. So the rows of ball u start
+// where the kept rows of the balls before u end: the balls' kept counts, put
+// at their input ids by the last pruning kernel, are scanned (k_rec_*), and
+// k_rows writes every kept candidate to its ball's start plus its rank among
+// the ball's kept ones. No sort; the writes of a ball are contiguous (balls
+// are numbered in no spatial order in general, so consecutive balls of a
+// block write to different places).
+//
+// The merge of a partitioned build, whose rows come from several slabs, sorts:
+// rows keyed by their least id with the remaining ids and the Size as payload.
+// A bucket is 2^shift consecutive ids (at most EK_KEYS; smaller for small
+// inputs, so that there are some hundred buckets). A stable LSD radix sort
+// over the key bits above the bucket (8-bit passes) makes every bucket's rows
+// contiguous; k_key_starts finds where each bucket starts, and k_emit_block
+// finishes one bucket per block in LDS: it loads the bucket's rows, counts the
+// rows of each id with LDS atomics, scans the counts, orders the rows by id,
+// ranks each row in its id's group by the remaining ids and writes it to its
+// final place. Every global access is a contiguous range; no global atomics,
+// no scattered writes (a bucket with more rows than LDS holds is finished
+// through global scratch instead).
 #pragma once
 #include "common.hpp"
 #include "radix.hpp"
+#include "simplices.hpp"
 
 namespace acx {
 
@@ -38,22 +46,11 @@ __device__ __forceinline__ double double_of(unsigned lo, unsigned hi) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Key and payload of a candidate with input ids v[0..K) (any order): key =
-// least id, payload = the others ascending and `size` (K = 2, 3) or the
-// candidate index c (K = 4). Not kept: the drop key, empty payload.
+// Key and payload of a row with ascending input ids v[0..K): key = least id,
+// payload = the others and `size` (K = 2, 3) or the row's place c (K = 4).
 template <int K>
-__device__ __forceinline__ void emit_pack(bool kept, int (&v)[4], double size, int c, unsigned drop, unsigned &key,
+__device__ __forceinline__ void emit_pack(const int (&v)[4], double size, int c, unsigned &key,
                                           typename EmitPay<K>::type &pay) {
-    pay = typename EmitPay<K>::type{};
-    if (!kept) {
-        key = drop;
-        return;
-    }
-#pragma unroll
-    for (int a = 1; a < K; a++)
-#pragma unroll
-        for (int b = a; b > 0; b--)
-            if (v[b - 1] > v[b]) { const int t = v[b]; v[b] = v[b - 1]; v[b - 1] = t; }
     key = (unsigned)v[0];
     if constexpr (K == 2) {
         const uint2 z = bits_of(size);
@@ -135,18 +132,17 @@ __device__ __forceinline__ bool ids_less(const unsigned (&v)[3], const unsigned 
 // single > 0: one block takes every row unsorted (at most ek_rows<K>(), ids
 // below single <= EK_KEYS, shift EK_SHIFT): the rows whose key is single or
 // more are dropped ones and skipped, and the block writes the kept count.
-// `start` is then unused and the row count is rows_cap, or *live if given.
-// A build of a few hundred balls then needs no radix sort.
+// `start` is then unused and the row count is rows_in. A few hundred balls
+// then need no radix sort.
 template <int K>
 __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restrict__ key,
                                                           const typename EmitPay<K>::type *__restrict__ pay,
                                                           const int *__restrict__ start, int shift, int nb,
                                                           unsigned *__restrict__ gkey,
                                                           typename EmitPay<K>::type *__restrict__ gpay,
-                                                          const double *__restrict__ size_in, int to_A2,
+                                                          const double *__restrict__ size_in,
                                                           int *__restrict__ out, double *__restrict__ out_size,
-                                                          int *__restrict__ m_out, int single = 0, int rows_cap = 0,
-                                                          const int *__restrict__ live = nullptr) {
+                                                          int *__restrict__ m_out, int single = 0, int rows_in = 0) {
     constexpr int NI = K - 1;  // ids after the least
     constexpr bool SLIM = ek_slim<K>();
     constexpr int NW = SLIM ? NI : (K == 2 ? 3 : 4);  // payload words held in LDS
@@ -162,7 +158,7 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
     const int b = blockIdx.x, t = threadIdx.x;
     const bool one = single > 0;
     if (!one && b == 0 && t == 0) *m_out = start[nb];
-    const int bs = one ? 0 : start[b], rows = one ? live_count(rows_cap, live) : start[b + 1] - bs;
+    const int bs = one ? 0 : start[b], rows = one ? rows_in : start[b + 1] - bs;
     const unsigned k0 = (unsigned)b << shift;  // the bucket's ids: [k0, k0 + 2^shift), 2^shift <= EK_KEYS
     for (int k = t; k <= EK_KEYS; k += EK_BLOCK) cnt[k] = 0;
     __syncthreads();
@@ -253,8 +249,7 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
             }
             const long long pos = (long long)bs + g0 + rank;
             write_row<K>(out, pos, k0 + k, r);
-            const double z = pay_size<K>(me, size_in);
-            out_size[pos] = to_A2 ? z / 1.0e6 : z;
+            out_size[pos] = pay_size<K>(me, size_in);
         }
         return;
     }
@@ -282,8 +277,291 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
         }
         const long long pos = (long long)bs + g0 + rank;
         write_row<K>(out, pos, k0 + k, r);
-        const double z = pay_size<K>(me, size_in);
-        out_size[pos] = to_A2 ? z / 1.0e6 : z;
+        out_size[pos] = pay_size<K>(me, size_in);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Scan of the balls' output records (input order): rec[u] = kept edges,
+// triangles, tetrahedra and vertex state of ball u becomes base[u] = the rows
+// of those dimensions before ball u's, with the vertices' in .w; base[n] = the
+// totals (also in Counters). Tiles of REC_TILE balls: k_rec_sums adds up each
+// tile, k_rec_prefix scans the tiles in one block (and folds the groups'
+// candidate totals), k_rec_apply scans inside the tiles and writes the
+// vertices, whose rows are then known. Up to REC_TILE balls one block does
+// all of it (k_rec_apply with tile_off = nullptr).
+constexpr int REC_BLOCK = 1024;
+constexpr int REC_IPT = 4;  // records of a lane, a wave apart (coalesced 16-byte accesses)
+constexpr int REC_TILE = REC_BLOCK * REC_IPT;
+
+__device__ __forceinline__ int4 operator+(int4 a, int4 b) { return make_int4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+__device__ __forceinline__ int4 operator-(int4 a, int4 b) { return make_int4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); }
+
+// Counts of ball u's record; vert_min: least Size of a kept incident edge of
+// a ball that fails AC2 at its own centre.
+__device__ __forceinline__ int4 rec_counts(const int4 &r, const long long *__restrict__ vert_min, int u) {
+    return make_int4(r.x, r.y, r.z, r.w > 0 || (r.w == VERT_MAYBE && vert_min[u] != ORDERED_POS_INF));
+}
+
+__device__ __forceinline__ int4 wave_inclusive_scan4(int4 v) {
+    return make_int4(wave_inclusive_scan(v.x), wave_inclusive_scan(v.y), wave_inclusive_scan(v.z),
+                     wave_inclusive_scan(v.w));
+}
+__device__ __forceinline__ int4 last_lane4(int4 v) {
+    return make_int4(__shfl(v.x, WAVE - 1, WAVE), __shfl(v.y, WAVE - 1, WAVE), __shfl(v.z, WAVE - 1, WAVE),
+                     __shfl(v.w, WAVE - 1, WAVE));
+}
+
+// Sum of v over the waves of a block before this one (v: the same in every
+// lane of a wave); *total receives the block's sum.
+template <int NT>
+__device__ __forceinline__ int4 waves_before4(int4 v, int4 *total) {
+    __shared__ int4 wsum[NT / WAVE];
+    const int w = threadIdx.x / WAVE;
+    if (lane_id() == 0) wsum[w] = v;
+    __syncthreads();
+    int4 off = make_int4(0, 0, 0, 0), tot = off;
+#pragma unroll
+    for (int k = 0; k < NT / WAVE; k++) {
+        if (k < w) off = off + wsum[k];
+        tot = tot + wsum[k];
+    }
+    __syncthreads();
+    *total = tot;
+    return off;
+}
+
+__global__ void __launch_bounds__(REC_BLOCK) k_rec_sums(const int4 *__restrict__ rec,
+                                                         const long long *__restrict__ vert_min, int n,
+                                                         int4 *__restrict__ tile_sum, const int *__restrict__ stop) {
+    if (stop && *stop) return;
+    const int u0 = blockIdx.x * REC_TILE;
+    int4 s = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < REC_IPT; k++) {
+        const int u = u0 + k * REC_BLOCK + threadIdx.x;
+        if (u < n) s = s + rec_counts(rec[u], vert_min, u);
+    }
+    int4 tot;
+    (void)waves_before4<REC_BLOCK>(last_lane4(wave_inclusive_scan4(s)), &tot);
+    if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
+}
+
+// Totals of a finished scan (one thread), and the capacity check of a
+// recorded build's outputs (cap: rows of dimensions 1..3).
+struct OutCap {
+    int E, T, Q;
+};
+__device__ __forceinline__ void rec_totals(int4 t, Counters *cnt, bool fixed, OutCap cap, int why) {
+    cnt->m0 = t.w;
+    cnt->m1 = t.x;
+    cnt->m2 = t.y;
+    cnt->m3 = t.z;
+    if (fixed && (t.x > cap.E || t.y > cap.T || t.z > cap.Q || cnt->overflow)) cnt->stop |= why;
+}
+
+// Candidate triangles and tetrahedra of all groups (one block).
+template <int NT>
+__device__ __forceinline__ void fold_candidates(const int *__restrict__ tri_cnt, const int *__restrict__ tet_cand,
+                                                int groups, Counters *cnt) {
+    __shared__ long long ws[2][NT / WAVE];
+    long long a = 0, b = 0;
+    for (int k = threadIdx.x; k < groups; k += NT) {
+        a += tri_cnt[k];
+        b += tet_cand[k];
+    }
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, WAVE);
+        b += __shfl_xor(b, o, WAVE);
+    }
+    if (lane_id() == 0) {
+        ws[0][threadIdx.x / WAVE] = a;
+        ws[1][threadIdx.x / WAVE] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a = b = 0;
+        for (int k = 0; k < NT / WAVE; k++) {
+            a += ws[0][k];
+            b += ws[1][k];
+        }
+        cnt->T = a;
+        cnt->Q = b;
+    }
+}
+
+__global__ void __launch_bounds__(1024) k_rec_prefix(int4 *__restrict__ tile_sum, int tiles,
+                                                      const int *__restrict__ tri_cnt, const int *__restrict__ tet_cand,
+                                                      int groups, Counters *cnt, int fixed, OutCap cap, int why) {
+    if (fixed && cnt->stop) return;
+    int4 carry = make_int4(0, 0, 0, 0);
+    for (int c0 = 0; c0 < tiles; c0 += 1024) {
+        const int k = c0 + threadIdx.x;
+        const int4 v = k < tiles ? tile_sum[k] : make_int4(0, 0, 0, 0);
+        int4 tot;
+        const int4 in = wave_inclusive_scan4(v);
+        const int4 ex = carry + waves_before4<1024>(last_lane4(in), &tot) + (in - v);
+        if (k < tiles) tile_sum[k] = ex;
+        carry = carry + tot;
+    }
+    fold_candidates<1024>(tri_cnt, tet_cand, groups, cnt);
+    if (threadIdx.x == 0) rec_totals(carry, cnt, fixed, cap, why);
+}
+
+__global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec, const long long *__restrict__ vert_min,
+                                                          int n, const int4 *__restrict__ tile_off, int *__restrict__ out,
+                                                          double *__restrict__ out_size,
+                                                          const int *__restrict__ tri_cnt,
+                                                          const int *__restrict__ tet_cand, int groups, Counters *cnt,
+                                                          int fixed, OutCap cap, int why) {
+    if (fixed && cnt->stop) return;
+    // a wave takes REC_IPT runs of WAVE consecutive records
+    const int u0 = blockIdx.x * REC_TILE + (threadIdx.x / WAVE) * (WAVE * REC_IPT) + lane_id();
+    int4 r[REC_IPT], c[REC_IPT], ex[REC_IPT], s = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < REC_IPT; k++) r[k] = u0 + k * WAVE < n ? rec[u0 + k * WAVE] : make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < REC_IPT; k++) {
+        c[k] = u0 + k * WAVE < n ? rec_counts(r[k], vert_min, u0 + k * WAVE) : r[k];
+        const int4 in = wave_inclusive_scan4(c[k]);
+        ex[k] = s + (in - c[k]);
+        s = s + last_lane4(in);
+    }
+    int4 tot;
+    int4 before = waves_before4<REC_BLOCK>(s, &tot);
+    if (tile_off) before = before + tile_off[blockIdx.x];
+#pragma unroll
+    for (int k = 0; k < REC_IPT; k++) {
+        const int u = u0 + k * WAVE;
+        if (u >= n) break;
+        const int4 at = before + ex[k];
+        rec[u] = at;
+        if (c[k].w) {
+            const double sz = r[k].w > 0 ? -(double)r[k].w : double_from_ordered(vert_min[u]);
+            out[at.w] = u;
+            out_size[at.w] = sz / 1.0e6;  // mA^2 -> A^2
+        }
+        if (u == n - 1) rec[n] = at + c[k];
+    }
+    if (!tile_off) {
+        fold_candidates<REC_BLOCK>(tri_cnt, tet_cand, groups, cnt);
+        if (threadIdx.x == 0) rec_totals(tot, cnt, fixed, cap, why);
+    }
+}
+
+// Rows of each molecule of a batch: molecule m's d-simplices are rows
+// [rows[d][m], rows[d][m + 1]), rows[d] = out + d (n_mol + 1), from the scanned
+// records at the molecules' first balls (bound, n_mol + 1 entries).
+__global__ void __launch_bounds__(256) k_mol_rows(const int4 *__restrict__ base, const long long *__restrict__ bound,
+                                                   int n_mol, long long *__restrict__ out,
+                                                   const int *__restrict__ stop) {
+    const int m = blockIdx.x * 256 + threadIdx.x;
+    if (m > n_mol || (stop && *stop)) return;
+    const int4 b = base[bound[m]];
+    out[m] = b.w;
+    out[(n_mol + 1) + m] = b.x;
+    out[2LL * (n_mol + 1) + m] = b.y;
+    out[3LL * (n_mol + 1) + m] = b.z;
+}
+
+// Kept edges, triangles and tetrahedra of a group to their output rows: ball
+// u's first row (base[u]) plus the rank among the ball's kept ones. Waves take
+// runs of 64 candidates, each for itself: the kept ones of the lane's ball
+// before the lane are counted in the wave's ballot, those of the run's first
+// ball before the run by a look back at their status (a block scan per round
+// would make every wave wait for the slowest of four scattered writes).
+// Kept candidates [first, x) of the ball that owns candidate x = c0 + lane
+// (first: the ball's first candidate), given the kept ballot of the run.
+__device__ __forceinline__ int rank_in_ball(unsigned long long kept, int lane, int first, int c0, int carry) {
+    const unsigned long long before = kept & ((1ull << lane) - 1ull);
+    return first > c0 ? __popcll(before >> (first - c0)) : carry + __popcll(before);
+}
+
+__global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const int4 *__restrict__ base,
+                                                 const unsigned char *__restrict__ egab,
+                                                 const long long *__restrict__ edge_min,
+                                                 const unsigned char *__restrict__ tgab,
+                                                 const double *__restrict__ tsize,
+                                                 const long long *__restrict__ tri_min,
+                                                 Tets tt, int *__restrict__ out1, double *__restrict__ size1,
+                                                 int *__restrict__ out2, double *__restrict__ size2,
+                                                 int *__restrict__ out3, double *__restrict__ size3,
+                                                 const int *__restrict__ stop) {
+    if (stop && *stop) return;
+    const int g = xcd_block();
+    const int b0 = g << cd.gshift, b1 = min(b0 + (1 << cd.gshift), cd.n);
+    const int w = threadIdx.x / WAVE, lane = lane_id();
+    const int e0 = cd.up_start[b0], e1 = cd.up_start[b1];
+    // the balls' input ids and first rows, gathered once (a ball's record lies
+    // in a line of its own: read per row they would cost more than the rows)
+    __shared__ int ids[GROUP], row0[3][GROUP];
+    if (b0 + (int)threadIdx.x < b1) {
+        const int u = cd.perm[b0 + threadIdx.x];
+        const int4 r = base[u];
+        ids[threadIdx.x] = u;
+        row0[0][threadIdx.x] = r.x;
+        row0[1][threadIdx.x] = r.y;
+        row0[2][threadIdx.x] = r.z;
+    }
+    __syncthreads();
+    for (int c0 = e0 + w * WAVE; c0 < e1; c0 += BLOCK) {
+        const int e = c0 + lane;
+        const int st = e < e1 ? egab[e] : FACE_OUT;
+        const int i = e < e1 ? cd.edge_i[e] : 0;
+        const int first = e < e1 ? cd.up_start[i] : 0;
+        const unsigned long long kept = __ballot(st != FACE_OUT);
+        const int f0 = __shfl(first, 0, WAVE);
+        int carry = 0;
+        for (int x = f0; x < c0; x += WAVE) carry += __popcll(__ballot(x + lane < c0 && egab[x + lane] != FACE_OUT));
+        if (st == FACE_OUT) continue;
+        const int u = ids[i - b0];
+        const long long p = row0[0][i - b0] + rank_in_ball(kept, lane, first, c0, carry);
+        const double sz = st == FACE_GABRIEL ? edge_size_canon(cd.atom[i], cd.atom[cd.up[e]]) : double_from_ordered(edge_min[e]);
+        reinterpret_cast<int2 *>(out1)[p] = make_int2(u, cd.up_id[e]);
+        size1[p] = sz / 1.0e6;  // mA^2 -> A^2
+    }
+    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
+    for (int c0 = t0 + w * WAVE; c0 < t1; c0 += BLOCK) {
+        const int t = c0 + lane;
+        const int st = t < t1 ? tgab[t] : FACE_OUT;
+        const int e = t < t1 ? cd.tri_e[t] : 0;
+        const int i = t < t1 ? cd.edge_i[e] : -1;
+        const unsigned long long kept = __ballot(st != FACE_OUT);
+        // the lane's ball's first triangle, where it lies in the run: after
+        // the last lane at or before this one whose ball differs from its
+        // predecessor's
+        const int prev = __shfl_up(i, 1, WAVE);
+        const unsigned long long starts = __ballot(lane > 0 && i != prev) & (~0ull >> (WAVE - 1 - lane));
+        const int first = starts ? c0 + (WAVE - 1 - __clzll((long long)starts)) : c0;
+        int carry = 0;
+        const int i0 = __shfl(i, 0, WAVE);
+        for (int x = c0;;) {  // runs of 64 before this one, while they hold that ball's triangles
+            x -= WAVE;
+            const int y = x + lane;
+            const bool same = y >= t0 && cd.edge_i[cd.tri_e[y]] == i0;
+            carry += __popcll(__ballot(same && tgab[y] != FACE_OUT));
+            if (x <= t0 || !__shfl((int)same, 0, WAVE)) break;
+        }
+        if (st == FACE_OUT) continue;
+        const int u = ids[i - b0];
+        const long long p = row0[1][i - b0] + rank_in_ball(kept, lane, first, c0, carry);
+        const double sz = st == FACE_GABRIEL ? tsize[t] : double_from_ordered(tri_min[t]);
+        out2[3 * p] = u;
+        out2[3 * p + 1] = cd.up_id[e];
+        out2[3 * p + 2] = cd.up_id[cd.tri_f[t]];
+        size2[p] = sz / 1.0e6;
+    }
+    const int qb = tt.base(g), qn = tt.kept[g];
+    for (int x = threadIdx.x; x < qn; x += BLOCK) {
+        const int t = tt.t[qb + x], f2 = tt.t2[qb + x];
+        const int e = cd.tri_e[t], i = cd.edge_i[e];
+        // rank: the group's tetrahedra are in order, all kept
+        int rank = 0;
+        while (rank < x && cd.edge_i[cd.tri_e[tt.t[qb + x - rank - 1]]] == i) rank++;
+        const int u = ids[i - b0];
+        const long long p = row0[2][i - b0] + rank;
+        reinterpret_cast<int4 *>(out3)[p] = make_int4(u, cd.up_id[e], cd.up_id[cd.tri_f[t]], cd.up_id[f2]);
+        size3[p] = tt.size[qb + x] / 1.0e6;
     }
 }
 

@@ -11,7 +11,7 @@
 // ball within 4 s_g (plus a margin) of its core decides the simplices whose
 // owner vertex lies in the core exactly as a build of all balls does.
 #pragma once
-#include "kernels.hpp"
+#include "emit.hpp"
 
 namespace acx {
 
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(BLOCK) k_own_emit(const int *__restrict__ rows
     int v[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int u = 0; u < K; u++) v[u] = sel[rows[(long long)s * K + u]];
-    emit_pack<K>(true, v, size[s], idx_base + p, 0, key[p], pay[p]);
+    emit_pack<K>(v, size[s], idx_base + p, key[p], pay[p]);
     if (K == 4) out_size[p] = size[s];
 }
 

@@ -1,11 +1,11 @@
 // Kernels of a recorded build: the pipeline with every size fixed in advance
 // (grid cells per molecule, candidate capacities), so that a whole build is a
 // fixed sequence of launches with no value read back by the host, and can be
-// captured once in a HIP graph and replayed on new coordinates. Each launch
-// that depends on a count takes it from device memory (the live counts of
-// Counters); when the input does not fit what was recorded, the build stops
-// (every later count 0, reason in Counters::stop) and the host builds again
-// the ordinary way.
+// captured once in a HIP graph and replayed on new coordinates. The launches
+// after the neighbour search run one block per group of balls, whose ranges
+// they take from device memory; when the input does not fit what was recorded,
+// the build stops (reason in Counters::stop, the later kernels return at once)
+// and the host builds again the ordinary way.
 #pragma once
 #include "kernels.hpp"
 
@@ -60,32 +60,17 @@ __global__ void __launch_bounds__(BLOCK) k_plan_grids(const Stats *__restrict__ 
     grids[m] = g;
 }
 
-// After a stage's totals (stage 0: neighbours -> candidate edges; 1:
-// triangles; 2: tetrahedra): the stage's live count, or 0 for every later
-// stage once the build has stopped.
-__global__ void k_plan_guard(Counters *cnt, int stage, int cap) {
+// After the neighbour search: stops the build if a row outgrew its slot, two
+// centres are equal, or the candidate edges or pairs exceed their capacity.
+// Every later kernel of the build returns at once when the build has stopped
+// (k_rec_prefix / k_rec_apply stop it for the output totals).
+__global__ void k_plan_guard(Counters *cnt, int E_cap, int P_cap) {
     if (threadIdx.x != 0) return;
-    const int tot = stage == 0 ? cnt->E : (stage == 1 ? cnt->T : cnt->Q);
     int why = cnt->stop;
     if (cnt->overflow) why |= STOP_SLOT;
     if (cnt->dup) why |= STOP_DUP;
-    if (tot > cap) why |= STOP_CAPACITY;
+    if (cnt->E > E_cap || cnt->P > P_cap) why |= STOP_CAPACITY;
     cnt->stop = why;
-    if (why) {
-        cnt->El = 0;
-        cnt->Tl = 0;
-        cnt->Ql = 0;
-    } else if (stage == 0) {
-        cnt->El = tot;
-    } else if (stage == 1) {
-        cnt->Tl = tot;
-    } else {
-        cnt->Ql = tot;
-    }
-}
-
-__global__ void k_copy_int(const int *__restrict__ src, int *__restrict__ dst) {
-    if (threadIdx.x == 0) *dst = *src;
 }
 
 }  // namespace acx

@@ -50,6 +50,7 @@ struct PredParams {
     double gmax;   // bound on |gamma|: 4 sg2 + W_max
     i64 sgc;       // ceil(sqrt(sg2))
     int force_exact;
+    int fast;      // sg2 < 2^25: 4 rho_a^2 rho_b^2 < 2^52, exact in float64
 };
 
 // a * b for |a|, |b| < 2^23 and |a b| < 2^31 (exact)
@@ -59,13 +60,12 @@ struct Counters {
     unsigned long long exact_fallbacks;
     int dup;       // duplicate centres seen
     int lookup;    // a facet lookup failed (must not happen)
-    int Nn, E, T, Q;  // neighbour entries and candidate counts, copied from scan totals
-    int m0, m1, m2, m3;
-    int overflow;  // a single-pass stage ran out of its per-block room (then the two-pass path runs)
-    // recorded builds only (sizes fixed in advance): the live candidate
-    // counts the later launches read, and why the build stopped (0: it did not)
-    int El, Tl, Ql;
-    int stop;
+    long long Nn, E, P;  // neighbour entries, candidate edges, pairs of upper entries of one ball
+    long long T, Q;      // candidate triangles and tetrahedra
+    int m0, m1, m2, m3;  // kept simplices
+    int vng;             // some ball fails AC2 at its own centre
+    int overflow;        // a row or a group ran out of its single-pass room (then a counted pass runs)
+    int stop;            // recorded builds only: why the build stopped (0: it did not)
 };
 
 __device__ __forceinline__ int sgn128(i128 v) { return (v > 0) - (v < 0); }
@@ -122,6 +122,21 @@ __device__ __forceinline__ Edge edge_setup(int4 v0, int4 v1) {
 __device__ __forceinline__ bool edge_ac3(const Edge &e, i64 aq) {
     const i64 rhs = 4 * (i64)e.den * ((i64)e.v0.w + aq);
     return (i64)e.beta * e.beta <= rhs;
+}
+
+// Whether the grown spheres of two balls of one neighbour row cross, i.e. the
+// pair is a candidate edge. With L = |a|^2 - rho_a^2 - rho_b^2 the test of
+// edge_ac3 reads L^2 <= 4 rho_a^2 rho_b^2 (the two differences from zero are
+// the same polynomial). The balls lie within 2 s_g of a common one, so
+// |a|^2 <= 16 s_g^2 <= 2^30. pp.fast: the right side is an exact float64 below
+// 2^52 while L^2 is exact below 2^53 and rounds to at least 2^53 above.
+__device__ __forceinline__ bool spheres_cross(int4 a, int4 b, const PredParams &pp) {
+    const int dx = b.x - a.x, dy = b.y - a.y, dz = b.z - a.z;
+    const int d2 = m24(dx, dx) + m24(dy, dy) + m24(dz, dz);
+    const int ra = a.w + (int)pp.aq, rb = b.w + (int)pp.aq;
+    const int L = d2 - ra - rb;
+    if (pp.fast) return (double)L * (double)L <= 4.0 * (double)ra * (double)rb;
+    return (i64)L * L <= 4 * (i64)ra * rb;
 }
 
 __device__ __forceinline__ double edge_orthosize(const Edge &e) {
@@ -247,30 +262,28 @@ __device__ __forceinline__ double tri_orthosize(const Tri &t) {
     return M2 / (4.0 * d * d) - (double)t.v0.w;
 }
 
-// Floating-point filter of tri_violation_sign: the sign of P when the
-// rounding bound certifies it, 0 when the exact path has to decide.
-__device__ __forceinline__ int tri_violation_filter(const Tri &t, int4 q) {
+// What the floating-point filter of a triangle's AC2 needs of tri_setup: an
+// AC2 loop keeps this much in registers, and the exact test, which few
+// neighbours need, sets the triangle up again.
+struct TriFilter {
+    int4 v0;
+    double den, Mx, My, Mz, eP;
+};
+
+__device__ __forceinline__ TriFilter tri_filter(const Tri &t) {
+    return TriFilter{t.v0, (double)t.den, t.Mx, t.My, t.Mz, t.eP};
+}
+
+// P = |n|^2 gamma - M.b: its sign when the rounding bound certifies it, 0 when
+// the exact path has to decide.
+__device__ __forceinline__ int tri_violation_filter(const TriFilter &t, int4 q, double &P) {
     const int bx = q.x - t.v0.x, by = q.y - t.v0.y, bz = q.z - t.v0.z;
     const int gam = m24(bx, bx) + m24(by, by) + m24(bz, bz) - q.w + t.v0.w;
-    const double P = (double)t.den * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
+    P = t.den * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
     return (P > t.eP) - (P < -t.eP);
 }
 
 // Exact sign of P (int128), with simulation of simplicity on a tie.
-__device__ __forceinline__ int tri_violation_exact(const Tri &t, int s0, int s1, int s2, int4 q, int sq,
-                                                   const int *perm);
-
-// P = |n|^2 gamma - M.b
-__device__ __forceinline__ int tri_violation_sign(const Tri &t, int s0, int s1, int s2, int4 q, int sq, const int *perm,
-                                                  const PredParams &pp, Counters *cnt) {
-    if (!pp.force_exact) {
-        const int f = tri_violation_filter(t, q);
-        if (f) return f;
-        note_fallback(cnt);
-    }
-    return tri_violation_exact(t, s0, s1, s2, q, sq, perm);
-}
-
 __device__ __forceinline__ int tri_violation_exact(const Tri &t, int s0, int s1, int s2, int4 q, int sq,
                                                    const int *perm) {
     const i64 bx = q.x - t.v0.x, by = q.y - t.v0.y, bz = q.z - t.v0.z;
@@ -332,24 +345,33 @@ __device__ __forceinline__ void tet_exact_M(const Tet &t, i128 &Mx, i128 &My, i1
     Mz = (i128)t.b1 * t.c1z + (i128)t.b2 * t.c2z + (i128)t.b3 * t.c3z;
 }
 
-// AC3 for a tetrahedron: |M|^2 <= 4 D^2 (W0 + alpha).
-__device__ __forceinline__ bool tet_ac3(const Tet &t, const PredParams &pp, Counters *cnt) {
-    const i64 wa = t.v0.w + pp.aq;
-    if (!pp.force_exact) {
-        const double L = t.Mx * t.Mx + t.My * t.My + t.Mz * t.Mz;
-        const double Dd = (double)t.D;
-        const double R = 4.0 * (Dd * Dd) * (double)wa;
-        const double e = 16.0 * ACX_U * (t.Mabs2 + fabs(R));
-        const double diff = L - R;
-        if (diff < -e) return true;
-        if (diff > e) return false;
-        note_fallback(cnt);
-    }
+// AC3 for a tetrahedron: |M|^2 <= 4 D^2 (W0 + alpha). The filter gives 1 (holds)
+// or -1 (fails) where the rounding bound certifies it, 0 where the exact test
+// has to decide.
+__device__ __forceinline__ int tet_ac3_filter(const Tet &t, const PredParams &pp) {
+    const double L = t.Mx * t.Mx + t.My * t.My + t.Mz * t.Mz;
+    const double Dd = (double)t.D;
+    const double R = 4.0 * (Dd * Dd) * (double)(t.v0.w + pp.aq);
+    const double e = 16.0 * ACX_U * (t.Mabs2 + fabs(R));
+    const double diff = L - R;
+    return diff < -e ? 1 : (diff > e ? -1 : 0);
+}
+
+__device__ __forceinline__ bool tet_ac3_exact(const Tet &t, const PredParams &pp) {
     i128 Mx, My, Mz;
     tet_exact_M(t, Mx, My, Mz);
     const i128 L = Mx * Mx + My * My + Mz * Mz;
-    const i128 R = (i128)4 * ((i128)t.D * t.D) * wa;
+    const i128 R = (i128)4 * ((i128)t.D * t.D) * (t.v0.w + pp.aq);
     return L <= R;
+}
+
+__device__ __forceinline__ bool tet_ac3(const Tet &t, const PredParams &pp, Counters *cnt) {
+    if (!pp.force_exact) {
+        const int sg = tet_ac3_filter(t, pp);
+        if (sg) return sg > 0;
+        note_fallback(cnt);
+    }
+    return tet_ac3_exact(t, pp);
 }
 
 __device__ __forceinline__ double tet_orthosize(const Tet &t) {
@@ -358,18 +380,32 @@ __device__ __forceinline__ double tet_orthosize(const Tet &t) {
     return M2 / (4.0 * d * d) - (double)t.v0.w;
 }
 
-// P = sign(D) (D gamma - M.b)
-__device__ __forceinline__ int tet_violation_sign(const Tet &t, int s0, int s1, int s2, int s3, int4 q, int sq,
-                                                  const int *perm, const PredParams &pp, Counters *cnt) {
+// What the filter of a tetrahedron's AC2 needs of tet_setup (see TriFilter).
+struct TetFilter {
+    int4 v0;
+    double D, Mx, My, Mz, eP;
+};
+
+__device__ __forceinline__ TetFilter tet_filter(const Tet &t) {
+    return TetFilter{t.v0, (double)t.D, t.Mx, t.My, t.Mz, t.eP};
+}
+
+// P = sign(D) (D gamma - M.b): its sign when the rounding bound certifies it,
+// 0 when the exact path has to decide.
+__device__ __forceinline__ int tet_violation_filter(const TetFilter &t, int4 q) {
+    const int bx = q.x - t.v0.x, by = q.y - t.v0.y, bz = q.z - t.v0.z;
+    const int gam = m24(bx, bx) + m24(by, by) + m24(bz, bz) - q.w + t.v0.w;
+    const double P = t.D * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
+    const int sD = t.D > 0 ? 1 : -1;
+    return P > t.eP ? sD : (P < -t.eP ? -sD : 0);
+}
+
+// Exact sign of P (int128), with simulation of simplicity on a tie.
+__device__ __forceinline__ int tet_violation_exact(const Tet &t, int s0, int s1, int s2, int s3, int4 q, int sq,
+                                                   const int *perm) {
     const int bx = q.x - t.v0.x, by = q.y - t.v0.y, bz = q.z - t.v0.z;
     const int gam = m24(bx, bx) + m24(by, by) + m24(bz, bz) - q.w + t.v0.w;
     const int sD = t.D > 0 ? 1 : -1;
-    if (!pp.force_exact) {
-        const double P = (double)t.D * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
-        if (P > t.eP) return sD;
-        if (P < -t.eP) return -sD;
-        note_fallback(cnt);
-    }
     i128 Mx, My, Mz;
     tet_exact_M(t, Mx, My, Mz);
     const i128 P = (i128)t.D * gam - (Mx * bx + My * by + Mz * bz);

@@ -25,9 +25,7 @@ constexpr int RS_TILE = RS_BLOCK * RS_IPT;
 static_assert(RS_BINS == RS_BLOCK, "one histogram bin per thread");
 
 __global__ void __launch_bounds__(RS_BLOCK) k_rs_hist(const unsigned *__restrict__ keys, int n, int shift,
-                                                       int *__restrict__ hist, int tiles,
-                                                       const int *__restrict__ live = nullptr) {
-    n = live_count(n, live);
+                                                       int *__restrict__ hist, int tiles) {
     __shared__ int h[RS_BINS];
     h[threadIdx.x] = 0;
     __syncthreads();
@@ -94,12 +92,10 @@ template <class P>
 __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const unsigned *__restrict__ kin, const P *__restrict__ pin,
                                                           unsigned *__restrict__ kout, P *__restrict__ pout, int n,
                                                           int shift, const int *__restrict__ prefix,
-                                                          const int *__restrict__ totals, int tiles,
-                                                          const int *__restrict__ live = nullptr) {
-    n = live_count(n, live);
+                                                          const int *__restrict__ totals, int tiles) {
     // consecutive tiles on one XCD: their pieces of each digit run are
     // adjacent, so the partial lines they write meet in that XCD's L2
-    const int tb = xcd_block(n / RS_TILE + (n % RS_TILE != 0));
+    const int tb = xcd_block();
     constexpr int NW = RS_BLOCK / WAVE;
     constexpr int CHUNK = WAVE * RS_IPT;  // each wave owns a contiguous chunk of the tile
     __shared__ int gbase[RS_BINS];        // output start of each digit for this tile
@@ -205,8 +201,7 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const unsigned *__restr
 constexpr int KS_BLOCK = 256;
 constexpr int KS_PT = 4;
 __global__ void __launch_bounds__(KS_BLOCK) k_key_starts(const unsigned *__restrict__ key, int m, int shift, int nb,
-                                                        int *__restrict__ start, const int *__restrict__ live = nullptr) {
-    m = live_count(m, live);
+                                                        int *__restrict__ start) {
     const long long p0 = ((long long)blockIdx.x * KS_BLOCK + threadIdx.x) * KS_PT;
     if (p0 > m) return;
     unsigned k[KS_PT];

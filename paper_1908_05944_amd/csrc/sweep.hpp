@@ -11,7 +11,7 @@
 // alpha are then integer comparisons, the attachment of Steps 3-5 and a
 // compaction, all streaming over the output order.
 #pragma once
-#include "kernels.hpp"
+#include "emit.hpp"
 
 namespace acx {
 
@@ -36,90 +36,121 @@ __device__ int entry_threshold(double est, i64 lo, i64 hi, F &&ac3) {
 
 constexpr int NO_ENTRY = INT_MAX;  // threshold of a candidate that fails AC2
 
-// Edges: candidate e goes to place p = spos[e] of the output order.
-__global__ void __launch_bounds__(BLOCK) k_sweep_prep_edge(const int4 *__restrict__ atom, const int *__restrict__ up,
-                                                            const int *__restrict__ edge_i, int E,
-                                                            const unsigned char *__restrict__ egab,
-                                                            const int *__restrict__ spos, i64 aq_max,
+// Output record of every ball of a sweep: all its candidates, kept at some
+// alpha or not (tetrahedra: those that pass AC2; the others are in no K_alpha).
+__global__ void __launch_bounds__(BLOCK) k_sweep_counts(Cands cd, Tets tt, int4 *__restrict__ rec) {
+    __shared__ int tc[GROUP], qc[GROUP];
+    const int g = xcd_block();
+    const int b0 = g << cd.gshift, nb = min(1 << cd.gshift, cd.n - b0);
+    tc[threadIdx.x] = qc[threadIdx.x] = 0;
+    __syncthreads();
+    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
+    for (int t = t0 + threadIdx.x; t < t1; t += BLOCK) atomicAdd(&tc[cd.edge_i[cd.tri_e[t]] - b0], 1);
+    const int qb = tt.base(g), qn = tt.kept[g];
+    for (int x = threadIdx.x; x < qn; x += BLOCK) atomicAdd(&qc[cd.edge_i[cd.tri_e[tt.t[qb + x]]] - b0], 1);
+    __syncthreads();
+    const int s = b0 + threadIdx.x;
+    if ((int)threadIdx.x < nb)
+        rec[cd.perm[s]] = make_int4(cd.up_start[s + 1] - cd.up_start[s], tc[threadIdx.x], qc[threadIdx.x], VERT_OUT);
+}
+
+// From the scanned records (base): the place in the output order of candidate
+// c of dimension d owned by sorted ball s is adj[s].d + c (d = 1, 2, 3 in .x,
+// .y, .z).
+__global__ void __launch_bounds__(BLOCK) k_sweep_adj(Cands cd, Tets tt, const int4 *__restrict__ base,
+                                                      int4 *__restrict__ adj) {
+    const int g = blockIdx.x, s = (g << cd.gshift) + threadIdx.x;
+    const bool in = (int)threadIdx.x < (1 << cd.gshift) && s < cd.n;
+    const int u = in ? cd.perm[s] : 0;
+    const int4 lo = in ? base[u] : make_int4(0, 0, 0, 0), hi = in ? base[u + 1] : lo;
+    int tot;
+    const int ft = cd.tri_base[g] + block_exclusive_scan<BLOCK>(hi.y - lo.y, &tot);
+    const int fq = tt.base(g) + block_exclusive_scan<BLOCK>(hi.z - lo.z, &tot);
+    if (in) adj[s] = make_int4(lo.x - cd.up_start[s], lo.y - ft, lo.z - fq, 0);
+}
+
+// Edges: threshold, Size, row and end balls of every candidate, at its place.
+__global__ void __launch_bounds__(BLOCK) k_sweep_prep_edge(Cands cd, int E, const unsigned char *__restrict__ egab,
+                                                            const int4 *__restrict__ adj, i64 aq_max,
                                                             int *__restrict__ thr, double *__restrict__ sz,
-                                                            int2 *__restrict__ ends) {
+                                                            int *__restrict__ rows, int2 *__restrict__ ends) {
     const int e = xcd_block() * BLOCK + threadIdx.x;
     if (e >= E) return;
-    const int i = edge_i[e], j = up[e];
-    const int p = spos[e];
+    const int i = cd.edge_i[e], j = cd.up[e];
+    const int p = adj[i].x + e;
     ends[p] = make_int2(i, j);
+    reinterpret_cast<int2 *>(rows)[p] = make_int2(cd.perm[i], cd.up_id[e]);
     if (!egab[e]) {
         thr[p] = NO_ENTRY;
         return;
     }
-    const int4 vi = atom[i], vj = atom[j];
+    const int4 vi = cd.atom[i], vj = cd.atom[j];
     const Edge ed = edge_setup(vi, vj);
     thr[p] = entry_threshold(edge_orthosize(ed), -(i64)vi.w - 1, aq_max, [&](i64 a) { return edge_ac3(ed, a); });
     sz[p] = edge_size_canon(vi, vj);
 }
 
-// Triangles: threshold, Size (the canonical OrthoSize), and the places of
-// the three edges in the edge output order.
-__global__ void __launch_bounds__(BLOCK) k_sweep_prep_tri(const int4 *__restrict__ atom, const int *__restrict__ up,
-                                                           const int *__restrict__ edge_i, const int *__restrict__ tri_k,
-                                                           const int *__restrict__ tri_e, int T,
-                                                           const unsigned char *__restrict__ tgab,
+// Triangles of a group: threshold, Size (the canonical OrthoSize), row, and
+// the places of the three edges in the edge output order.
+__global__ void __launch_bounds__(BLOCK) k_sweep_prep_tri(Cands cd, const unsigned char *__restrict__ tgab,
                                                            const double *__restrict__ tsize,
-                                                           const int2 *__restrict__ tedge, const int *__restrict__ spos_t,
-                                                           const int *__restrict__ spos_e, PredParams pp,
+                                                           const int4 *__restrict__ adj, PredParams pp,
                                                            int *__restrict__ thr, double *__restrict__ sz,
-                                                           int4 *__restrict__ face, Counters *cnt) {
-    const int t = xcd_block() * BLOCK + threadIdx.x;
-    if (t >= T) return;
-    const int e = tri_e[t];
-    const int p = spos_t[t];
-    const int2 f = tedge[t];
-    face[p] = make_int4(spos_e[e], f.x < 0 ? -1 : spos_e[f.x], f.y < 0 ? -1 : spos_e[f.y], 0);
-    if (!tgab[t]) {
-        thr[p] = NO_ENTRY;
-        return;
+                                                           int *__restrict__ rows, int4 *__restrict__ face,
+                                                           Counters *cnt) {
+    const int g = xcd_block();
+    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
+    for (int t = t0 + threadIdx.x; t < t1; t += BLOCK) {
+        const int e = cd.tri_e[t], f = cd.tri_f[t];
+        const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[f];
+        const int4 a = adj[i];
+        const int p = a.y + t;
+        const int r = find_edge(cd, j, cd.up_id[f]);
+        face[p] = make_int4(a.x + e, a.x + f, r < 0 ? -1 : adj[j].x + r, 0);
+        rows[3LL * p] = cd.perm[i];
+        rows[3LL * p + 1] = cd.up_id[e];
+        rows[3LL * p + 2] = cd.up_id[f];
+        if (!tgab[t]) {
+            thr[p] = NO_ENTRY;
+            continue;
+        }
+        const int4 vi = cd.atom[i], vj = cd.atom[j], vk = cd.atom[k];
+        PredParams q = pp;
+        thr[p] = entry_threshold(tri_orthosize(tri_setup(vi, vj, vk, pp)), -(i64)vi.w - 1, pp.aq, [&](i64 x) {
+            q.aq = x;
+            return tri_candidate(vi, vj, vk, q, cnt);
+        });
+        sz[p] = tsize[t];
     }
-    const int4 vi = atom[edge_i[e]], vj = atom[up[e]], vk = atom[tri_k[t]];
-    PredParams q = pp;
-    thr[p] = entry_threshold(tri_orthosize(tri_setup(vi, vj, vk, pp)), -(i64)vi.w - 1, pp.aq, [&](i64 a) {
-        q.aq = a;
-        return tri_candidate(vi, vj, vk, q, cnt);
-    });
-    sz[p] = tsize[t];
 }
 
-// Tetrahedra: threshold (AC2 from k_tet_ac2<true> in qgab), Size, and the
+// Tetrahedra of a group (those that pass AC2): threshold, Size, row, and the
 // places of the four facets in the triangle output order.
-__global__ void __launch_bounds__(BLOCK) k_sweep_prep_tet(const int4 *__restrict__ atom, const int *__restrict__ up,
-                                                           const int *__restrict__ edge_i, const int *__restrict__ tri_k,
-                                                           const int *__restrict__ tri_e, const int *__restrict__ tet_t,
-                                                           const int *__restrict__ tet_l, int Q,
-                                                           const unsigned char *__restrict__ qgab,
-                                                           const double *__restrict__ qsize,
-                                                           const int4 *__restrict__ tface, const int *__restrict__ spos_q,
-                                                           const int *__restrict__ spos_t, PredParams pp,
+__global__ void __launch_bounds__(BLOCK) k_sweep_prep_tet(Cands cd, Tets tt, const int4 *__restrict__ adj, PredParams pp,
                                                            int *__restrict__ thr, double *__restrict__ sz,
-                                                           int4 *__restrict__ face, Counters *cnt) {
-    const int c = xcd_block() * BLOCK + threadIdx.x;
-    if (c >= Q) return;
-    const int p = spos_q[c];
-    if (!qgab[c]) {
-        thr[p] = NO_ENTRY;
-        return;
+                                                           int *__restrict__ rows, int4 *__restrict__ face,
+                                                           Counters *cnt) {
+    const int g = xcd_block();
+    const int qb = tt.base(g), qn = tt.kept[g];
+    for (int x = qb + threadIdx.x; x < qb + qn; x += BLOCK) {
+        const int t = tt.t[x], f2 = tt.t2[x];
+        const int e = cd.tri_e[t], f = cd.tri_f[t];
+        const int i = cd.edge_i[e], j = cd.up[e];
+        const int4 a = adj[i];
+        const int p = a.z + x;
+        const int4 v0 = cd.atom[i];
+        const Tet te = tet_setup(v0, cd.atom[j], cd.atom[cd.up[f]], cd.atom[cd.up[f2]], pp);
+        PredParams q = pp;
+        thr[p] = entry_threshold(tet_orthosize(te), -(i64)v0.w - 1, pp.aq, [&](i64 y) {
+            q.aq = y;
+            return tet_ac3(te, q, cnt);
+        });
+        sz[p] = tt.size[x];
+        reinterpret_cast<int4 *>(rows)[p] = make_int4(cd.perm[i], cd.up_id[e], cd.up_id[f], cd.up_id[f2]);
+        const int4 fc = tt.face[x];
+        face[p] = make_int4(fc.x < 0 ? -1 : a.y + fc.x, fc.y < 0 ? -1 : a.y + fc.y, fc.z < 0 ? -1 : a.y + fc.z,
+                            fc.w < 0 ? -1 : adj[j].y + fc.w);
     }
-    const int t = tet_t[c];
-    const int e = tri_e[t];
-    const int4 v0 = atom[edge_i[e]];
-    const Tet te = tet_setup(v0, atom[up[e]], atom[tri_k[t]], atom[tet_l[c]], pp);
-    PredParams q = pp;
-    thr[p] = entry_threshold(tet_orthosize(te), -(i64)v0.w - 1, pp.aq, [&](i64 a) {
-        q.aq = a;
-        return tet_ac3(te, q, cnt);
-    });
-    sz[p] = qsize[c];
-    const int4 f = tface[c];
-    auto at = [&](int x) { return x < 0 ? -1 : spos_t[x]; };
-    face[p] = make_int4(at(f.x), at(f.y), at(f.z), at(f.w));
 }
 
 // A kept coface records itself on face f unless f passes AC2 (threshold not
