@@ -738,24 +738,50 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
 
         // ---- binning ----
         tm.mark(ST_BIN);
-        unsigned *ckey = sc.get<unsigned>(n);
-        unsigned *cidx = sc.get<unsigned>(n);
-        int *cell_count = sc.get<int>(ncell + 1);
         int *cell_start = sc.get<int>(ncell + 1);
-        k_cell_key<<<grid_for(n), BLOCK, 0, s>>>(q, n, d_grids, n_mol, ckey, cidx);
-        LAUNCH_CHECK();
-        radix_sort<unsigned>(ckey, cidx, n, bits_for(ncell), s, sc);
-        // the cell table from the populations (most cells are empty, so the
-        // starts are not taken from the sorted keys as the emit's buckets are:
-        // one thread would fill each run of empty cells)
-        fill<int>(cell_count, 0, ncell, s);
-        k_cell_runs<<<grid_for(n), BLOCK, 0, s>>>(ckey, n, cell_count);
-        LAUNCH_CHECK();
-        scan_i32(cell_count, cell_start, ncell, s, sc);
         int4 *atom = sc.get<int4>(n);
         int *perm = sc.get<int>(n);
-        k_gather_atoms<<<grid_for(n), BLOCK, 0, s>>>(q, cidx, ckey, n, atom, perm, cnt);
-        LAUNCH_CHECK();
+        if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
+            k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, (int)ncell, cell_start, atom, perm, cnt);
+            LAUNCH_CHECK();
+        } else {
+            // bucket: at most BIN_CELLS cells, and a bucket of full cells (2.5
+            // times the mean: molecules fill a third to a half of their box)
+            // within BIN_ROWS balls; as few radix passes as that allows, and of
+            // the shifts these passes reach the least that leaves a bucket 128
+            // balls on average
+            const int bits = bits_for(ncell);
+            int most = 0;
+            while (most < BIN_SHIFT && most < bits - 1 &&
+                   (double)(2LL << most) * 2.5 * (double)n <= (double)BIN_ROWS * (double)ncell)
+                most++;
+            int shift = std::max(0, bits - RS_BITS * ((bits - most + RS_BITS - 1) / RS_BITS));
+            while (shift < most && (double)(1LL << shift) * (double)n < 128.0 * (double)ncell) shift++;
+            const int nb = (int)((ncell - 1) >> shift) + 1;
+            const int tiles = (n + RS_TILE - 1) / RS_TILE;
+            unsigned *kin = sc.get<unsigned>(n), *kout = sc.get<unsigned>(n);
+            unsigned *pin = sc.get<unsigned>(n), *pout = sc.get<unsigned>(n);
+            int *hist = sc.get<int>((size_t)RS_BINS * tiles), *totals = sc.get<int>(RS_BINS);
+            int *start = sc.get<int>((size_t)nb + 1);
+            for (int sh = shift; sh < bits; sh += RS_BITS) {
+                const bool first = sh == shift;
+                if (first)
+                    k_cell_hist<<<tiles, RS_BLOCK, 0, s>>>(q, n, d_grids, n_mol, kin, sh, hist, tiles);
+                else
+                    k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, sh, hist, tiles);
+                k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
+                if (first)
+                    k_rs_scatter<unsigned, true><<<tiles, RS_BLOCK, 0, s>>>(kin, nullptr, kout, pout, n, sh, hist, totals, tiles);
+                else
+                    k_rs_scatter<unsigned><<<tiles, RS_BLOCK, 0, s>>>(kin, pin, kout, pout, n, sh, hist, totals, tiles);
+                LAUNCH_CHECK();
+                std::swap(kin, kout);
+                std::swap(pin, pout);
+            }
+            key_starts(kin, n, shift, nb, start, s);
+            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, start, shift, ncell, q, pout, cell_start, atom, perm, cnt);
+            LAUNCH_CHECK();
+        }
 
         // ---- neighbours and candidate edges: one pass into per-block slabs,
         // then compaction; count, scan and fill if a ball's rows overflow ----

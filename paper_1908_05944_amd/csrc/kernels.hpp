@@ -211,8 +211,8 @@ __global__ void __launch_bounds__(BLOCK) k_prune_init(long long T, long long E, 
 }
 
 // ---------------------------------------------------------------------------
-// Binning (Sec. 4.2): cell key per ball, a stable radix sort by key (inside a
-// cell the balls keep input order), then the dense cell table.
+// Binning (Sec. 4.2): the balls sorted by cell (inside a cell in input order)
+// and the dense cell table.
 __device__ __forceinline__ long long cell_id(const Grid &g, int cx, int cy, int cz) {
     if (g.order == ORDER_MORTON)
         return (long long)(spread3((unsigned)cx) | (spread3((unsigned)cy) << 1) | (spread3((unsigned)cz) << 2));
@@ -223,61 +223,205 @@ __device__ __forceinline__ long long cell_of(const Grid &g, int x, int y, int z)
     return cell_id(g, (x - g.ox) / g.s, (y - g.oy) / g.s, (z - g.oz) / g.s);
 }
 
-__global__ void __launch_bounds__(BLOCK) k_cell_key(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
-                                                     int n_mol, unsigned *__restrict__ key, unsigned *__restrict__ idx) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= n) return;
-    const int4 a = q[i];
+__device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *__restrict__ grids, int n_mol) {
     const Grid &g = grids[mol_of(grids, n_mol, i)];
-    key[i] = (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
-    idx[i] = (unsigned)i;
+    return (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
 }
 
-// After the stable sort by cell: the first ball of each cell writes the
-// cell's population (cells are short runs of equal keys).
-__global__ void __launch_bounds__(BLOCK) k_cell_runs(const unsigned *__restrict__ key, int n,
-                                                      int *__restrict__ cell_count) {
-    const int p = blockIdx.x * BLOCK + threadIdx.x;
-    if (p >= n) return;
-    const unsigned c = key[p];
-    if (p > 0 && key[p - 1] == c) return;
-    int e = p + 1;
-    while (e < n && key[e] == c) e++;
-    cell_count[c] = e - p;
-}
+// The balls are sorted by cell in two parts: radix passes over the key bits
+// above a bucket of 2^shift consecutive cells make the bucket's balls
+// contiguous, and k_bin_finish then orders each bucket by cell in LDS, writes
+// its part of the cell table, gathers its balls and checks for equal centres.
+// So the low bits need no pass, and the table no count, fill and scan over all
+// cells (most of them empty).
 
-// Sorted balls and their input indices (one gather per ball), and the check
-// for equal centres: they share a cell, so they are adjacent in the sorted
-// order; each ball compares itself with the following balls of its cell (of
-// this block from LDS, past its end from their inputs).
-__global__ void __launch_bounds__(BLOCK) k_gather_atoms(const int4 *__restrict__ q, const unsigned *__restrict__ idx,
-                                                         const unsigned *__restrict__ key, int n,
-                                                         int4 *__restrict__ atom, int *__restrict__ perm, Counters *cnt) {
-    __shared__ int4 sa[BLOCK];
-    __shared__ unsigned sk[BLOCK];
-    const int b0 = blockIdx.x * BLOCK;
-    const int p = b0 + threadIdx.x;
-    int4 a = make_int4(0, 0, 0, 0);
-    unsigned c = 0;
-    if (p < n) {
-        const int me = (int)idx[p];
-        a = q[me];
-        c = key[p];
-        atom[p] = a;
-        perm[p] = me;
-    }
-    sa[threadIdx.x] = a;
-    sk[threadIdx.x] = c;
+// Keys of a radix tile's balls, and the tile's histogram of the first digit.
+__global__ void __launch_bounds__(RS_BLOCK) k_cell_hist(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
+                                                         int n_mol, unsigned *__restrict__ key, int shift,
+                                                         int *__restrict__ hist, int tiles) {
+    __shared__ int h[RS_BINS];
+    h[threadIdx.x] = 0;
     __syncthreads();
-    if (p >= n) return;
-    bool dup = false;
-    for (int k = p + 1; k < n; k++) {
-        const int t = k - b0;
-        if ((t < BLOCK ? sk[t] : key[k]) != c) break;
-        const int4 o = t < BLOCK ? sa[t] : q[idx[k]];
-        dup |= o.x == a.x && o.y == a.y && o.z == a.z;
+    const int base = blockIdx.x * RS_TILE;
+    int4 a[RS_IPT];
+#pragma unroll
+    for (int r = 0; r < RS_IPT; r++) {
+        const int i = base + r * RS_BLOCK + (int)threadIdx.x;
+        a[r] = i < n ? q[i] : make_int4(0, 0, 0, 0);
     }
-    if (dup) cnt->dup = 1;
+#pragma unroll
+    for (int r = 0; r < RS_IPT; r++) {
+        const int i = base + r * RS_BLOCK + (int)threadIdx.x;
+        if (i >= n) break;
+        const unsigned k = cell_key(a[r], i, grids, n_mol);
+        key[i] = k;
+        atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
+    }
+    __syncthreads();
+    hist[(long long)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+}
+
+// One bucket per block: balls [s, e) of the bucket's cells [k0, k0 + cells).
+constexpr int BIN_BLOCK = 256;
+constexpr int BIN_ROWS = 2048;   // balls of a bucket held in LDS
+constexpr int BIN_SHIFT = 12;    // largest bucket: 2^12 cells
+constexpr int BIN_CELLS = 1 << BIN_SHIFT;
+
+// Exclusive scan of cnt[0..m) in place (m <= BIN_CELLS, all threads).
+__device__ __forceinline__ void bin_scan(int *cnt, int m) {
+    constexpr int PT = BIN_CELLS / BIN_BLOCK;
+    const int per = (m + BIN_BLOCK - 1) / BIN_BLOCK;  // <= PT
+    const int c0 = threadIdx.x * per;
+    int s = 0;
+    for (int u = 0; u < PT && u < per; u++) s += c0 + u < m ? cnt[c0 + u] : 0;
+    int tot;
+    int run = block_exclusive_scan<BIN_BLOCK>(s, &tot);
+    for (int u = 0; u < PT && u < per; u++)
+        if (c0 + u < m) {
+            const int c = cnt[c0 + u];
+            cnt[c0 + u] = run;
+            run += c;
+        }
+    __syncthreads();
+}
+
+// start: first ball of every bucket (nb + 1 entries). Inside a cell the balls
+// keep input order (the radix passes are stable; the LDS places of a cell are
+// ranked). gidx: n entries of scratch, for a bucket with more than BIN_ROWS balls.
+__global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ idx,
+                                                           const int *__restrict__ start, int shift, long long ncell,
+                                                           const int4 *__restrict__ q, unsigned *__restrict__ gidx,
+                                                           int *__restrict__ cell_start, int4 *__restrict__ atom,
+                                                           int *__restrict__ perm, Counters *cnt) {
+    __shared__ int cc[BIN_CELLS];              // balls per cell, then each cell's first ball, then its end
+    __shared__ unsigned short sc[BIN_ROWS];    // cell of each ball, in load order
+    __shared__ unsigned short so[BIN_ROWS];    // load positions by cell
+    const int b = blockIdx.x, t = threadIdx.x;
+    const int s = start[b], rows = start[b + 1] - s;
+    const long long k0 = (long long)b << shift;
+    const int cells = (int)min((long long)1 << shift, ncell - k0);
+    if (rows == 0) {
+        for (int c = t; c < cells; c += BIN_BLOCK) cell_start[k0 + c] = s;
+        if (b == gridDim.x - 1 && t == 0) cell_start[ncell] = s;
+        return;
+    }
+    for (int c = t; c < cells; c += BIN_BLOCK) cc[c] = 0;
+    __syncthreads();
+    const bool lds = rows <= BIN_ROWS;
+    for (int p = t; p < rows; p += BIN_BLOCK) {
+        const int c = (int)((long long)key[s + p] - k0);
+        if (lds) sc[p] = (unsigned short)c;
+        atomicAdd(&cc[c], 1);
+    }
+    __syncthreads();
+    bin_scan(cc, cells);
+    for (int c = t; c < cells; c += BIN_BLOCK) cell_start[k0 + c] = s + cc[c];
+    if (b == gridDim.x - 1 && t == 0) cell_start[ncell] = s + rows;
+    __syncthreads();
+    if (lds) {
+        for (int p = t; p < rows; p += BIN_BLOCK) so[atomicAdd(&cc[sc[p]], 1)] = (unsigned short)p;
+        __syncthreads();
+        // cc[c]: end of cell c
+        for (int x = t; x < rows; x += BIN_BLOCK) {
+            const int p = so[x], c = sc[p];
+            const int c0 = c > 0 ? cc[c - 1] : 0, c1 = cc[c];
+            int rank = 0;
+            for (int y = c0; y < c1; y++) rank += so[y] < p;
+            const unsigned id = idx[s + p];
+            const int4 a = q[id];
+            atom[s + c0 + rank] = a;
+            perm[s + c0 + rank] = (int)id;
+            // equal centres share a cell: compare with the cell's earlier balls
+            bool dup = false;
+            for (int y = c0; y < c1; y++)
+                if (so[y] < p) {
+                    const int4 o = q[idx[s + so[y]]];
+                    dup |= o.x == a.x && o.y == a.y && o.z == a.z;
+                }
+            if (dup) cnt->dup = 1;
+        }
+        return;
+    }
+    for (int p = t; p < rows; p += BIN_BLOCK) gidx[s + atomicAdd(&cc[(int)((long long)key[s + p] - k0)], 1)] = idx[s + p];
+    __threadfence_block();
+    __syncthreads();
+    for (int p = t; p < rows; p += BIN_BLOCK) {
+        const int c = (int)((long long)key[s + p] - k0);
+        const int c0 = c > 0 ? cc[c - 1] : 0, c1 = cc[c];
+        const unsigned id = idx[s + p];
+        const int4 a = q[id];
+        int rank = 0;
+        bool dup = false;
+        for (int y = c0; y < c1; y++) {
+            const unsigned o = gidx[s + y];
+            if (o >= id) continue;
+            rank++;
+            const int4 v = q[o];
+            dup |= v.x == a.x && v.y == a.y && v.z == a.z;
+        }
+        atom[s + c0 + rank] = a;
+        perm[s + c0 + rank] = (int)id;
+        if (dup) cnt->dup = 1;
+    }
+}
+
+// The whole binning of up to SMALL_BALLS balls on up to SMALL_CELLS cells, in
+// one block: keys, cell table, sorted balls and the check for equal centres
+// (the passes above cost a small build five launches of some microseconds).
+constexpr int SMALL_BLOCK = 1024;
+constexpr int SMALL_BALLS = 2048;
+constexpr int SMALL_CELLS = 12288;
+__global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
+                                                            int n_mol, int ncell, int *__restrict__ cell_start,
+                                                            int4 *__restrict__ atom, int *__restrict__ perm,
+                                                            Counters *cnt) {
+    __shared__ int cc[SMALL_CELLS];
+    __shared__ unsigned short sc[SMALL_BALLS], so[SMALL_BALLS];
+    const int t = threadIdx.x;
+    for (int c = t; c < ncell; c += SMALL_BLOCK) cc[c] = 0;
+    __syncthreads();
+    for (int i = t; i < n; i += SMALL_BLOCK) {
+        const unsigned k = cell_key(q[i], i, grids, n_mol);
+        sc[i] = (unsigned short)k;
+        atomicAdd(&cc[k], 1);
+    }
+    __syncthreads();
+    constexpr int PT = SMALL_CELLS / SMALL_BLOCK;
+    int c[PT], sum = 0, tot;
+#pragma unroll
+    for (int u = 0; u < PT; u++) {
+        c[u] = t * PT + u < ncell ? cc[t * PT + u] : 0;
+        sum += c[u];
+    }
+    int run = block_exclusive_scan<SMALL_BLOCK>(sum, &tot);
+#pragma unroll
+    for (int u = 0; u < PT; u++)
+        if (t * PT + u < ncell) {
+            cell_start[t * PT + u] = run;
+            cc[t * PT + u] = run;
+            run += c[u];
+        }
+    if (t == 0) cell_start[ncell] = n;
+    __syncthreads();
+    for (int i = t; i < n; i += SMALL_BLOCK) so[atomicAdd(&cc[sc[i]], 1)] = (unsigned short)i;
+    __syncthreads();
+    for (int x = t; x < n; x += SMALL_BLOCK) {
+        const int i = so[x], k = sc[i];
+        const int c0 = k > 0 ? cc[k - 1] : 0, c1 = cc[k];
+        const int4 a = q[i];
+        int rank = 0;
+        bool dup = false;
+        for (int y = c0; y < c1; y++) {
+            const int o = so[y];
+            if (o >= i) continue;
+            rank++;
+            const int4 v = q[o];
+            dup |= v.x == a.x && v.y == a.y && v.z == a.z;
+        }
+        atom[c0 + rank] = a;
+        perm[c0 + rank] = i;
+        if (dup) cnt->dup = 1;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -405,7 +549,7 @@ k_neighbours(const int4 *__restrict__ atom, const int *__restrict__ perm, int n,
                                 const int d2 = __mul24(dx, dx) + __mul24(dy, dy) + __mul24(dz, dz);
                                 const int rb2 = bb.w + (int)pp.aq;
                                 const int L = d2 - ra - rb2;
-                                // d2 == 0: the ball itself (equal centres are reported by k_gather_atoms)
+                                // d2 == 0: the ball itself (equal centres are reported by the binning)
                                 meet = (d2 <= lim) & (d2 != 0) &
                                        ((L <= 0) | ((double)L * (double)L <= ra4 * (double)rb2));
                             } else {
@@ -417,7 +561,7 @@ k_neighbours(const int4 *__restrict__ atom, const int *__restrict__ perm, int n,
                                 const int d2 = dx * dx + dy * dy + dz * dz;
                                 const int rb2 = bb.w + (int)pp.aq;
                                 const int L = d2 - ra - rb2;
-                                // grown balls meet: d <= rho_a + rho_b; equal centres are reported by k_gather_atoms
+                                // grown balls meet: d <= rho_a + rho_b; equal centres are reported by the binning
                                 meet = (j != i) & (d2 <= lim) & (d2 != 0) & (rb2 >= 0) &
                                        ((L <= 0) | ((i64)L * L <= 4 * (i64)ra * rb2));
                             }

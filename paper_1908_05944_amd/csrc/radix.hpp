@@ -88,7 +88,8 @@ __device__ __forceinline__ uint4 rs_to_reg(const uint3 &p) { return make_uint4(p
 template <class P, class R> __device__ __forceinline__ P rs_from_reg(const R &r) { return r; }
 template <> __device__ __forceinline__ uint3 rs_from_reg<uint3, uint4>(const uint4 &r) { return make_uint3(r.x, r.y, r.z); }
 
-template <class P>
+// IOTA: the payload of element i is i itself (pin is not read).
+template <class P, bool IOTA = false>
 __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const unsigned *__restrict__ kin, const P *__restrict__ pin,
                                                           unsigned *__restrict__ kout, P *__restrict__ pout, int n,
                                                           int shift, const int *__restrict__ prefix,
@@ -131,7 +132,8 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const unsigned *__restr
     for (int r = 0; r < RS_IPT; r++) {
         const long long idx = base + (long long)r * WAVE + lane;
         key[r] = idx < n ? kin[idx] : 0u;
-        pv[r] = idx < n ? rs_to_reg(pin[idx]) : R{};
+        if constexpr (IOTA) pv[r] = (R)idx;
+        else pv[r] = idx < n ? rs_to_reg(pin[idx]) : R{};
     }
 #pragma unroll
     for (int r = 0; r < RS_IPT; r++) {
