@@ -17,6 +17,7 @@
 #include <queue>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "alphacx.h"
@@ -740,9 +741,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         tm.mark(ST_BIN);
         int *cell_start = sc.get<int>(ncell + 1);
         int4 *atom = sc.get<int4>(n);
+        float4 *sball = sc.get<float4>(n);
         int *perm = sc.get<int>(n);
         if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
-            k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, (int)ncell, cell_start, atom, perm, cnt);
+            k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, (int)ncell, cell_start, atom, sball,
+                                                 (int)aq, perm, cnt);
             LAUNCH_CHECK();
         } else {
             // bucket: at most BIN_CELLS cells, and a bucket of full cells (2.5
@@ -779,7 +782,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 std::swap(pin, pout);
             }
             key_starts(kin, n, shift, nb, start, s);
-            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, start, shift, ncell, q, pout, cell_start, atom, perm, cnt);
+            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, start, shift, ncell, q, pout, cell_start, atom, sball,
+                                                   (int)aq, perm, cnt);
             LAUNCH_CHECK();
         }
 
@@ -791,49 +795,52 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         long long *vert_min = sc.get<long long>(n);
         const unsigned nbN = grid_for(n);
         // slot per ball: wide for grown radii between 1.9 and 2.6 A (alpha > 0
-        // with van der Waals radii), where rows outgrow 16 entries; beyond,
-        // rows outgrow 32 too and the counted fill runs anyway
-        const int slot = (pp.sgc > 1900 && pp.sgc <= 2600) ? NB_SLOT_WIDE : NB_SLOT;
+        // with van der Waals radii), where rows outgrow 16 entries, wider still
+        // up to 3.4 A (solvent-accessible radii); beyond, the counted fill
+        const int slot = pp.sgc <= 1900 ? NB_SLOT : pp.sgc <= 2600 ? NB_SLOT_WIDE : pp.sgc <= 3400 ? NB_SLOT_SAS : NB_SLOT;
+        // lanes per ball: the search of a few balls is a chain of dependent
+        // loads; from 2^18 balls on one lane each fills the GPU. Rows of the
+        // widest slot are always shared by four (a lane lists at most 32).
+        const int lpb = slot == NB_SLOT_SAS ? 4 : n >= (1 << 18) ? 1 : n >= (1 << 13) ? 4 : 16;
         if (fx && fx->learn) fx->slot = slot;
-        const long long nb_slab = (long long)BLOCK * slot;
-        int *nslab = sc.get<int>((size_t)nbN * nb_slab + NBR_PAD);
-        unsigned *upmask = sc.get<unsigned>(n);
-        const int nbs = (int)(nbN + 3) & ~3;
+        const unsigned nbB = (unsigned)((n + BLOCK / lpb - 1) / (BLOCK / lpb));  // blocks of the search
+        int *nslab = sc.get<int>((size_t)nbB * (BLOCK / lpb) * slot + NBR_PAD);
+        const int nbs = (int)(nbB + 3) & ~3;
         int *nbtot = sc.get<int>(3 * (size_t)nbs);
-        int *uoff = sc.get<int>(nbN), *poff = sc.get<int>(nbN);
+        int *uoff = sc.get<int>(nbB), *poff = sc.get<int>(nbB);
         // balls of a group: enough groups to fill the GPU, else as many balls as
         // a block's steps serve well (fewer waits per ball)
-        const int gshift = n >= (1 << 18) ? 8 : (n >= (1 << 17) ? 7 : 6);
+        int gshift = 4;
+        while (gshift < 8 && (n >> gshift) >= 2048) gshift++;
         const int groups = ((n - 1) >> gshift) + 1;
         unsigned char *eng = sc.get<unsigned char>(n);
         int *pair_base = sc.get<int>((size_t)groups + 1);
         const int *stop = fixed ? &cnt->stop : nullptr;  // kernels of a stopped recorded build return at once
-        // the fast exact pair test applies when every scanned offset stays
-        // below 26 A per axis, s_g^2 < 2^25 and alpha >= 0 (see k_neighbours)
-        bool nb_fast = pp.aq >= 0 && pp.sg2 < (1LL << 25);
-        for (const Grid &g : (fixed ? fx->grids : grids))
-            nb_fast = nb_fast && (long long)(g.reach + 1) * g.s < 26000;
+        // f(SLOT, LPB) with the two as constants
+        auto with_slot = [&](auto &&f) {
+            using std::integral_constant;
+            auto lanes = [&](auto sl) {
+                if (lpb == 1) f(sl, integral_constant<int, 1>{});
+                else if (lpb == 4) f(sl, integral_constant<int, 4>{});
+                else f(sl, integral_constant<int, 16>{});
+            };
+            if (slot == NB_SLOT_SAS) f(integral_constant<int, NB_SLOT_SAS>{}, integral_constant<int, 4>{});
+            else if (slot == NB_SLOT_WIDE) lanes(integral_constant<int, NB_SLOT_WIDE>{});
+            else lanes(integral_constant<int, NB_SLOT>{});
+        };
         tm.mark(ST_NBR_COUNT);
-        if (slot == NB_SLOT_WIDE && nb_fast)
-            k_neighbours<NB_ONEPASS, NB_SLOT_WIDE, true><<<nbN, BLOCK, 0, s>>>(
-                atom, perm, n, d_grids, n_mol, cell_start, pp, deg_n, deg_up, upmask, nslab, nbtot, nullptr, nullptr,
-                nullptr, nullptr, nullptr, vgab, vert_min, cnt);
-        else if (slot == NB_SLOT_WIDE)
-            k_neighbours<NB_ONEPASS, NB_SLOT_WIDE><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp,
-                                                                        deg_n, deg_up, upmask, nslab, nbtot, nullptr,
-                                                                        nullptr, nullptr, nullptr, nullptr, vgab, vert_min,
-                                                                        cnt);
-        else if (nb_fast)
-            k_neighbours<NB_ONEPASS, NB_SLOT, true><<<nbN, BLOCK, 0, s>>>(
-                atom, perm, n, d_grids, n_mol, cell_start, pp, deg_n, deg_up, upmask, nslab, nbtot, nullptr, nullptr,
-                nullptr, nullptr, nullptr, vgab, vert_min, cnt);
-        else
-            k_neighbours<NB_ONEPASS, NB_SLOT><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp, deg_n,
-                                                                   deg_up, upmask, nslab, nbtot, nullptr, nullptr,
-                                                                   nullptr, nullptr, nullptr, vgab, vert_min, cnt);
+        with_slot([&](auto sl, auto lp) {
+            constexpr int SLOT = decltype(sl)::value, LPB = decltype(lp)::value;
+            if (n_mol == 1)
+                k_neighbours<SLOT, LPB, true><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp,
+                                                                   deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
+            else
+                k_neighbours<SLOT, LPB, false><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp,
+                                                                    deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
+        });
         LAUNCH_CHECK();
         tm.mark(ST_NBR_SCAN);
-        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbN, nbs, uoff, poff, cnt);
+        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbB, nbs, uoff, poff, cnt);
         LAUNCH_CHECK();
         Counters c0{};
         if (fixed) {
@@ -848,7 +855,9 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const bool nbr_two_pass = c0.overflow != 0;
         int *pairs = nullptr;
         if (nbr_two_pass) {
-            // exact totals: neighbour entries, candidate edges, pairs
+            // exact counts and totals: neighbour entries, candidate edges, pairs
+            k_nbr_rows<false><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp, deg_n, deg_up, vgab,
+                                                   nullptr, nullptr, nullptr, nullptr, nullptr, vert_min, cnt);
             pairs = sc.get<int>(groups);
             k_group_pairs<<<(groups + NWAVE - 1) / NWAVE, BLOCK, 0, s>>>(deg_up, n, gshift, groups, pairs, eng);
             LAUNCH_CHECK();
@@ -867,7 +876,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         if (fx && fx->learn) {
             fx->E = E;
             fx->P = c0.P;
-            fx->two_pass |= nbr_two_pass || counted;
+            // (rows of the widest slot have no recorded build either)
+            fx->two_pass |= nbr_two_pass || counted || slot == NB_SLOT_SAS;
         }
         // neighbour rows: in the slabs after the one-pass search, else in CSR
         const size_t E1 = E > 0 ? E : 1;
@@ -875,27 +885,23 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         int *up = sc.get<int>(E1), *up_id = sc.get<int>(E1), *edge_i = sc.get<int>(E1);
         tm.mark(ST_NBR_FILL);
         if (!nbr_two_pass) {
-            if (slot == NB_SLOT_WIDE)
-                k_nbr_compact<NB_SLOT_WIDE><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uoff, poff, perm,
-                                                                 nbr_start, up_start, up, up_id, edge_i, pair_base, gshift,
-                                                                 eng, stop);
-            else
-                k_nbr_compact<NB_SLOT><<<nbN, BLOCK, 0, s>>>(deg_n, deg_up, upmask, n, nslab, uoff, poff, perm, nbr_start,
-                                                            up_start, up, up_id, edge_i, pair_base, gshift, eng, stop);
+            with_slot([&](auto sl, auto lp) {
+                constexpr int SLOT = decltype(sl)::value, LPB = decltype(lp)::value;
+                // the balls of a block: as many as one lane each where the search
+                // had one lane per ball, else one wave's
+                constexpr int CB = LPB == 1 ? BLOCK : WAVE;
+                k_nbr_compact<SLOT, LPB, CB><<<(n + CB - 1) / CB, BLOCK, 0, s>>>(deg_n, deg_up, n, nslab, uoff, poff, perm,
+                                                                                nbr_start, up_start, up, up_id, edge_i,
+                                                                                pair_base, gshift, eng, stop);
+            });
             LAUNCH_CHECK();
         } else {
             scan_i32(deg_n, nbr_start, n, s, sc);
             scan_i32(deg_up, up_start, n, s, sc);
             if (!counted) scan_i32(pairs, pair_base, groups, s, sc);
             int *up_scan = sc.get<int>(E1), *id_scan = sc.get<int>(E1);
-            if (nb_fast)
-                k_neighbours<NB_FILL, NB_SLOT, true><<<nbN, BLOCK, 0, s>>>(
-                    atom, perm, n, d_grids, n_mol, cell_start, pp, nullptr, nullptr, nullptr, nullptr, nullptr, nbr_start,
-                    up_start, nbr, up_scan, edge_i, vgab, vert_min, cnt);
-            else
-                k_neighbours<NB_FILL, NB_SLOT><<<nbN, BLOCK, 0, s>>>(atom, perm, n, d_grids, n_mol, cell_start, pp, nullptr,
-                                                                    nullptr, nullptr, nullptr, nullptr, nbr_start,
-                                                                    up_start, nbr, up_scan, edge_i, vgab, vert_min, cnt);
+            k_nbr_rows<true><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp, nullptr, nullptr,
+                                                  nullptr, nbr_start, up_start, nbr, up_scan, edge_i, vert_min, cnt);
             k_up_ids<<<grid_for(E), BLOCK, 0, s>>>(up_scan, E, perm, id_scan);
             k_up_rank<<<grid_for(E), BLOCK, 0, s>>>(up_scan, id_scan, E, edge_i, up_start, up, up_id);
             LAUNCH_CHECK();
@@ -961,7 +967,9 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             k_tri_ac2<false><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tsize, apex, cnt, stop);
         LAUNCH_CHECK();
         Tets tt{};
-        tt.cap = (pp.sgc > 2000 ? 16 : 8) << gshift;
+        // entries a ball: 2 to 3 times the candidates of dense parts at 0.05 atoms
+        // per A^3, and some more for the spread of small groups
+        tt.cap = ((pp.sgc <= 2000 ? 8 : pp.sgc <= 2350 || use_apex ? 16 : 48) << gshift) + (pp.sgc <= 2000 ? 64 : 320);
         tt.num = sc.get<int>(groups);
         tt.kept = sc.get<int>(groups);
         tt.cand = sc.get<int>(groups);

@@ -223,6 +223,14 @@ __device__ __forceinline__ long long cell_of(const Grid &g, int x, int y, int z)
     return cell_id(g, (x - g.ox) / g.s, (y - g.oy) / g.s, (z - g.oz) / g.s);
 }
 
+// Float32 form of a sorted ball for the scan; rho NaN where W + alpha < 0 (the
+// ball meets none).
+__device__ __forceinline__ float4 scan_ball(const int4 &a, int aq) {
+    const int r2 = a.w + aq;  // below 2^26: rounded by at most 2^-24
+    return make_float4((float)a.x, (float)a.y, (float)a.z,
+                       r2 >= 0 ? sqrtf((float)r2) * (1.0f + 1.0f / (1 << 19)) : __int_as_float(0x7fc00000));
+}
+
 __device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *__restrict__ grids, int n_mol) {
     const Grid &g = grids[mol_of(grids, n_mol, i)];
     return (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
@@ -292,7 +300,8 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
                                                            const int *__restrict__ start, int shift, long long ncell,
                                                            const int4 *__restrict__ q, unsigned *__restrict__ gidx,
                                                            int *__restrict__ cell_start, int4 *__restrict__ atom,
-                                                           int *__restrict__ perm, Counters *cnt) {
+                                                           float4 *__restrict__ sball, int aq, int *__restrict__ perm,
+                                                           Counters *cnt) {
     __shared__ int cc[BIN_CELLS];              // balls per cell, then each cell's first ball, then its end
     __shared__ unsigned short sc[BIN_ROWS];    // cell of each ball, in load order
     __shared__ unsigned short so[BIN_ROWS];    // load positions by cell
@@ -330,6 +339,7 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
             const unsigned id = idx[s + p];
             const int4 a = q[id];
             atom[s + c0 + rank] = a;
+            sball[s + c0 + rank] = scan_ball(a, aq);
             perm[s + c0 + rank] = (int)id;
             // equal centres share a cell: compare with the cell's earlier balls
             bool dup = false;
@@ -360,6 +370,7 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
             dup |= v.x == a.x && v.y == a.y && v.z == a.z;
         }
         atom[s + c0 + rank] = a;
+        sball[s + c0 + rank] = scan_ball(a, aq);
         perm[s + c0 + rank] = (int)id;
         if (dup) cnt->dup = 1;
     }
@@ -373,8 +384,8 @@ constexpr int SMALL_BALLS = 2048;
 constexpr int SMALL_CELLS = 12288;
 __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
                                                             int n_mol, int ncell, int *__restrict__ cell_start,
-                                                            int4 *__restrict__ atom, int *__restrict__ perm,
-                                                            Counters *cnt) {
+                                                            int4 *__restrict__ atom, float4 *__restrict__ sball,
+                                                            int aq, int *__restrict__ perm, Counters *cnt) {
     __shared__ int cc[SMALL_CELLS];
     __shared__ unsigned short sc[SMALL_BALLS], so[SMALL_BALLS];
     const int t = threadIdx.x;
@@ -419,241 +430,274 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restric
             dup |= v.x == a.x && v.y == a.y && v.z == a.z;
         }
         atom[c0 + rank] = a;
+        sball[c0 + rank] = scan_ball(a, aq);
         perm[c0 + rank] = i;
         if (dup) cnt->dup = 1;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Neighbour lists and candidate edges (Sec. 4.3, first step). A thread per
-// ball scans the cells within `reach`; cells of one grid row are contiguous
-// in the sorted order, so each (dz, dy) row is one contiguous range. The
-// pass also decides AC2 for the ball as a vertex (Step 5): every ball that
-// could be strictly closer in power to its centre is in its neighbour list.
+// Neighbour lists and candidate edges (Sec. 4.3, first step). The cells of one
+// grid row are contiguous in the sorted order, so a ball scans one contiguous
+// range per (dz, dy) row of the cells within `reach`. The pass also decides
+// AC2 for the ball as a vertex (Step 5): every ball that could be strictly
+// closer in power to its centre is in its neighbour list.
 // A candidate edge belongs to its end with the smaller input id: a ball's
 // upper row holds the other ends with larger input ids, so that every simplex
 // belongs to the ball that comes first in its output row.
-// MODE: NB_ONEPASS writes each ball's neighbour row into an LDS slot of
-// SLOT entries and marks in a 32-bit mask which of them are upper
-// candidate edges (the upper row is a filtered part of the neighbour row);
-// the block packs the rows into a slab of its own, and k_nbr_compact writes
-// the upper rows into place, by input id, once the block totals are scanned.
-// Exact counts are kept; a ball with more than SLOT neighbours sets
-// cnt->overflow, after which the host runs NB_FILL over the scanned counts
-// instead (same result). NB_FILL writes the rows into the CSR rows the counts
-// sized (each thread's row contiguous, consecutive rows adjacent; the upper
-// rows in scan order, k_up_rank orders them).
-enum { NB_ONEPASS = 0, NB_FILL = 1 };
+//
+// The scan tests |p_j - p_i|^2 <= (rho_i + rho_j)^2 in float32, on the balls as
+// float4 {x, y, z, rho} with rho = sqrt(W + alpha): coordinates below 2^19 are
+// exact and so are their differences, the squares and rho are within 2^-21 of
+// their values, and rho is scaled up by 2^-19 (scan_ball), so no neighbour
+// is missed. The balls that pass are listed and then tested exactly: where the
+// wave's lanes are mostly busy, and where one ball in a million fails. (The
+// exact test of every scanned ball, in integers with a float64 comparison,
+// cost 24 instructions against 10.)
+
+// Whether the grown balls of a and b meet (d <= rho_a + rho_b), exactly, for
+// balls that passed the scan (so |b - a|^2 < 2^29); not for a ball and itself.
+__device__ __forceinline__ bool balls_meet(const int4 &a, const int4 &b, const PredParams &pp) {
+    const int dx = b.x - a.x, dy = b.y - a.y, dz = b.z - a.z;
+    const int d2 = m24(dx, dx) + m24(dy, dy) + m24(dz, dz);
+    const int ra = a.w + (int)pp.aq, rb = b.w + (int)pp.aq;
+    const int L = d2 - ra - rb;
+    if (L <= 0) return true;
+    if (pp.fast) return (double)L * (double)L <= 4.0 * (double)ra * (double)rb;
+    return (i64)L * L <= 4 * (i64)ra * rb;
+}
+
+// (x - o) / s for 0 <= x - o < 2^21: float32 quotient, corrected.
+__device__ __forceinline__ int cell_coord(int x, int o, int s, float inv) {
+    const int t = x - o;
+    int c = (int)((float)t * inv);
+    const int r = t - c * s;
+    c += (r >= s) - (r < 0);
+    return c;
+}
+
+// Calls f(j) for every sorted ball j (i itself among them) that passes the
+// scan, of the rows part, part + parts, ... of ball i's cell neighbourhood.
+template <class F>
+__device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, int i, const float4 *__restrict__ sball,
+                                          const int *__restrict__ cell_start, const PredParams &pp, int part, int parts,
+                                          F &&f) {
+    const float inv = 1.0f / (float)g.s;
+    const int cx = cell_coord(a.x, g.ox, g.s, inv), cy = cell_coord(a.y, g.oy, g.s, inv),
+              cz = cell_coord(a.z, g.oz, g.s, inv);
+    const int x0 = max(cx - g.reach, 0), x1 = min(cx + g.reach, g.nx - 1);
+    const int y0 = max(cy - g.reach, 0), y1 = min(cy + g.reach, g.ny - 1);
+    const int z0 = max(cz - g.reach, 0), z1 = min(cz + g.reach, g.nz - 1);
+    const int ny = y1 - y0 + 1, rows = ny * (z1 - z0 + 1);
+    const int lim = 4 * (int)pp.sg2;     // (2 s_g)^2 < 2^28
+    const int reach1 = 2 * (int)pp.sgc;  // 2 ceil(s_g) <= 2^14
+    const float4 me = sball[i];
+    auto scan_range = [&](int s, int e) {
+        // four loads in flight (past the range its last ball again, not used)
+        for (int j = s; j < e; j += 4) {
+            float4 b[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) b[u] = sball[min(j + u, e - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const float dx = b[u].x - me.x, dy = b[u].y - me.y, dz = b[u].z - me.z;
+                const float rho = me.w + b[u].w;
+                if ((j + u < e) & (dx * dx + dy * dy + dz * dz <= rho * rho)) f(j + u);
+            }
+        }
+    };
+    // a row's balls, or none where all its cells lie farther than 2 s_g
+    auto row_of = [&](int y, int z) {
+        const int zlo = g.oz + z * g.s, ylo = g.oy + y * g.s;
+        const int dz = max(max(zlo - a.z, a.z - (zlo + g.s - 1)), 0), dy = max(max(ylo - a.y, a.y - (ylo + g.s - 1)), 0);
+        const bool far = dz > reach1 || dy > reach1 || lim - dz * dz < dy * dy;
+        const long long rb = g.base + ((long long)z * g.ny + y) * g.nx;
+        return far ? make_int2(0, 0) : make_int2(cell_start[rb + x0], cell_start[rb + x1 + 1]);
+    };
+    if (rows <= 0 || g.reach < 0) return;  // reach < 0: a stopped recorded build's grid
+    if (g.order == ORDER_MORTON) {
+        for (int r = part; r < rows; r += parts)
+            for (int x = x0; x <= x1; x++) {
+                const long long c = g.base + cell_id(g, x, y0 + r % ny, z0 + r / ny);
+                scan_range(cell_start[c], cell_start[c + 1]);
+            }
+        return;
+    }
+    int y = y0 + part, z = z0;
+    while (y > y1) {
+        y -= ny;
+        z++;
+    }
+    int2 next = z <= z1 ? row_of(y, z) : make_int2(0, 0);
+    while (z <= z1) {
+        // the next row's bounds are loaded while this row is scanned
+        const int2 now = next;
+        y += parts;
+        while (y > y1) {
+            y -= ny;
+            z++;
+        }
+        if (z <= z1) next = row_of(y, z);
+        scan_range(now.x, now.y);
+    }
+}
+
+// One pass: LPB lanes per ball, each scanning its share of the rows into an LDS
+// list of LSLOT entries (a launch of few balls is a chain of dependent loads,
+// which more lanes shorten; a launch of many fills the GPU with one lane per
+// ball, 8 waves per SIMD). The lanes' lists are packed, block by block, into a
+// slab of BLOCK / LPB balls x SLOT entries, each ball's upper entries first;
+// k_nbr_compact puts the upper rows into place once the block totals are
+// scanned. Exact counts are kept unless a row outgrows its room; then
+// cnt->overflow is set, and the host counts with k_nbr_count and fills with
+// k_nbr_fill (same result).
 // Slot sizes: 16 holds every row of the van der Waals workloads at alpha = 0
-// (largest degree 14); 32 serves grown radii up to about 2.6 A.
+// (largest degree 14); 32 serves grown radii up to about 2.6 A, 128 the
+// solvent-accessible ones up to 3.4 A (43 entries on average).
 constexpr int NB_SLOT = 16;
 constexpr int NB_SLOT_WIDE = 32;
-
-// FAST: the pair test without clamping and with full-rate arithmetic, for
-// grids where it is exact (the launch checks: every scanned offset below
-// 26 A per axis, s_g^2 < 2^25 mA^2, alpha >= 0): offsets of balls of cells
-// within `reach` are below (reach + 1) s, so d^2 < 2^31 and each square is a
-// 24-bit product; the grown balls meet iff L = d^2 - rho_a^2 - rho_b^2 <= 0
-// or L^2 <= 4 rho_a^2 rho_b^2, and in float64 4 rho_a^2 rho_b^2 < 2^52 is
-// exact while L^2 is exact below 2^53 and, above, rounds to at least 2^53:
-// the comparison is decided exactly either way.
-// The one-pass kernel with 16-entry slots runs eight waves per SIMD (64
-// registers, a few values spilled; its LDS allows eight blocks per CU): the
-// eighth wave hides more of the latency of the cell-row loads than the
-// spills cost (0.259 ms against 0.268 at the compiler's 66 registers and
-// seven waves, on the 3M-atom shell). The other forms are held to fewer
-// waves by their LDS.
-template <int MODE, int SLOT>
-constexpr int nb_waves() { return MODE == NB_ONEPASS && SLOT == NB_SLOT ? 8 : 1; }
-template <int MODE, int SLOT, bool FAST = false>
-__global__ void __launch_bounds__(BLOCK, (nb_waves<MODE, SLOT>()))
-k_neighbours(const int4 *__restrict__ atom, const int *__restrict__ perm, int n,
-             const Grid *__restrict__ grids, int n_mol,
-             const int *__restrict__ cell_start, PredParams pp,
-             int *__restrict__ deg_n, int *__restrict__ deg_up,
-             unsigned *__restrict__ upmask, int *__restrict__ nslab,
-             int *__restrict__ block_tot,
-             const int *__restrict__ nbr_start, const int *__restrict__ up_start,
-             int *__restrict__ nbr, int *__restrict__ up,
-             int *__restrict__ edge_i, unsigned char *__restrict__ vgab,
-             long long *__restrict__ vert_min, Counters *cnt) {
-    static_assert(SLOT <= 32, "one mask bit per slot entry");
-    constexpr int NB_SLAB = BLOCK * SLOT;
-    constexpr bool ONE = MODE == NB_ONEPASS;
-    // NB_FILL stages the block's rows in LDS and writes them out as one
-    // contiguous range (the block's rows are adjacent in the CSR arrays);
-    // rows written straight from the scan would be partial-line scattered
-    // stores. A block whose rows exceed the LDS buffers writes directly.
-    constexpr int LDS_N = ONE ? NB_SLAB : 4096, LDS_U = ONE ? 1 : 2048;
-    __shared__ int sn[LDS_N];
-    __shared__ int su[LDS_U];
+constexpr int NB_SLOT_SAS = 128;
+template <int SLOT, int LPB>
+constexpr int nb_waves() { return SLOT == NB_SLOT && LPB == 1 ? 8 : 4; }
+template <int SLOT, int LPB, bool SINGLE>
+__global__ void __launch_bounds__(BLOCK, (nb_waves<SLOT, LPB>()))
+k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, const int *__restrict__ perm, int n,
+             const Grid *__restrict__ grids, int n_mol, const int *__restrict__ cell_start, PredParams pp,
+             int *__restrict__ deg_n, int *__restrict__ deg_up, int *__restrict__ nslab, int *__restrict__ block_tot,
+             unsigned char *__restrict__ vgab, long long *__restrict__ vert_min, Counters *cnt) {
+    constexpr int BALLS = BLOCK / LPB;             // of a block
+    constexpr int LSLOT = SLOT > 32 ? 32 : SLOT;  // of a lane (a mask bit per entry)
+    __shared__ int sn[BLOCK * LSLOT];
     const int b = xcd_block();
-    const int b0 = b * BLOCK;
-    const int i = b0 + threadIdx.x;
+    const int i = b * BALLS + (int)threadIdx.x / LPB, part = (int)threadIdx.x % LPB;
     const bool valid = i < n;
-    int bn = 0, bu = 0, en = 0, eu = 0;
-    bool staged = false;
-    if (!ONE) {
-        const int last = min(b0 + BLOCK, n);
-        bn = nbr_start[b0]; en = nbr_start[last];
-        bu = up_start[b0]; eu = up_start[last];
-        staged = en - bn <= LDS_N && eu - bu <= LDS_U;
-    }
     const int4 a = valid ? atom[i] : make_int4(0, 0, 0, 0);
-    const int ra = valid ? a.w + (int)pp.aq : -1;  // |aq| < 2^26 and W < 2^26
     const int me = valid ? perm[i] : 0;
-    int cn = 0, cu = 0;
+    const bool ball = valid && a.w + (int)pp.aq >= 0;  // |aq| < 2^26 and W < 2^26
+    int cn = 0;
     unsigned mask = 0;
     bool gab = true;
-    if (ra >= 0) {
-        // where this ball's rows go: its LDS slot (entry k at k * BLOCK, so
-        // that a wave's lanes hit distinct banks), or its CSR rows
-        constexpr int RS = ONE ? BLOCK : 1;
-        int *const rn = ONE ? sn + threadIdx.x : (staged ? sn + (nbr_start[i] - bn) : nbr + nbr_start[i]);
-        int *const ru = ONE ? nullptr : (staged ? su + (up_start[i] - bu) : up + up_start[i]);
-        const int capn = ONE ? SLOT : INT_MAX;
-        const Grid g = grids[mol_of(grids, n_mol, i)];
-        const int cx = (a.x - g.ox) / g.s, cy = (a.y - g.oy) / g.s, cz = (a.z - g.oz) / g.s;
-        const int x0 = max(cx - g.reach, 0), x1 = min(cx + g.reach, g.nx - 1);
-        const int y0 = max(cy - g.reach, 0), y1 = min(cy + g.reach, g.ny - 1);
-        const int z0 = max(cz - g.reach, 0), z1 = min(cz + g.reach, g.nz - 1);
-        const int lim = 4 * (int)pp.sg2;     // (2 s_g)^2 < 2^28
-        const int reach1 = 2 * (int)pp.sgc;  // 2 ceil(s_g) <= 2^14
-        const double ra4 = 4.0 * (double)ra;
-        // the balls whose grown balls meet this one's, in cell order
-        auto scan = [&](auto &&on_meet) {
-            for (int z = z0; z <= z1; z++) {
-                // rows whose cells all lie farther than 2 s_g are skipped
-                const int zlo = g.oz + z * g.s, zhi = zlo + g.s - 1;
-                const int dzm = a.z < zlo ? zlo - a.z : (a.z > zhi ? a.z - zhi : 0);
-                if (dzm > reach1) continue;
-                const int rz = lim - dzm * dzm;
-                if (rz < 0) continue;
-                for (int y = y0; y <= y1; y++) {
-                    const int ylo = g.oy + y * g.s, yhi = ylo + g.s - 1;
-                    const int dym = a.y < ylo ? ylo - a.y : (a.y > yhi ? a.y - yhi : 0);
-                    if (dym > reach1 || rz - dym * dym < 0) continue;
-                    // the row's balls: one range (row-major), or one per cell (Morton)
-                    const bool morton = g.order == ORDER_MORTON;
-                    const long long rb = g.base + ((long long)z * g.ny + y) * g.nx;
-                    for (int xc = x0; xc <= (morton ? x1 : x0); xc++) {
-                        const long long c0 = morton ? g.base + cell_id(g, xc, y, z) : rb + x0;
-                        const int s = cell_start[c0], e = cell_start[morton ? c0 + 1 : rb + x1 + 1];
-                        for (int j = s; j < e; j++) {
-                            const int4 bb = atom[j];
-                            // one combined test (a branch per condition costs more
-                            // exec-mask work than the arithmetic it would skip)
-                            bool meet;
-                            if constexpr (FAST) {
-                                const int dx = bb.x - a.x, dy = bb.y - a.y, dz = bb.z - a.z;
-                                const int d2 = __mul24(dx, dx) + __mul24(dy, dy) + __mul24(dz, dz);
-                                const int rb2 = bb.w + (int)pp.aq;
-                                const int L = d2 - ra - rb2;
-                                // d2 == 0: the ball itself (equal centres are reported by the binning)
-                                meet = (d2 <= lim) & (d2 != 0) &
-                                       ((L <= 0) | ((double)L * (double)L <= ra4 * (double)rb2));
-                            } else {
-                                // offsets clamped to reach1 + 1: d2 then fits int32, and
-                                // a clamped offset alone gives d2 > (2 ceil s_g)^2 >= lim
-                                const int dx = min(max(bb.x - a.x, -reach1 - 1), reach1 + 1);
-                                const int dy = min(max(bb.y - a.y, -reach1 - 1), reach1 + 1);
-                                const int dz = min(max(bb.z - a.z, -reach1 - 1), reach1 + 1);
-                                const int d2 = dx * dx + dy * dy + dz * dz;
-                                const int rb2 = bb.w + (int)pp.aq;
-                                const int L = d2 - ra - rb2;
-                                // grown balls meet: d <= rho_a + rho_b; equal centres are reported by the binning
-                                meet = (j != i) & (d2 <= lim) & (d2 != 0) & (rb2 >= 0) &
-                                       ((L <= 0) | ((i64)L * L <= 4 * (i64)ra * rb2));
-                            }
-                            if (meet) on_meet(j, bb);
-                        }
-                    }
-                }
-            }
-        };
-        // AC2 of the vertex and AC3 of the edge for neighbour number k
-        auto tests = [&](int j, int4 bb, int k) {
-            if (gab && vertex_violation_sign(a, i, bb, j, perm) < 0) gab = false;
-            if (perm[j] > me && edge_ac3(edge_setup(a, bb), pp.aq)) {
-                if (ONE) {
-                    if (k < 32) mask |= 1u << k;
-                } else {
-                    ru[cu] = j;
-                }
-                cu++;
-            }
-        };
-        // the scan only collects the row; the float64 tests then run over the
-        // row, where a wave's lanes are mostly busy (inside the scan they would
-        // run whenever any lane of the wave met a ball)
-        scan([&](int j, int4) {
-            if (cn < capn) rn[cn * RS] = j;
+    // entry k of a lane's list at k * BLOCK: a wave's lanes hit distinct banks
+    int *const rn = sn + threadIdx.x;
+    if (ball) {
+        const Grid g = grids[SINGLE ? 0 : mol_of(grids, n_mol, i)];
+        scan_rows(g, a, i, sball, cell_start, pp, part, LPB, [&](int j) {
+            if (j == i) return;
+            if (cn < LSLOT) rn[cn * BLOCK] = j;
             cn++;
         });
-        const int kn = min(cn, capn);
-        for (int k = 0; k < kn; k++) {
-            const int j = rn[k * RS];
-            tests(j, atom[j], k);
-        }
-        if (cn > capn) {
-            // one-pass mode, row longer than the slot: the exact counts still
-            // need the tests of the rest (the fill pass redoes this row)
-            int k = 0;
-            scan([&](int j, int4 bb) {
-                if (k >= capn) tests(j, bb, k);
-                k++;
-            });
-        }
     }
-    if (valid) {
-        vgab[i] = (unsigned char)(ra >= 0 && gab);
+    const bool lane_full = cn > LSLOT;
+    const int kn = min(cn, LSLOT);
+    cn = 0;
+    // the exact test, AC2 of the vertex and AC3 of the edge for each listed
+    // ball; the list keeps the neighbours
+    for (int k = 0; k < kn; k++) {
+        const int j = rn[k * BLOCK];
+        const int4 bb = atom[j];
+        if (!balls_meet(a, bb, pp)) continue;
+        if (vertex_violation_sign(a, i, bb, j, perm) < 0) gab = false;
+        if (perm[j] > me && edge_ac3(edge_setup(a, bb), pp.aq)) mask |= 1u << cn;
+        rn[cn * BLOCK] = j;
+        cn++;
+    }
+    // places in the slab: the ball's upper entries, then the others, each by lane
+    const int cu = __popc(mask);
+    int bn = cn, bu = cu, pu = 0, pl = 0;  // of the ball; before this lane: upper, others
+#pragma unroll
+    for (int off = 1; off < LPB; off <<= 1) {
+        const int xn = __shfl_xor(bn, off, WAVE), xu = __shfl_xor(bu, off, WAVE);
+        if (part & off) {
+            pu += xu;
+            pl += xn - xu;
+        }
+        bn += xn;
+        bu += xu;
+    }
+    bool bg = gab;
+#pragma unroll
+    for (int off = 1; off < LPB; off <<= 1) bg &= (bool)__shfl_xor((int)bg, off, WAVE);
+    const bool head = part == 0;
+    int off3[3], tot3[3];
+    block_exclusive_scan3<BLOCK>(head ? bn : 0, head ? bu : 0, head ? bu * (bu - 1) / 2 : 0, off3, tot3);  // bu <= LSLOT LPB
+    int first = off3[0];  // of the head lane
+    if (LPB > 1) first = __shfl(first, lane_id() & ~(LPB - 1), WAVE);
+    if (valid && head) {
+        vgab[i] = (unsigned char)(ball && bg);
         // start of the least Size of a kept incident edge, by input id (only
         // read for a ball that fails AC2 at its own centre)
-        if (ONE && !(ra >= 0 && gab)) {
+        if (!(ball && bg)) {
             vert_min[me] = ORDERED_POS_INF;
-            if (ra >= 0) cnt->vng = 1;
+            if (ball) cnt->vng = 1;
         }
+        deg_n[i] = bn;
+        deg_up[i] = bu;
     }
-    if (ONE) {
-        if (valid) {
-            deg_n[i] = cn;
-            deg_up[i] = cu;
-            upmask[i] = mask;
-        }
-        if (cn > SLOT) cnt->overflow = 1;
-        const int kn = min(cn, SLOT);
-        int off3[3], tot3[3];
-        block_exclusive_scan3<BLOCK>(kn, cu, kn < cn ? 0 : cu * (cu - 1) / 2, off3, tot3);  // kn == cn: cu <= 32
-        const int offn = off3[0];
-        if (threadIdx.x == 0) {
-            const int stride = (gridDim.x + 3) & ~3;
-            block_tot[b] = tot3[0];               // neighbour entries of the block
-            block_tot[stride + b] = tot3[1];      // upper entries of the block
-            block_tot[2 * stride + b] = tot3[2];  // pairs of upper entries of one ball
-        }
-        int *dn = nslab + (long long)b * NB_SLAB + offn;
-        for (int k = 0; k < kn; k++) dn[k] = sn[k * BLOCK + threadIdx.x];
-        return;
+    if (lane_full || bn > SLOT) cnt->overflow = 1;
+    if (threadIdx.x == 0) {
+        const int stride = (gridDim.x + 3) & ~3;
+        block_tot[b] = tot3[0];               // neighbour entries of the block
+        block_tot[stride + b] = tot3[1];      // upper entries of the block
+        block_tot[2 * stride + b] = tot3[2];  // pairs of upper entries of one ball
     }
-    if (!staged) {
-        // rows went straight to nbr / up; the upper rows' owner ids remain
-        if (valid) {
-            const int pu = up_start[i];
-            for (int k = 0; k < cu; k++) edge_i[pu + k] = i;
-        }
-        return;
+    if (tot3[0] > BALLS * SLOT) return;  // some row outgrew its room: overflow is set
+    int *dn = nslab + (long long)b * (BALLS * SLOT) + first;
+    pl += bu;
+    for (int k = 0; k < cn; k++) {
+        const int j = rn[k * BLOCK];
+        if ((mask >> k) & 1u) dn[pu++] = j;
+        else dn[pl++] = j;
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < en - bn; k += BLOCK) nbr[bn + k] = sn[k];
-    for (int k = threadIdx.x; k < eu - bu; k += BLOCK) up[bu + k] = su[k];
-    __syncthreads();
-    // owner of each upper-row slot: a ball writes its id over its own slots
-    if (valid) {
-        const int pu = up_start[i] - bu;
-        for (int k = 0; k < cu; k++) su[pu + k] = i;
+}
+
+// The counted rows of inputs that outgrow the slots, a thread per ball: counts,
+// and after their scans the rows (CSR; upper entries with their owner, in scan
+// order).
+template <bool FILL>
+__global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ atom, const float4 *__restrict__ sball,
+                                                     const int *__restrict__ perm, int n, const Grid *__restrict__ grids,
+                                                     int n_mol, const int *__restrict__ cell_start, PredParams pp,
+                                                     int *__restrict__ deg_n, int *__restrict__ deg_up,
+                                                     unsigned char *__restrict__ vgab, const int *__restrict__ nbr_start,
+                                                     const int *__restrict__ up_start, int *__restrict__ nbr,
+                                                     int *__restrict__ up, int *__restrict__ edge_i,
+                                                     long long *__restrict__ vert_min, Counters *cnt) {
+    const int i = xcd_block() * BLOCK + threadIdx.x;
+    if (i >= n) return;
+    const int4 a = atom[i];
+    const int me = perm[i];
+    const bool ball = a.w + (int)pp.aq >= 0;
+    int cn = 0, cu = 0;
+    bool gab = true;
+    const int pn = FILL ? nbr_start[i] : 0, pu = FILL ? up_start[i] : 0;
+    if (ball) {
+        const Grid g = grids[mol_of(grids, n_mol, i)];
+        scan_rows(g, a, i, sball, cell_start, pp, 0, 1, [&](int j) {
+            if (j == i) return;
+            const int4 bb = atom[j];
+            if (!balls_meet(a, bb, pp)) return;
+            const bool upper = perm[j] > me && edge_ac3(edge_setup(a, bb), pp.aq);
+            if (FILL) {
+                nbr[pn + cn] = j;
+                if (upper) {
+                    up[pu + cu] = j;
+                    edge_i[pu + cu] = i;
+                }
+            } else if (vertex_violation_sign(a, i, bb, j, perm) < 0) {
+                gab = false;
+            }
+            cn++;
+            cu += upper;
+        });
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < eu - bu; k += BLOCK) edge_i[bu + k] = su[k];
+    if (FILL) return;
+    deg_n[i] = cn;
+    deg_up[i] = cu;
+    vgab[i] = (unsigned char)(ball && gab);
+    if (!(ball && gab)) {
+        vert_min[me] = ORDERED_POS_INF;
+        if (ball) cnt->vng = 1;
+    }
 }
 
 // After a one-pass neighbour search: the neighbour rows stay where the pass
@@ -665,9 +709,9 @@ k_neighbours(const int4 *__restrict__ atom, const int *__restrict__ perm, int n,
 // entry. pair_base[g]: pairs of upper entries before group g (2^gshift balls;
 // poff: exclusive scan of the blocks' pair totals). eng (balls owning an edge
 // that fails AC2) starts at 0.
-template <int SLOT>
-__global__ void __launch_bounds__(BLOCK) k_nbr_compact(const int *__restrict__ deg_n, const int *__restrict__ deg_up,
-                                                        const unsigned *__restrict__ upmask, int n,
+// CB balls a block: 64 where there are few (more blocks, one entry a thread).
+template <int SLOT, int LPB, int CB>
+__global__ void __launch_bounds__(BLOCK) k_nbr_compact(const int *__restrict__ deg_n, const int *__restrict__ deg_up, int n,
                                                         const int *__restrict__ nslab, const int *__restrict__ uoff,
                                                         const int *__restrict__ poff, const int *__restrict__ perm,
                                                         int *__restrict__ nbr_start, int *__restrict__ up_start,
@@ -683,47 +727,51 @@ __global__ void __launch_bounds__(BLOCK) k_nbr_compact(const int *__restrict__ d
     // block has 900 at alpha = 0 and slots of 16, 2,000 at 2 A^2 and slots of
     // 32); a block with more ranks its entries from global memory, a thread
     // per ball.
-    constexpr int UP_LDS = BLOCK * SLOT / 2;
+    constexpr int UP_LDS = CB * SLOT / 2;
+    constexpr int BALLS = BLOCK / LPB;  // balls of a slab
+    constexpr int SLABS = CB / BALLS;
+    static_assert(SLABS >= 1, "a block's balls are whole slabs");
     __shared__ int s_id[UP_LDS];
     __shared__ unsigned short s_pos[UP_LDS];
     __shared__ unsigned char s_own[UP_LDS];
-    __shared__ int s_row[BLOCK + 1];
+    __shared__ int s_row[CB + 1];
     const int b = blockIdx.x;
-    const int i = b * BLOCK + threadIdx.x;
-    const int cn = i < n ? deg_n[i] : 0, cu = i < n ? deg_up[i] : 0;
-    const unsigned mask = i < n ? upmask[i] : 0u;
-    const int gu = uoff[b], gp = poff[b];
+    const int i = b * CB + threadIdx.x;
+    const bool mine = (int)threadIdx.x < CB && i < n;
+    const int cn = mine ? deg_n[i] : 0, cu = mine ? deg_up[i] : 0;
+    const int gu = uoff[b * SLABS], gp = poff[b * SLABS];
     int tot3[3], off3[3];
     block_exclusive_scan3<BLOCK>(cn, cu, cu * (cu - 1) / 2, off3, tot3);
-    const int offn = off3[0], offu = off3[1], totu = tot3[1];
-    const int base = b * (BLOCK * SLOT);  // the block's slab
+    // the ball's row less the slabs' start: its slab, the rows before it there
+    int offn = off3[0];
+    if (LPB > 1) {
+        offn -= __shfl(offn, lane_id() & ~(BALLS - 1), WAVE);
+        offn += (int)threadIdx.x / BALLS * (BALLS * SLOT);
+    }
+    const int offu = off3[1], totu = tot3[1];
+    const int base = b * (CB * SLOT);
     const bool lds = totu <= UP_LDS;
-    s_row[threadIdx.x] = offu;
-    if (threadIdx.x == 0) s_row[BLOCK] = totu;
-    if (i < n) {
+    if ((int)threadIdx.x < CB) s_row[threadIdx.x] = offu;
+    if (threadIdx.x == 0) s_row[CB] = totu;
+    if (mine) {
         if ((i & ((1 << gshift) - 1)) == 0) pair_base[i >> gshift] = gp + off3[2];
         eng[i] = 0;
         nbr_start[i] = base + offn;
         up_start[i] = gu + offu;
         if (i == n - 1) up_start[n] = gu + offu + cu;
-        unsigned m = mask;
-        int q = offu;
-        while (m) {
-            const int k = __ffs((int)m) - 1;
-            m &= m - 1;
+        for (int k = 0; k < cu; k++) {
             if (lds) {
-                s_pos[q] = (unsigned short)(offn + k);
-                s_own[q] = (unsigned char)threadIdx.x;
+                s_pos[offu + k] = (unsigned short)(offn + k);
+                s_own[offu + k] = (unsigned char)threadIdx.x;
             } else {
                 const int j = nslab[base + offn + k], id = perm[j];
                 int rank = 0;
-                for (unsigned r = mask; r; r &= r - 1) rank += perm[nslab[base + offn + __ffs((int)r) - 1]] < id;
+                for (int r = 0; r < cu; r++) rank += perm[nslab[base + offn + r]] < id;
                 const int e = gu + offu + rank;
                 up[e] = j;
                 up_id[e] = id;
                 edge_i[e] = i;
             }
-            q++;
         }
     }
     if (!lds) return;
@@ -738,7 +786,7 @@ __global__ void __launch_bounds__(BLOCK) k_nbr_compact(const int *__restrict__ d
         const int e = gu + r0 + rank;
         up[e] = nslab[base + s_pos[k]];
         up_id[e] = id;
-        edge_i[e] = b * BLOCK + o;
+        edge_i[e] = b * CB + o;
     }
 }
 
