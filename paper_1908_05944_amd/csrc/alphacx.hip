@@ -174,6 +174,58 @@ static void dev_free(void *p) {
     P.live.erase(it);
 }
 
+// Pinned host memory of results (host copies of rows and Sizes) and of uploads:
+// size classes like the device pool's, at most HOST_POOL_BYTES of unused blocks
+// kept (a copy into pageable memory is staged, and fresh pages fault in one by
+// one: 16 MB of results took 1.2 ms of a 58,674-atom host call). nullptr when
+// the host has no more to pin; callers then use pageable memory.
+namespace {
+constexpr size_t HOST_POOL_BYTES = (size_t)256 << 20;
+struct HostPool {
+    std::mutex mu;
+    std::multimap<size_t, void *> free_blocks;
+    size_t unused = 0;
+};
+HostPool &host_pool() {
+    static HostPool *p = new HostPool();
+    return *p;
+}
+}  // namespace
+static void *host_alloc(size_t n) {
+    const size_t c = size_class(n < 4096 ? 4096 : n);
+    HostPool &P = host_pool();
+    {
+        std::lock_guard<std::mutex> g(P.mu);
+        auto it = P.free_blocks.find(c);
+        if (it != P.free_blocks.end()) {
+            void *p = it->second;
+            P.free_blocks.erase(it);
+            P.unused -= c;
+            return p;
+        }
+    }
+    void *p = nullptr;
+    if (hipHostMalloc(&p, c, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return p;
+}
+static void host_free(void *p, size_t n) {
+    if (!p) return;
+    const size_t c = size_class(n < 4096 ? 4096 : n);
+    HostPool &P = host_pool();
+    {
+        std::lock_guard<std::mutex> g(P.mu);
+        if (P.unused + c <= HOST_POOL_BYTES) {
+            P.free_blocks.emplace(c, p);
+            P.unused += c;
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 // Allocations of one call, returned to the pool when the call ends.
 struct Scope {
     std::vector<void *> held;
@@ -203,6 +255,10 @@ struct ac_complex {
     std::vector<int32_t> h_mol[4];     // per dimension: molecule of each row (built on first ac_molecule)
     int32_t *d_simp[4] = {nullptr, nullptr, nullptr, nullptr};
     double *d_size[4] = {nullptr, nullptr, nullptr, nullptr};
+    // host copies: in one pinned block per dimension (Sizes, then rows), or in
+    // the vectors (streamed builds, or no pinned memory)
+    void *h_block[4] = {nullptr, nullptr, nullptr, nullptr};
+    size_t h_bytes[4] = {0, 0, 0, 0};
     std::vector<int32_t> h_simp[4];
     std::vector<double> h_size[4];
     bool host_ready[4] = {false, false, false, false};
@@ -225,6 +281,7 @@ static void free_complex(ac_complex *c) {
     for (int d = 0; d < 4; d++) {
         dev_free(c->d_simp[d]);
         dev_free(c->d_size[d]);
+        host_free(c->h_block[d], c->h_bytes[d]);
     }
     dev_free(c->inc_slot);
     dev_free(c->inc_start);
@@ -288,6 +345,45 @@ static void *pinned_block(size_t bytes) {
         cap = c;
     }
     return p;
+}
+
+// Mail block of this thread (see Mail): one message at a time, numbered so that
+// an earlier one is never taken for it. Every build waits for the messages it
+// asks for, or for its stream when it fails, so none arrives after its build.
+struct MailBox {
+    Mail *host = nullptr, *dev = nullptr;
+    unsigned seq = 0;
+};
+static MailBox &mail_box() {
+    thread_local MailBox b;
+    if (!b.host) {
+        void *p = nullptr, *d = nullptr;
+        HIP_TRY(hipHostMalloc(&p, sizeof(Mail), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
+        if (hipHostGetDevicePointer(&d, p, 0) != hipSuccess) {
+            (void)hipHostFree(p);
+            throw HipError{AC_E_DEVICE, "pinned host memory has no device address"};
+        }
+        std::memset(p, 0, sizeof(Mail));
+        b.host = static_cast<Mail *>(p);
+        b.dev = static_cast<Mail *>(d);
+    }
+    return b;
+}
+
+// Waits for message `seq`. The stream is asked now and then: when its work has
+// ended (or failed) no message can come any more.
+static const Mail &mail_wait(const MailBox &b, unsigned seq, hipStream_t s) {
+    for (long long spin = 0;; spin++) {
+        if (__atomic_load_n(&b.host->seq, __ATOMIC_ACQUIRE) == seq) return *b.host;
+        if ((spin & 0xfff) == 0xfff) {
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) continue;
+            HIP_TRY(e);
+            if (__atomic_load_n(&b.host->seq, __ATOMIC_ACQUIRE) == seq) return *b.host;
+            throw HipError{AC_E_DEVICE, "internal error: the build ended without its message"};
+        }
+        __builtin_ia32_pause();
+    }
 }
 
 // Copies n items from the device into h through the pinned block (synchronises s).
@@ -599,6 +695,15 @@ struct Fixed {
     long long *d_rows = nullptr;
 };
 
+// Output arrays of the caller (the build without allocation): rows go there if
+// every dimension fits.
+struct Ext {
+    int32_t *const *simp;
+    double *const *size;
+    const int64_t *cap;
+    bool fits;
+};
+
 // The whole pipeline from device arrays, for n_alpha >= 1 alpha values: one
 // candidate search at the largest, then pruning and output per value (the
 // candidates of a smaller alpha are those of the larger that pass AC3 at the
@@ -606,7 +711,7 @@ struct Fixed {
 // alphas[k] on success; nothing is left allocated on failure.
 static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n64, const Batch &bt,
                               const double *alphas, int n_alpha, const Options &o, hipStream_t s, ac_complex **outs,
-                              Fixed *fx = nullptr) {
+                              Fixed *fx = nullptr, Ext *ext = nullptr) {
     for (int k = 0; k < n_alpha; k++) outs[k] = nullptr;
     // fixed: sizes from fx, nothing read back (only with one alpha)
     const bool fixed = fx && !fx->learn;
@@ -643,14 +748,25 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const int n_mol = (int)bt.off.size() - 1;
         int4 *q = sc.get<int4>(n);
         Counters *cnt = sc.get<Counters>(1);
-        static_assert(sizeof(Counters) % sizeof(int) == 0, "Counters cleared as ints");
-        fill<int>(reinterpret_cast<int *>(cnt), 0, sizeof(Counters) / sizeof(int), s);  // a kernel: graph-safe
-        std::vector<int2> tiles;
-        std::vector<int> tile_first;
-        quantise_tiles(bt, tiles, tile_first);
+        // messages to the host: not from a recorded build, and not on fixed
+        // scratch (the mail block would be an allocation)
+        MailBox *mb = fixed || t_arena ? nullptr : &mail_box();
+        Mail *const mail = mb ? mb->dev : nullptr;
         std::vector<Stats> hs(n_mol);
         Stats *st = sc.get<Stats>(n_mol);
-        {
+        if (n_mol == 1) {
+            const int n_tiles = (n + QTILE - 1) / QTILE;
+            Stats *part = sc.get<Stats>(n_tiles);
+            k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, cnt);
+            const unsigned seq = mb ? ++mb->seq : 0;
+            k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, mail, seq);
+            LAUNCH_CHECK();
+            if (mb) hs[0] = mail_wait(*mb, seq, s).st;
+            else if (!fixed) read_back(hs.data(), st, 1, s);
+        } else {
+            std::vector<int2> tiles;
+            std::vector<int> tile_first;
+            quantise_tiles(bt, tiles, tile_first);
             const int2 *d_tiles = fixed ? fx->d_tiles : sc.get<int2>(tiles.size());
             const int *d_tile_first = fixed ? fx->d_tile_first : sc.get<int>(n_mol + 1);
             Stats *part = sc.get<Stats>(tiles.size());
@@ -660,9 +776,9 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 HIP_TRY(hipMemcpyAsync(const_cast<int *>(d_tile_first), tile_first.data(), (n_mol + 1) * sizeof(int),
                                        hipMemcpyHostToDevice, s));
             }
-            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, q, part);
+            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, n, q, part, cnt);
             LAUNCH_CHECK();
-            k_stats_reduce<<<(unsigned)n_mol, BLOCK, 0, s>>>(part, d_tile_first, st);
+            k_stats_reduce<<<(unsigned)n_mol, BLOCK, 0, s>>>(part, d_tile_first, 0, st, nullptr, 0);
             LAUNCH_CHECK();
             if (!fixed) read_back(hs.data(), st, (size_t)n_mol, s);
         }
@@ -727,13 +843,15 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         if (fx && fx->learn) fx->grids = grids;
         if (fixed) ncell = fx->ncell;
         if (ncell >= (long long)INT_MAX) throw HipError{AC_E_CAPACITY, "too many grid cells"};
-        Grid *d_grids = sc.get<Grid>(n_mol);
+        // one molecule's grid is an argument of the kernels that need it
+        Grid *d_grids = fixed || n_mol > 1 ? sc.get<Grid>(n_mol) : nullptr;
+        const Grid g0 = fixed || n_mol > 1 ? Grid{} : grids[0];
         if (fixed) {
             // this run's boxes, the recorded sides and capacities
             k_plan_grids<<<grid_for(n_mol), BLOCK, 0, s>>>(st, n_mol, fx->d_tmpl, fx->d_cell_cap, fx->wmax, d_grids,
                                                            cnt);
             LAUNCH_CHECK();
-        } else {
+        } else if (n_mol > 1) {
             HIP_TRY(hipMemcpyAsync(d_grids, grids.data(), n_mol * sizeof(Grid), hipMemcpyHostToDevice, s));
         }
 
@@ -744,7 +862,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         float4 *sball = sc.get<float4>(n);
         int *perm = sc.get<int>(n);
         if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
-            k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, (int)ncell, cell_start, atom, sball,
+            k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, (int)ncell, cell_start, atom, sball,
                                                  (int)aq, perm, cnt);
             LAUNCH_CHECK();
         } else {
@@ -769,7 +887,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             for (int sh = shift; sh < bits; sh += RS_BITS) {
                 const bool first = sh == shift;
                 if (first)
-                    k_cell_hist<<<tiles, RS_BLOCK, 0, s>>>(q, n, d_grids, n_mol, kin, sh, hist, tiles);
+                    k_cell_hist<<<tiles, RS_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, kin, sh, hist, tiles);
                 else
                     k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, sh, hist, tiles);
                 k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
@@ -832,15 +950,16 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         with_slot([&](auto sl, auto lp) {
             constexpr int SLOT = decltype(sl)::value, LPB = decltype(lp)::value;
             if (n_mol == 1)
-                k_neighbours<SLOT, LPB, true><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp,
+                k_neighbours<SLOT, LPB, true><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
                                                                    deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
             else
-                k_neighbours<SLOT, LPB, false><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp,
+                k_neighbours<SLOT, LPB, false><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
                                                                     deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
         });
         LAUNCH_CHECK();
         tm.mark(ST_NBR_SCAN);
-        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbB, nbs, uoff, poff, cnt);
+        const unsigned nbr_seq = mb ? ++mb->seq : 0;
+        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbB, nbs, uoff, poff, cnt, mail, nbr_seq);
         LAUNCH_CHECK();
         Counters c0{};
         if (fixed) {
@@ -849,14 +968,14 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             c0.E = fx->E_cap;
             c0.P = fx->P_cap;
         } else {
-            c0 = read_one(cnt, s);
+            c0 = mb ? mail_wait(*mb, nbr_seq, s).c : read_one(cnt, s);
         }
         if (c0.dup) throw HipError{AC_E_DUPLICATE, "two balls have equal quantised centres"};
         const bool nbr_two_pass = c0.overflow != 0;
         int *pairs = nullptr;
         if (nbr_two_pass) {
             // exact counts and totals: neighbour entries, candidate edges, pairs
-            k_nbr_rows<false><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp, deg_n, deg_up, vgab,
+            k_nbr_rows<false><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp, deg_n, deg_up, vgab,
                                                    nullptr, nullptr, nullptr, nullptr, nullptr, vert_min, cnt);
             pairs = sc.get<int>(groups);
             k_group_pairs<<<(groups + NWAVE - 1) / NWAVE, BLOCK, 0, s>>>(deg_up, n, gshift, groups, pairs, eng);
@@ -900,7 +1019,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             scan_i32(deg_up, up_start, n, s, sc);
             if (!counted) scan_i32(pairs, pair_base, groups, s, sc);
             int *up_scan = sc.get<int>(E1), *id_scan = sc.get<int>(E1);
-            k_nbr_rows<true><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, cell_start, pp, nullptr, nullptr,
+            k_nbr_rows<true><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp, nullptr, nullptr,
                                                   nullptr, nbr_start, up_start, nbr, up_scan, edge_i, vert_min, cnt);
             k_up_ids<<<grid_for(E), BLOCK, 0, s>>>(up_scan, E, perm, id_scan);
             k_up_rank<<<grid_for(E), BLOCK, 0, s>>>(up_scan, id_scan, E, edge_i, up_start, up, up_id);
@@ -1029,16 +1148,21 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         OutCap out_cap{INT_MAX, INT_MAX, INT_MAX};
         if (fixed) out_cap = {fx->E_cap, fx->T_cap, fx->Q_cap};
         // the records scanned, and the vertices (out0 / size0; a sweep's records hold none)
+        unsigned rec_seq = 0;
         auto scan_records = [&](int *out0, double *size0) {
-            if (rec_tiles > 1) {
+            rec_seq = mb ? ++mb->seq : 0;
+            const bool one = rec_tiles == 1;
+            if (!one) {
                 k_rec_sums<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, stop);
                 k_rec_prefix<<<1, 1024, 0, s>>>(tile_sum, rec_tiles, cd.tri_cnt, tt.cand, groups, cnt, fixed, out_cap,
-                                               STOP_CAPACITY);
+                                               STOP_CAPACITY, mail, rec_seq);
             }
-            k_rec_apply<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, out0, size0, cd.tri_cnt, tt.cand,
-                                                       groups, cnt, fixed, out_cap, STOP_CAPACITY);
+            k_rec_apply<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, out0, size0, cd.tri_cnt, tt.cand, groups,
+                                                       cnt, fixed, out_cap, STOP_CAPACITY, one ? mail : nullptr, rec_seq);
             LAUNCH_CHECK();
         };
+        // the counters as the scan of the records left them
+        auto rec_counters = [&]() { return mb ? mail_wait(*mb, rec_seq, s).c : read_one(cnt, s); };
         auto dev_rows = [&](ac_complex *r, int d, long long rows) {
             const size_t m = rows > 0 ? (size_t)rows : 1;
             r->d_simp[d] = static_cast<int32_t *>(dev_alloc(m * (d + 1) * sizeof(int32_t)));
@@ -1083,7 +1207,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             // rows are then written before the counts are read, one wait in
             // all. Else the counts are read first.
             const long long q_room = (long long)groups * tt.cap;
-            const bool roomy = fixed || E * 16LL + room * 20LL + q_room * 24LL <= OUT_ROOM;
+            const bool roomy = fixed || !ext && E * 16LL + room * 20LL + q_room * 24LL <= OUT_ROOM;
             if (roomy) {
                 dev_rows(res, 1, fixed ? fx->E_cap : E);
                 dev_rows(res, 2, fixed ? fx->T_cap : room);
@@ -1099,12 +1223,12 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 outs[0] = res;
                 return AC_OK;
             }
-            cf = read_one(cnt, s);
+            cf = rec_counters();
             const bool again = cf.overflow != 0;  // a group kept more tetrahedra than its slab holds
             if (again) {
                 tet_counted();
                 prune();
-                cf = read_one(cnt, s);
+                cf = rec_counters();
             }
             if (cf.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
             if (again && roomy) {
@@ -1114,18 +1238,40 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 res->d_size[3] = nullptr;
                 dev_rows(res, 3, cf.m3);
             }
-            if (!roomy) {
+            if (ext) {
+                // into the caller's arrays, if they are large enough
+                const int m[4] = {cf.m0, cf.m1, cf.m2, cf.m3};
+                ext->fits = true;
+                for (int d = 0; d < 4; d++) ext->fits = ext->fits && m[d] <= ext->cap[d];
+                if (ext->fits) {
+                    for (int d = 1; d < 4; d++) {
+                        res->d_simp[d] = ext->simp[d];
+                        res->d_size[d] = ext->size[d];
+                    }
+                    if (m[0] > 0) {
+                        HIP_TRY(hipMemcpyAsync(ext->simp[0], res->d_simp[0], (size_t)m[0] * sizeof(int32_t),
+                                               hipMemcpyDeviceToDevice, s));
+                        HIP_TRY(hipMemcpyAsync(ext->size[0], res->d_size[0], (size_t)m[0] * sizeof(double),
+                                               hipMemcpyDeviceToDevice, s));
+                    }
+                }
+            } else if (!roomy) {
                 dev_rows(res, 1, cf.m1);
                 dev_rows(res, 2, cf.m2);
                 dev_rows(res, 3, cf.m3);
             }
-            if (again || !roomy) {
+            if ((again || !roomy) && !(ext && !ext->fits)) {
                 tm.mark(ST_EMIT);
                 write_rows();
                 tm.mark(ST_COUNT);
-                // the scratch goes back to the pool: its last reader has to end
-                HIP_TRY(hipStreamSynchronize(s));
             }
+            // the scratch goes back to the pool: its last reader has to end
+            HIP_TRY(hipStreamSynchronize(s));
+            if (ext)
+                for (int d = 1; d < 4; d++) {
+                    res->d_simp[d] = nullptr;
+                    res->d_size[d] = nullptr;
+                }
             cm[0] = cf;
             if (fx && fx->learn) {
                 fx->T = cf.T;
@@ -1139,7 +1285,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 k_sweep_counts<<<groups, BLOCK, 0, s>>>(cd, tt, rec);
                 LAUNCH_CHECK();
                 scan_records(nullptr, nullptr);
-                return read_one(cnt, s);
+                return rec_counters();
             };
             Counters cp = places();
             if (cp.overflow) {
@@ -1279,6 +1425,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         }
     } catch (const HipError &e) {
         (void)hipStreamSynchronize(s);
+        if (ext && res)
+            for (int d = 1; d < 4; d++) {  // the caller's
+                res->d_simp[d] = nullptr;
+                res->d_size[d] = nullptr;
+            }
         for (ac_complex *r : rs) free_complex(r);
         return set_error(e.st, e.msg);
     }
@@ -1374,17 +1525,11 @@ static ac_status run_partitioned(const double *d_xyz, const double *d_r, int64_t
     try {
         // quantised centres, bounding box and the largest weight
         int4 *q = sc.get<int4>(n);
-        std::vector<int2> tiles;
-        for (int a = 0; a < n; a += QTILE) tiles.push_back(make_int2(a, std::min(a + QTILE, n)));
-        int2 *d_tiles = sc.get<int2>(tiles.size());
-        int *d_tile_first = sc.get<int>(2);
-        const int tf[2] = {0, (int)tiles.size()};
-        Stats *part = sc.get<Stats>(tiles.size());
+        const int n_tiles = (n + QTILE - 1) / QTILE;
+        Stats *part = sc.get<Stats>(n_tiles);
         Stats *st = sc.get<Stats>(1);
-        HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync(d_tile_first, tf, sizeof(tf), hipMemcpyHostToDevice, s));
-        k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, q, part);
-        k_stats_reduce<<<1, BLOCK, 0, s>>>(part, d_tile_first, st);
+        k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, nullptr);
+        k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, nullptr, 0);
         LAUNCH_CHECK();
         const Stats h = read_one(st, s);
         if (h.flags & 1) throw HipError{AC_E_INVALID, "non-finite coordinate, or radius not positive"};
@@ -2115,16 +2260,19 @@ static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
         r->fallbacks = (int64_t)c.exact_fallbacks;
         r->work[0] = p->fx.ncell;
         r->work[1] = c.Nn;
+        CopyList cl{};
+        long long most = 0;
         for (int d = 0; d < 4; d++) {
             r->count[d] = m[d];
             r->d_simp[d] = static_cast<int32_t *>(dev_alloc((size_t)(m[d] > 0 ? m[d] : 1) * (d + 1) * sizeof(int32_t)));
             r->d_size[d] = static_cast<double *>(dev_alloc((size_t)(m[d] > 0 ? m[d] : 1) * sizeof(double)));
-            if (m[d] > 0) {
-                HIP_TRY(hipMemcpyAsync(r->d_simp[d], p->out_simp[d], (size_t)m[d] * (d + 1) * sizeof(int32_t),
-                                       hipMemcpyDeviceToDevice, s));
-                HIP_TRY(hipMemcpyAsync(r->d_size[d], p->out_size[d], (size_t)m[d] * sizeof(double),
-                                       hipMemcpyDeviceToDevice, s));
-            }
+            cl.src[2 * d] = p->out_simp[d];
+            cl.dst[2 * d] = r->d_simp[d];
+            cl.words[2 * d] = (long long)m[d] * (d + 1);
+            cl.src[2 * d + 1] = reinterpret_cast<const int *>(p->out_size[d]);
+            cl.dst[2 * d + 1] = reinterpret_cast<int *>(r->d_size[d]);
+            cl.words[2 * d + 1] = (long long)m[d] * 2;
+            most = std::max(most, std::max(cl.words[2 * d], cl.words[2 * d + 1]));
             if (n_mol > 1) {
                 const int64_t *b0 = rows.data() + (size_t)d * (n_mol + 1);
                 r->mol_rows[d].assign(b0, b0 + (n_mol + 1));
@@ -2132,6 +2280,8 @@ static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
                 r->mol_rows[d] = {0, r->count[d]};
             }
         }
+        k_copy_list<<<dim3((unsigned)std::min<long long>(most / 1024 + 1, 2048), 8), 256, 0, s>>>(cl);
+        LAUNCH_CHECK();
     } catch (...) {
         (void)hipStreamSynchronize(s);
         free_complex(r);
@@ -2169,6 +2319,42 @@ static char *scratch_on(int dev) {
         g_scratch_ptr[dev] = p;
     }
     return static_cast<char *>(g_scratch_ptr[dev]);
+}
+
+// Host copies of dimensions d0..d1 of a device result: every copy enqueued,
+// then one wait. False (with the error set) on a failed copy.
+static bool host_copies(ac_complex *c, int d0, int d1) {
+    for (int d = d0; d <= d1; d++) {
+        const size_t m = (size_t)c->count[d];
+        const size_t rows = m * (d + 1) * sizeof(int32_t), sizes = m * sizeof(double);
+        void *rp = nullptr;
+        double *zp = nullptr;
+        if (!c->h_block[d]) {
+            c->h_block[d] = host_alloc(rows + sizes + sizeof(double));
+            c->h_bytes[d] = rows + sizes + sizeof(double);
+        }
+        if (c->h_block[d]) {
+            zp = static_cast<double *>(c->h_block[d]);
+            rp = zp + m;
+        } else {
+            c->h_simp[d].resize(m * (d + 1) + 1);
+            c->h_size[d].resize(m + 1);
+            rp = c->h_simp[d].data();
+            zp = c->h_size[d].data();
+        }
+        if (m && (hipMemcpyAsync(rp, c->d_simp[d], rows, hipMemcpyDeviceToHost, nullptr) != hipSuccess ||
+                  hipMemcpyAsync(zp, c->d_size[d], sizes, hipMemcpyDeviceToHost, nullptr) != hipSuccess)) {
+            (void)hipStreamSynchronize(nullptr);
+            set_error(AC_E_DEVICE, "device-to-host copy failed");
+            return false;
+        }
+    }
+    if (hipStreamSynchronize(nullptr) != hipSuccess) {
+        set_error(AC_E_DEVICE, "device-to-host copy failed");
+        return false;
+    }
+    for (int d = d0; d <= d1; d++) c->host_ready[d] = true;
+    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -2233,21 +2419,11 @@ ac_status ac_alpha_complex_noalloc(const double *d_xyz, const double *d_radii, i
         Batch bt;
         bt.off = {0, n};
         const Options o = parse(opt);
-        const ac_status st = run_pipeline(d_xyz, d_radii, n, bt, alpha, o, s, &c);  // synchronises s on error
+        Ext ext{d_simp, d_size, capacity, false};
+        const ac_status st = run_pipeline(d_xyz, d_radii, n, bt, &alpha, 1, o, s, &c, nullptr, &ext);  // synchronises s
         if (st != AC_OK) return st;
-        bool fits = true;
-        for (int d = 0; d < 4; d++) {
-            counts[d] = c->count[d];
-            fits = fits && c->count[d] <= capacity[d];
-        }
-        for (int d = 0; fits && d < 4; d++) {
-            const size_t m = (size_t)c->count[d];
-            if (m == 0) continue;
-            HIP_TRY(hipMemcpyAsync(d_simp[d], c->d_simp[d], m * (d + 1) * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-            HIP_TRY(hipMemcpyAsync(d_size[d], c->d_size[d], m * sizeof(double), hipMemcpyDeviceToDevice, s));
-        }
-        // the next call may reuse the scratch only once these copies are done
-        HIP_TRY(hipStreamSynchronize(s));
+        const bool fits = ext.fits;
+        for (int d = 0; d < 4; d++) counts[d] = c->count[d];
         free_complex(c);  // host object only: its arrays lie in the scratch
         c = nullptr;
         if (!fits) return set_error(AC_E_CAPACITY, "an output buffer is smaller than the result (counts holds the sizes)");
@@ -2317,36 +2493,52 @@ ac_status ac_alpha_complex(const double *xyz, const double *radii, int64_t n, do
                            ac_complex **out) {
     if (!out) return set_error(AC_E_INVALID, "out is NULL");
     *out = nullptr;
-    void *dx = nullptr, *dr = nullptr;
+    void *dx = nullptr, *dr = nullptr, *stage = nullptr;
+    size_t stage_bytes = 0;
+    auto release = [&]() {
+        // a failed call may leave copies in flight
+        if (stage) (void)hipStreamSynchronize(nullptr);
+        dev_free(dx);
+        dev_free(dr);
+        host_free(stage, stage_bytes);
+    };
     try {
         const Options o = parse(opt);
         if (!xyz || !radii) return set_error(AC_E_INVALID, "NULL input pointer");
         if (n < 1 || n >= (1 << 26)) return set_error(AC_E_INVALID, "n must be in [1, 2^26)");
         dx = dev_alloc((size_t)n * 3 * sizeof(double));
         dr = dev_alloc((size_t)n * sizeof(double));
-        HIP_TRY(hipMemcpy(dx, xyz, (size_t)n * 3 * sizeof(double), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(dr, radii, (size_t)n * sizeof(double), hipMemcpyHostToDevice));
+        const size_t xb = (size_t)n * 3 * sizeof(double), rb = (size_t)n * sizeof(double);
+        // through pinned memory where that is a moderate block; it stays in use
+        // until the build below has ended
+        if (xb + rb <= HOST_POOL_BYTES / 4) stage = host_alloc(stage_bytes = xb + rb);
+        if (stage) {
+            std::memcpy(stage, xyz, xb);
+            std::memcpy(static_cast<char *>(stage) + xb, radii, rb);
+            HIP_TRY(hipMemcpyAsync(dx, stage, xb, hipMemcpyHostToDevice, nullptr));
+            HIP_TRY(hipMemcpyAsync(dr, static_cast<char *>(stage) + xb, rb, hipMemcpyHostToDevice, nullptr));
+        } else {
+            HIP_TRY(hipMemcpy(dx, xyz, xb, hipMemcpyHostToDevice));
+            HIP_TRY(hipMemcpy(dr, radii, rb, hipMemcpyHostToDevice));
+        }
         Batch bt;
         bt.off = {0, n};
         ac_status st = run_pipeline(static_cast<double *>(dx), static_cast<double *>(dr), n, bt, alpha, o, nullptr, out);
-        dev_free(dx);
-        dev_free(dr);
+        release();
+        dx = dr = stage = nullptr;
         if (st != AC_OK) return st;
         (*out)->device_result = false;
-        for (int d = 0; d < 4; d++)
-            if (!ac_simplices(*out, d) || !ac_sizes(*out, d)) {
-                ac_free(*out);
-                *out = nullptr;
-                return set_error(AC_E_DEVICE, "device-to-host copy failed");
-            }
+        if (!host_copies(*out, 0, 3)) {
+            ac_free(*out);
+            *out = nullptr;
+            return AC_E_DEVICE;
+        }
         return AC_OK;
     } catch (const HipError &e) {
-        dev_free(dx);
-        dev_free(dr);
+        release();
         return set_error(e.st, e.msg);
     } catch (...) {
-        dev_free(dx);
-        dev_free(dr);
+        release();
         return set_error(AC_E_DEVICE, "unexpected host exception");
     }
 }
@@ -2537,26 +2729,14 @@ int64_t ac_count(const ac_complex *c, int dim) {
 
 const int32_t *ac_simplices(ac_complex *c, int dim) {
     if (!c || dim < 0 || dim > 3) return nullptr;
-    if (!c->host_ready[dim]) {
-        const size_t m = (size_t)c->count[dim];
-        c->h_simp[dim].resize(m * (dim + 1) + 1);
-        c->h_size[dim].resize(m + 1);
-        if (m) {
-            if (hipMemcpy(c->h_simp[dim].data(), c->d_simp[dim], m * (dim + 1) * sizeof(int32_t),
-                          hipMemcpyDeviceToHost) != hipSuccess ||
-                hipMemcpy(c->h_size[dim].data(), c->d_size[dim], m * sizeof(double), hipMemcpyDeviceToHost) !=
-                    hipSuccess) {
-                set_error(AC_E_DEVICE, "device-to-host copy failed");
-                return nullptr;
-            }
-        }
-        c->host_ready[dim] = true;
-    }
+    if (!c->host_ready[dim] && !host_copies(c, dim, dim)) return nullptr;
+    if (c->h_block[dim]) return reinterpret_cast<const int32_t *>(static_cast<const double *>(c->h_block[dim]) + c->count[dim]);
     return c->h_simp[dim].data();
 }
 
 const double *ac_sizes(ac_complex *c, int dim) {
     if (!ac_simplices(c, dim)) return nullptr;
+    if (c->h_block[dim]) return static_cast<const double *>(c->h_block[dim]);
     return c->h_size[dim].data();
 }
 
@@ -2694,6 +2874,11 @@ ac_status ac_release_workspace(void) {
     std::lock_guard<std::mutex> g(P.mu);
     for (auto &kv : P.free_blocks[dev]) (void)hipFree(kv.second);
     P.free_blocks[dev].clear();
+    HostPool &H = host_pool();
+    std::lock_guard<std::mutex> gh(H.mu);
+    for (auto &kv : H.free_blocks) (void)hipHostFree(kv.second);
+    H.free_blocks.clear();
+    H.unused = 0;
     return AC_OK;
 }
 

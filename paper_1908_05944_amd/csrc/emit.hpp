@@ -392,7 +392,8 @@ __device__ __forceinline__ void fold_candidates(const int *__restrict__ tri_cnt,
 
 __global__ void __launch_bounds__(1024) k_rec_prefix(int4 *__restrict__ tile_sum, int tiles,
                                                       const int *__restrict__ tri_cnt, const int *__restrict__ tet_cand,
-                                                      int groups, Counters *cnt, int fixed, OutCap cap, int why) {
+                                                      int groups, Counters *cnt, int fixed, OutCap cap, int why, Mail *mail,
+                                                      unsigned seq) {
     if (fixed && cnt->stop) return;
     int4 carry = make_int4(0, 0, 0, 0);
     for (int c0 = 0; c0 < tiles; c0 += 1024) {
@@ -405,7 +406,13 @@ __global__ void __launch_bounds__(1024) k_rec_prefix(int4 *__restrict__ tile_sum
         carry = carry + tot;
     }
     fold_candidates<1024>(tri_cnt, tet_cand, groups, cnt);
-    if (threadIdx.x == 0) rec_totals(carry, cnt, fixed, cap, why);
+    if (threadIdx.x == 0) {
+        rec_totals(carry, cnt, fixed, cap, why);
+        if (mail) {
+            mail->c = *cnt;
+            mail_post(mail, seq);
+        }
+    }
 }
 
 __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec, const long long *__restrict__ vert_min,
@@ -413,7 +420,7 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
                                                           double *__restrict__ out_size,
                                                           const int *__restrict__ tri_cnt,
                                                           const int *__restrict__ tet_cand, int groups, Counters *cnt,
-                                                          int fixed, OutCap cap, int why) {
+                                                          int fixed, OutCap cap, int why, Mail *mail, unsigned seq) {
     if (fixed && cnt->stop) return;
     // a wave takes REC_IPT runs of WAVE consecutive records
     const int u0 = blockIdx.x * REC_TILE + (threadIdx.x / WAVE) * (WAVE * REC_IPT) + lane_id();
@@ -445,8 +452,31 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
     }
     if (!tile_off) {
         fold_candidates<REC_BLOCK>(tri_cnt, tet_cand, groups, cnt);
-        if (threadIdx.x == 0) rec_totals(tot, cnt, fixed, cap, why);
+        if (threadIdx.x == 0) {
+            rec_totals(tot, cnt, fixed, cap, why);
+            if (mail) {
+                mail->c = *cnt;
+                mail_post(mail, seq);
+            }
+        }
     }
+}
+
+// Up to eight arrays copied in one launch (blockIdx.y: the array; all 16-byte
+// aligned, sizes multiples of 4): a copy call each would cost a launch each.
+struct CopyList {
+    const int *src[8];
+    int *dst[8];
+    long long words[8];
+};
+__global__ void __launch_bounds__(256) k_copy_list(CopyList l) {
+    const int a = blockIdx.y;
+    const long long n = l.words[a], n4 = n / 4;
+    const int4 *s4 = reinterpret_cast<const int4 *>(l.src[a]);
+    int4 *d4 = reinterpret_cast<int4 *>(l.dst[a]);
+    const long long t = (long long)blockIdx.x * 256 + threadIdx.x, stride = (long long)gridDim.x * 256;
+    for (long long k = t; k < n4; k += stride) d4[k] = s4[k];
+    if (t < n - 4 * n4) l.dst[a][4 * n4 + t] = l.src[a][4 * n4 + t];
 }
 
 // Rows of each molecule of a batch: molecule m's d-simplices are rows

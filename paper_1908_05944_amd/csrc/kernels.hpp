@@ -69,16 +69,20 @@ constexpr int GROUP = BLOCK;
 
 // ---------------------------------------------------------------------------
 // Quantise: x -> rint(1000 x) (round half to even), W = R^2. Block b handles
-// the balls [tiles[b].x, tiles[b].y) (at most QTILE, all of one molecule) and
-// writes their bounding box and flags; k_stats_reduce folds each molecule's
-// tiles. Every load of a thread is issued before the first conversion.
+// the balls [tiles[b].x, tiles[b].y) (at most QTILE, all of one molecule; of a
+// single molecule of n balls the b-th QTILE, tiles = nullptr) and writes their
+// bounding box and flags; k_stats_reduce folds each molecule's tiles. Block 0
+// also clears the counters of the build, whose first kernel this is. Every load of a thread is issued before the first conversion.
 constexpr int QTILE = 1024;  // balls per block
 __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ xyz, const double *__restrict__ r,
-                                                     const int2 *__restrict__ tiles, int4 *__restrict__ q,
-                                                     Stats *__restrict__ part) {
+                                                     const int2 *__restrict__ tiles, int n, int4 *__restrict__ q,
+                                                     Stats *__restrict__ part, Counters *cnt) {
+    static_assert(sizeof(Counters) % sizeof(int) == 0 && sizeof(Counters) / sizeof(int) <= BLOCK, "cleared as ints");
+    if (cnt && blockIdx.x == 0 && threadIdx.x < sizeof(Counters) / sizeof(int)) reinterpret_cast<int *>(cnt)[threadIdx.x] = 0;
     constexpr int PT = QTILE / BLOCK;
     int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN}, wmax = 0, flags = 0;
-    const int2 tile = tiles[blockIdx.x];
+    const int2 tile = tiles ? tiles[blockIdx.x]
+                            : make_int2((int)blockIdx.x * QTILE, min(((int)blockIdx.x + 1) * QTILE, n));
     double vx[PT][3], vr[PT];
 #pragma unroll
     for (int u = 0; u < PT; u++) {
@@ -148,12 +152,27 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
     }
 }
 
+// What a build tells the host while it runs: a block of pinned host memory that
+// a kernel writes and the host polls (a copy and a wait for the stream cost
+// about 15 us each time). seq: the number of the message, written last.
+struct Mail {
+    Counters c;
+    Stats st;
+    unsigned seq;
+};
+__device__ __forceinline__ void mail_post(Mail *mail, unsigned seq) {
+    __threadfence_system();
+    __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Block m folds the partials of molecule m's tiles [tile_first[m],
-// tile_first[m+1]) into st[m].
+// tile_first[m+1]) into st[m] (of a single molecule: the n_tiles, tile_first =
+// nullptr), and mails a single molecule's.
 __global__ void __launch_bounds__(BLOCK) k_stats_reduce(const Stats *__restrict__ part, const int *__restrict__ tile_first,
-                                                         Stats *st) {
+                                                         int n_tiles, Stats *st, Mail *mail, unsigned seq) {
     Stats b{INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN, 0, 0};
-    for (int k = tile_first[blockIdx.x] + threadIdx.x; k < tile_first[blockIdx.x + 1]; k += BLOCK) {
+    const int k0 = tile_first ? tile_first[blockIdx.x] : 0, k1 = tile_first ? tile_first[blockIdx.x + 1] : n_tiles;
+    for (int k = k0 + threadIdx.x; k < k1; k += BLOCK) {
         const Stats &o = part[k];
         b.minx = min(b.minx, o.minx); b.miny = min(b.miny, o.miny); b.minz = min(b.minz, o.minz);
         b.maxx = max(b.maxx, o.maxx); b.maxy = max(b.maxy, o.maxy); b.maxz = max(b.maxz, o.maxz);
@@ -181,6 +200,10 @@ __global__ void __launch_bounds__(BLOCK) k_stats_reduce(const Stats *__restrict_
             b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags;
         }
         st[blockIdx.x] = b;
+        if (mail) {
+            mail->st = b;
+            mail_post(mail, seq);
+        }
     }
 }
 
@@ -231,8 +254,9 @@ __device__ __forceinline__ float4 scan_ball(const int4 &a, int aq) {
                        r2 >= 0 ? sqrtf((float)r2) * (1.0f + 1.0f / (1 << 19)) : __int_as_float(0x7fc00000));
 }
 
-__device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *__restrict__ grids, int n_mol) {
-    const Grid &g = grids[mol_of(grids, n_mol, i)];
+// grids = nullptr: one molecule, whose grid is g0 (a kernel argument: no upload).
+__device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *__restrict__ grids, int n_mol, const Grid &g0) {
+    const Grid &g = grids ? grids[mol_of(grids, n_mol, i)] : g0;
     return (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
 }
 
@@ -245,7 +269,7 @@ __device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *_
 
 // Keys of a radix tile's balls, and the tile's histogram of the first digit.
 __global__ void __launch_bounds__(RS_BLOCK) k_cell_hist(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
-                                                         int n_mol, unsigned *__restrict__ key, int shift,
+                                                         int n_mol, Grid g0, unsigned *__restrict__ key, int shift,
                                                          int *__restrict__ hist, int tiles) {
     __shared__ int h[RS_BINS];
     h[threadIdx.x] = 0;
@@ -261,7 +285,7 @@ __global__ void __launch_bounds__(RS_BLOCK) k_cell_hist(const int4 *__restrict__
     for (int r = 0; r < RS_IPT; r++) {
         const int i = base + r * RS_BLOCK + (int)threadIdx.x;
         if (i >= n) break;
-        const unsigned k = cell_key(a[r], i, grids, n_mol);
+        const unsigned k = cell_key(a[r], i, grids, n_mol, g0);
         key[i] = k;
         atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
     }
@@ -383,7 +407,7 @@ constexpr int SMALL_BLOCK = 1024;
 constexpr int SMALL_BALLS = 2048;
 constexpr int SMALL_CELLS = 12288;
 __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
-                                                            int n_mol, int ncell, int *__restrict__ cell_start,
+                                                            int n_mol, Grid g0, int ncell, int *__restrict__ cell_start,
                                                             int4 *__restrict__ atom, float4 *__restrict__ sball,
                                                             int aq, int *__restrict__ perm, Counters *cnt) {
     __shared__ int cc[SMALL_CELLS];
@@ -392,7 +416,7 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restric
     for (int c = t; c < ncell; c += SMALL_BLOCK) cc[c] = 0;
     __syncthreads();
     for (int i = t; i < n; i += SMALL_BLOCK) {
-        const unsigned k = cell_key(q[i], i, grids, n_mol);
+        const unsigned k = cell_key(q[i], i, grids, n_mol, g0);
         sc[i] = (unsigned short)k;
         atomicAdd(&cc[k], 1);
     }
@@ -562,7 +586,7 @@ constexpr int nb_waves() { return SLOT == NB_SLOT && LPB == 1 ? 8 : 4; }
 template <int SLOT, int LPB, bool SINGLE>
 __global__ void __launch_bounds__(BLOCK, (nb_waves<SLOT, LPB>()))
 k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, const int *__restrict__ perm, int n,
-             const Grid *__restrict__ grids, int n_mol, const int *__restrict__ cell_start, PredParams pp,
+             const Grid *__restrict__ grids, int n_mol, Grid g0, const int *__restrict__ cell_start, PredParams pp,
              int *__restrict__ deg_n, int *__restrict__ deg_up, int *__restrict__ nslab, int *__restrict__ block_tot,
              unsigned char *__restrict__ vgab, long long *__restrict__ vert_min, Counters *cnt) {
     constexpr int BALLS = BLOCK / LPB;             // of a block
@@ -580,7 +604,7 @@ k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, co
     // entry k of a lane's list at k * BLOCK: a wave's lanes hit distinct banks
     int *const rn = sn + threadIdx.x;
     if (ball) {
-        const Grid g = grids[SINGLE ? 0 : mol_of(grids, n_mol, i)];
+        const Grid g = SINGLE ? (grids ? grids[0] : g0) : grids[mol_of(grids, n_mol, i)];
         scan_rows(g, a, i, sball, cell_start, pp, part, LPB, [&](int j) {
             if (j == i) return;
             if (cn < LSLOT) rn[cn * BLOCK] = j;
@@ -656,7 +680,7 @@ k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, co
 template <bool FILL>
 __global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ atom, const float4 *__restrict__ sball,
                                                      const int *__restrict__ perm, int n, const Grid *__restrict__ grids,
-                                                     int n_mol, const int *__restrict__ cell_start, PredParams pp,
+                                                     int n_mol, Grid g0, const int *__restrict__ cell_start, PredParams pp,
                                                      int *__restrict__ deg_n, int *__restrict__ deg_up,
                                                      unsigned char *__restrict__ vgab, const int *__restrict__ nbr_start,
                                                      const int *__restrict__ up_start, int *__restrict__ nbr,
@@ -671,7 +695,7 @@ __global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ ato
     bool gab = true;
     const int pn = FILL ? nbr_start[i] : 0, pu = FILL ? up_start[i] : 0;
     if (ball) {
-        const Grid g = grids[mol_of(grids, n_mol, i)];
+        const Grid g = grids ? grids[mol_of(grids, n_mol, i)] : g0;
         scan_rows(g, a, i, sball, cell_start, pp, 0, 1, [&](int j) {
             if (j == i) return;
             const int4 bb = atom[j];
@@ -837,7 +861,8 @@ __global__ void __launch_bounds__(BLOCK) k_group_pairs(const int *__restrict__ d
 constexpr int NBS_BLOCK = 1024;
 constexpr int NBS_IPT = 4;
 __global__ void __launch_bounds__(NBS_BLOCK) k_nbr_scan(const int *__restrict__ tot, int nb, int stride,
-                                                         int *__restrict__ uoff, int *__restrict__ poff, Counters *cnt) {
+                                                         int *__restrict__ uoff, int *__restrict__ poff, Counters *cnt, Mail *mail,
+                                                         unsigned seq) {
     long long nn = 0, cu = 0, cp = 0;
     for (int c0 = 0; c0 < nb; c0 += NBS_BLOCK * NBS_IPT) {
         const int base = c0 + threadIdx.x * NBS_IPT;
@@ -878,6 +903,10 @@ __global__ void __launch_bounds__(NBS_BLOCK) k_nbr_scan(const int *__restrict__ 
         cnt->Nn = t;
         cnt->E = cu;
         cnt->P = cp;
+        if (mail) {
+            mail->c = *cnt;
+            mail_post(mail, seq);
+        }
     }
 }
 
