@@ -1907,34 +1907,66 @@ static void check_measure_args(const ac_complex *c, const double *d_xyz, const d
     if (incidence_count(c) >= INT_MAX) throw HipError{AC_E_CAPACITY, "too many simplex corners"};
 }
 
+static Simplices simplices_of(const ac_complex *c) {
+    Simplices sx{};
+    long long first = 0;
+    int block0 = 0;
+    for (int d = 0; d < 4; d++) {
+        const long long corners = c->count[d] * (d + 1);
+        sx.simp[d] = c->d_simp[d];
+        sx.count[d] = c->count[d];
+        sx.first[d] = first;
+        sx.blocks[d] = (int)((corners + MEASURE_BLOCK - 1) / MEASURE_BLOCK);
+        sx.block0[d] = block0;
+        first += corners;
+        block0 += sx.blocks[d];
+    }
+    return sx;
+}
+static int measure_blocks(const Simplices &sx) { return sx.block0[3] + sx.blocks[3]; }
+
 // Sorts the corners of all simplices by ball id once per complex.
 static void ensure_incidence(ac_complex *c, hipStream_t s) {
     if (c->inc_slot) return;
-    const long long M = incidence_count(c);
+    const int M = (int)incidence_count(c);
     const int n = (int)c->n;
     int32_t *slot = static_cast<int32_t *>(dev_alloc((size_t)(M > 0 ? M : 1) * sizeof(int32_t)));
     int32_t *start = nullptr;
     try {
         start = static_cast<int32_t *>(dev_alloc((size_t)(n + 1) * sizeof(int32_t)));
         Scope sc;
-        unsigned *key = sc.get<unsigned>(M > 0 ? M : 1);
-        long long off = 0;
-        for (int d = 0; d < 4; d++) {
-            const long long m = c->count[d] * (d + 1);
-            if (m) HIP_TRY(hipMemcpyAsync(key + off, c->d_simp[d], m * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-            off += m;
-        }
         if (M > 0) {
-            k_iota<<<(unsigned)((M + MEASURE_BLOCK - 1) / MEASURE_BLOCK), MEASURE_BLOCK, 0, s>>>(slot, M);
+            // buckets of at most INC_KEYS balls, as small as the radix passes reach
+            const int bits = bits_for(n);
+            const int passes = std::max(1, (bits - INC_SHIFT + RS_BITS - 1) / RS_BITS);
+            const int shift = std::max(0, bits - RS_BITS * passes);
+            const int nb = ((n - 1) >> shift) + 1;
+            const int tiles = (M + RS_TILE - 1) / RS_TILE;
+            unsigned *kin = sc.get<unsigned>(M), *kout = sc.get<unsigned>(M);
+            unsigned *pin = sc.get<unsigned>(M), *pout = sc.get<unsigned>(M);
+            int *hist = sc.get<int>((size_t)RS_BINS * tiles), *totals = sc.get<int>(RS_BINS);
+            int *first = sc.get<int>((size_t)nb + 1);
+            const Simplices sx = simplices_of(c);
+            for (int k = 0, sh = shift; k < passes; k++, sh += RS_BITS) {
+                if (k == 0)
+                    k_inc_hist<<<tiles, RS_BLOCK, 0, s>>>(sx, M, kin, sh, hist, tiles);
+                else
+                    k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, M, sh, hist, tiles);
+                k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
+                if (k == 0)
+                    k_rs_scatter<unsigned, true><<<tiles, RS_BLOCK, 0, s>>>(kin, nullptr, kout, pout, M, sh, hist, totals, tiles);
+                else
+                    k_rs_scatter<unsigned><<<tiles, RS_BLOCK, 0, s>>>(kin, pin, kout, pout, M, sh, hist, totals, tiles);
+                LAUNCH_CHECK();
+                std::swap(kin, kout);
+                std::swap(pin, pout);
+            }
+            key_starts(kin, M, shift, nb, first, s);
+            k_inc_finish<<<nb, INC_BLOCK, 0, s>>>(kin, pin, first, shift, n, start, slot);
             LAUNCH_CHECK();
-            int32_t *sorted = slot;
-            radix_sort<int>(key, sorted, (int)M, bits_for(n), s, sc);
-            if (sorted != slot)
-                HIP_TRY(hipMemcpyAsync(slot, sorted, (size_t)M * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+        } else {
+            fill<int>(start, 0, n + 1, s);
         }
-        k_incidence_start<<<(unsigned)((n + 1 + MEASURE_BLOCK - 1) / MEASURE_BLOCK), MEASURE_BLOCK, 0, s>>>(key, M, n,
-                                                                                                          start);
-        LAUNCH_CHECK();
         HIP_TRY(hipStreamSynchronize(s));  // before the scope's blocks go back to the pool
     } catch (...) {
         dev_free(slot);
@@ -1945,51 +1977,32 @@ static void ensure_incidence(ac_complex *c, hipStream_t s) {
     c->inc_start = start;
 }
 
-template <int K>
-static void measure_fwd_dim(const ac_complex *c, const double *x, const double *r, double *part, int &nb,
-                            hipStream_t s) {
-    const long long m = c->count[K - 1];
-    if (m == 0) return;
-    const unsigned b = (unsigned)((m * K + MEASURE_BLOCK - 1) / MEASURE_BLOCK);
-    k_measure_fwd<K><<<b, MEASURE_BLOCK, 0, s>>>(c->d_simp[K - 1], m, x, r, part + 2LL * nb);
+// Launches the measure kernels of every dimension.
+template <bool VA, bool GRAD>
+static void measure_launch(const Simplices &sx, const double *x, const double *r, const double *g, double4 *contrib,
+                           double *part, hipStream_t s) {
+    const int nb = measure_blocks(sx);
+    if (nb > 0) k_measure<VA, GRAD><<<nb, MEASURE_BLOCK, 0, s>>>(sx, x, r, g, contrib, part);
     LAUNCH_CHECK();
-    nb += (int)b;
+}
+
+// The complex's buffer of block parts, then V and A.
+static double *measure_parts(ac_complex *c, int nb) {
+    if (!c->meas_part) c->meas_part = static_cast<double *>(dev_alloc((size_t)(2 * (size_t)nb + 2) * sizeof(double)));
+    return c->meas_part;
 }
 
 // Writes V, A to d_out (device), or to the complex's own buffer if d_out is
 // NULL; returns where they are.
 static double *measure_forward(ac_complex *c, const double *x, const double *r, double *d_out, hipStream_t s) {
-    long long nb_total = 0;
-    for (int d = 0; d < 4; d++) nb_total += (c->count[d] * (d + 1) + MEASURE_BLOCK - 1) / MEASURE_BLOCK;
-    if (!c->meas_part) c->meas_part = static_cast<double *>(dev_alloc((size_t)(2 * nb_total + 2) * sizeof(double)));
-    double *part = c->meas_part;
-    if (!d_out) d_out = part + 2 * nb_total;
-    int nb = 0;
-    measure_fwd_dim<1>(c, x, r, part, nb, s);
-    measure_fwd_dim<2>(c, x, r, part, nb, s);
-    measure_fwd_dim<3>(c, x, r, part, nb, s);
-    measure_fwd_dim<4>(c, x, r, part, nb, s);
+    const Simplices sx = simplices_of(c);
+    const int nb = measure_blocks(sx);
+    double *part = measure_parts(c, nb);
+    if (!d_out) d_out = part + 2 * (size_t)nb;
+    measure_launch<true, false>(sx, x, r, nullptr, nullptr, part, s);
     k_measure_total<<<1, MEASURE_BLOCK, 0, s>>>(part, nb, d_out);
     LAUNCH_CHECK();
     return d_out;
-}
-
-// Backward of dimension K - 1; with part, also the forward's block parts
-// (part + 2 nb onwards, nb advanced as in measure_fwd_dim).
-template <int K>
-static void measure_bwd_dim(const ac_complex *c, const double *x, const double *r, const double *g, double4 *contrib,
-                            long long &off, hipStream_t s, double *part = nullptr, int *nb = nullptr) {
-    const long long m = c->count[K - 1];
-    if (m == 0) return;
-    const unsigned b = (unsigned)((m * K + MEASURE_BLOCK - 1) / MEASURE_BLOCK);
-    if (part) {
-        k_measure_bwd<K, true><<<b, MEASURE_BLOCK, 0, s>>>(c->d_simp[K - 1], m, x, r, g, contrib + off, part + 2LL * *nb);
-        *nb += (int)b;
-    } else {
-        k_measure_bwd<K, false><<<b, MEASURE_BLOCK, 0, s>>>(c->d_simp[K - 1], m, x, r, g, contrib + off, nullptr);
-    }
-    LAUNCH_CHECK();
-    off += m * K;
 }
 
 // Validated molecule offsets of a batch call.
@@ -2803,26 +2816,16 @@ static void measure_backward(ac_complex *c, const double *x, const double *r, in
     ensure_incidence(c, s);
     const long long M = incidence_count(c);
     if (!c->meas_contrib) c->meas_contrib = static_cast<double4 *>(dev_alloc((size_t)(M > 0 ? M : 1) * sizeof(double4)));
-    double4 *contrib = c->meas_contrib;
-    double *part = nullptr;
-    if (d_out) {
-        long long nb_total = 0;
-        for (int d = 0; d < 4; d++) nb_total += (c->count[d] * (d + 1) + MEASURE_BLOCK - 1) / MEASURE_BLOCK;
-        if (!c->meas_part) c->meas_part = static_cast<double *>(dev_alloc((size_t)(2 * nb_total + 2) * sizeof(double)));
-        part = c->meas_part;
-    }
-    long long off = 0;
-    int nb = 0;
-    measure_bwd_dim<1>(c, x, r, g, contrib, off, s, part, &nb);
-    measure_bwd_dim<2>(c, x, r, g, contrib, off, s, part, &nb);
-    measure_bwd_dim<3>(c, x, r, g, contrib, off, s, part, &nb);
-    measure_bwd_dim<4>(c, x, r, g, contrib, off, s, part, &nb);
-    if (d_out) {
-        k_measure_total<<<1, MEASURE_BLOCK, 0, s>>>(part, nb, d_out);
-        LAUNCH_CHECK();
-    }
-    k_measure_gather<<<(unsigned)((n + MEASURE_BLOCK - 1) / MEASURE_BLOCK), MEASURE_BLOCK, 0, s>>>(
-        c->inc_start, c->inc_slot, contrib, (int)n, dx, dr);
+    const Simplices sx = simplices_of(c);
+    const int nb = measure_blocks(sx);
+    double *part = d_out ? measure_parts(c, nb) : nullptr;
+    if (d_out)
+        measure_launch<true, true>(sx, x, r, g, c->meas_contrib, part, s);
+    else
+        measure_launch<false, true>(sx, x, r, g, c->meas_contrib, nullptr, s);
+    constexpr int BALLS = MEASURE_BLOCK / GATHER_LPB;
+    k_measure_gather<<<(unsigned)((n + BALLS - 1) / BALLS) + (d_out ? 1 : 0), MEASURE_BLOCK, 0, s>>>(
+        c->inc_start, c->inc_slot, c->meas_contrib, (int)n, dx, dr, part, nb, d_out);
     LAUNCH_CHECK();
 }
 

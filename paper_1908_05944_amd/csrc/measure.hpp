@@ -18,11 +18,12 @@
 // cot(psi/2) times the length (or int n ds) of each boundary arc of P_i, psi
 // the interior dihedral angle of I there.
 //
-// One thread per simplex; float64 throughout. The coordinates are the
+// One thread per corner of a simplex; float64 throughout. The coordinates are the
 // caller's float64 ones (not the quantised values the complex was built
 // from), so square roots and arc cosines are clamped to their domain.
 #pragma once
 #include "common.hpp"
+#include "radix.hpp"
 
 namespace acx {
 
@@ -206,100 +207,42 @@ __device__ __forceinline__ void load_balls(const int *__restrict__ simp, long lo
 
 constexpr int MEASURE_BLOCK = 256;
 
-// One thread per (simplex, corner) of dimension K - 1 (thread t: simplex
-// t / K, corner t % K). Per block: the signed sums of the corners' volume
-// and patch-area parts, written to part[2 * block] and part[2 * block + 1].
-template <int K>
-__global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_fwd(const int *__restrict__ simp, long long m,
-                                                                const double *__restrict__ xyz,
-                                                                const double *__restrict__ rad, double *__restrict__ part) {
-    __shared__ double sv[MEASURE_BLOCK / WAVE], sa[MEASURE_BLOCK / WAVE];
-    const long long t = (long long)blockIdx.x * MEASURE_BLOCK + threadIdx.x;
-    double v = 0, a = 0;
-    if (t < m * K) {
-        D3 P[K];
-        double R[K];
-        load_balls<K>(simp, t / K, (int)(t % K), xyz, rad, P, R);
-        CornerTerms ct;
-        corner_terms<K, false>(P, R, ct);
-        v = ct.vol;
-        a = ct.area;
-        if ((K - 1) & 1) {
-            v = -v;
-            a = -a;
-        }
-    }
-    for (int off = WAVE / 2; off > 0; off >>= 1) {
-        v += __shfl_down(v, off, WAVE);
-        a += __shfl_down(a, off, WAVE);
-    }
-    const int w = threadIdx.x / WAVE;
-    if (lane_id() == 0) {
-        sv[w] = v;
-        sa[w] = a;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tv = 0, ta = 0;
-        for (int k = 0; k < MEASURE_BLOCK / WAVE; k++) {
-            tv += sv[k];
-            ta += sa[k];
-        }
-        part[2 * blockIdx.x] = tv;
-        part[2 * blockIdx.x + 1] = ta;
-    }
-}
+// Simplices of a complex by dimension (rows simp[d], count[d] of them), the
+// blocks of a launch per dimension, and where a dimension's corners start among
+// all (slot of corner k of simplex s of dimension d: first[d] + s (d + 1) + k)
+// and its blocks among the blocks of all dimensions.
+struct Simplices {
+    const int *simp[4];
+    long long count[4], first[4];
+    int blocks[4], block0[4];
+};
 
-__global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_total(const double *__restrict__ part, int nb,
-                                                                  double *__restrict__ out) {
-    __shared__ double sv[MEASURE_BLOCK], sa[MEASURE_BLOCK];
-    double v = 0, a = 0;
-    for (int b = threadIdx.x; b < nb; b += MEASURE_BLOCK) {
-        v += part[2 * b];
-        a += part[2 * b + 1];
-    }
-    sv[threadIdx.x] = v;
-    sa[threadIdx.x] = a;
-    __syncthreads();
-    for (int h = MEASURE_BLOCK / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            sv[threadIdx.x] += sv[threadIdx.x + h];
-            sa[threadIdx.x] += sa[threadIdx.x + h];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = sv[0];
-        out[1] = sa[0];
-    }
-}
-
-// Per incidence slot (simplex s, corner c at slot base + s*K + c; one thread
-// each): the corner's contribution gV * d(V)/d(p, r) + gA * d(A)/d(p, r),
-// as (x, y, z, r), with (gV, gA) = (g[0], g[1]) read from device memory.
-// VA: the block's signed volume and area parts too, as k_measure_fwd writes
-// them (forward and backward in one pass).
-template <int K, bool VA>
-__global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_bwd(const int *__restrict__ simp, long long m,
-                                                                const double *__restrict__ xyz,
-                                                                const double *__restrict__ rad,
-                                                                const double *__restrict__ g,
-                                                                double4 *__restrict__ contrib,
-                                                                double *__restrict__ part) {
-    const long long t = (long long)blockIdx.x * MEASURE_BLOCK + threadIdx.x;
+// Block b of dimension K - 1, one thread per (simplex, corner) (thread t:
+// simplex t / K, corner t % K).
+// GRAD: the corner's contribution gV d(V)/d(p, r) + gA d(A)/d(p, r) to its ball,
+// as (x, y, z, r), at its slot of contrib, with (gV, gA) = (g[0], g[1]) read
+// from device memory. VA: the signed sums of the block's volume and patch-area
+// parts at part[2 * block] and part[2 * block + 1].
+template <int K, bool VA, bool GRAD>
+__device__ __forceinline__ void measure_block(const Simplices &sx, int b, const double *__restrict__ xyz,
+                                              const double *__restrict__ rad, const double *__restrict__ g,
+                                              double4 *__restrict__ contrib, double *__restrict__ part) {
+    const long long t = (long long)b * MEASURE_BLOCK + threadIdx.x;
     const double sg = ((K - 1) & 1) ? -1.0 : 1.0;
     double v = 0, a = 0;
-    if (t < m * K) {
-        const double gV = g[0], gA = g[1];
+    if (t < sx.count[K - 1] * K) {
         D3 P[K];
         double R[K];
-        load_balls<K>(simp, t / K, (int)(t % K), xyz, rad, P, R);
+        load_balls<K>(sx.simp[K - 1], t / K, (int)(t % K), xyz, rad, P, R);
         CornerTerms ct;
-        corner_terms<K, true>(P, R, ct);
-        const double ir = 2.0 / R[0];
-        const D3 gx = (sg * gV) * ct.vec + (sg * gA) * (ir * ct.vec + ct.arc_vec);
-        const double gr = sg * (gV * ct.area + gA * (ir * ct.area + ct.arc_len));
-        contrib[t] = make_double4(gx.x, gx.y, gx.z, gr);
+        corner_terms<K, GRAD>(P, R, ct);
+        if (GRAD) {
+            const double gV = g[0], gA = g[1];
+            const double ir = 2.0 / R[0];
+            const D3 gx = (sg * gV) * ct.vec + (sg * gA) * (ir * ct.vec + ct.arc_vec);
+            const double gr = sg * (gV * ct.area + gA * (ir * ct.area + ct.arc_len));
+            contrib[sx.first[K - 1] + t] = make_double4(gx.x, gx.y, gx.z, gr);
+        }
         v = sg * ct.vol;
         a = sg * ct.area;
     }
@@ -321,49 +264,198 @@ __global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_bwd(const int *__rest
             tv += sv[k];
             ta += sa[k];
         }
-        part[2 * blockIdx.x] = tv;
-        part[2 * blockIdx.x + 1] = ta;
+        part[2LL * (sx.block0[K - 1] + b)] = tv;
+        part[2LL * (sx.block0[K - 1] + b) + 1] = ta;
     }
 }
 
-// vstart[i] = first position of vertex i in the sorted incidence keys (i in [0, n]).
-__global__ void __launch_bounds__(MEASURE_BLOCK) k_incidence_start(const unsigned *__restrict__ key, long long M, int n,
-                                                                    int *__restrict__ vstart) {
-    const long long i = (long long)blockIdx.x * MEASURE_BLOCK + threadIdx.x;
-    if (i > n) return;
-    long long lo = 0, hi = M;
-    while (lo < hi) {
-        const long long mid = (lo + hi) >> 1;
-        if ((long long)key[mid] < i) lo = mid + 1; else hi = mid;
-    }
-    vstart[i] = (int)lo;
+// All dimensions in one launch, the largest simplices (the longest blocks)
+// first. Bound by the float64 chains of the tetrahedra's and triangles' corners
+// (square roots, arc cosines), so that it does not matter that points and edges
+// run with the tetrahedra's registers (240 a lane with GRAD, two waves per
+// SIMD). Fused call, one launch a dimension 43 us at 4,001 balls, this 14; with
+// points and edges in a launch of their own 17.4 (25.5 against 22.2 at 16,000,
+// 76.9 against 76.1 at 100,000, 145 against 147 at 200,000).
+template <bool VA, bool GRAD>
+__global__ void __launch_bounds__(MEASURE_BLOCK) k_measure(Simplices sx, const double *__restrict__ xyz,
+                                                            const double *__restrict__ rad, const double *__restrict__ g,
+                                                            double4 *__restrict__ contrib, double *__restrict__ part) {
+    int b = blockIdx.x;
+    if (b < sx.blocks[3]) return measure_block<4, VA, GRAD>(sx, b, xyz, rad, g, contrib, part);
+    b -= sx.blocks[3];
+    if (b < sx.blocks[2]) return measure_block<3, VA, GRAD>(sx, b, xyz, rad, g, contrib, part);
+    b -= sx.blocks[2];
+    if (b < sx.blocks[1]) return measure_block<2, VA, GRAD>(sx, b, xyz, rad, g, contrib, part);
+    measure_block<1, VA, GRAD>(sx, b - sx.blocks[1], xyz, rad, g, contrib, part);
 }
 
-// Gradient of ball i: the sum of its incidence slots' contributions, in slot
-// order (deterministic).
+// V, A from the nb blocks' parts, summed in a fixed order by one block.
+__device__ __forceinline__ void measure_total(const double *__restrict__ part, int nb, double *__restrict__ out) {
+    __shared__ double sv[MEASURE_BLOCK / WAVE], sa[MEASURE_BLOCK / WAVE];
+    double v = 0, a = 0;
+    const double2 *p = reinterpret_cast<const double2 *>(part);
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += MEASURE_BLOCK) {
+        const double2 x = p[b];
+        v += x.x;
+        a += x.y;
+    }
+    for (int off = WAVE / 2; off > 0; off >>= 1) {
+        v += __shfl_down(v, off, WAVE);
+        a += __shfl_down(a, off, WAVE);
+    }
+    const int w = threadIdx.x / WAVE;
+    if (lane_id() == 0) {
+        sv[w] = v;
+        sa[w] = a;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double tv = 0, ta = 0;
+        for (int k = 0; k < MEASURE_BLOCK / WAVE; k++) {
+            tv += sv[k];
+            ta += sa[k];
+        }
+        out[0] = tv;
+        out[1] = ta;
+    }
+}
+__global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_total(const double *__restrict__ part, int nb,
+                                                                  double *__restrict__ out) {
+    measure_total(part, nb, out);
+}
+
+// ---------------------------------------------------------------------------
+// The corners of all simplices sorted by ball (slots ascending within a ball),
+// once per complex: radix passes over the key bits above a bucket of 2^shift
+// balls, then k_inc_finish orders each bucket on the low bits.
+
+// Ball of every corner slot, and the histogram of the first digit.
+__global__ void __launch_bounds__(RS_BLOCK) k_inc_hist(Simplices sx, int M, unsigned *__restrict__ key, int shift,
+                                                        int *__restrict__ hist, int tiles) {
+    __shared__ int h[RS_BINS];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * RS_TILE;
+#pragma unroll
+    for (int r = 0; r < RS_IPT; r++) {
+        const int i = base + r * RS_BLOCK + (int)threadIdx.x;
+        if (i >= M) break;
+        const int d = (i >= sx.first[1]) + (i >= sx.first[2]) + (i >= sx.first[3]);
+        const int *p = d == 0 ? sx.simp[0] : d == 1 ? sx.simp[1] : d == 2 ? sx.simp[2] : sx.simp[3];
+        const long long f = d == 0 ? 0 : d == 1 ? sx.first[1] : d == 2 ? sx.first[2] : sx.first[3];
+        const unsigned k = (unsigned)p[i - f];
+        key[i] = k;
+        atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
+    }
+    __syncthreads();
+    hist[(long long)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+}
+
+// One bucket per block: its rows [start[b], start[b + 1]) of (key, slot), in
+// slot order, are ordered by ball, stably: each wave takes a contiguous part and
+// ranks its rows among equal balls with ballots and counters of its own, a
+// scan over (ball, wave) places them. No limit on the rows of a bucket or ball.
+// At 100,000 balls (196 buckets of some 7,000 rows) 18 us, with 256 threads a
+// block 44; three full radix passes and a search for every ball's start, which
+// this replaces, took 150.
+constexpr int INC_SHIFT = 9;
+constexpr int INC_KEYS = 1 << INC_SHIFT;
+constexpr int INC_BLOCK = 1024;
+__global__ void __launch_bounds__(INC_BLOCK) k_inc_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ pay,
+                                                     const int *__restrict__ start, int shift, int n,
+                                                     int *__restrict__ inc_start, int *__restrict__ inc_slot) {
+    constexpr int NW = INC_BLOCK / WAVE;
+    static_assert(INC_KEYS <= INC_BLOCK, "a ball per thread");
+    __shared__ int cnt[NW][INC_KEYS];
+    const int b = blockIdx.x, t = threadIdx.x, lane = lane_id(), w = t / WAVE;
+    const int s = start[b], rows = start[b + 1] - s;
+    const int k0 = b << shift, keys = min(1 << shift, n - k0);
+    for (int c = t; c < NW * INC_KEYS; c += INC_BLOCK) (&cnt[0][0])[c] = 0;
+    __syncthreads();
+    const int part = ((rows + NW - 1) / NW + WAVE - 1) / WAVE * WAVE;
+    const int p0 = min(w * part, rows), p1 = min(p0 + part, rows);
+    // lanes of the wave with this lane's ball
+    auto peers_of = [&](int k, bool valid) {
+        unsigned long long m = __ballot(valid);
+        for (int bit = 0; bit < shift; bit++) {
+            const unsigned long long x = __ballot((k >> bit) & 1);
+            m &= ((k >> bit) & 1) ? x : ~x;
+        }
+        return m;
+    };
+    for (int p = p0 + lane; p - lane < p1; p += WAVE)
+        if (p < p1) atomicAdd(&cnt[w][(int)key[s + p] - k0], 1);
+    __syncthreads();
+    {
+        int sum = 0, tot;
+        if (t < INC_KEYS)
+            for (int v = 0; v < NW; v++) sum += cnt[v][t];
+        int run = block_exclusive_scan<INC_BLOCK>(sum, &tot);
+        if (t < keys) inc_start[k0 + t] = s + run;
+        if (t < INC_KEYS)
+            for (int v = 0; v < NW; v++) {
+                const int c = cnt[v][t];
+                cnt[v][t] = run;
+                run += c;
+            }
+    }
+    if (b == gridDim.x - 1 && t == 0) inc_start[n] = s + rows;
+    __syncthreads();
+    for (int p = p0 + lane; p - lane < p1; p += WAVE) {
+        const bool valid = p < p1;
+        const int k = valid ? (int)key[s + p] - k0 : 0;
+        const unsigned long long peers = peers_of(k, valid);
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+        int at = 0;
+        if (valid) at = cnt[w][k] + rank;
+        __builtin_amdgcn_wave_barrier();  // every lane has read its counter
+        if (valid && rank == 0) cnt[w][k] += __popcll(peers);
+        if (valid) inc_slot[s + at] = (int)pay[s + p];
+    }
+}
+
+// Gradient of ball i: the sum of its incidence slots' contributions, by LPB
+// lanes each taking every LPB-th slot and then a fixed tree (deterministic; one
+// lane alone walks a chain of two dependent loads per slot, some 15 of them:
+// 20 us at 4,001 balls against 4, 34 against 24 at 100,000). Past the balls' blocks, one block sums V and
+// A (nb parts to va) where asked to.
+constexpr int GATHER_LPB = 8;
 __global__ void __launch_bounds__(MEASURE_BLOCK) k_measure_gather(const int *__restrict__ vstart,
                                                                    const int *__restrict__ slot,
                                                                    const double4 *__restrict__ contrib, int n,
-                                                                   double *__restrict__ dxyz, double *__restrict__ dr) {
-    const int i = blockIdx.x * MEASURE_BLOCK + threadIdx.x;
-    if (i >= n) return;
-    double gx = 0, gy = 0, gz = 0, gr = 0;
-    for (int q = vstart[i]; q < vstart[i + 1]; q++) {
-        const double4 c = contrib[slot[q]];
-        gx += c.x;
-        gy += c.y;
-        gz += c.z;
-        gr += c.w;
+                                                                   double *__restrict__ dxyz, double *__restrict__ dr,
+                                                                   const double *__restrict__ part, int nb,
+                                                                   double *__restrict__ va) {
+    constexpr int BALLS = MEASURE_BLOCK / GATHER_LPB;
+    if ((int)blockIdx.x * BALLS >= n) {
+        measure_total(part, nb, va);
+        return;
     }
+    const int i = blockIdx.x * BALLS + threadIdx.x / GATHER_LPB, l = threadIdx.x % GATHER_LPB;
+    const int q0 = i < n ? vstart[i] : 0, q1 = i < n ? vstart[i + 1] : 0;
+    double gx = 0, gy = 0, gz = 0, gr = 0;
+    for (int q = q0 + l; q < q1; q += 2 * GATHER_LPB) {
+        const bool two = q + GATHER_LPB < q1;
+        const int s0 = slot[q], s1 = slot[two ? q + GATHER_LPB : q];
+        const double4 c = contrib[s0], e = contrib[s1];
+        gx += c.x + (two ? e.x : 0.0);
+        gy += c.y + (two ? e.y : 0.0);
+        gz += c.z + (two ? e.z : 0.0);
+        gr += c.w + (two ? e.w : 0.0);
+    }
+#pragma unroll
+    for (int off = 1; off < GATHER_LPB; off <<= 1) {
+        gx += __shfl_xor(gx, off, WAVE);
+        gy += __shfl_xor(gy, off, WAVE);
+        gz += __shfl_xor(gz, off, WAVE);
+        gr += __shfl_xor(gr, off, WAVE);
+    }
+    if (i >= n || l != 0) return;
     dxyz[3LL * i] = gx;
     dxyz[3LL * i + 1] = gy;
     dxyz[3LL * i + 2] = gz;
     dr[i] = gr;
-}
-
-__global__ void __launch_bounds__(MEASURE_BLOCK) k_iota(int *__restrict__ p, long long m) {
-    const long long i = (long long)blockIdx.x * MEASURE_BLOCK + threadIdx.x;
-    if (i < m) p[i] = (int)i;
 }
 
 }  // namespace acx
