@@ -36,6 +36,9 @@ _lib = None
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # no vectors of floats either: without packed operations they only cost the
+    # AC2 walks registers (copies of each constant for four neighbours, spilled)
+    "-fno-slp-vectorize",
 ]
 
 STATUS = {0: "ok", 1: "invalid argument", 2: "duplicate centres", 3: "out of range", 4: "out of memory",

@@ -859,11 +859,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         tm.mark(ST_BIN);
         int *cell_start = sc.get<int>(ncell + 1);
         int4 *atom = sc.get<int4>(n);
-        float4 *sball = sc.get<float4>(n);
+        float4 *sball = sc.get<float4>(n), *wball = sc.get<float4>(n);
         int *perm = sc.get<int>(n);
         if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
             k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, (int)ncell, cell_start, atom, sball,
-                                                 (int)aq, perm, cnt);
+                                                 wball, (int)aq, perm, cnt);
             LAUNCH_CHECK();
         } else {
             // bucket: at most BIN_CELLS cells, and a bucket of full cells (2.5
@@ -901,7 +901,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             }
             key_starts(kin, n, shift, nb, start, s);
             k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, start, shift, ncell, q, pout, cell_start, atom, sball,
-                                                   (int)aq, perm, cnt);
+                                                   wball, (int)aq, perm, cnt);
             LAUNCH_CHECK();
         }
 
@@ -1028,9 +1028,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned char *egab = sc.get<unsigned char>(E1);
         long long *edge_min = sc.get<long long>(E1);
 
-        // ---- AC2 of the candidate edges, candidate triangles of every group ----
+        // ---- candidate triangles of every group ----
         Cands cd{};
         cd.atom = atom;
+        cd.wball = wball;
         cd.perm = perm;
         cd.nbr_start = nbr_start;
         cd.nbr_cnt = deg_n;
@@ -1043,14 +1044,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         cd.tri_cnt = sc.get<int>(groups);
         cd.n = n;
         cd.gshift = gshift;
-        // the edge count on the device (a recorded build's launch is sized for its capacity)
-        const int *E_dev = up_start + n;
-        if (split) tm.mark(ST_EDGE_AC2); else tm.mark(ST_TRI_COUNT);
-        if (E > 0) {
-            k_edge_ac2<<<grid_for(E), BLOCK, 0, s>>>(cd, E_dev, pp, egab, edge_min, eng, stop);
-            LAUNCH_CHECK();
-        }
-        if (split) tm.mark(ST_TRI_COUNT);
+        // balls of a block of k_ac2: no more than a group, and rows that fit
+        cd.sshift = gshift;
+        while ((slot << cd.sshift) > AC2_ROWS) cd.sshift--;
+        cd.tri_sub = sc.get<int>(((size_t)(n - 1) >> cd.sshift) + 1);
+        tm.mark(ST_TRI_COUNT);
         long long room = c0.P;
         if (counted) {
             k_triangles<true><<<groups, BLOCK, 0, s>>>(cd, pp, nullptr, cnt, stop);
@@ -1071,20 +1069,36 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         tm.mark(ST_TRI_SCAN);  // the triangles are in place: no scan, no fill
         tm.mark(ST_TRI_FILL);
 
-        // ---- AC2 of the triangles, candidate tetrahedra and Step 2.
+        // ---- AC2 of the edges and triangles, candidate tetrahedra and Step 2.
         // Kept tetrahedra are those of the regular triangulation, about 6.8 a
         // ball at most where the radii are large, far fewer at alpha = 0 with
         // van der Waals radii; a group past its slab is counted and run again
-        if (split) tm.mark(ST_TRI_AC2); else tm.mark(ST_TRI_GABRIEL);
         // grown radii beyond the wide slots: some 170 candidate tetrahedra a
         // ball, of which 6 are kept; each triangle's apex balls rule out the rest
         const bool use_apex = pp.sgc > 2600;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
-        if (use_apex)
-            k_tri_ac2<true><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tsize, apex, cnt, stop);
-        else
-            k_tri_ac2<false><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tsize, apex, cnt, stop);
-        LAUNCH_CHECK();
+        auto ac2 = [&](auto sl, int what) {
+            constexpr int SLOT = decltype(sl)::value;
+            const int parts = (int)((n - 1) >> cd.sshift) + 1;
+            if (use_apex)
+                k_ac2<SLOT, true><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, egab, edge_min, eng, tgab, tsize, apex, cnt, stop);
+            else
+                k_ac2<SLOT, false><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, egab, edge_min, eng, tgab, tsize, apex, cnt, stop);
+            LAUNCH_CHECK();
+        };
+        auto ac2_of = [&](int what) {
+            if (nbr_two_pass) ac2(std::integral_constant<int, 0>{}, what);
+            else with_slot([&](auto sl, auto) { ac2(sl, what); });
+        };
+        if (split) {
+            tm.mark(ST_EDGE_AC2);
+            ac2_of(AC2_EDGES);
+            tm.mark(ST_TRI_AC2);
+            ac2_of(AC2_TRIANGLES);
+        } else {
+            tm.mark(ST_TRI_GABRIEL);
+            ac2_of(AC2_EDGES | AC2_TRIANGLES);
+        }
         Tets tt{};
         // entries a ball: 2 to 3 times the candidates of dense parts at 0.05 atoms
         // per A^3, and some more for the spread of small groups

@@ -144,18 +144,6 @@ __device__ __forceinline__ double edge_orthosize(const Edge &e) {
     return b * b / (4.0 * (double)e.den) - (double)e.v0.w;
 }
 
-// Floating-point filter of edge_violation_sign: the sign of P when the
-// rounding bound certifies it, 0 when the exact path has to decide.
-__device__ __forceinline__ int edge_violation_filter(const Edge &e, int4 q) {
-    const int bx = q.x - e.v0.x, by = q.y - e.v0.y, bz = q.z - e.v0.z;
-    const int gam = m24(bx, bx) + m24(by, by) + m24(bz, bz) - q.w + e.v0.w;
-    const int t = m24(e.ax, bx) + m24(e.ay, by) + m24(e.az, bz);
-    const double p1 = (double)e.den * (double)gam, p2 = (double)e.beta * (double)t;
-    const double P = p1 - p2;
-    const double eb = 4.0 * ACX_U * (fabs(p1) + fabs(p2));
-    return (P > eb) - (P < -eb);
-}
-
 // P = |a|^2 gamma - beta (a.b)
 __device__ __forceinline__ int edge_violation_sign(const Edge &e, int s0, int s1, int4 q, int sq, const int *perm,
                                                    int force_exact) {
@@ -262,9 +250,7 @@ __device__ __forceinline__ double tri_orthosize(const Tri &t) {
     return M2 / (4.0 * d * d) - (double)t.v0.w;
 }
 
-// What the floating-point filter of a triangle's AC2 needs of tri_setup: an
-// AC2 loop keeps this much in registers, and the exact test, which few
-// neighbours need, sets the triangle up again.
+// What the float64 filter of a triangle's AC2 needs of tri_setup.
 struct TriFilter {
     int4 v0;
     double den, Mx, My, Mz, eP;
@@ -276,10 +262,10 @@ __device__ __forceinline__ TriFilter tri_filter(const Tri &t) {
 
 // P = |n|^2 gamma - M.b: its sign when the rounding bound certifies it, 0 when
 // the exact path has to decide.
-__device__ __forceinline__ int tri_violation_filter(const TriFilter &t, int4 q, double &P) {
+__device__ __forceinline__ int tri_violation_filter(const TriFilter &t, int4 q) {
     const int bx = q.x - t.v0.x, by = q.y - t.v0.y, bz = q.z - t.v0.z;
     const int gam = m24(bx, bx) + m24(by, by) + m24(bz, bz) - q.w + t.v0.w;
-    P = t.den * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
+    const double P = t.den * (double)gam - (t.Mx * (double)bx + t.My * (double)by + t.Mz * (double)bz);
     return (P > t.eP) - (P < -t.eP);
 }
 
@@ -417,6 +403,36 @@ __device__ __forceinline__ int tet_violation_exact(const Tet &t, int s0, int s1,
     i128 coef[5] = {-(i128)(t.D > 0 ? t.D : -t.D), (i128)sD * k1, (i128)sD * k2, (i128)sD * k3,
                     (i128)sD * (t.D - k1 - k2 - k3)};
     return sos_first<5>(ids, coef);
+}
+
+// ---------------------------------------------------------------------------
+// AC2 of a simplex in float32, for the walks along a neighbour row: most
+// neighbours are far from a tie.
+// Power of ball q at the simplex's ortho-centre, times a positive denominator:
+// P = den gamma - M.b with b = q - v0 and gamma = |b|^2 - W_q + W_0, from balls as
+// float4 {x, y, z, W}: the coordinates are exact (below 2^24), so b is. With
+// u = 2^-24, gamma is within 6 u gmax (two rounded weights, four sums), the
+// product with the rounded den within 8 u den gmax, M (of one ball pair: three
+// rounded factors) within 3 u of its value, and the three sums within
+// 3 u (den gmax + bmax |M|_1): in all less than 11 u (den gmax + bmax |M|_1); e
+// takes 16 u. |P| <= e: undecided. P of the simplex's own balls is 0, so these
+// are always undecided.
+struct Power32 {
+    float den, mx, my, mz, e;
+};
+// eP: what the float64 error of M can move P by.
+__device__ __forceinline__ Power32 power32(double den, double Mx, double My, double Mz, double eP, const PredParams &pp) {
+    const double M1 = fabs(Mx) + fabs(My) + fabs(Mz);
+    return Power32{(float)den, (float)Mx, (float)My, (float)Mz,
+                   (float)(16.0 / (1 << 24) * (den * pp.gmax + pp.bmax * M1) + eP)};
+}
+// {b, gamma} of ball q about ball v0.
+__device__ __forceinline__ float4 relative_ball(const float4 &v0, const float4 &q) {
+    const float bx = q.x - v0.x, by = q.y - v0.y, bz = q.z - v0.z;
+    return make_float4(bx, by, bz, fmaf(bx, bx, fmaf(by, by, fmaf(bz, bz, v0.w - q.w))));
+}
+__device__ __forceinline__ float power_of(const Power32 &f, const float4 &r) {
+    return fmaf(-f.mx, r.x, fmaf(-f.my, r.y, fmaf(-f.mz, r.z, f.den * r.w)));
 }
 
 }  // namespace acx

@@ -1,10 +1,11 @@
 // Candidate triangles and tetrahedra and the pruning (Steps 1-5), for gfx950.
 //
 // Every simplex belongs to its vertex with the least input id, so the work is
-// laid out by ball: a block takes a group of consecutive balls (in sorted order), whose candidate edges are consecutive (upper rows, ordered by
-// input id), and enumerates and tests all simplices of those balls. With the
-// rows in id order, each ball's simplices come out in output order, so the
-// emit needs no sort.
+// laid out by ball: a block takes a group of consecutive balls (in sorted
+// order), whose candidate edges are consecutive (upper rows, ordered by input
+// id), and enumerates and tests all simplices of those balls. With the rows in
+// id order, each ball's simplices come out in output order, so the emit needs
+// no sort.
 //
 // A candidate triangle of ball i is a pair (j, k) of its upper row whose own
 // grown spheres cross (tested from the two balls, no search in j's row) and
@@ -23,10 +24,9 @@
 // first and passes their scan instead. Tetrahedra of a group go to a slab of
 // fixed size, or to counted ranges if a group outgrew its slab.
 //
-// The AC2 tests (long walks along neighbour rows, a thread per simplex) are
-// kernels of their own: beside the pair machinery they would hold far more
-// registers (194 against 64), and a block's few tetrahedra would wait on its
-// triangles.
+// The AC2 tests (walks along neighbour rows, a thread per simplex) are kernels
+// of their own: beside the pair machinery they would hold far more registers
+// (194 against 64), and a block's few tetrahedra would wait on its triangles.
 #pragma once
 #include "kernels.hpp"
 
@@ -42,13 +42,15 @@ constexpr int NWAVE = BLOCK / WAVE;
 // tri_cnt[g]).
 struct Cands {
     const int4 *atom;
+    const float4 *wball;  // the balls as float4 {x, y, z, W}
     const int *perm;
     const int *nbr_start, *nbr_cnt, *nbr;
     const int *up_start, *up, *up_id, *edge_i;
     const int *tri_base;
     int *tri_cnt, *tri_e, *tri_f;
     int *tri_first;  // first triangle of an edge, where it has any
-    int n, gshift;
+    int *tri_sub;    // first triangle of each 2^sshift balls (sshift <= gshift)
+    int n, gshift, sshift;
 };
 
 // The pairs (a, b), a < b, of entries of one row, for the PT consecutive
@@ -179,68 +181,95 @@ constexpr int AC2_GROUP = 4;  // neighbours loaded together in the AC2 loops
 // the row are replaced, not used).
 constexpr int NBR_PAD = AC2_GROUP;
 
-// Runs f(q, ball q) over ball i's neighbour row in groups of AC2_GROUP whose
-// loads are all issued before the first call, the next group's indices loaded
-// while this group is tested. The last group is filled up with `pad`. f
-// returns nothing; done() ends the walk after a group.
-template <class F, class G>
-__device__ __forceinline__ void walk_row(const Cands &cd, int i, int pad, F &&f, G &&done) {
-    const int ns = cd.nbr_start[i], ne = ns + cd.nbr_cnt[i];
-    int nx[AC2_GROUP];
+// The AC2 tests below walk ball i's neighbour row in float32 (power_of), in
+// groups of AC2_GROUP neighbours whose loads are issued together. `own` of the
+// row's balls are the simplex's, undecided by themselves, as are the entries
+// that fill up the last group (i itself: b = 0, gamma = 0, P = 0), so the
+// undecided ones are counted and none is compared with the simplex's balls.
+// Where no violator is certain but more are undecided (near ties: 18 of 2.2
+// million triangles of 20,000 atoms with solvent-accessible radii), the row is
+// walked once more with the float64 filter and the exact test.
+// f(r, P, k): called with each neighbour's {b, gamma}, its power and its place
+// in the row. STOP: end after the first group with a violator.
+// Two forms: the row as {b, gamma} about i in LDS (RowLds, of many simplices of
+// one ball), or gathered from memory.
+enum { AC2_HOLDS = 0, AC2_VIOLATED = 1, AC2_UNSURE = 2 };
+// status of a face; AC2 leaves 0 or 1
+enum { FACE_OUT = 0, FACE_GABRIEL = 1, FACE_ATTACHED = 2, FACE_UNSURE = 3 };
+struct RowLds {
+    const float4 *row;  // filled up with zeros to a multiple of AC2_GROUP
+    int len;
+    __device__ __forceinline__ void begin() {}
+    __device__ __forceinline__ void load(int k, float4 (&r)[AC2_GROUP]) {
 #pragma unroll
-    for (int u = 0; u < AC2_GROUP; u++) nx[u] = cd.nbr[ns + u];  // in bounds: NBR_PAD
-    for (int p0 = ns; p0 < ne; p0 += AC2_GROUP) {
-        int qs[AC2_GROUP];
-        int4 aqs[AC2_GROUP];
-#pragma unroll
-        for (int u = 0; u < AC2_GROUP; u++) qs[u] = p0 + u < ne ? nx[u] : pad;
-        const int pn = p0 + AC2_GROUP < ne ? p0 + AC2_GROUP : p0;  // the last group reloads itself
-#pragma unroll
-        for (int u = 0; u < AC2_GROUP; u++) nx[u] = cd.nbr[pn + u];
-#pragma unroll
-        for (int u = 0; u < AC2_GROUP; u++) aqs[u] = cd.atom[qs[u]];
-#pragma unroll
-        for (int u = 0; u < AC2_GROUP; u++) f(qs[u], aqs[u]);
-        if (done()) break;
+        for (int u = 0; u < AC2_GROUP; u++) r[u] = row[k + u];
     }
+};
+struct RowMem {
+    const float4 *wball;
+    const int *row;
+    int i, len;
+    float4 me;
+    int nx[AC2_GROUP];  // the next group's indices, one 16-byte load while this group is tested
+    __device__ __forceinline__ RowMem(const Cands &cd, int i_)
+        : wball(cd.wball), row(cd.nbr + cd.nbr_start[i_]), i(i_), len(cd.nbr_cnt[i_]) {}
+    __device__ __forceinline__ void begin() {
+        me = wball[i];
+        __builtin_memcpy(nx, row, sizeof nx);  // in bounds: NBR_PAD
+    }
+    __device__ __forceinline__ void load(int k, float4 (&r)[AC2_GROUP]) {
+        float4 q[AC2_GROUP];
+#pragma unroll
+        for (int u = 0; u < AC2_GROUP; u++) q[u] = wball[k + u < len ? nx[u] : i];
+        __builtin_memcpy(nx, row + (k + AC2_GROUP < len ? k + AC2_GROUP : k), sizeof nx);  // the last group reloads itself
+#pragma unroll
+        for (int u = 0; u < AC2_GROUP; u++) r[u] = relative_ball(me, q[u]);
+    }
+};
+template <bool STOP, class R, class F>
+__device__ __forceinline__ int walk_row(R row, const Power32 &pw, int own, F &&f) {
+    bool viol = false;
+    int undecided = 0;
+    row.begin();
+    for (int k = 0; k < row.len; k += AC2_GROUP) {
+        float4 r[AC2_GROUP];
+        row.load(k, r);
+#pragma unroll
+        for (int u = 0; u < AC2_GROUP; u++) {
+            const float P = power_of(pw, r[u]);
+            viol |= P < -pw.e;
+            undecided += fabsf(P) <= pw.e;
+            f(r[u], P, k + u);
+        }
+        if (STOP && viol) break;
+    }
+    if (viol) return AC2_VIOLATED;
+    return undecided == own + (-row.len & (AC2_GROUP - 1)) ? AC2_HOLDS : AC2_UNSURE;
 }
 
-// The AC2 tests below walk the row with the float64 filter alone. Where it
-// certified no violator but left some neighbour undecided (exact ties and near
-// ties), the row is walked once more with the exact test: inside the first
-// walk that code would be there once per neighbour of a group, and the terms
-// it needs would be held through the loop (108 registers against 60 for the
-// triangles' test).
-
-// AC2 of candidate edge e = (i, j) at its own ortho-centre (Step 4): every
-// violator meets the ortho-centre, so it is in i's neighbour row. Writes
-// egab[e], and for an edge that fails starts edge_min[e] (the least Size of a
-// kept coface) and flags its owner in eng. Every neighbour is tested (no early
-// exit: most edges pass, and the loop stays convergent).
-__device__ __forceinline__ void edge_ac2(const Cands &cd, const PredParams &pp, int e, int i, int j,
-                                         unsigned char *__restrict__ egab, long long *__restrict__ edge_min,
-                                         unsigned char *__restrict__ eng) {
+// AC2 of candidate edge (i, j) at its own ortho-centre (Step 4): every violator
+// meets the ortho-centre, so it is in i's neighbour row. Every neighbour is
+// tested (no early exit: most edges pass, and the loop stays convergent).
+template <class R>
+__device__ __forceinline__ int edge_ac2(const PredParams &pp, R row, const int4 &vi, const int4 &vj) {
+    if (pp.force_exact) return AC2_UNSURE;
+    // P = |a|^2 gamma - beta (a.b)
+    const Edge ed = edge_setup(vi, vj);
+    const float den = (float)ed.den, be = (float)ed.beta;
+    Power32 pw{den, be * (float)ed.ax, be * (float)ed.ay, be * (float)ed.az, 0.0f};
+    pw.e = 16.0f / (1 << 24) * fmaf(den, (float)pp.gmax, (float)pp.bmax * (fabsf(pw.mx) + fabsf(pw.my) + fabsf(pw.mz)));
+    return walk_row<false>(row, pw, 1, [](const float4 &, float, int) {});
+}
+__device__ __forceinline__ bool edge_violated(const Cands &cd, const PredParams &pp, int i, int j) {
     const Edge ed = edge_setup(cd.atom[i], cd.atom[j]);
-    bool viol = false, unsure = pp.force_exact;
-    if (!pp.force_exact)
-        walk_row(cd, i, j, [&](int q, int4 aq) {
-            const int sg = edge_violation_filter(ed, aq);
-            viol |= (sg < 0) & (q != j);  // padding entries repeat j
-            unsure |= (sg == 0) & (q != j);
-        }, [] { return false; });
-    if (unsure && !viol) {
-        const int ns = cd.nbr_start[i], ne = ns + cd.nbr_cnt[i];
+    const int ns = cd.nbr_start[i], ne = ns + cd.nbr_cnt[i];
+    bool viol = false;
 #pragma unroll 1
-        for (int p = ns; p < ne && !viol; p++) {
-            const int q = cd.nbr[p];
-            viol = q != j && edge_violation_sign(ed, i, j, cd.atom[q], q, cd.perm, pp.force_exact) < 0;
-        }
+    for (int p = ns; p < ne && !viol; p++) {
+        const int q = cd.nbr[p];
+        viol = q != j && edge_violation_sign(ed, i, j, cd.atom[q], q, cd.perm, pp.force_exact) < 0;
     }
-    egab[e] = (unsigned char)!viol;
-    if (viol) {
-        edge_min[e] = ORDERED_POS_INF;
-        eng[i] = 1;
-    }
+    return viol;
 }
 
 // OrthoSize evaluated with the vertices in lexicographic order of their
@@ -267,12 +296,6 @@ __device__ __forceinline__ void sort_centres(int4 (&v)[K]) {
             }
 }
 
-__device__ __forceinline__ double tri_size_canon(int4 a, int4 b, int4 c, const PredParams &pp) {
-    int4 v[3] = {a, b, c};
-    sort_centres<3>(v);
-    return tri_orthosize(tri_setup(v[0], v[1], v[2], pp));
-}
-
 __device__ __forceinline__ double tet_size_canon(int4 a, int4 b, int4 c, int4 d, const PredParams &pp) {
     int4 v[4] = {a, b, c, d};
     sort_centres<4>(v);
@@ -280,81 +303,80 @@ __device__ __forceinline__ double tet_size_canon(int4 a, int4 b, int4 c, int4 d,
 }
 
 // AC2 of candidate triangle t = (i, j, k) at its own ortho-centre (Step 3;
-// violators are in i's neighbour row) and its OrthoSize. Writes tgab[t] and
-// tsize[t]. Every neighbour is tested (no early exit, convergent loop).
+// violators are in i's neighbour row) and its OrthoSize (tsize[t]). Every
+// neighbour is tested (no early exit, convergent loop). The triangle is set up
+// once, in the order of its Size; relative to ball i, whose distances to its
+// neighbours are bounded, M is that of the order's first ball moved by
+// 2 |n|^2 (v0 - v_i).
 // APEX: also two neighbours that rule out most tetrahedra on the triangle. The
 // ortho-centres of all balls with the triangle lie on its axis, c_t + s n up to
 // a scale; ball q, at signed distance D = n.b from the plane, violates a centre
 // iff P_q - s D < 0, so on its side of the plane the ball of least P / D (where
 // D > 0; of the largest where D < 0) violates every tetrahedron of another
-// apex there. The two are found in float32: they are only the first neighbours
-// that a candidate is tested against, with the exact predicate.
-template <bool APEX>
-__device__ __forceinline__ void tri_ac2(const Cands &cd, const PredParams &pp, int t, int i, int j, int k,
-                                        unsigned char *__restrict__ tgab, double *__restrict__ tsize,
-                                        int2 *__restrict__ apex, Counters *cnt) {
-    const int4 vi = cd.atom[i], vj = cd.atom[j], vk = cd.atom[k];
-    tsize[t] = tri_size_canon(vi, vj, vk, pp);
-    const Tri ts = tri_setup(vi, vj, vk, pp);
-    const TriFilter tf = tri_filter(ts);
+// apex there. The two are found in float32, their places in the row in the low
+// 8 bits of the quotient (past 256 neighbours another one of the row): they are
+// only the first neighbours that a candidate is tested against, with the exact
+// predicate.
+template <bool APEX, class R>
+__device__ __forceinline__ int tri_ac2(const PredParams &pp, R row, const int4 &vi, const int4 &vj, const int4 &vk,
+                                       double &size, int2 &apex) {
+    int4 v[3] = {vi, vj, vk};
+    sort_centres<3>(v);
+    const Tri ts = tri_setup(v[0], v[1], v[2], pp);
+    size = tri_orthosize(ts);
+    apex = make_int2(-1, -1);
+    if (pp.force_exact) return AC2_UNSURE;
+    const double den = (double)ts.den, den2 = 2.0 * den;
+    const double Mx = ts.Mx + den2 * (double)(v[0].x - vi.x), My = ts.My + den2 * (double)(v[0].y - vi.y),
+                 Mz = ts.Mz + den2 * (double)(v[0].z - vi.z);
+    const Power32 pw = power32(den, Mx, My, Mz, ts.eP, pp);
     const float nx = (float)ts.nx, ny = (float)ts.ny, nz = (float)ts.nz;
-    bool viol = false, unsure = pp.force_exact;
     float lo = INFINITY, hi = -INFINITY;
-    int qlo = j, qhi = j;  // j: none
-    if (!pp.force_exact)
-        walk_row(cd, i, j, [&](int q, int4 aq) {
-            const bool other = (q != j) & (q != k);
-            double P;
-            const int sg = tri_violation_filter(tf, aq, P);
-            viol |= (sg < 0) & other;
-            unsure |= (sg == 0) & other;
-            if (APEX) {
-                const float D = nx * (float)(aq.x - tf.v0.x) + ny * (float)(aq.y - tf.v0.y) + nz * (float)(aq.z - tf.v0.z);
-                const float s = (float)P * __builtin_amdgcn_rcpf(D);
-                const bool l = other & (D > 0.0f) & (s < lo), h = other & (D < 0.0f) & (s > hi);
-                lo = l ? s : lo;
-                qlo = l ? q : qlo;
-                hi = h ? s : hi;
-                qhi = h ? q : qhi;
-            }
-        }, [] { return false; });
-    if (APEX) apex[t] = make_int2(qlo, qhi);
-    if (unsure && !viol) {
-        // set up from indices the optimiser cannot follow: nothing of it is
-        // kept through the walk above
-        const int io = opaque(i);
-        const Tri tr = tri_setup(cd.atom[io], cd.atom[j], cd.atom[k], pp);
-        const int ns = cd.nbr_start[io], ne = ns + cd.nbr_cnt[io];
-#pragma unroll 1
-        for (int p = ns; p < ne && !viol; p++) {
-            const int q = cd.nbr[p];
-            if (q == j || q == k) continue;
-            const int4 aq = cd.atom[q];
-            double P;
-            int sg = pp.force_exact ? 0 : tri_violation_filter(tri_filter(tr), aq, P);
-            if (sg == 0) {
-                if (!pp.force_exact) note_fallback(cnt);
-                sg = tri_violation_exact(tr, i, j, k, aq, q, cd.perm);
-            }
-            viol = sg < 0;
+    const int res = walk_row<false>(row, pw, 2, [&](const float4 &r, float P, int at) {
+        if (APEX) {
+            const float D = fmaf(nx, r.x, fmaf(ny, r.y, nz * r.z));
+            const float s = __uint_as_float((__float_as_uint(P * __builtin_amdgcn_rcpf(D)) & ~255u) | (at & 255u));
+            const bool other = fabsf(P) > pw.e;
+            lo = fminf(lo, other & (D > 0.0f) ? s : INFINITY);
+            hi = fmaxf(hi, other & (D < 0.0f) ? s : -INFINITY);
         }
+    });
+    if (lo < INFINITY) apex.x = __float_as_uint(lo) & 255u;
+    if (hi > -INFINITY) apex.y = __float_as_uint(hi) & 255u;
+    return res;
+}
+__device__ __forceinline__ bool tri_violated(const Cands &cd, const PredParams &pp, int i, int j, int k, Counters *cnt) {
+    const Tri tr = tri_setup(cd.atom[i], cd.atom[j], cd.atom[k], pp);
+    const int ns = cd.nbr_start[i], ne = ns + cd.nbr_cnt[i];
+    bool viol = false;
+#pragma unroll 1
+    for (int p = ns; p < ne && !viol; p++) {
+        const int q = cd.nbr[p];
+        if (q == j || q == k) continue;
+        const int4 aq = cd.atom[q];
+        int sg = pp.force_exact ? 0 : tri_violation_filter(tri_filter(tr), aq);
+        if (sg == 0) {
+            if (!pp.force_exact) note_fallback(cnt);
+            sg = tri_violation_exact(tr, i, j, k, aq, q, cd.perm);
+        }
+        viol = sg < 0;
     }
-    tgab[t] = (unsigned char)!viol;
+    return viol;
 }
 
 // AC2 of tetrahedron (i, j, k, l) against i's neighbour row, ending at the
 // first violator (most candidates of large radii fail within a few).
-__device__ __forceinline__ bool tet_ac2(const Cands &cd, const TetFilter &tf, const PredParams &pp, int i, int j, int k,
+__device__ __forceinline__ bool tet_ac2(const Cands &cd, const Tet &ts, const PredParams &pp, int i, int j, int k,
                                         int l, Counters *cnt) {
-    bool viol = false, unsure = pp.force_exact;
-    if (!pp.force_exact)
-        walk_row(cd, i, j, [&](int q, int4 aq) {
-            const bool other = (q != j) & (q != k) & (q != l);
-            const int sg = tet_violation_filter(tf, aq);
-            viol |= (sg < 0) & other;
-            unsure |= (sg == 0) & other;
-        }, [&] { return viol; });
-    if (unsure && !viol) {
+    int res = AC2_UNSURE;
+    if (!pp.force_exact) {
+        // P = sign(D) (D gamma - M.b)
+        const double sD = ts.D > 0 ? 1.0 : -1.0;
+        const Power32 pw = power32(fabs((double)ts.D), sD * ts.Mx, sD * ts.My, sD * ts.Mz, ts.eP, pp);
+        res = walk_row<true>(RowMem(cd, i), pw, 3, [](const float4 &, float, int) {});
+    }
+    bool viol = res == AC2_VIOLATED;
+    if (res == AC2_UNSURE) {
         const int io = opaque(i);
         const Tet te = tet_setup(cd.atom[io], cd.atom[j], cd.atom[k], cd.atom[l], pp);
         const int ns = cd.nbr_start[io], ne = ns + cd.nbr_cnt[io];
@@ -375,17 +397,6 @@ __device__ __forceinline__ bool tet_ac2(const Cands &cd, const TetFilter &tf, co
 }
 
 // ---------------------------------------------------------------------------
-// AC2 of the candidate edges.
-__global__ void __launch_bounds__(BLOCK) k_edge_ac2(Cands cd, const int *__restrict__ E, PredParams pp,
-                                                     unsigned char *__restrict__ egab, long long *__restrict__ edge_min,
-                                                     unsigned char *__restrict__ eng, const int *__restrict__ stop) {
-    if (stop && *stop) return;
-    const int e = xcd_block() * BLOCK + threadIdx.x;
-    if (e >= *E) return;
-    const int i = cd.edge_i[e], j = cd.up[e];
-    edge_ac2(cd, pp, e, i, j, egab, edge_min, eng);
-}
-
 // Candidate triangles (Sec. 4.3) of a group's edges. The balls of EDGE_CH
 // edges' other ends (and of the next EDGE_AHEAD, where a row goes on) are held
 // in LDS, so that the pair tests wait for no memory. COUNT: the groups' totals
@@ -398,6 +409,7 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
     __shared__ int4 sat[EDGE_CH + EDGE_AHEAD];
     __shared__ unsigned short own[PAIR_WIN], hit[PAIR_WIN], res[PAIR_WIN];
     __shared__ int soff[EDGE_CH];
+    __shared__ unsigned char part_no[EDGE_CH];  // part of the group an edge belongs to
     __shared__ int wtot[2][NWAVE];
     const int g = xcd_block();
     const int b0 = g << cd.gshift, b1 = min(b0 + (1 << cd.gshift), cd.n);
@@ -405,13 +417,17 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
     const int w = wave_id(), lane = lane_id();
     int out = COUNT ? 0 : cd.tri_base[g];
     const int out0 = out;
+    int last_part = -1;  // part of the last triangle so far
+    int *const sub = COUNT ? nullptr : cd.tri_sub + (b0 >> cd.sshift);
     for (int c0 = e0; c0 < e1; c0 += EDGE_CH) {
         for (int x = threadIdx.x; x < min(EDGE_CH + EDGE_AHEAD, e1 - c0); x += BLOCK) sat[x] = cd.atom[cd.up[c0 + x]];
         int later[EDGE_PT];
 #pragma unroll
         for (int u = 0; u < EDGE_PT; u++) {
             const int e = c0 + threadIdx.x * EDGE_PT + u;
-            later[u] = e < e1 ? cd.up_start[cd.edge_i[e] + 1] - e - 1 : 0;
+            const int i = e < e1 ? cd.edge_i[e] : 0;
+            later[u] = e < e1 ? cd.up_start[i + 1] - e - 1 : 0;
+            part_no[threadIdx.x * EDGE_PT + u] = (unsigned char)((i - b0) >> cd.sshift);
         }
         int pairs;
         const int off = pair_scan<EDGE_PT>(later, soff, &pairs);
@@ -452,18 +468,27 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
                     cd.tri_f[out + x] = c0 + second(v);
                     tri_min[out + x] = ORDERED_POS_INF;  // no kept coface yet
                     // the edge's first triangle (an edge cut by the window sets it
-                    // in the window of its first)
-                    const bool first = x > 0 ? own[res[rs.slot(x - 1)]] != o : prev != o;
-                    if (first) cd.tri_first[c0 + o] = out + x;
+                    // in the window of its first), and that of each part from the
+                    // one after its predecessor's on
+                    const int before = x > 0 ? own[res[rs.slot(x - 1)]] : prev;
+                    if (before != o) {
+                        cd.tri_first[c0 + o] = out + x;
+                        for (int k = x > 0 ? part_no[before] + 1 : last_part + 1; k <= part_no[o]; k++) sub[k] = out + x;
+                    }
                 }
             }
-            if (rs.total > 0) prev = own[res[rs.slot(rs.total - 1)]];
+            if (rs.total > 0) {
+                prev = own[res[rs.slot(rs.total - 1)]];
+                last_part = part_no[prev];
+            }
             out += rs.total;
             __syncthreads();
         }
         __syncthreads();  // sat and soff are rewritten by the next round
     }
     if (threadIdx.x == 0) cd.tri_cnt[g] = out - out0;
+    if (!COUNT)
+        for (int k = last_part + 1 + threadIdx.x; k << cd.sshift < b1 - b0; k += BLOCK) sub[k] = out;
 }
 
 // ---------------------------------------------------------------------------
@@ -472,7 +497,6 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
 // Size of their kept cofaces (order-preserving integer; +inf while none), so
 // such a face is kept iff that minimum is finite.
 // gab: the faces' status.
-enum { FACE_OUT = 0, FACE_GABRIEL = 1, FACE_ATTACHED = 2 };  // AC2 leaves 0 or 1
 __device__ __forceinline__ void mark_face(const unsigned char *gab, long long *mins, int f, long long key,
                                           Counters *cnt) {
     if (f < 0) { atomicOr(&cnt->lookup, 1); return; }
@@ -491,20 +515,173 @@ __device__ __forceinline__ int4 tet_facets(const Cands &cd, int g, int t, int t2
     return make_int4(t, t2, a, b);
 }
 
-// AC2 and OrthoSize of a group's candidate triangles. Eight waves per SIMD: the
-// walk along the neighbour row needs less than 64 registers, what is spilled
-// belongs to the exact test.
-template <bool APEX>
-__global__ void __launch_bounds__(BLOCK, 8) k_tri_ac2(Cands cd, PredParams pp, unsigned char *__restrict__ tgab,
-                                                       double *__restrict__ tsize, int2 *__restrict__ apex,
-                                                       Counters *cnt, const int *__restrict__ stop) {
+// AC2 of the candidate edges and triangles, and the triangles' OrthoSize. A
+// block takes a part of a group, 2^sshift consecutive balls (at most AC2_ROWS /
+// SLOT), and puts their neighbour rows in LDS as {b, gamma}: 7 neighbours a ball
+// are gathered and made relative once instead of once per simplex (3.5 edges
+// and 2 triangles a ball at alpha = 0, 21 and 110 with solvent-accessible
+// radii: gathers of a line each were what bound the edges' test), and a test
+// costs 8 instructions a neighbour against 27 in integers and float64. Rows
+// start SLOT + 1 entries apart (other banks; the last entry holds the length).
+// Waves take 64 triangles or 64 edges each. Bound by instruction issue (two
+// thirds; the triangles' float64 setup most of it) and by the chain of loads
+// before the walk, so the first simplex of each thread is loaded along with the
+// rows, level by level. Eight waves per SIMD: the walk needs less than 64
+// registers; a simplex that it leaves undecided is marked and looked at again
+// at the end (inside the loop, the exact test's registers were spilled around
+// it by every wave: 390 us).
+// Both tests at 3M atoms and alpha = 0: 308 us as two kernels without LDS, 239
+// as this; 100,000 atoms with solvent-accessible radii 1,150 and 417. Rows of
+// 1,024 entries and 256 threads: 512 threads 285 and 405, 512 entries 261 and
+// 416, with 128 threads 250 and 442.
+// SLOT = 0: rows of any length (after a counted neighbour search), gathered per
+// simplex. `what`: bit 0 edges, bit 1 triangles.
+constexpr int AC2_BLOCK = 256;
+constexpr int AC2_ROWS = 1024;
+enum { AC2_EDGES = 1, AC2_TRIANGLES = 2 };
+template <int SLOT, bool APEX>
+__global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, int what, unsigned char *__restrict__ egab,
+                                                   long long *__restrict__ edge_min, unsigned char *__restrict__ eng,
+                                                   unsigned char *__restrict__ tgab, double *__restrict__ tsize,
+                                                   int2 *__restrict__ apex, Counters *cnt, const int *__restrict__ stop) {
     if (stop && *stop) return;
-    const int g = xcd_block();
-    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
-    for (int t = t0 + threadIdx.x; t < t1; t += BLOCK) {
-        const int e = cd.tri_e[t];
-        const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[cd.tri_f[t]];
-        tri_ac2<APEX>(cd, pp, t, i, j, k, tgab, tsize, apex, cnt);
+    constexpr int STRIDE = SLOT + 1, PT = AC2_ROWS / AC2_BLOCK;
+    __shared__ float4 rows[SLOT ? AC2_ROWS / (SLOT ? SLOT : 1) * STRIDE : 1];
+    const int part = xcd_block();
+    const int b0 = part << cd.sshift, b1 = min(b0 + (1 << cd.sshift), cd.n);
+    const int g = b0 >> cd.gshift;
+    const int lane = lane_id();
+    // the block's edges and triangles, and its rows
+    const int e0 = cd.up_start[b0], e1 = cd.up_start[b1];
+    const int t0 = cd.tri_sub[part];
+    const int t1 = b1 < cd.n && b1 >> cd.gshift == g ? cd.tri_sub[part + 1] : cd.tri_base[g] + cd.tri_cnt[g];
+    int len[PT], ns[PT];
+    if (SLOT) {
+#pragma unroll
+        for (int r = 0; r < PT; r++) {
+            const int b = min(b0 + ((int)threadIdx.x + r * AC2_BLOCK) / (SLOT ? SLOT : 1), b1 - 1);
+            len[r] = min(cd.nbr_cnt[b], SLOT);
+            ns[r] = cd.nbr_start[b];
+        }
+    }
+    const int tw = what & AC2_TRIANGLES ? (t1 - t0 + WAVE - 1) / WAVE : 0;
+    const int ew = what & AC2_EDGES ? (e1 - e0 + WAVE - 1) / WAVE : 0;
+    // a thread's simplex of wave item w (x < 0: none): first a triangle's edges
+    // or an edge's ends, then a triangle's ends, then the balls
+    struct Item {
+        int x, i, j, k;
+        int4 vi, vj, vk;
+    };
+    auto fetch_ids = [&](int w) {
+        Item it;
+        it.x = -1;
+        if (w < tw) {
+            const int x = t0 + w * WAVE + lane;
+            if (x < t1) {
+                it.x = x;
+                it.i = cd.tri_e[x];
+                it.k = cd.tri_f[x];
+            }
+        } else if (w < tw + ew) {
+            const int x = e0 + (w - tw) * WAVE + lane;
+            if (x < e1) {
+                it.x = x;
+                it.i = cd.edge_i[x];
+                it.j = cd.up[x];
+            }
+        }
+        return it;
+    };
+    auto fetch_ends = [&](int w, Item &it) {
+        if (w < tw && it.x >= 0) {
+            const int e = it.i;
+            it.i = cd.edge_i[e];
+            it.j = cd.up[e];
+            it.k = cd.up[it.k];
+        }
+    };
+    auto fetch_balls = [&](int w, Item &it) {
+        if (it.x < 0) return;
+        it.vi = cd.atom[it.i];
+        it.vj = cd.atom[it.j];
+        if (w < tw) it.vk = cd.atom[it.k];
+    };
+    int w = wave_id();
+    Item it = fetch_ids(w);
+    if constexpr (SLOT != 0) {
+        int q[PT];
+#pragma unroll
+        for (int r = 0; r < PT; r++) {
+            const int k = ((int)threadIdx.x + r * AC2_BLOCK) % SLOT;
+            q[r] = k < len[r] ? cd.nbr[ns[r] + k] : -1;
+        }
+        fetch_ends(w, it);
+#pragma unroll
+        for (int r = 0; r < PT; r++) {
+            const int y = (int)threadIdx.x + r * AC2_BLOCK, b = y / SLOT, k = y % SLOT;
+            if (b0 + b < b1 && k < len[r] + (-len[r] & (AC2_GROUP - 1)))
+                rows[b * STRIDE + k] = relative_ball(cd.wball[b0 + b], cd.wball[q[r] < 0 ? b0 + b : q[r]]);
+            if (k == 0) rows[b * STRIDE + SLOT].x = __int_as_float(len[r]);
+        }
+        fetch_balls(w, it);
+        __syncthreads();
+    } else {
+        fetch_ends(w, it);
+        fetch_balls(w, it);
+    }
+    auto row_of = [&](int i) {
+        if constexpr (SLOT != 0) return RowLds{rows + (i - b0) * STRIDE, __float_as_int(rows[(i - b0) * STRIDE + SLOT].x)};
+        else return RowMem(cd, i);
+    };
+    // an edge's verdict; one that fails starts edge_min[e] (the least Size of a
+    // kept coface) and flags its owner in eng
+    auto edge_is = [&](int e, int i, bool viol) {
+        egab[e] = (unsigned char)!viol;
+        if (viol) {
+            edge_min[e] = ORDERED_POS_INF;
+            eng[i] = 1;
+        }
+    };
+    bool unsure = false;
+#pragma unroll 1
+    while (w < tw + ew) {
+        const int x = it.x;
+        if (x >= 0) {
+            if (w < tw) {
+                double size;
+                int2 at;
+                const int res = tri_ac2<APEX>(pp, row_of(it.i), it.vi, it.vj, it.vk, size, at);
+                tsize[x] = size;
+                tgab[x] = res == AC2_UNSURE ? FACE_UNSURE : (unsigned char)(res == AC2_HOLDS);
+                unsure |= res == AC2_UNSURE;
+                if (APEX) {  // j: none
+                    const int *nb = cd.nbr + cd.nbr_start[it.i];
+                    apex[x] = make_int2(at.x < 0 ? it.j : nb[at.x], at.y < 0 ? it.j : nb[at.y]);
+                }
+            } else {
+                const int res = edge_ac2(pp, row_of(it.i), it.vi, it.vj);
+                if (res == AC2_UNSURE) egab[x] = FACE_UNSURE;
+                else edge_is(x, it.i, res == AC2_VIOLATED);
+                unsure |= res == AC2_UNSURE;
+            }
+        }
+        w += AC2_BLOCK / WAVE;
+        it = fetch_ids(w);
+        fetch_ends(w, it);
+        fetch_balls(w, it);
+    }
+    // each wave's own undecided ones, once more
+    if (!__any(unsure)) return;
+#pragma unroll 1
+    for (w = wave_id(); w < tw + ew; w += AC2_BLOCK / WAVE) {
+        Item un = fetch_ids(w);
+        fetch_ends(w, un);
+        if (un.x < 0) continue;
+        if (w < tw) {
+            if (tgab[un.x] == FACE_UNSURE) tgab[un.x] = (unsigned char)!tri_violated(cd, pp, un.i, un.j, un.k, cnt);
+        } else {
+            if (egab[un.x] == FACE_UNSURE) edge_is(un.x, un.i, edge_violated(cd, pp, un.i, un.j));
+        }
     }
 }
 
@@ -668,7 +845,7 @@ __global__ void __launch_bounds__(NT, 4) k_tet_ac2(Cands cd, PredParams pp, cons
             const int e = cd.tri_e[t];
             const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[cd.tri_f[t]], l = cd.up[f2];
             const int4 vi = cd.atom[i], vj = cd.atom[j], vk = cd.atom[k], vl = cd.atom[l];
-            keep = tet_ac2(cd, tet_filter(tet_setup(vi, vj, vk, vl, pp)), pp, i, j, k, l, cnt);
+            keep = tet_ac2(cd, tet_setup(vi, vj, vk, vl, pp), pp, i, j, k, l, cnt);
         }
         const unsigned long long mask = __ballot(keep);
         if (lane == 0) wtot[turn][w] = __popcll(mask);
