@@ -859,7 +859,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         tm.mark(ST_BIN);
         int *cell_start = sc.get<int>(ncell + 1);
         int4 *atom = sc.get<int4>(n);
-        float4 *sball = sc.get<float4>(n), *wball = sc.get<float4>(n);
+        int2 *sball = sc.get<int2>((size_t)n + SCAN_PAD);
+        float4 *wball = sc.get<float4>(n);
         int *perm = sc.get<int>(n);
         if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
             k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, (int)ncell, cell_start, atom, sball,

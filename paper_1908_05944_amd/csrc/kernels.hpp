@@ -62,6 +62,14 @@ __device__ __forceinline__ int mol_of(const Grid *__restrict__ grids, int n_mol,
     return lo;
 }
 
+// The molecule that holds all of [i0, i1] (the same in every lane), -1 where none
+// does: its grid is then one for the wave, read through the scalar cache and
+// held in scalar registers.
+__device__ __forceinline__ int mol_of_all(const Grid *__restrict__ grids, int n_mol, int i0, int i1) {
+    const int m = mol_of(grids, n_mol, __builtin_amdgcn_readfirstlane(i0));
+    return __builtin_amdgcn_readfirstlane(i1) < grids[m].a1 ? m : -1;
+}
+
 constexpr int BLOCK = 256;
 // Most balls of a group: the simplices of consecutive balls (in sorted order)
 // are enumerated, pruned and written by one block.
@@ -246,12 +254,16 @@ __device__ __forceinline__ long long cell_of(const Grid &g, int x, int y, int z)
     return cell_id(g, (x - g.ox) / g.s, (y - g.oy) / g.s, (z - g.oz) / g.s);
 }
 
-// Float32 form of a sorted ball for the scan; rho NaN where W + alpha < 0 (the
+// Eight-byte form of a sorted ball for the scan: the low 16 bits of its
+// coordinates, and rho = sqrt(W + alpha) rounded up (0 where W + alpha < 0: the
 // ball meets none).
-__device__ __forceinline__ float4 scan_ball(const int4 &a, int aq) {
-    const int r2 = a.w + aq;  // below 2^26: rounded by at most 2^-24
-    return make_float4((float)a.x, (float)a.y, (float)a.z,
-                       r2 >= 0 ? sqrtf((float)r2) * (1.0f + 1.0f / (1 << 19)) : __int_as_float(0x7fc00000));
+typedef short short2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int scan_rho(const int4 &a, int aq) {
+    const int r2 = a.w + aq;  // below 2^26
+    return r2 > 0 ? (int)ceilf(sqrtf((float)r2) * (1.0f + 1.0f / (1 << 20))) : 0;
+}
+__device__ __forceinline__ int2 scan_ball(const int4 &a, int aq) {
+    return make_int2((a.x & 0xffff) | (int)((unsigned)a.y << 16), (a.z & 0xffff) | (scan_rho(a, aq) << 16));
 }
 
 // Float32 form for the AC2 walks.
@@ -260,8 +272,7 @@ __device__ __forceinline__ float4 weight_ball(const int4 &a) {
 }
 
 // grids = nullptr: one molecule, whose grid is g0 (a kernel argument: no upload).
-__device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid *__restrict__ grids, int n_mol, const Grid &g0) {
-    const Grid &g = grids ? grids[mol_of(grids, n_mol, i)] : g0;
+__device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid &g) {
     return (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
 }
 
@@ -286,11 +297,12 @@ __global__ void __launch_bounds__(RS_BLOCK) k_cell_hist(const int4 *__restrict__
         const int i = base + r * RS_BLOCK + (int)threadIdx.x;
         a[r] = i < n ? q[i] : make_int4(0, 0, 0, 0);
     }
+    const int m = grids ? mol_of_all(grids, n_mol, base, min(base + RS_TILE, n) - 1) : -1;
 #pragma unroll
     for (int r = 0; r < RS_IPT; r++) {
         const int i = base + r * RS_BLOCK + (int)threadIdx.x;
         if (i >= n) break;
-        const unsigned k = cell_key(a[r], i, grids, n_mol, g0);
+        const unsigned k = cell_key(a[r], i, !grids ? g0 : grids[m >= 0 ? m : mol_of(grids, n_mol, i)]);
         key[i] = k;
         atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
     }
@@ -329,7 +341,7 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
                                                            const int *__restrict__ start, int shift, long long ncell,
                                                            const int4 *__restrict__ q, unsigned *__restrict__ gidx,
                                                            int *__restrict__ cell_start, int4 *__restrict__ atom,
-                                                           float4 *__restrict__ sball, float4 *__restrict__ wball, int aq,
+                                                           int2 *__restrict__ sball, float4 *__restrict__ wball, int aq,
                                                            int *__restrict__ perm, Counters *cnt) {
     __shared__ int cc[BIN_CELLS];              // balls per cell, then each cell's first ball, then its end
     __shared__ unsigned short sc[BIN_ROWS];    // cell of each ball, in load order
@@ -415,7 +427,7 @@ constexpr int SMALL_BALLS = 2048;
 constexpr int SMALL_CELLS = 12288;
 __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
                                                             int n_mol, Grid g0, int ncell, int *__restrict__ cell_start,
-                                                            int4 *__restrict__ atom, float4 *__restrict__ sball,
+                                                            int4 *__restrict__ atom, int2 *__restrict__ sball,
                                                             float4 *__restrict__ wball, int aq, int *__restrict__ perm,
                                                             Counters *cnt) {
     __shared__ int cc[SMALL_CELLS];
@@ -424,7 +436,7 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restric
     for (int c = t; c < ncell; c += SMALL_BLOCK) cc[c] = 0;
     __syncthreads();
     for (int i = t; i < n; i += SMALL_BLOCK) {
-        const unsigned k = cell_key(q[i], i, grids, n_mol, g0);
+        const unsigned k = cell_key(q[i], i, grids ? grids[mol_of(grids, n_mol, i)] : g0);
         sc[i] = (unsigned short)k;
         atomicAdd(&cc[k], 1);
     }
@@ -479,25 +491,33 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restric
 // upper row holds the other ends with larger input ids, so that every simplex
 // belongs to the ball that comes first in its output row.
 //
-// The scan tests |p_j - p_i|^2 <= (rho_i + rho_j)^2 in float32, on the balls as
-// float4 {x, y, z, rho} with rho = sqrt(W + alpha): coordinates below 2^19 are
-// exact and so are their differences, the squares and rho are within 2^-21 of
-// their values, and rho is scaled up by 2^-19 (scan_ball), so no neighbour
-// is missed. The balls that pass are listed and then tested exactly: where the
-// wave's lanes are mostly busy, and where one ball in a million fails. (The
-// exact test of every scanned ball, in integers with a float64 comparison,
-// cost 24 instructions against 10.)
+// The scan tests |p_j - p_i|^2 <= (rho_i + rho_j)^2 on the balls' eight-byte forms
+// in 16-bit integers: no coordinate difference in the scanned cells reaches 2^15
+// (else, in grids of very large cells, the balls themselves are scanned), so the
+// differences are exact, and rho is rounded up, so no neighbour is missed. The
+// balls that pass are listed and then tested exactly, where the wave's lanes are
+// mostly busy. Seven instructions a scanned ball and eight bytes: with float4
+// balls (and addresses, list and row bounds in 64 bits) the kernel was held up
+// by the vector caches, 0.9 lines a clock and CU; it is now bound by instruction
+// issue (0.8). 283 -> 226 us at 3M atoms and alpha = 0, 23.7 -> 18.4 at 100,000,
+// 634 -> 534 for 512 molecules of 5.5M atoms in all.
 
-// Whether the grown balls of a and b meet (d <= rho_a + rho_b), exactly, for
-// balls that passed the scan (so |b - a|^2 < 2^29); not for a ball and itself.
-__device__ __forceinline__ bool balls_meet(const int4 &a, const int4 &b, const PredParams &pp) {
-    const int dx = b.x - a.x, dy = b.y - a.y, dz = b.z - a.z;
-    const int d2 = m24(dx, dx) + m24(dy, dy) + m24(dz, dz);
+// Whether the grown balls of two balls meet (d <= rho_a + rho_b) and whether
+// their spheres cross (|rho_a - rho_b| <= d too: AC3 of the edge), exactly, for
+// balls that passed the scan (so d2 = |b - a|^2 < 2^29), W_a + alpha >= 0; not for
+// a ball and itself. L^2 <= 4 rho_a^2 rho_b^2 with L = d^2 - rho_a^2 - rho_b^2; balls one inside
+// the other have L < 0. (pp.fast: see spheres_cross.)
+enum { BALLS_APART = 0, BALLS_NESTED = 1, BALLS_CROSS = 2 };
+__device__ __forceinline__ int balls_meet(const int4 &a, const int4 &b, int d2, const PredParams &pp) {
     const int ra = a.w + (int)pp.aq, rb = b.w + (int)pp.aq;
+    if (rb < 0) return BALLS_APART;
     const int L = d2 - ra - rb;
-    if (L <= 0) return true;
-    if (pp.fast) return (double)L * (double)L <= 4.0 * (double)ra * (double)rb;
-    return (i64)L * L <= 4 * (i64)ra * rb;
+    const bool cross = pp.fast ? (double)L * (double)L <= 4.0 * (double)ra * (double)rb : (i64)L * L <= 4 * (i64)ra * rb;
+    return cross ? BALLS_CROSS : L < 0 ? BALLS_NESTED : BALLS_APART;
+}
+__device__ __forceinline__ int dist2(const int4 &a, const int4 &b) {
+    const int dx = b.x - a.x, dy = b.y - a.y, dz = b.z - a.z;
+    return m24(dx, dx) + m24(dy, dy) + m24(dz, dz);
 }
 
 // (x - o) / s for 0 <= x - o < 2^21: float32 quotient, corrected.
@@ -509,12 +529,14 @@ __device__ __forceinline__ int cell_coord(int x, int o, int s, float inv) {
     return c;
 }
 
-// Calls f(j) for every sorted ball j (i itself among them) that passes the
-// scan, of the rows part, part + parts, ... of ball i's cell neighbourhood.
+// Calls f(j) for every sorted ball j (the ball a itself among them) that passes
+// the scan, of the rows part, part + parts, ... of a's cell neighbourhood. sball
+// has SCAN_PAD entries more than balls.
+constexpr int SCAN_GROUP = 4, SCAN_PAD = SCAN_GROUP - 1;
 template <class F>
-__device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, int i, const float4 *__restrict__ sball,
-                                          const int *__restrict__ cell_start, const PredParams &pp, int part, int parts,
-                                          F &&f) {
+__device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, const int4 *__restrict__ atom,
+                                          const int2 *__restrict__ sball, const int *__restrict__ cell_start,
+                                          const PredParams &pp, int part, int parts, F &&f) {
     const float inv = 1.0f / (float)g.s;
     const int cx = cell_coord(a.x, g.ox, g.s, inv), cy = cell_coord(a.y, g.oy, g.s, inv),
               cz = cell_coord(a.z, g.oz, g.s, inv);
@@ -522,30 +544,35 @@ __device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, int i, c
     const int y0 = max(cy - g.reach, 0), y1 = min(cy + g.reach, g.ny - 1);
     const int z0 = max(cz - g.reach, 0), z1 = min(cz + g.reach, g.nz - 1);
     const int ny = y1 - y0 + 1, rows = ny * (z1 - z0 + 1);
-    const int lim = 4 * (int)pp.sg2;     // (2 s_g)^2 < 2^28
-    const int reach1 = 2 * (int)pp.sgc;  // 2 ceil(s_g) <= 2^14
-    const float4 me = sball[i];
+    const bool wide = (long long)(g.reach + 1) * g.s > 32767;
+    const int rho = scan_rho(a, (int)pp.aq);
+    const short2v mxy = {(short)a.x, (short)a.y}, mzr = {(short)a.z, (short)-rho};
     auto scan_range = [&](int s, int e) {
-        // four loads in flight (past the range its last ball again, not used)
-        for (int j = s; j < e; j += 4) {
-            float4 b[4];
+        if (wide) {
+            for (int j = s; j < e; j++) {
+                const int4 b = atom[j];
+                const float dx = (float)(b.x - a.x), dy = (float)(b.y - a.y), dz = (float)(b.z - a.z);
+                const float r = (float)(rho + scan_rho(b, (int)pp.aq)) * (1.0f + 1.0f / (1 << 19));
+                if (dx * dx + dy * dy + dz * dz <= r * r) f(j);
+            }
+            return;
+        }
+        // the group's loads at fixed offsets of one address (past the range
+        // they are some other ball's, or padding, and not used)
+        for (int j = s; j < e; j += SCAN_GROUP) {
+            const int2 *p = sball + j;
+            const int left = e - j;
+            int2 b[SCAN_GROUP];
 #pragma unroll
-            for (int u = 0; u < 4; u++) b[u] = sball[min(j + u, e - 1)];
+            for (int u = 0; u < SCAN_GROUP; u++) b[u] = p[u];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const float dx = b[u].x - me.x, dy = b[u].y - me.y, dz = b[u].z - me.z;
-                const float rho = me.w + b[u].w;
-                if ((j + u < e) & (dx * dx + dy * dy + dz * dz <= rho * rho)) f(j + u);
+            for (int u = 0; u < SCAN_GROUP; u++) {
+                const short2v dxy = __builtin_bit_cast(short2v, b[u].x) - mxy;
+                const short2v dzr = __builtin_bit_cast(short2v, b[u].y) - mzr;  // (dz, rho_j + rho_i)
+                const unsigned d2 = (unsigned)__builtin_amdgcn_sdot2(dxy, dxy, (int)dzr.x * (int)dzr.x, false);
+                if ((u < left) & (d2 <= (unsigned)((int)dzr.y * (int)dzr.y))) f(j + u);
             }
         }
-    };
-    // a row's balls, or none where all its cells lie farther than 2 s_g
-    auto row_of = [&](int y, int z) {
-        const int zlo = g.oz + z * g.s, ylo = g.oy + y * g.s;
-        const int dz = max(max(zlo - a.z, a.z - (zlo + g.s - 1)), 0), dy = max(max(ylo - a.y, a.y - (ylo + g.s - 1)), 0);
-        const bool far = dz > reach1 || dy > reach1 || lim - dz * dz < dy * dy;
-        const long long rb = g.base + ((long long)z * g.ny + y) * g.nx;
-        return far ? make_int2(0, 0) : make_int2(cell_start[rb + x0], cell_start[rb + x1 + 1]);
     };
     if (rows <= 0 || g.reach < 0) return;  // reach < 0: a stopped recorded build's grid
     if (g.order == ORDER_MORTON) {
@@ -556,21 +583,45 @@ __device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, int i, c
             }
         return;
     }
-    int y = y0 + part, z = z0;
-    while (y > y1) {
-        y -= ny;
-        z++;
-    }
-    int2 next = z <= z1 ? row_of(y, z) : make_int2(0, 0);
+    // a row's balls, or none where all its cells lie farther from the ball than
+    // rho + s_g. In float32: the cells' corners are exact, R2 is scaled up by
+    // more than the sum's rounding. Cells are below 2^31 in all.
+    const float R = (float)(rho + (int)pp.sgc), R2 = R * R * (1.0f + 1.0f / (1 << 19));
+    const float side = (float)g.s, last = side - 1.0f, oy = (float)g.oy, oz = (float)g.oz;
+    const float ay = (float)a.y, az = (float)a.z;
+    const int slab = g.ny * g.nx;
+    int y = y0 + part, z = z0, zbase = 0;
+    float dz2 = 0.0f;
+    auto enter = [&]() {
+        const float lo = fmaf((float)z, side, oz);
+        const float d = fmaxf(fmaxf(lo - az, az - (lo + last)), 0.0f);
+        dz2 = d * d;
+        zbase = (int)((unsigned)g.base + (unsigned)z * (unsigned)slab);
+    };
+    auto wrap = [&]() {
+        if (y <= y1) return;
+        do {
+            y -= ny;
+            z++;
+        } while (y > y1);
+        enter();
+    };
+    auto bounds = [&]() {
+        const float lo = fmaf((float)y, side, oy);
+        const float d = fmaxf(fmaxf(lo - ay, ay - (lo + last)), 0.0f);
+        if (z > z1 || fmaf(d, d, dz2) > R2) return make_int2(0, 0);
+        const int *c = cell_start + (zbase + __mul24(y, g.nx));
+        return make_int2(c[x0], c[x1 + 1]);
+    };
+    enter();
+    wrap();
+    int2 next = bounds();
     while (z <= z1) {
         // the next row's bounds are loaded while this row is scanned
         const int2 now = next;
         y += parts;
-        while (y > y1) {
-            y -= ny;
-            z++;
-        }
-        if (z <= z1) next = row_of(y, z);
+        wrap();
+        next = bounds();
         scan_range(now.x, now.y);
     }
 }
@@ -594,46 +645,63 @@ template <int SLOT, int LPB>
 constexpr int nb_waves() { return SLOT == NB_SLOT && LPB == 1 ? 8 : 4; }
 template <int SLOT, int LPB, bool SINGLE>
 __global__ void __launch_bounds__(BLOCK, (nb_waves<SLOT, LPB>()))
-k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, const int *__restrict__ perm, int n,
+k_neighbours(const int4 *__restrict__ atom, const int2 *__restrict__ sball, const int *__restrict__ perm, int n,
              const Grid *__restrict__ grids, int n_mol, Grid g0, const int *__restrict__ cell_start, PredParams pp,
              int *__restrict__ deg_n, int *__restrict__ deg_up, int *__restrict__ nslab, int *__restrict__ block_tot,
              unsigned char *__restrict__ vgab, long long *__restrict__ vert_min, Counters *cnt) {
     constexpr int BALLS = BLOCK / LPB;             // of a block
     constexpr int LSLOT = SLOT > 32 ? 32 : SLOT;  // of a lane (a mask bit per entry)
-    __shared__ int sn[BLOCK * LSLOT];
+    // room of a lane's list: its entries, the ball itself, and one for what
+    // does not fit
+    constexpr int FULL = LSLOT + 1;
+    __shared__ int sn[BLOCK * (FULL + 2)];
     const int b = xcd_block();
     const int i = b * BALLS + (int)threadIdx.x / LPB, part = (int)threadIdx.x % LPB;
     const bool valid = i < n;
     const int4 a = valid ? atom[i] : make_int4(0, 0, 0, 0);
     const int me = valid ? perm[i] : 0;
     const bool ball = valid && a.w + (int)pp.aq >= 0;  // |aq| < 2^26 and W < 2^26
-    int cn = 0;
+    int at = threadIdx.x;  // entry k of a lane's list at k * BLOCK: a wave's lanes hit distinct banks
     unsigned mask = 0;
     bool gab = true;
-    // entry k of a lane's list at k * BLOCK: a wave's lanes hit distinct banks
-    int *const rn = sn + threadIdx.x;
-    if (ball) {
-        const Grid g = SINGLE ? (grids ? grids[0] : g0) : grids[mol_of(grids, n_mol, i)];
-        scan_rows(g, a, i, sball, cell_start, pp, part, LPB, [&](int j) {
-            if (j == i) return;
-            if (cn < LSLOT) rn[cn * BLOCK] = j;
-            cn++;
+    auto scan = [&](const Grid &g) {
+        if (!ball) return;
+        scan_rows(g, a, atom, sball, cell_start, pp, part, LPB, [&](int j) {
+            sn[at] = j;
+            at = min(at + BLOCK, (int)threadIdx.x + (FULL + 1) * BLOCK);
         });
+    };
+    if constexpr (SINGLE) {
+        scan(grids ? grids[0] : g0);
+    } else {
+        const int w0 = b * BALLS + (int)threadIdx.x / WAVE * (WAVE / LPB);
+        const int m = w0 < n ? mol_of_all(grids, n_mol, w0, min(w0 + WAVE / LPB, n) - 1) : 0;
+        if (m >= 0) scan(grids[m]);
+        else if (ball) scan(grids[mol_of(grids, n_mol, i)]);
     }
-    const bool lane_full = cn > LSLOT;
-    const int kn = min(cn, LSLOT);
-    cn = 0;
+    int *const rn = sn + threadIdx.x;
+    const int listed = at / BLOCK;
+    const int kn = min(listed, FULL);
+    int cn = 0;
     // the exact test, AC2 of the vertex and AC3 of the edge for each listed
     // ball; the list keeps the neighbours
     for (int k = 0; k < kn; k++) {
         const int j = rn[k * BLOCK];
+        if (j == i) continue;
         const int4 bb = atom[j];
-        if (!balls_meet(a, bb, pp)) continue;
-        if (vertex_violation_sign(a, i, bb, j, perm) < 0) gab = false;
-        if (perm[j] > me && edge_ac3(edge_setup(a, bb), pp.aq)) mask |= 1u << cn;
-        rn[cn * BLOCK] = j;
+        const int id = perm[j];
+        const int d2 = dist2(a, bb);
+        const int meet = balls_meet(a, bb, d2, pp);
+        if (meet == BALLS_APART) continue;
+        // power of the ball at a's centre (vertex_violation_sign, ties by id)
+        const int P = d2 - bb.w + a.w;
+        gab &= P > 0 || (P == 0 && id > me);
+        mask |= (unsigned)(id > me && meet == BALLS_CROSS) << (cn & 31);
+        if (cn < LSLOT) rn[cn * BLOCK] = j;
         cn++;
     }
+    const bool lane_full = listed > FULL || cn > LSLOT;
+    cn = min(cn, LSLOT);
     // places in the slab: the ball's upper entries, then the others, each by lane
     const int cu = __popc(mask);
     int bn = cn, bu = cu, pu = 0, pl = 0;  // of the ball; before this lane: upper, others
@@ -687,7 +755,7 @@ k_neighbours(const int4 *__restrict__ atom, const float4 *__restrict__ sball, co
 // and after their scans the rows (CSR; upper entries with their owner, in scan
 // order).
 template <bool FILL>
-__global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ atom, const float4 *__restrict__ sball,
+__global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ atom, const int2 *__restrict__ sball,
                                                      const int *__restrict__ perm, int n, const Grid *__restrict__ grids,
                                                      int n_mol, Grid g0, const int *__restrict__ cell_start, PredParams pp,
                                                      int *__restrict__ deg_n, int *__restrict__ deg_up,
@@ -705,11 +773,12 @@ __global__ void __launch_bounds__(BLOCK) k_nbr_rows(const int4 *__restrict__ ato
     const int pn = FILL ? nbr_start[i] : 0, pu = FILL ? up_start[i] : 0;
     if (ball) {
         const Grid g = grids ? grids[mol_of(grids, n_mol, i)] : g0;
-        scan_rows(g, a, i, sball, cell_start, pp, 0, 1, [&](int j) {
+        scan_rows(g, a, atom, sball, cell_start, pp, 0, 1, [&](int j) {
             if (j == i) return;
             const int4 bb = atom[j];
-            if (!balls_meet(a, bb, pp)) return;
-            const bool upper = perm[j] > me && edge_ac3(edge_setup(a, bb), pp.aq);
+            const int meet = balls_meet(a, bb, dist2(a, bb), pp);
+            if (meet == BALLS_APART) return;
+            const bool upper = perm[j] > me && meet == BALLS_CROSS;
             if (FILL) {
                 nbr[pn + cn] = j;
                 if (upper) {
