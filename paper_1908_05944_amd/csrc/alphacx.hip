@@ -548,6 +548,9 @@ static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double
     LAUNCH_CHECK();
 }
 
+// Bytes of the minima of the alphas that a sweep takes in one launch.
+constexpr size_t SWEEP_ROOM = 256u << 20;
+
 // Pairs of upper entries a build makes room for (25 bytes each); past it the
 // candidate triangles are counted first.
 constexpr long long PAIR_ROOM = 1LL << 28;
@@ -1310,94 +1313,72 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             const int M[4] = {n, cp.m1, cp.m2, cp.m3};
             const int T = M[2], Q = M[3];
             const size_t T1s = T > 0 ? T : 1, Q1 = Q > 0 ? Q : 1;
-            int *tri_att = sc.get<int>(T1s), *edge_att = sc.get<int>(E1), *vert_att = sc.get<int>(n);
-            long long *stri_min = sc.get<long long>(T1s);
-            long long *svert_min = sc.get<long long>(n);
-            int *rows_s[4] = {}, *thr[4] = {}, *tsum[4] = {}, *toff[4] = {};
-            unsigned char *in_s[4] = {};
-            double *sz_s[4] = {}, *szp[4] = {};
+            int *rows_s[4] = {}, *thr[4] = {};
+            double *szp[4] = {};
             for (int d = 1; d <= 3; d++) {
-                const int m = M[d] > 0 ? M[d] : 1;
-                const unsigned nb = grid_for(m);
-                rows_s[d] = sc.get<int>((size_t)m * (d + 1));
-                in_s[d] = sc.get<unsigned char>(m);
-                tsum[d] = sc.get<int>(nb);
-                toff[d] = sc.get<int>((size_t)nb + 1);
-                sz_s[d] = sc.get<double>(m);
+                const size_t m = M[d] > 0 ? M[d] : 1;
+                rows_s[d] = sc.get<int>(m * (d + 1));
                 thr[d] = sc.get<int>(m);
                 szp[d] = sc.get<double>(m);
             }
-            int2 *ends = sc.get<int2>(E1);
+            int2 *vert = sc.get<int2>(n);
             int4 *face2 = sc.get<int4>(T1s);
             int4 *face3 = sc.get<int4>(Q1);
             int4 *adj = sc.get<int4>(n);
             k_sweep_adj<<<groups, BLOCK, 0, s>>>(cd, tt, rec, adj);
             if (E > 0)
-                k_sweep_prep_edge<<<grid_for(E), BLOCK, 0, s>>>(cd, E, egab, adj, aq, thr[1], szp[1], rows_s[1], ends);
+                k_sweep_prep_edge<<<grid_for(E), BLOCK, 0, s>>>(cd, E, egab, adj, aq, thr[1], szp[1], rows_s[1]);
             k_sweep_prep_tri<<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, adj, pp, thr[2], szp[2], rows_s[2], face2, cnt);
             k_sweep_prep_tet<<<groups, BLOCK, 0, s>>>(cd, tt, adj, pp, thr[3], szp[3], rows_s[3], face3, cnt);
+            k_sweep_prep_vert<<<grid_for(n), BLOCK, 0, s>>>(cd, vgab, o.vertex_shortcut, vert);
             LAUNCH_CHECK();
-            double *vsize_in = sc.get<double>(n);
-            int *vflag = sc.get<int>(n);
-            int *vpos = sc.get<int>((size_t)n + 1);
             // per-alpha kept counts (m0..m3 of cs[k]); the main counters keep
             // the candidate totals, the fallback count and the lookup flag
             Counters *cs = sc.get<Counters>(n_alpha);
             HIP_TRY(hipMemsetAsync(cs, 0, n_alpha * sizeof(Counters), s));
+            // alphas of a launch: as many as their minima have room for
+            const size_t per = (size_t)n + E + T;
+            const int chunk = (int)std::min<long long>(std::min(n_alpha, SWEEP_ALPHAS),
+                                                       std::max<long long>(1, (long long)(SWEEP_ROOM / (8 * per))));
+            Sweep sw{};
+            sw.vert = vert;
+            sw.face2 = face2;
+            sw.face3 = face3;
+            long long *mins = sc.get<long long>(per * chunk);
+            sw.mins[0] = mins;
+            sw.mins[1] = mins + (size_t)n * chunk;
+            sw.mins[2] = sw.mins[1] + (size_t)E * chunk;
+            for (int d = 0; d < 4; d++) {
+                sw.m[d] = M[d];
+                sw.nb[d] = M[d] > 0 ? (int)grid_for(M[d]) : 0;
+                sw.thr[d] = thr[d];
+                sw.sz[d] = szp[d];
+                sw.rows[d] = rows_s[d];
+                sw.tsum[d] = sc.get<int>((size_t)std::max(sw.nb[d], 1) * chunk);
+            }
             tm.mark(ST_TRI_FINAL);
             tm.mark(ST_EDGE_FINAL);
             tm.mark(ST_VERT_FINAL);
             tm.mark(ST_EMIT);
-            for (int k = 0; k < n_alpha; k++) {
-                PredParams pa = pp;
-                pa.aq = aqs[k];
-                ac_complex *r = rs[k];
-                const long long mx = std::max<long long>(std::max<long long>(T, E), n);
-                k_prune_init<<<(unsigned)std::min<long long>((mx + BLOCK - 1) / BLOCK, 65536), BLOCK, 0, s>>>(
-                    T, E, n, tri_att, stri_min, edge_att, edge_min, vert_att, svert_min);
-                LAUNCH_CHECK();
-                if (Q > 0) {
-                    k_sweep_tets<<<grid_for(Q), BLOCK, 0, s>>>(Q, pa.aq, thr[3], szp[3], face3, thr[2], tri_att, stri_min,
-                                                              in_s[3], sz_s[3], tsum[3], cnt);
-                    LAUNCH_CHECK();
-                }
-                if (T > 0) {
-                    k_sweep_tris<<<grid_for(T), BLOCK, 0, s>>>(T, pa.aq, thr[2], szp[2], face2, tri_att, stri_min, thr[1],
-                                                              edge_att, edge_min, in_s[2], sz_s[2], tsum[2], cnt);
-                    LAUNCH_CHECK();
-                }
-                if (E > 0) {
-                    k_sweep_edges<<<grid_for(E), BLOCK, 0, s>>>(E, pa.aq, thr[1], szp[1], ends, edge_att, edge_min, vgab,
-                                                               vert_att, svert_min, in_s[1], sz_s[1], tsum[1]);
-                    LAUNCH_CHECK();
-                }
-                k_vert_final<<<grid_for(n), BLOCK, 0, s>>>(atom, perm, n, pa, o.vertex_shortcut, vgab, svert_min, vsize_in);
-                k_vert_flags<<<grid_for(n), BLOCK, 0, s>>>(vsize_in, n, vflag);
-                LAUNCH_CHECK();
-                scan_i32(vflag, vpos, n, s, sc, &cs[k].m0);
-                dev_rows(r, 0, n);
-                k_vert_emit<<<grid_for(n), BLOCK, 0, s>>>(vsize_in, vpos, n, r->d_simp[0], r->d_size[0]);
-                LAUNCH_CHECK();
-                int *m_out[4] = {&cs[k].m0, &cs[k].m1, &cs[k].m2, &cs[k].m3};
-                for (int d = 1; d <= 3; d++) {
-                    dev_rows(r, d, M[d]);
-                    if (M[d] == 0) {
-                        fill<int>(m_out[d], 0, 1, s);
-                        continue;
+            for (int k0 = 0; k0 < n_alpha; k0 += chunk) {
+                const int na = std::min(chunk, n_alpha - k0);
+                for (int a = 0; a < na; a++) {
+                    sw.aq[a] = aqs[k0 + a];
+                    sw.totals[a] = cs + k0 + a;
+                    for (int d = 0; d < 4; d++) {
+                        dev_rows(rs[k0 + a], d, M[d]);
+                        sw.out[a][d] = rs[k0 + a]->d_simp[d];
+                        sw.out_size[a][d] = rs[k0 + a]->d_size[d];
                     }
-                    const unsigned nb = grid_for(M[d]);
-                    scan_i32(tsum[d], toff[d], nb, s, sc, m_out[d]);
-                    if (d == 1)
-                        k_sweep_write<2><<<nb, BLOCK, 0, s>>>(in_s[d], toff[d], rows_s[d], sz_s[d], M[d], r->d_simp[d],
-                                                             r->d_size[d]);
-                    else if (d == 2)
-                        k_sweep_write<3><<<nb, BLOCK, 0, s>>>(in_s[d], toff[d], rows_s[d], sz_s[d], M[d], r->d_simp[d],
-                                                             r->d_size[d]);
-                    else
-                        k_sweep_write<4><<<nb, BLOCK, 0, s>>>(in_s[d], toff[d], rows_s[d], sz_s[d], M[d], r->d_simp[d],
-                                                             r->d_size[d]);
-                    LAUNCH_CHECK();
                 }
+                fill<long long>(mins, ORDERED_POS_INF, (long long)per * chunk, s);
+                if (sw.nb[3]) k_sweep_mark<3><<<dim3(sw.nb[3], na), BLOCK, 0, s>>>(sw, cnt);
+                if (sw.nb[2]) k_sweep_mark<2><<<dim3(sw.nb[2], na), BLOCK, 0, s>>>(sw, cnt);
+                if (sw.nb[1]) k_sweep_mark<1><<<dim3(sw.nb[1], na), BLOCK, 0, s>>>(sw, cnt);
+                k_sweep_mark<0><<<dim3(sw.nb[0], na), BLOCK, 0, s>>>(sw, cnt);
+                k_sweep_scan<<<dim3(4, na), 1024, 0, s>>>(sw);
+                k_sweep_write<<<dim3(sw.nb[0] + sw.nb[1] + sw.nb[2] + sw.nb[3], na), BLOCK, 0, s>>>(sw);
+                LAUNCH_CHECK();
             }
             tm.mark(ST_COUNT);
             read_back(cm.data(), cs, (size_t)n_alpha, s);

@@ -595,24 +595,4 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
     }
 }
 
-// ---------------------------------------------------------------------------
-// Vertices in input order. k_vert_final writes one float64 per ball to its
-// input position: its Size in mA^2, or NaN when the ball is not in K_alpha;
-// the kept flags for the scan are taken from those words in order.
-__global__ void __launch_bounds__(256) k_vert_flags(const double *__restrict__ vsize_in, int n, int *__restrict__ flag) {
-    const int u = blockIdx.x * 256 + threadIdx.x;
-    if (u < n) flag[u] = vsize_in[u] == vsize_in[u];  // not NaN
-}
-
-__global__ void __launch_bounds__(256) k_vert_emit(const double *__restrict__ vsize_in, const int *__restrict__ vpos,
-                                                    int n, int *__restrict__ out, double *__restrict__ out_size) {
-    const int u = blockIdx.x * 256 + threadIdx.x;
-    if (u >= n) return;
-    const double z = vsize_in[u];
-    if (z != z) return;
-    const int p = vpos[u];
-    out[p] = u;
-    out_size[p] = z / 1.0e6;  // mA^2 -> A^2
-}
-
 }  // namespace acx

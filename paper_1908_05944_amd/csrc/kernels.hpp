@@ -220,27 +220,6 @@ __global__ void __launch_bounds__(BLOCK) k_fill(T *__restrict__ p, T v, long lon
     for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (long long)gridDim.x * BLOCK) p[i] = v;
 }
 
-// Start values of the pruning stage's attachment flags (0) and minima (+inf
-// in the ordered-integer encoding) for T triangles, E edges and n vertices.
-__global__ void __launch_bounds__(BLOCK) k_prune_init(long long T, long long E, long long n, int *__restrict__ tri_att,
-                                                       long long *__restrict__ tri_min, int *__restrict__ edge_att,
-                                                       long long *__restrict__ edge_min, int *__restrict__ vert_att,
-                                                       long long *__restrict__ vert_min) {
-    const long long stride = (long long)gridDim.x * BLOCK;
-    for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < T; i += stride) {
-        tri_att[i] = 0;
-        tri_min[i] = ORDERED_POS_INF;
-    }
-    for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < E; i += stride) {
-        edge_att[i] = 0;
-        edge_min[i] = ORDERED_POS_INF;
-    }
-    for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n; i += stride) {
-        vert_att[i] = 0;
-        vert_min[i] = ORDERED_POS_INF;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Binning (Sec. 4.2): the balls sorted by cell (inside a cell in input order)
 // and the dense cell table.
@@ -1016,32 +995,6 @@ __global__ void __launch_bounds__(BLOCK) k_fold_i64(const long long *__restrict_
         for (int k = 0; k < BLOCK / WAVE; k++) t += ws[k];
         *out = t;
     }
-}
-
-// Vertices (Step 5): a ball with -W <= alpha is kept iff no ball is strictly
-// closer in power to its own centre (decided in k_neighbours), or it ends a
-// kept edge. With `shortcut`, every such ball is kept with Size -W (the
-// paper's implementation shortcut). One float64 per ball goes to its input
-// position: the Size in mA^2, NaN when not kept.
-__global__ void __launch_bounds__(BLOCK) k_vert_final(const int4 *__restrict__ atom, const int *__restrict__ perm, int n,
-                                                       PredParams pp, int shortcut,
-                                                       const unsigned char *__restrict__ vgab,
-                                                       const long long *__restrict__ vert_min,
-                                                       double *__restrict__ vsize_in) {
-    const int v = xcd_block() * BLOCK + threadIdx.x;
-    if (v >= n) return;
-    const int w = atom[v].w;
-    double sz = __longlong_as_double(0x7ff8000000000000LL);  // NaN: not kept
-    if ((i64)w + pp.aq >= 0) {
-        const bool gab = shortcut || vgab[v];
-        if (gab) {
-            sz = -(double)w;
-        } else {
-            const long long mn = vert_min[v];
-            if (mn != ORDERED_POS_INF) sz = double_from_ordered(mn);
-        }
-    }
-    vsize_in[perm[v]] = sz;
 }
 
 }  // namespace acx

@@ -69,16 +69,15 @@ __global__ void __launch_bounds__(BLOCK) k_sweep_adj(Cands cd, Tets tt, const in
     if (in) adj[s] = make_int4(lo.x - cd.up_start[s], lo.y - ft, lo.z - fq, 0);
 }
 
-// Edges: threshold, Size, row and end balls of every candidate, at its place.
+// Edges: threshold, Size and row of every candidate, at its place.
 __global__ void __launch_bounds__(BLOCK) k_sweep_prep_edge(Cands cd, int E, const unsigned char *__restrict__ egab,
                                                             const int4 *__restrict__ adj, i64 aq_max,
                                                             int *__restrict__ thr, double *__restrict__ sz,
-                                                            int *__restrict__ rows, int2 *__restrict__ ends) {
+                                                            int *__restrict__ rows) {
     const int e = xcd_block() * BLOCK + threadIdx.x;
     if (e >= E) return;
     const int i = cd.edge_i[e], j = cd.up[e];
     const int p = adj[i].x + e;
-    ends[p] = make_int2(i, j);
     reinterpret_cast<int2 *>(rows)[p] = make_int2(cd.perm[i], cd.up_id[e]);
     if (!egab[e]) {
         thr[p] = NO_ENTRY;
@@ -153,122 +152,151 @@ __global__ void __launch_bounds__(BLOCK) k_sweep_prep_tet(Cands cd, Tets tt, con
     }
 }
 
+// W and whether it passes AC2 at its own centre (or is taken as if), of every
+// ball at its input id.
+__global__ void __launch_bounds__(BLOCK) k_sweep_prep_vert(Cands cd, const unsigned char *__restrict__ vgab, int shortcut,
+                                                            int2 *__restrict__ vert) {
+    const int s = xcd_block() * BLOCK + threadIdx.x;
+    if (s < cd.n) vert[cd.perm[s]] = make_int2(cd.atom[s].w, shortcut || vgab[s]);
+}
+
+// The prepared candidates and the chunk of at most SWEEP_ALPHAS alphas that a
+// launch takes (blockIdx.y: the alpha; in launches of their own, 19 an alpha,
+// the kernels of 100,000 balls leave the device idle: 495 us for five alphas
+// against 217, most of it writes and atomic minima of the kept rows). m[d]: candidates of dimension d, nb[d]: blocks of
+// BLOCK of them; mins[d]: m[d] entries an alpha, the least Size of a kept coface
+// (order-preserving integer, +inf while none); tsum[d]: nb[d] entries an alpha,
+// the kept ones of each block, then their exclusive scan.
+constexpr int SWEEP_ALPHAS = 8;
+struct Sweep {
+    int m[4], nb[4];
+    const int2 *vert;
+    const int *thr[4];
+    const double *sz[4];
+    const int *rows[4];
+    const int4 *face2, *face3;
+    long long *mins[3];
+    int *tsum[4];
+    i64 aq[SWEEP_ALPHAS];
+    Counters *totals[SWEEP_ALPHAS];
+    int *out[SWEEP_ALPHAS][4];
+    double *out_size[SWEEP_ALPHAS][4];
+};
+
+// Whether candidate p of dimension D is in K of alpha a, and its Size in mA^2:
+// kept are the candidates that pass AC2 and AC3 (thr <= alpha), and those a
+// kept coface recorded itself on.
+template <int D>
+__device__ __forceinline__ bool sweep_kept(const Sweep &sw, int a, int p, double &size) {
+    bool own;
+    if constexpr (D == 0) {
+        const int2 v = sw.vert[p];
+        if ((i64)v.x + sw.aq[a] < 0) return false;
+        own = v.y;
+        size = -(double)v.x;
+    } else {
+        own = sw.thr[D][p] <= sw.aq[a];
+        if (own) size = sw.sz[D][p];
+    }
+    if constexpr (D == 3) {
+        return own;
+    } else {
+        if (own) return true;
+        const long long mn = sw.mins[D][(long long)a * sw.m[D] + p];
+        if (mn == ORDERED_POS_INF) return false;
+        size = double_from_ordered(mn);
+        return true;
+    }
+}
+
 // A kept coface records itself on face f unless f passes AC2 (threshold not
 // NO_ENTRY: such a face is in K with its own Size whenever a coface is).
-__device__ __forceinline__ void sweep_mark(const int *__restrict__ thr, int *att, long long *mins, int f,
-                                           long long key, Counters *cnt) {
+__device__ __forceinline__ void sweep_mark(const int *__restrict__ thr, long long *mins, int f, long long key, Counters *cnt) {
     if (f < 0) { atomicOr(&cnt->lookup, 1); return; }
     if (thr[f] != NO_ENTRY) return;
-    atomicOr(&att[f], 1);
     atomicMin(&mins[f], key);
 }
 
-// The kernels of one alpha run one thread per row of the output order, in
-// blocks of BLOCK rows; each writes its rows' kept flags and its block's
-// kept total (tsum), whose scan places the kept rows in k_sweep_write.
-
-// One alpha (aq in mA^2), tetrahedra in output order (Step 2).
-__global__ void __launch_bounds__(BLOCK) k_sweep_tets(int Q, i64 aq, const int *__restrict__ thr3,
-                                                       const double *__restrict__ sz3, const int4 *__restrict__ face3,
-                                                       const int *__restrict__ thr2, int *__restrict__ tri_att,
-                                                       long long *__restrict__ tri_min, unsigned char *__restrict__ in_s,
-                                                       double *__restrict__ sz_s, int *__restrict__ tsum,
-                                                       Counters *cnt) {
-    const int p = blockIdx.x * BLOCK + threadIdx.x;
-    const bool in = p < Q && thr3[p] <= aq;
-    if (p < Q) in_s[p] = in;
-    if (in) {
-        const double sz = sz3[p];
-        sz_s[p] = sz;
-        const long long key = ordered_from_double(sz);
-        const int4 f = face3[p];
-        sweep_mark(thr2, tri_att, tri_min, f.x, key, cnt);
-        sweep_mark(thr2, tri_att, tri_min, f.y, key, cnt);
-        sweep_mark(thr2, tri_att, tri_min, f.z, key, cnt);
-        sweep_mark(thr2, tri_att, tri_min, f.w, key, cnt);
-    }
-    int tot;
-    (void)block_exclusive_scan<BLOCK>(in, &tot);
-    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
-}
-
-// One alpha, triangles in output order (Step 3).
-__global__ void __launch_bounds__(BLOCK) k_sweep_tris(int T, i64 aq, const int *__restrict__ thr2,
-                                                       const double *__restrict__ sz2, const int4 *__restrict__ face2,
-                                                       const int *__restrict__ tri_att,
-                                                       const long long *__restrict__ tri_min,
-                                                       const int *__restrict__ thr1, int *__restrict__ edge_att,
-                                                       long long *__restrict__ edge_min,
-                                                       unsigned char *__restrict__ in_s, double *__restrict__ sz_s,
-                                                       int *__restrict__ tsum, Counters *cnt) {
-    const int p = blockIdx.x * BLOCK + threadIdx.x;
-    bool in = false;
-    if (p < T) {
-        const bool gab = thr2[p] <= aq;
-        in = gab || tri_att[p];
-        in_s[p] = in;
-        if (in) {
-            const double sz = gab ? sz2[p] : double_from_ordered(tri_min[p]);
-            sz_s[p] = sz;
-            const long long key = ordered_from_double(sz);
-            const int4 f = face2[p];
-            sweep_mark(thr1, edge_att, edge_min, f.x, key, cnt);
-            sweep_mark(thr1, edge_att, edge_min, f.y, key, cnt);
-            sweep_mark(thr1, edge_att, edge_min, f.z, key, cnt);
+// Candidates of dimension D (3, 2, 1, 0 in turn; Steps 2-5), one thread per row
+// of the output order: the kept ones record themselves on their faces and are
+// counted by block.
+template <int D>
+__global__ void __launch_bounds__(BLOCK) k_sweep_mark(Sweep sw, Counters *cnt) {
+    const int p = blockIdx.x * BLOCK + threadIdx.x, a = blockIdx.y;
+    double size;
+    const bool in = p < sw.m[D] && sweep_kept<D>(sw, a, p, size);
+    if (D > 0 && in) {
+        const long long key = ordered_from_double(size);
+        long long *const mins = sw.mins[D - 1] + (long long)a * sw.m[D - 1];
+        if constexpr (D == 3) {
+            const int4 f = sw.face3[p];
+            sweep_mark(sw.thr[2], mins, f.x, key, cnt);
+            sweep_mark(sw.thr[2], mins, f.y, key, cnt);
+            sweep_mark(sw.thr[2], mins, f.z, key, cnt);
+            sweep_mark(sw.thr[2], mins, f.w, key, cnt);
+        } else if constexpr (D == 2) {
+            const int4 f = sw.face2[p];
+            sweep_mark(sw.thr[1], mins, f.x, key, cnt);
+            sweep_mark(sw.thr[1], mins, f.y, key, cnt);
+            sweep_mark(sw.thr[1], mins, f.z, key, cnt);
+        } else if constexpr (D == 1) {
+            const int2 v = reinterpret_cast<const int2 *>(sw.rows[1])[p];
+            if (!sw.vert[v.x].y) atomicMin(&mins[v.x], key);
+            if (!sw.vert[v.y].y) atomicMin(&mins[v.y], key);
         }
     }
-    int tot;
-    (void)block_exclusive_scan<BLOCK>(in, &tot);
-    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
+    const int kept = __syncthreads_count(in);
+    if (threadIdx.x == 0) sw.tsum[D][(long long)a * sw.nb[D] + blockIdx.x] = kept;
 }
 
-// One alpha, edges in output order (Step 4); kept edges record themselves on
-// their ends that fail AC2 (Step 5).
-__global__ void __launch_bounds__(BLOCK) k_sweep_edges(int E, i64 aq, const int *__restrict__ thr1,
-                                                        const double *__restrict__ sz1, const int2 *__restrict__ ends,
-                                                        const int *__restrict__ edge_att,
-                                                        const long long *__restrict__ edge_min,
-                                                        const unsigned char *__restrict__ vgab,
-                                                        int *__restrict__ vert_att, long long *__restrict__ vert_min,
-                                                        unsigned char *__restrict__ in_s, double *__restrict__ sz_s,
-                                                        int *__restrict__ tsum) {
-    const int p = blockIdx.x * BLOCK + threadIdx.x;
-    bool in = false;
-    if (p < E) {
-        const bool gab = thr1[p] <= aq;
-        in = gab || edge_att[p];
-        in_s[p] = in;
-        if (in) {
-            const double sz = gab ? sz1[p] : double_from_ordered(edge_min[p]);
-            sz_s[p] = sz;
-            const long long key = ordered_from_double(sz);
-            const int2 v = ends[p];
-            if (!vgab[v.x]) { atomicOr(&vert_att[v.x], 1); atomicMin(&vert_min[v.x], key); }
-            if (!vgab[v.y]) { atomicOr(&vert_att[v.y], 1); atomicMin(&vert_min[v.y], key); }
-        }
+// Block (d, a): exclusive scan of the blocks' kept counts of dimension d and
+// alpha a, and their total.
+__global__ void __launch_bounds__(1024) k_sweep_scan(Sweep sw) {
+    const int d = blockIdx.x, a = blockIdx.y, nb = sw.nb[d];
+    int *const t = sw.tsum[d] + (long long)a * nb;
+    int run = 0;
+    for (int c0 = 0; c0 < nb; c0 += 1024) {
+        const int k = c0 + threadIdx.x;
+        const int v = k < nb ? t[k] : 0;
+        int tot;
+        const int off = block_exclusive_scan<1024>(v, &tot);
+        if (k < nb) t[k] = run + off;
+        run += tot;
     }
-    int tot;
-    (void)block_exclusive_scan<BLOCK>(in, &tot);
-    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
+    if (threadIdx.x == 0) {
+        Counters *c = sw.totals[a];
+        *(d == 0 ? &c->m0 : d == 1 ? &c->m1 : d == 2 ? &c->m2 : &c->m3) = run;
+    }
 }
 
-// One alpha, output of dimension K - 1: the kept rows in output order, each
-// at its block's offset (toff: exclusive scan of the block totals) plus its
-// place among the block's kept rows.
-template <int K>
-__global__ void __launch_bounds__(BLOCK) k_sweep_write(const unsigned char *__restrict__ in_s,
-                                                        const int *__restrict__ toff, const int *__restrict__ rows_s,
-                                                        const double *__restrict__ sz_s, int m, int *__restrict__ out,
-                                                        double *__restrict__ out_size) {
-    const int p = blockIdx.x * BLOCK + threadIdx.x;
-    const bool in = p < m && in_s[p];
+// The kept rows of dimension D in output order: block b's first place (scanned
+// tsum) plus the place among the block's kept rows.
+template <int D>
+__device__ __forceinline__ void sweep_write(const Sweep &sw, int b) {
+    const int p = b * BLOCK + threadIdx.x, a = blockIdx.y;
+    double size;
+    const bool in = p < sw.m[D] && sweep_kept<D>(sw, a, p, size);
     int tot;
     const int local = block_exclusive_scan<BLOCK>(in, &tot);
     if (!in) return;
-    const int o = toff[blockIdx.x] + local;
+    const long long o = sw.tsum[D][(long long)a * sw.nb[D] + b] + local;
+    int *const out = sw.out[a][D];
+    if constexpr (D == 0) out[o] = p;
+    else if constexpr (D == 1) reinterpret_cast<int2 *>(out)[o] = reinterpret_cast<const int2 *>(sw.rows[D])[p];
+    else if constexpr (D == 3) reinterpret_cast<int4 *>(out)[o] = reinterpret_cast<const int4 *>(sw.rows[D])[p];
+    else
 #pragma unroll
-    for (int u = 0; u < K; u++) out[(long long)o * K + u] = rows_s[(long long)p * K + u];
-    out_size[o] = sz_s[p] / 1.0e6;  // mA^2 -> A^2
+        for (int u = 0; u < 3; u++) out[3 * o + u] = sw.rows[D][3LL * p + u];
+    sw.out_size[a][D][o] = size / 1.0e6;  // mA^2 -> A^2
+}
+__global__ void __launch_bounds__(BLOCK) k_sweep_write(Sweep sw) {
+    int b = blockIdx.x;
+    if (b < sw.nb[3]) return sweep_write<3>(sw, b);
+    b -= sw.nb[3];
+    if (b < sw.nb[2]) return sweep_write<2>(sw, b);
+    b -= sw.nb[2];
+    if (b < sw.nb[1]) return sweep_write<1>(sw, b);
+    sweep_write<0>(sw, b - sw.nb[1]);
 }
 
 }  // namespace acx
