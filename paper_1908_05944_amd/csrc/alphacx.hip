@@ -458,7 +458,7 @@ static void radix_sort(unsigned *&key, P *&pay, int n, int lo, int hi, hipStream
         int *totals = sc.get<int>(RS_BINS);
         for (int shift = lo; shift < hi; shift += RS_BITS) {
             k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, shift, hist, tiles);
-            k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
+            if (tiles > RS_FEW) k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
             k_rs_scatter<P><<<tiles, RS_BLOCK, 0, s>>>(kin, pin, kout, pout, n, shift, hist, totals, tiles);
             LAUNCH_CHECK();
             std::swap(kin, kout);
@@ -760,9 +760,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         if (n_mol == 1) {
             const int n_tiles = (n + QTILE - 1) / QTILE;
             Stats *part = sc.get<Stats>(n_tiles);
-            k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, cnt);
             const unsigned seq = mb ? ++mb->seq : 0;
-            k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, mail, seq);
+            const bool one = n_tiles == 1;
+            k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, one ? st : part, cnt, one ? mail : nullptr, seq);
+            if (!one) k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, mail, seq);
             LAUNCH_CHECK();
             if (mb) hs[0] = mail_wait(*mb, seq, s).st;
             else if (!fixed) read_back(hs.data(), st, 1, s);
@@ -779,7 +780,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 HIP_TRY(hipMemcpyAsync(const_cast<int *>(d_tile_first), tile_first.data(), (n_mol + 1) * sizeof(int),
                                        hipMemcpyHostToDevice, s));
             }
-            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, n, q, part, cnt);
+            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, n, q, part, cnt, nullptr, 0);
             LAUNCH_CHECK();
             k_stats_reduce<<<(unsigned)n_mol, BLOCK, 0, s>>>(part, d_tile_first, 0, st, nullptr, 0);
             LAUNCH_CHECK();
@@ -894,7 +895,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                     k_cell_hist<<<tiles, RS_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, kin, sh, hist, tiles);
                 else
                     k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, n, sh, hist, tiles);
-                k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
+                if (tiles > RS_FEW) k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
                 if (first)
                     k_rs_scatter<unsigned, true><<<tiles, RS_BLOCK, 0, s>>>(kin, nullptr, kout, pout, n, sh, hist, totals, tiles);
                 else
@@ -903,8 +904,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 std::swap(kin, kout);
                 std::swap(pin, pout);
             }
-            key_starts(kin, n, shift, nb, start, s);
-            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, start, shift, ncell, q, pout, cell_start, atom, sball,
+            if (n > KS_SEARCH) key_starts(kin, n, shift, nb, start, s);
+            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, n > KS_SEARCH ? start : nullptr, n, shift, ncell, q, pout, cell_start, atom, sball,
                                                    wball, (int)aq, perm, cnt);
             LAUNCH_CHECK();
         }
@@ -931,9 +932,13 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         int *nbtot = sc.get<int>(3 * (size_t)nbs);
         int *uoff = sc.get<int>(nbB), *poff = sc.get<int>(nbB);
         // balls of a group: enough groups to fill the GPU, else as many balls as
-        // a block's steps serve well (fewer waits per ball)
+        // a block's steps serve well (fewer waits per ball). Rows of the widest
+        // slot hold some ten times the triangles: smaller groups, more evenly
+        // spread (100,000 atoms with solvent-accessible radii: all kernels 2,304
+        // us with 16 balls a group, 2,354 with 32, 2,553 with 64; with van der
+        // Waals radii 188 with 32, 172 with 64, 182 with 128)
         int gshift = 4;
-        while (gshift < 8 && (n >> gshift) >= 2048) gshift++;
+        while (gshift < 8 && (n >> gshift) >= (slot == NB_SLOT_SAS ? 8192 : 2048)) gshift++;
         const int groups = ((n - 1) >> gshift) + 1;
         unsigned char *eng = sc.get<unsigned char>(n);
         int *pair_base = sc.get<int>((size_t)groups + 1);
@@ -1169,14 +1174,14 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned rec_seq = 0;
         auto scan_records = [&](int *out0, double *size0) {
             rec_seq = mb ? ++mb->seq : 0;
-            const bool one = rec_tiles == 1;
-            if (!one) {
-                k_rec_sums<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, stop);
+            const bool sums = rec_tiles > 1 && rec_tiles <= REC_BLOCK, scanned = rec_tiles > REC_BLOCK;
+            if (rec_tiles > 1) k_rec_sums<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, stop);
+            if (scanned)
                 k_rec_prefix<<<1, 1024, 0, s>>>(tile_sum, rec_tiles, cd.tri_cnt, tt.cand, groups, cnt, fixed, out_cap,
                                                STOP_CAPACITY, mail, rec_seq);
-            }
-            k_rec_apply<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, out0, size0, cd.tri_cnt, tt.cand, groups,
-                                                       cnt, fixed, out_cap, STOP_CAPACITY, one ? mail : nullptr, rec_seq);
+            k_rec_apply<<<rec_tiles, REC_BLOCK, 0, s>>>(rec, vert_min, n, tile_sum, sums, out0, size0, cd.tri_cnt, tt.cand,
+                                                       groups, cnt, fixed, out_cap, STOP_CAPACITY,
+                                                       scanned ? nullptr : mail, rec_seq);
             LAUNCH_CHECK();
         };
         // the counters as the scan of the records left them
@@ -1524,7 +1529,7 @@ static ac_status run_partitioned(const double *d_xyz, const double *d_r, int64_t
         const int n_tiles = (n + QTILE - 1) / QTILE;
         Stats *part = sc.get<Stats>(n_tiles);
         Stats *st = sc.get<Stats>(1);
-        k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, nullptr);
+        k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, nullptr, nullptr, 0);
         k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, nullptr, 0);
         LAUNCH_CHECK();
         const Stats h = read_one(st, s);
@@ -1948,7 +1953,7 @@ static void ensure_incidence(ac_complex *c, hipStream_t s) {
                     k_inc_hist<<<tiles, RS_BLOCK, 0, s>>>(sx, M, kin, sh, hist, tiles);
                 else
                     k_rs_hist<<<tiles, RS_BLOCK, 0, s>>>(kin, M, sh, hist, tiles);
-                k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
+                if (tiles > RS_FEW) k_rs_digit_prefix<<<RS_BINS, RS_PREFIX_BLOCK, 0, s>>>(hist, tiles, totals);
                 if (k == 0)
                     k_rs_scatter<unsigned, true><<<tiles, RS_BLOCK, 0, s>>>(kin, nullptr, kout, pout, M, sh, hist, totals, tiles);
                 else
@@ -1957,8 +1962,8 @@ static void ensure_incidence(ac_complex *c, hipStream_t s) {
                 std::swap(kin, kout);
                 std::swap(pin, pout);
             }
-            key_starts(kin, M, shift, nb, first, s);
-            k_inc_finish<<<nb, INC_BLOCK, 0, s>>>(kin, pin, first, shift, n, start, slot);
+            if (M > KS_SEARCH) key_starts(kin, M, shift, nb, first, s);
+            k_inc_finish<<<nb, INC_BLOCK, 0, s>>>(kin, pin, M > KS_SEARCH ? first : nullptr, M, shift, n, start, slot);
             LAUNCH_CHECK();
         } else {
             fill<int>(start, 0, n + 1, s);

@@ -289,7 +289,9 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
 // tile, k_rec_prefix scans the tiles in one block (and folds the groups'
 // candidate totals), k_rec_apply scans inside the tiles and writes the
 // vertices, whose rows are then known. Up to REC_TILE balls one block does
-// all of it (k_rec_apply with tile_off = nullptr).
+// all of it (k_rec_apply with tile_off = nullptr); up to REC_BLOCK tiles there
+// is no k_rec_prefix, each block of k_rec_apply adds up the tiles before its own
+// (a launch of 5.6 us at 100,000 balls, 11 at 3M).
 constexpr int REC_BLOCK = 1024;
 constexpr int REC_IPT = 4;  // records of a lane, a wave apart (coalesced 16-byte accesses)
 constexpr int REC_TILE = REC_BLOCK * REC_IPT;
@@ -415,8 +417,11 @@ __global__ void __launch_bounds__(1024) k_rec_prefix(int4 *__restrict__ tile_sum
     }
 }
 
+// tile_off: the tiles' scanned offsets, or (sums) their sums, which each block
+// then adds up itself.
 __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec, const long long *__restrict__ vert_min,
-                                                          int n, const int4 *__restrict__ tile_off, int *__restrict__ out,
+                                                          int n, const int4 *__restrict__ tile_off, int sums,
+                                                          int *__restrict__ out,
                                                           double *__restrict__ out_size,
                                                           const int *__restrict__ tri_cnt,
                                                           const int *__restrict__ tet_cand, int groups, Counters *cnt,
@@ -436,7 +441,15 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
     }
     int4 tot;
     int4 before = waves_before4<REC_BLOCK>(s, &tot);
-    if (tile_off) before = before + tile_off[blockIdx.x];
+    if (sums) {  // at most REC_BLOCK tiles
+        const int4 v = (int)threadIdx.x < (int)blockIdx.x ? tile_off[threadIdx.x] : make_int4(0, 0, 0, 0);
+        int4 off;
+        (void)waves_before4<REC_BLOCK>(last_lane4(wave_inclusive_scan4(v)), &off);
+        before = before + off;
+        tot = tot + off;  // of the last block: of all
+    } else if (tile_off) {
+        before = before + tile_off[blockIdx.x];
+    }
 #pragma unroll
     for (int k = 0; k < REC_IPT; k++) {
         const int u = u0 + k * WAVE;
@@ -450,7 +463,7 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
         }
         if (u == n - 1) rec[n] = at + c[k];
     }
-    if (!tile_off) {
+    if (blockIdx.x == gridDim.x - 1 && (sums || !tile_off)) {
         fold_candidates<REC_BLOCK>(tri_cnt, tet_cand, groups, cnt);
         if (threadIdx.x == 0) {
             rec_totals(tot, cnt, fixed, cap, why);

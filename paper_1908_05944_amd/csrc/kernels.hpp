@@ -75,16 +75,31 @@ constexpr int BLOCK = 256;
 // are enumerated, pruned and written by one block.
 constexpr int GROUP = BLOCK;
 
+// What a build tells the host while it runs: a block of pinned host memory that
+// a kernel writes and the host polls (a copy and a wait for the stream cost
+// about 15 us each time). seq: the number of the message, written last.
+struct Mail {
+    Counters c;
+    Stats st;
+    unsigned seq;
+};
+__device__ __forceinline__ void mail_post(Mail *mail, unsigned seq) {
+    __threadfence_system();
+    __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------------------
 // Quantise: x -> rint(1000 x) (round half to even), W = R^2. Block b handles
 // the balls [tiles[b].x, tiles[b].y) (at most QTILE, all of one molecule; of a
 // single molecule of n balls the b-th QTILE, tiles = nullptr) and writes their
-// bounding box and flags; k_stats_reduce folds each molecule's tiles. Block 0
-// also clears the counters of the build, whose first kernel this is. Every load of a thread is issued before the first conversion.
+// bounding box and flags; k_stats_reduce folds each molecule's tiles (of a
+// single tile there is nothing to fold: it is mailed from here). Block 0 also
+// clears the counters of the build, whose first kernel this is. Every load of a
+// thread is issued before the first conversion.
 constexpr int QTILE = 1024;  // balls per block
 __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ xyz, const double *__restrict__ r,
                                                      const int2 *__restrict__ tiles, int n, int4 *__restrict__ q,
-                                                     Stats *__restrict__ part, Counters *cnt) {
+                                                     Stats *__restrict__ part, Counters *cnt, Mail *mail, unsigned seq) {
     static_assert(sizeof(Counters) % sizeof(int) == 0 && sizeof(Counters) / sizeof(int) <= BLOCK, "cleared as ints");
     if (cnt && blockIdx.x == 0 && threadIdx.x < sizeof(Counters) / sizeof(int)) reinterpret_cast<int *>(cnt)[threadIdx.x] = 0;
     constexpr int PT = QTILE / BLOCK;
@@ -157,20 +172,11 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
             b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags;
         }
         part[blockIdx.x] = b;
+        if (mail) {
+            mail->st = b;
+            mail_post(mail, seq);
+        }
     }
-}
-
-// What a build tells the host while it runs: a block of pinned host memory that
-// a kernel writes and the host polls (a copy and a wait for the stream cost
-// about 15 us each time). seq: the number of the message, written last.
-struct Mail {
-    Counters c;
-    Stats st;
-    unsigned seq;
-};
-__device__ __forceinline__ void mail_post(Mail *mail, unsigned seq) {
-    __threadfence_system();
-    __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Block m folds the partials of molecule m's tiles [tile_first[m],
@@ -286,7 +292,7 @@ __global__ void __launch_bounds__(RS_BLOCK) k_cell_hist(const int4 *__restrict__
         atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
     }
     __syncthreads();
-    hist[(long long)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+    hist[rs_hist_at(threadIdx.x, blockIdx.x, tiles)] = h[threadIdx.x];
 }
 
 // One bucket per block: balls [s, e) of the bucket's cells [k0, k0 + cells).
@@ -313,11 +319,11 @@ __device__ __forceinline__ void bin_scan(int *cnt, int m) {
     __syncthreads();
 }
 
-// start: first ball of every bucket (nb + 1 entries). Inside a cell the balls
+// start: first ball of every bucket (nb + 1 entries), or nullptr (searched for). Inside a cell the balls
 // keep input order (the radix passes are stable; the LDS places of a cell are
 // ranked). gidx: n entries of scratch, for a bucket with more than BIN_ROWS balls.
 __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ idx,
-                                                           const int *__restrict__ start, int shift, long long ncell,
+                                                           const int *__restrict__ start, int n, int shift, long long ncell,
                                                            const int4 *__restrict__ q, unsigned *__restrict__ gidx,
                                                            int *__restrict__ cell_start, int4 *__restrict__ atom,
                                                            int2 *__restrict__ sball, float4 *__restrict__ wball, int aq,
@@ -326,7 +332,8 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
     __shared__ unsigned short sc[BIN_ROWS];    // cell of each ball, in load order
     __shared__ unsigned short so[BIN_ROWS];    // load positions by cell
     const int b = blockIdx.x, t = threadIdx.x;
-    const int s = start[b], rows = start[b + 1] - s;
+    const int s = start ? start[b] : key_start(key, n, shift, b);
+    const int rows = (start ? start[b + 1] : key_start(key, n, shift, b + 1)) - s;
     const long long k0 = (long long)b << shift;
     const int cells = (int)min((long long)1 << shift, ncell - k0);
     if (rows == 0) {

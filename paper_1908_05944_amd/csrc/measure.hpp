@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(RS_BLOCK) k_inc_hist(Simplices sx, int M, unsi
         atomicAdd(&h[(k >> shift) & (RS_BINS - 1)], 1);
     }
     __syncthreads();
-    hist[(long long)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+    hist[rs_hist_at(threadIdx.x, blockIdx.x, tiles)] = h[threadIdx.x];
 }
 
 // One bucket per block: its rows [start[b], start[b + 1]) of (key, slot), in
@@ -363,13 +363,14 @@ constexpr int INC_SHIFT = 9;
 constexpr int INC_KEYS = 1 << INC_SHIFT;
 constexpr int INC_BLOCK = 1024;
 __global__ void __launch_bounds__(INC_BLOCK) k_inc_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ pay,
-                                                     const int *__restrict__ start, int shift, int n,
+                                                     const int *__restrict__ start, int M, int shift, int n,
                                                      int *__restrict__ inc_start, int *__restrict__ inc_slot) {
     constexpr int NW = INC_BLOCK / WAVE;
     static_assert(INC_KEYS <= INC_BLOCK, "a ball per thread");
     __shared__ int cnt[NW][INC_KEYS];
     const int b = blockIdx.x, t = threadIdx.x, lane = lane_id(), w = t / WAVE;
-    const int s = start[b], rows = start[b + 1] - s;
+    const int s = start ? start[b] : key_start(key, M, shift, b);
+    const int rows = (start ? start[b + 1] : key_start(key, M, shift, b + 1)) - s;
     const int k0 = b << shift, keys = min(1 << shift, n - k0);
     for (int c = t; c < NW * INC_KEYS; c += INC_BLOCK) (&cnt[0][0])[c] = 0;
     __syncthreads();

@@ -24,6 +24,15 @@ constexpr int RS_IPT = 8;
 constexpr int RS_TILE = RS_BLOCK * RS_IPT;
 static_assert(RS_BINS == RS_BLOCK, "one histogram bin per thread");
 
+// Up to RS_FEW tiles each scatter block takes its digits' sums over the tiles
+// itself, from a histogram laid out by tile, hist[tile][digit]; past that
+// k_rs_digit_prefix does, over hist[digit][tile]. (At 100,000 keys, 49 tiles: the
+// prefix kernel and its launch 5.5 us, the sums XX.)
+constexpr int RS_FEW = 64;
+__device__ __forceinline__ long long rs_hist_at(int digit, int tile, int tiles) {
+    return tiles <= RS_FEW ? (long long)tile * RS_BINS + digit : (long long)digit * tiles + tile;
+}
+
 __global__ void __launch_bounds__(RS_BLOCK) k_rs_hist(const unsigned *__restrict__ keys, int n, int shift,
                                                        int *__restrict__ hist, int tiles) {
     __shared__ int h[RS_BINS];
@@ -36,7 +45,7 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_hist(const unsigned *__restrict
         if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & (RS_BINS - 1)], 1);
     }
     __syncthreads();
-    hist[(long long)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+    hist[rs_hist_at(threadIdx.x, blockIdx.x, tiles)] = h[threadIdx.x];
 }
 
 // Per digit d (one block each): exclusive prefix over the tiles of the
@@ -108,13 +117,24 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const unsigned *__restr
     {
         // output start of digit d for this tile: the totals of the digits
         // below d, plus digit d's count in the tiles before this one
-        const int t = totals[threadIdx.x];
+        int t = 0, before = 0;
+        if (tiles <= RS_FEW) {
+#pragma unroll 8
+            for (int k = 0; k < tiles; k++) {
+                const int h = prefix[(long long)k * RS_BINS + threadIdx.x];
+                t += h;
+                before += k < tb ? h : 0;
+            }
+        } else {
+            t = totals[threadIdx.x];
+            before = prefix[(long long)threadIdx.x * tiles + tb];
+        }
         const int incl = wave_inclusive_scan(t);
         if (lane == WAVE - 1) wsum[wave] = incl;
         __syncthreads();
         int below = incl - t;
         for (int w = 0; w < wave; w++) below += wsum[w];
-        gbase[threadIdx.x] = below + prefix[(long long)threadIdx.x * tiles + tb];
+        gbase[threadIdx.x] = below + before;
     }
 #pragma unroll
     for (int w = 0; w < NW; w++) wcnt[w][threadIdx.x] = 0;
@@ -223,6 +243,23 @@ __global__ void __launch_bounds__(KS_BLOCK) k_key_starts(const unsigned *__restr
         for (int c = prev + 1; c <= cur; c++) start[c] = (int)p;
         prev = cur;
     }
+}
+
+// First row of m sorted keys whose key >> shift is at least x (m where none
+// is), by a wave: 64 rows looked at per step. Where a block reads the start of
+// its range only once and the chain of three or four steps does not matter:
+// up to KS_SEARCH rows (100,000: the starts' kernel and its launch 4 us, the
+// search one more in the kernel that needs them).
+constexpr int KS_SEARCH = 1 << 18;
+__device__ __forceinline__ int key_start(const unsigned *__restrict__ key, int m, int shift, int x) {
+    int lo = 0, hi = m;
+    while (lo < hi) {
+        const int step = (hi - lo + WAVE - 1) / WAVE;
+        const long long p = lo + (long long)(lane_id() + 1) * step - 1;
+        lo += step * __popcll(__ballot(p < hi && (int)(key[p] >> shift) < x));
+        hi = min(lo + step - 1, hi);
+    }
+    return lo;
 }
 
 }  // namespace acx
