@@ -1086,28 +1086,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         // ball, of which 6 are kept; each triangle's apex balls rule out the rest
         const bool use_apex = pp.sgc > 2600;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
-        auto ac2 = [&](auto sl, int what) {
-            constexpr int SLOT = decltype(sl)::value;
-            const int parts = (int)((n - 1) >> cd.sshift) + 1;
-            if (use_apex)
-                k_ac2<SLOT, true><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, egab, edge_min, eng, tgab, tsize, apex, cnt, stop);
-            else
-                k_ac2<SLOT, false><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, egab, edge_min, eng, tgab, tsize, apex, cnt, stop);
-            LAUNCH_CHECK();
-        };
-        auto ac2_of = [&](int what) {
-            if (nbr_two_pass) ac2(std::integral_constant<int, 0>{}, what);
-            else with_slot([&](auto sl, auto) { ac2(sl, what); });
-        };
-        if (split) {
-            tm.mark(ST_EDGE_AC2);
-            ac2_of(AC2_EDGES);
-            tm.mark(ST_TRI_AC2);
-            ac2_of(AC2_TRIANGLES);
-        } else {
-            tm.mark(ST_TRI_GABRIEL);
-            ac2_of(AC2_EDGES | AC2_TRIANGLES);
-        }
         Tets tt{};
         // entries a ball: 2 to 3 times the candidates of dense parts at 0.05 atoms
         // per A^3, and some more for the spread of small groups
@@ -1157,8 +1135,38 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             tetrahedra();
             tet_ac2();
         };
-        if (split) tm.mark(ST_TRI_GABRIEL);
-        tetrahedra();
+        const Ac2Out ao{egab, edge_min, eng, tgab, tsize, apex};
+        const int parts = (int)((n - 1) >> cd.sshift) + 1;
+        auto ac2 = [&](auto sl, int what) {
+            constexpr int SLOT = decltype(sl)::value;
+            if (use_apex)
+                k_ac2<SLOT, true><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
+            else
+                k_ac2<SLOT, false><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
+            LAUNCH_CHECK();
+        };
+        auto ac2_of = [&](int what) {
+            if (nbr_two_pass) ac2(std::integral_constant<int, 0>{}, what);
+            else with_slot([&](auto sl, auto) { ac2(sl, what); });
+        };
+        if (split) {
+            tm.mark(ST_EDGE_AC2);
+            ac2_of(AC2_EDGES);
+            tm.mark(ST_TRI_AC2);
+            ac2_of(AC2_TRIANGLES);
+            tm.mark(ST_TRI_GABRIEL);
+            tetrahedra();
+        } else if (n <= TET_AC2_BALLS && !use_apex && !nbr_two_pass) {
+            tm.mark(ST_TRI_GABRIEL);
+            with_slot([&](auto sl, auto) {
+                k_tetrahedra_ac2<decltype(sl)::value><<<groups + parts, BLOCK, 0, s>>>(cd, pp, groups, tt, ao, cnt, stop);
+                LAUNCH_CHECK();
+            });
+        } else {
+            tm.mark(ST_TRI_GABRIEL);
+            ac2_of(AC2_EDGES | AC2_TRIANGLES);
+            tetrahedra();
+        }
         tm.mark(ST_TET_COUNT);  // in place: no scan, no fill
         tm.mark(ST_TET_FILL);
         tm.mark(ST_TETRA);

@@ -34,12 +34,12 @@ __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 // contiguous range of the grid keeps spatially neighbouring work (and the
 // data it shares) in one L2. A bijection on [0, gridDim.x).
 constexpr int NUM_XCD = 8;
-__device__ __forceinline__ int xcd_block() {
-    const int nb = gridDim.x, b = blockIdx.x;
+__device__ __forceinline__ int xcd_block(int b, int nb) {
     const int q = nb / NUM_XCD, r = nb % NUM_XCD;
     const int x = b % NUM_XCD, k = b / NUM_XCD;
     return x * q + min(x, r) + k;
 }
+__device__ __forceinline__ int xcd_block() { return xcd_block(blockIdx.x, gridDim.x); }
 
 // Inclusive prefix sum over the 64 lanes of a wave: data-parallel-primitive
 // moves inside the vector ALU (shifts by 1, 2, 4, 8 inside each row of 16

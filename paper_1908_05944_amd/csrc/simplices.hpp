@@ -539,15 +539,23 @@ __device__ __forceinline__ int4 tet_facets(const Cands &cd, int g, int t, int t2
 constexpr int AC2_BLOCK = 256;
 constexpr int AC2_ROWS = 1024;
 enum { AC2_EDGES = 1, AC2_TRIANGLES = 2 };
+// What the tests write: status of edges and triangles, least Size of a kept
+// coface of an edge that fails, balls that own one, Size and apex balls of the
+// triangles.
+struct Ac2Out {
+    unsigned char *egab;
+    long long *edge_min;
+    unsigned char *eng;
+    unsigned char *tgab;
+    double *tsize;
+    int2 *apex;
+};
+template <int SLOT>
+constexpr int ac2_rows() { return SLOT ? AC2_ROWS / (SLOT ? SLOT : 1) * (SLOT + 1) : 1; }
 template <int SLOT, bool APEX>
-__global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, int what, unsigned char *__restrict__ egab,
-                                                   long long *__restrict__ edge_min, unsigned char *__restrict__ eng,
-                                                   unsigned char *__restrict__ tgab, double *__restrict__ tsize,
-                                                   int2 *__restrict__ apex, Counters *cnt, const int *__restrict__ stop) {
-    if (stop && *stop) return;
+__device__ __forceinline__ void ac2_part(const Cands &cd, const PredParams &pp, int part, int what, const Ac2Out &o,
+                                         Counters *cnt, float4 *rows) {
     constexpr int STRIDE = SLOT + 1, PT = AC2_ROWS / AC2_BLOCK;
-    __shared__ float4 rows[SLOT ? AC2_ROWS / (SLOT ? SLOT : 1) * STRIDE : 1];
-    const int part = xcd_block();
     const int b0 = part << cd.sshift, b1 = min(b0 + (1 << cd.sshift), cd.n);
     const int g = b0 >> cd.gshift;
     const int lane = lane_id();
@@ -633,13 +641,13 @@ __global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, i
         if constexpr (SLOT != 0) return RowLds{rows + (i - b0) * STRIDE, __float_as_int(rows[(i - b0) * STRIDE + SLOT].x)};
         else return RowMem(cd, i);
     };
-    // an edge's verdict; one that fails starts edge_min[e] (the least Size of a
+    // an edge's verdict; one that fails starts o.edge_min[e] (the least Size of a
     // kept coface) and flags its owner in eng
     auto edge_is = [&](int e, int i, bool viol) {
-        egab[e] = (unsigned char)!viol;
+        o.egab[e] = (unsigned char)!viol;
         if (viol) {
-            edge_min[e] = ORDERED_POS_INF;
-            eng[i] = 1;
+            o.edge_min[e] = ORDERED_POS_INF;
+            o.eng[i] = 1;
         }
     };
     bool unsure = false;
@@ -651,16 +659,16 @@ __global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, i
                 double size;
                 int2 at;
                 const int res = tri_ac2<APEX>(pp, row_of(it.i), it.vi, it.vj, it.vk, size, at);
-                tsize[x] = size;
-                tgab[x] = res == AC2_UNSURE ? FACE_UNSURE : (unsigned char)(res == AC2_HOLDS);
+                o.tsize[x] = size;
+                o.tgab[x] = res == AC2_UNSURE ? FACE_UNSURE : (unsigned char)(res == AC2_HOLDS);
                 unsure |= res == AC2_UNSURE;
                 if (APEX) {  // j: none
                     const int *nb = cd.nbr + cd.nbr_start[it.i];
-                    apex[x] = make_int2(at.x < 0 ? it.j : nb[at.x], at.y < 0 ? it.j : nb[at.y]);
+                    o.apex[x] = make_int2(at.x < 0 ? it.j : nb[at.x], at.y < 0 ? it.j : nb[at.y]);
                 }
             } else {
                 const int res = edge_ac2(pp, row_of(it.i), it.vi, it.vj);
-                if (res == AC2_UNSURE) egab[x] = FACE_UNSURE;
+                if (res == AC2_UNSURE) o.egab[x] = FACE_UNSURE;
                 else edge_is(x, it.i, res == AC2_VIOLATED);
                 unsure |= res == AC2_UNSURE;
             }
@@ -678,11 +686,18 @@ __global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, i
         fetch_ends(w, un);
         if (un.x < 0) continue;
         if (w < tw) {
-            if (tgab[un.x] == FACE_UNSURE) tgab[un.x] = (unsigned char)!tri_violated(cd, pp, un.i, un.j, un.k, cnt);
+            if (o.tgab[un.x] == FACE_UNSURE) o.tgab[un.x] = (unsigned char)!tri_violated(cd, pp, un.i, un.j, un.k, cnt);
         } else {
-            if (egab[un.x] == FACE_UNSURE) edge_is(un.x, un.i, edge_violated(cd, pp, un.i, un.j));
+            if (o.egab[un.x] == FACE_UNSURE) edge_is(un.x, un.i, edge_violated(cd, pp, un.i, un.j));
         }
     }
+}
+template <int SLOT, bool APEX>
+__global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, int what, Ac2Out o, Counters *cnt,
+                                                       const int *__restrict__ stop) {
+    if (stop && *stop) return;
+    __shared__ float4 rows[ac2_rows<SLOT>()];
+    ac2_part<SLOT, APEX>(cd, pp, xcd_block(), what, o, cnt, rows);
 }
 
 // Tetrahedra of a build: group g's are at [base, base + num[g]) with base =
@@ -706,17 +721,30 @@ struct Tets {
 // coface, Sec. 4.3). The balls k of TRI_CH triangles (i, j, k) and their edges
 // (i, j) are held in LDS. APEX: only those that the triangle's two apex balls do
 // not violate are left to test (large radii: one in thirty).
-constexpr int TRI_PT = 3, TRI_CH = TRI_PT * BLOCK, TRI_AHEAD = 64;
+// Bound by waits (half of the time; barriers between the tests and the loads of
+// a candidate's other balls), so by the blocks in flight: with 512 triangles
+// at a time, 26 KB of LDS and five blocks a CU, 101 us at 3M atoms and alpha = 0
+// and 663 at 100,000 with solvent-accessible radii; with 768 triangles, 32 KB and
+// four blocks 116 and 779; with 256 113 and 710.
+constexpr int TRI_PT = 2, TRI_CH = TRI_PT * BLOCK, TRI_AHEAD = 64;
+struct TetLds {
+    int4 sk[TRI_CH + TRI_AHEAD];
+    int se[TRI_CH + TRI_AHEAD];
+    unsigned short own[PAIR_WIN], hit[PAIR_WIN], res[PAIR_WIN];
+    int soff[TRI_CH];
+    int wtot[2][NWAVE], cands[NWAVE];
+};
 template <bool APEX>
-__global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra(Cands cd, PredParams pp, const int2 *__restrict__ apex, Tets tt,
-                                                          Counters *cnt, const int *__restrict__ stop) {
-    if (stop && *stop) return;
-    __shared__ int4 sk[TRI_CH + TRI_AHEAD];
-    __shared__ int se[TRI_CH + TRI_AHEAD];
-    __shared__ unsigned short own[PAIR_WIN], hit[PAIR_WIN], res[PAIR_WIN];
-    __shared__ int soff[TRI_CH];
-    __shared__ int wtot[2][NWAVE], cands[NWAVE];
-    const int g = xcd_block();
+__device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredParams &pp, int g,
+                                                 const int2 *__restrict__ apex, const Tets &tt, Counters *cnt, TetLds &l) {
+    auto &sk = l.sk;
+    auto &se = l.se;
+    auto &own = l.own;
+    auto &hit = l.hit;
+    auto &res = l.res;
+    auto &soff = l.soff;
+    auto &wtot = l.wtot;
+    auto &cands = l.cands;
     const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
     const int w = wave_id(), lane = lane_id();
     const int4 *const atom = cd.atom;
@@ -767,7 +795,12 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra(Cands cd, PredParams pp
                 const int o = own[v], o2 = second(v);
                 const int e = se[o];
                 const int i = cd.edge_i[e], j = cd.up[e];
-                const Tet te = tet_setup(atom[i], atom[j], sk[o], far_ball(o2), pp);
+                // the apex balls are loaded along with the tetrahedron's
+                const int2 q = APEX && !pp.force_exact ? apex[c0 + o] : make_int2(0, 0);
+                const int l = APEX ? cd.up[cd.tri_f[c0 + o2]] : 0;
+                const int4 vi = atom[i], vj = atom[j];
+                const int4 q0 = APEX ? atom[q.x] : vi, q1 = APEX ? atom[q.y] : vi;
+                const Tet te = tet_setup(vi, vj, sk[o], far_ball(o2), pp);
                 if (te.D == 0) return false;
                 const TetFilter tf = tet_filter(te);
                 int sg = pp.force_exact ? 0 : tet_ac3_filter(te, pp);
@@ -779,10 +812,8 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra(Cands cd, PredParams pp
                 if (sg < 0) return false;
                 nc++;
                 if (APEX && !pp.force_exact) {
-                    const int2 q = apex[c0 + o];
-                    const int l = cd.up[cd.tri_f[c0 + o2]];
-                    if (q.x != j && q.x != l && tet_violation_filter(tf, atom[q.x]) < 0) return false;
-                    if (q.y != j && q.y != l && tet_violation_filter(tf, atom[q.y]) < 0) return false;
+                    if (q.x != j && q.x != l && tet_violation_filter(tf, q0) < 0) return false;
+                    if (q.y != j && q.y != l && tet_violation_filter(tf, q1) < 0) return false;
                 }
                 return true;
             });
@@ -816,6 +847,33 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra(Cands cd, PredParams pp
         tt.cand[g] = s;
     }
 }
+template <bool APEX>
+__global__ void __launch_bounds__(BLOCK, 5) k_tetrahedra(Cands cd, PredParams pp, const int2 *__restrict__ apex, Tets tt,
+                                                          Counters *cnt, const int *__restrict__ stop) {
+    if (stop && *stop) return;
+    __shared__ __align__(16) char lds[sizeof(TetLds)];
+    tetrahedra_group<APEX>(cd, pp, xcd_block(), apex, tt, cnt, *reinterpret_cast<TetLds *>(lds));
+}
+
+// Both in one launch, the groups' tetrahedra first: neither needs the other
+// where no apex balls are used, and up to TET_AC2_BALLS balls each leaves room
+// beside it (with the tetrahedra's registers and LDS, four blocks a CU). A build
+// of 260 atoms 134 us against 138, 1,003 137 against 142, 16,000 at alpha = 2 224
+// against 233; at 50,000 and 100,000 the same within 1 %.
+constexpr int TET_AC2_BALLS = 1 << 16;
+template <int SLOT>
+__global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra_ac2(Cands cd, PredParams pp, int groups, Tets tt, Ac2Out o,
+                                                              Counters *cnt, const int *__restrict__ stop) {
+    if (stop && *stop) return;
+    static_assert(AC2_BLOCK == BLOCK, "one launch");
+    constexpr size_t ROWS = ac2_rows<SLOT>() * sizeof(float4);
+    __shared__ __align__(16) char lds[sizeof(TetLds) > ROWS ? sizeof(TetLds) : ROWS];
+    if ((int)blockIdx.x < groups)
+        tetrahedra_group<false>(cd, pp, xcd_block(blockIdx.x, groups), nullptr, tt, cnt, *reinterpret_cast<TetLds *>(lds));
+    else
+        ac2_part<SLOT, false>(cd, pp, xcd_block(blockIdx.x - groups, gridDim.x - groups), AC2_EDGES | AC2_TRIANGLES, o,
+                              cnt, reinterpret_cast<float4 *>(lds));
+}
 
 // AC2 of a group's candidate tetrahedra (Step 2): kept iff no ball is strictly
 // closer in power to the ortho-centre. The kept ones move to the front of the
@@ -823,9 +881,11 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra(Cands cd, PredParams pp
 // facets (Step 3) unless SWEEP (the candidates of several alpha values, pruned
 // per alpha later: tt.face then holds the facets). Blocks of NT threads: one
 // wave where a group has some tens of candidates (four times as many groups in
-// flight: 139 against 191 us at 3M atoms and alpha = 0), else BLOCK.
+// flight: 139 against 191 us at 3M atoms and alpha = 0), else BLOCK, with half
+// the registers for twice the waves (212 against 257 us at 100,000 atoms with
+// solvent-accessible radii; the one-wave blocks fit all at once either way).
 template <bool SWEEP, int NT>
-__global__ void __launch_bounds__(NT, 4) k_tet_ac2(Cands cd, PredParams pp, const unsigned char *__restrict__ tgab,
+__global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, PredParams pp, const unsigned char *__restrict__ tgab,
                                                        long long *__restrict__ tri_min, Tets tt, Counters *cnt,
                                                        const int *__restrict__ stop) {
     if (stop && *stop) return;
