@@ -1,0 +1,116 @@
+"""GPU builds at the edges of tiles, groups and launch rules, against the oracle.
+
+Sizes sit on both sides of the lines between the kernels' variants: blocks of
+16 balls and groups, one quantise tile (1,024), the one-block binning (2,048),
+record tiles (4,096), lanes per ball (2^13, 2^18), the joint launch of
+tetrahedra and AC2 (2^16), radix tiles whose digit sums the scatter takes
+(2^17), searched bucket starts (2^18) and record tiles of one block (2^22).
+Simplices are equal, Sizes within the oracle comparison's tolerance.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from parity import assert_same_complex
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def acx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1908_05944_amd as m
+    return m
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to("cuda:0")
+
+
+def _check(acx, xyz, rad, alpha, label, **opt):
+    print(f"[case] {label} n={len(rad)} alpha={alpha} {opt}", flush=True)
+    c = acx.ac_alpha_complex_device(_dev(xyz), _dev(rad), alpha, options=opt or None)
+    assert_same_complex(c, oracle.alpha_complex(xyz, rad, alpha), label)
+    return c
+
+
+@pytest.mark.parametrize("n", [15, 17, 255, 257, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192])
+@pytest.mark.parametrize("alpha", [0.0, 2.0])
+def test_sizes(acx, n, alpha):
+    m = synth.molecule(n, n)
+    _check(acx, m.xyz, m.radii, alpha, "size")
+
+
+@pytest.mark.parametrize("n", [65536, 65537, 131072, 131073, 262145])
+def test_large_sizes(acx, n):
+    m = synth.molecule(n, 5)
+    _check(acx, m.xyz, m.radii, 0.0, "large size")
+
+
+@pytest.mark.parametrize("n", [300, 9001])
+@pytest.mark.parametrize("grow_mA,alpha", [(0, 1.0), (700, 0.0), (1400, 0.5), (1400, -6.0), (2400, 0.0)])
+def test_row_lengths(acx, n, grow_mA, alpha):
+    """Neighbour rows of every slot, of more than the widest (counted), and
+    radii of which some vanish at a negative alpha."""
+    m = synth.molecule(n, 31).with_sas(grow_mA) if grow_mA else synth.molecule(n, 31)
+    _check(acx, m.xyz, m.radii, alpha, f"grown by {grow_mA}")
+
+
+@pytest.mark.parametrize("cell", [1200, 10922, 10923, 16383, 16384, 60000])
+def test_cell_sides(acx, cell):
+    """Cells on both sides of where coordinate differences in the scanned cells
+    reach 2^15, in one box of cells and in few."""
+    m = synth.molecule(1500, 77)
+    far = np.vstack([m.xyz, m.xyz[:40] + np.array([0.0, 65.536, 0.0])])  # apart by a multiple of 2^16
+    rad = np.concatenate([m.radii, m.radii[:40]])
+    _check(acx, far, rad, 0.0, f"cell {cell}", cell_mA=cell)
+
+
+@pytest.mark.parametrize("side,radius,alpha", [(10, 1.5, 0.0), (10, 1.5, 2.0), (7, 2.9, 0.0)])
+def test_undecided_in_every_block(acx, side, radius, alpha):
+    """Lattices: the float32 test leaves simplices of every block undecided."""
+    p = np.stack(np.meshgrid(*[np.arange(side) * 2.0] * 3, indexing="ij"), -1).reshape(-1, 3)
+    p = p[np.random.RandomState(3).permutation(len(p))]
+    _check(acx, p, np.full(len(p), radius), alpha, "lattice")
+
+
+@pytest.mark.parametrize("count", [8, 9, 17])
+def test_sweep_chunks(acx, count):
+    """One chunk of alphas, one more, and two and one, unsorted: each complex is
+    that of its own build."""
+    m = synth.molecule(3000, 12)
+    alphas = [round(float(a), 3) for a in np.random.RandomState(count).uniform(-1.0, 2.0, count)]
+    print(f"[case] sweep of {count}", flush=True)
+    X, R = _dev(m.xyz), _dev(m.radii)
+    for a, c in zip(alphas, acx.ac_alpha_sweep_device(X, R, alphas)):
+        single = acx.ac_alpha_complex_device(X, R, a)
+        assert c.counts() == single.counts(), a
+        for d in range(4):
+            assert np.array_equal(c.simplices(d), single.simplices(d)), (a, d)
+            assert np.array_equal(c.sizes(d), single.sizes(d)), (a, d)
+
+
+@pytest.mark.parametrize("copies,grow_mA", [(43, 0), (14, 1400)])
+def test_copies_of_a_molecule(acx, copies, grow_mA):
+    """Batches of copies of a molecule whose size is no multiple of a wave, each
+    equal to the molecule's own complex: 4.3 million balls (more record tiles than
+    a block adds up), and 1.4 million with so many pairs of candidate edges that
+    the triangles are counted first."""
+    m = synth.molecule(100003, 9)
+    m = m.with_sas(grow_mA) if grow_mA else m
+    print(f"[case] batch of {copies} x {m.n}", flush=True)
+    X, R = _dev(m.xyz), _dev(m.radii)
+    off = np.arange(copies + 1, dtype=np.int64) * m.n
+    c = acx.ac_alpha_complex_batch(X.repeat(copies, 1), R.repeat(copies), off, 0.0)
+    single = acx.ac_alpha_complex_device(X, R, 0.0)
+    for d in range(4):
+        rows, s, z = c.molecule_rows(d), c.simplices(d), c.sizes(d)
+        assert np.array_equal(np.diff(rows), np.full(copies, single.count(d)))
+        want_s, want_z = single.simplices(d), single.sizes(d)
+        for k in (0, 1, copies // 2, copies - 2, copies - 1):
+            assert np.array_equal(s[rows[k]:rows[k + 1]] - off[k], want_s), (d, k)
+            assert np.array_equal(z[rows[k]:rows[k + 1]], want_z), (d, k)
