@@ -864,11 +864,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         int *cell_start = sc.get<int>(ncell + 1);
         int4 *atom = sc.get<int4>(n);
         int2 *sball = sc.get<int2>((size_t)n + SCAN_PAD);
-        float4 *wball = sc.get<float4>(n);
         int *perm = sc.get<int>(n);
         if (n <= SMALL_BALLS && ncell <= SMALL_CELLS) {
             k_bin_small<<<1, SMALL_BLOCK, 0, s>>>(q, n, d_grids, n_mol, g0, (int)ncell, cell_start, atom, sball,
-                                                 wball, (int)aq, perm, cnt);
+                                                 (int)aq, perm, cnt);
             LAUNCH_CHECK();
         } else {
             // bucket: at most BIN_CELLS cells, and a bucket of full cells (2.5
@@ -906,7 +905,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             }
             if (n > KS_SEARCH) key_starts(kin, n, shift, nb, start, s);
             k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, n > KS_SEARCH ? start : nullptr, n, shift, ncell, q, pout, cell_start, atom, sball,
-                                                   wball, (int)aq, perm, cnt);
+                                                   (int)aq, perm, cnt);
             LAUNCH_CHECK();
         }
 
@@ -1040,7 +1039,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         // ---- candidate triangles of every group ----
         Cands cd{};
         cd.atom = atom;
-        cd.wball = wball;
         cd.perm = perm;
         cd.nbr_start = nbr_start;
         cd.nbr_cnt = deg_n;

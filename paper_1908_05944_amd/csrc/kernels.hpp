@@ -251,11 +251,6 @@ __device__ __forceinline__ int2 scan_ball(const int4 &a, int aq) {
     return make_int2((a.x & 0xffff) | (int)((unsigned)a.y << 16), (a.z & 0xffff) | (scan_rho(a, aq) << 16));
 }
 
-// Float32 form for the AC2 walks.
-__device__ __forceinline__ float4 weight_ball(const int4 &a) {
-    return make_float4((float)a.x, (float)a.y, (float)a.z, (float)a.w);
-}
-
 // grids = nullptr: one molecule, whose grid is g0 (a kernel argument: no upload).
 __device__ __forceinline__ unsigned cell_key(const int4 &a, int i, const Grid &g) {
     return (unsigned)(g.base + (g.order == ORDER_STOP ? i - g.a0 : cell_of(g, a.x, a.y, a.z)));
@@ -326,8 +321,8 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
                                                            const int *__restrict__ start, int n, int shift, long long ncell,
                                                            const int4 *__restrict__ q, unsigned *__restrict__ gidx,
                                                            int *__restrict__ cell_start, int4 *__restrict__ atom,
-                                                           int2 *__restrict__ sball, float4 *__restrict__ wball, int aq,
-                                                           int *__restrict__ perm, Counters *cnt) {
+                                                           int2 *__restrict__ sball, int aq, int *__restrict__ perm,
+                                                           Counters *cnt) {
     __shared__ int cc[BIN_CELLS];              // balls per cell, then each cell's first ball, then its end
     __shared__ unsigned short sc[BIN_ROWS];    // cell of each ball, in load order
     __shared__ unsigned short so[BIN_ROWS];    // load positions by cell
@@ -367,7 +362,6 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
             const int4 a = q[id];
             atom[s + c0 + rank] = a;
             sball[s + c0 + rank] = scan_ball(a, aq);
-            wball[s + c0 + rank] = weight_ball(a);
             perm[s + c0 + rank] = (int)id;
             // equal centres share a cell: compare with the cell's earlier balls
             bool dup = false;
@@ -399,7 +393,6 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
         }
         atom[s + c0 + rank] = a;
         sball[s + c0 + rank] = scan_ball(a, aq);
-        wball[s + c0 + rank] = weight_ball(a);
         perm[s + c0 + rank] = (int)id;
         if (dup) cnt->dup = 1;
     }
@@ -414,8 +407,7 @@ constexpr int SMALL_CELLS = 12288;
 __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restrict__ q, int n, const Grid *__restrict__ grids,
                                                             int n_mol, Grid g0, int ncell, int *__restrict__ cell_start,
                                                             int4 *__restrict__ atom, int2 *__restrict__ sball,
-                                                            float4 *__restrict__ wball, int aq, int *__restrict__ perm,
-                                                            Counters *cnt) {
+                                                            int aq, int *__restrict__ perm, Counters *cnt) {
     __shared__ int cc[SMALL_CELLS];
     __shared__ unsigned short sc[SMALL_BALLS], so[SMALL_BALLS];
     const int t = threadIdx.x;
@@ -461,7 +453,6 @@ __global__ void __launch_bounds__(SMALL_BLOCK) k_bin_small(const int4 *__restric
         }
         atom[c0 + rank] = a;
         sball[c0 + rank] = scan_ball(a, aq);
-        wball[c0 + rank] = weight_ball(a);
         perm[c0 + rank] = i;
         if (dup) cnt->dup = 1;
     }

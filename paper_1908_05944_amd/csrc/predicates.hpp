@@ -409,12 +409,11 @@ __device__ __forceinline__ int tet_violation_exact(const Tet &t, int s0, int s1,
 // AC2 of a simplex in float32, for the walks along a neighbour row: most
 // neighbours are far from a tie.
 // Power of ball q at the simplex's ortho-centre, times a positive denominator:
-// P = den gamma - M.b with b = q - v0 and gamma = |b|^2 - W_q + W_0, from balls as
-// float4 {x, y, z, W}: the coordinates are exact (below 2^24), so b is. With
-// u = 2^-24, gamma is within 6 u gmax (two rounded weights, four sums), the
-// product with the rounded den within 8 u den gmax, M (of one ball pair: three
+// P = den gamma - M.b with b = q - v0 (exact, below 2^14) and gamma = |b|^2 - W_q +
+// W_0. With u = 2^-24, gamma is within 4 u gmax (the rounded difference of the
+// weights, three sums), the product with the rounded den within 6 u den gmax, M (of one ball pair: three
 // rounded factors) within 3 u of its value, and the three sums within
-// 3 u (den gmax + bmax |M|_1): in all less than 11 u (den gmax + bmax |M|_1); e
+// 3 u (den gmax + bmax |M|_1): in all less than 10 u (den gmax + bmax |M|_1); e
 // takes 16 u. |P| <= e: undecided. P of the simplex's own balls is 0, so these
 // are always undecided.
 struct Power32 {
@@ -427,9 +426,9 @@ __device__ __forceinline__ Power32 power32(double den, double Mx, double My, dou
                    (float)(16.0 / (1 << 24) * (den * pp.gmax + pp.bmax * M1) + eP)};
 }
 // {b, gamma} of ball q about ball v0.
-__device__ __forceinline__ float4 relative_ball(const float4 &v0, const float4 &q) {
-    const float bx = q.x - v0.x, by = q.y - v0.y, bz = q.z - v0.z;
-    return make_float4(bx, by, bz, fmaf(bx, bx, fmaf(by, by, fmaf(bz, bz, v0.w - q.w))));
+__device__ __forceinline__ float4 relative_ball(const int4 &v0, const int4 &q) {
+    const float bx = (float)(q.x - v0.x), by = (float)(q.y - v0.y), bz = (float)(q.z - v0.z);
+    return make_float4(bx, by, bz, fmaf(bx, bx, fmaf(by, by, fmaf(bz, bz, (float)(v0.w - q.w)))));
 }
 __device__ __forceinline__ float power_of(const Power32 &f, const float4 &r) {
     return fmaf(-f.mx, r.x, fmaf(-f.my, r.y, fmaf(-f.mz, r.z, f.den * r.w)));

@@ -42,7 +42,6 @@ constexpr int NWAVE = BLOCK / WAVE;
 // tri_cnt[g]).
 struct Cands {
     const int4 *atom;
-    const float4 *wball;  // the balls as float4 {x, y, z, W}
     const int *perm;
     const int *nbr_start, *nbr_cnt, *nbr;
     const int *up_start, *up, *up_id, *edge_i;
@@ -206,21 +205,21 @@ struct RowLds {
     }
 };
 struct RowMem {
-    const float4 *wball;
+    const int4 *atom;
     const int *row;
     int i, len;
-    float4 me;
+    int4 me;
     int nx[AC2_GROUP];  // the next group's indices, one 16-byte load while this group is tested
     __device__ __forceinline__ RowMem(const Cands &cd, int i_)
-        : wball(cd.wball), row(cd.nbr + cd.nbr_start[i_]), i(i_), len(cd.nbr_cnt[i_]) {}
+        : atom(cd.atom), row(cd.nbr + cd.nbr_start[i_]), i(i_), len(cd.nbr_cnt[i_]) {}
     __device__ __forceinline__ void begin() {
-        me = wball[i];
+        me = atom[i];
         __builtin_memcpy(nx, row, sizeof nx);  // in bounds: NBR_PAD
     }
     __device__ __forceinline__ void load(int k, float4 (&r)[AC2_GROUP]) {
-        float4 q[AC2_GROUP];
+        int4 q[AC2_GROUP];
 #pragma unroll
-        for (int u = 0; u < AC2_GROUP; u++) q[u] = wball[k + u < len ? nx[u] : i];
+        for (int u = 0; u < AC2_GROUP; u++) q[u] = atom[k + u < len ? nx[u] : i];
         __builtin_memcpy(nx, row + (k + AC2_GROUP < len ? k + AC2_GROUP : k), sizeof nx);  // the last group reloads itself
 #pragma unroll
         for (int u = 0; u < AC2_GROUP; u++) r[u] = relative_ball(me, q[u]);
@@ -530,10 +529,11 @@ __device__ __forceinline__ int4 tet_facets(const Cands &cd, int g, int t, int t2
 // registers; a simplex that it leaves undecided is marked and looked at again
 // at the end (inside the loop, the exact test's registers were spilled around
 // it by every wave: 390 us).
-// Both tests at 3M atoms and alpha = 0: 308 us as two kernels without LDS, 239
-// as this; 100,000 atoms with solvent-accessible radii 1,150 and 417. Rows of
-// 1,024 entries and 256 threads: 512 threads 285 and 405, 512 entries 261 and
-// 416, with 128 threads 250 and 442.
+// Both tests at 3M atoms and alpha = 0: 308 us as two kernels without LDS, 222
+// as this; 100,000 atoms with solvent-accessible radii 1,150 and 412. With rows
+// gathered from a float4 copy of the balls (16 bytes a ball more to write and
+// hold) 239 and 417, and of that 512 threads 285 and 405, 512 entries 261 and 416,
+// with 128 threads 250 and 442.
 // SLOT = 0: rows of any length (after a counted neighbour search), gathered per
 // simplex. `what`: bit 0 edges, bit 1 triangles.
 constexpr int AC2_BLOCK = 256;
@@ -628,7 +628,7 @@ __device__ __forceinline__ void ac2_part(const Cands &cd, const PredParams &pp, 
         for (int r = 0; r < PT; r++) {
             const int y = (int)threadIdx.x + r * AC2_BLOCK, b = y / SLOT, k = y % SLOT;
             if (b0 + b < b1 && k < len[r] + (-len[r] & (AC2_GROUP - 1)))
-                rows[b * STRIDE + k] = relative_ball(cd.wball[b0 + b], cd.wball[q[r] < 0 ? b0 + b : q[r]]);
+                rows[b * STRIDE + k] = relative_ball(cd.atom[b0 + b], cd.atom[q[r] < 0 ? b0 + b : q[r]]);
             if (k == 0) rows[b * STRIDE + SLOT].x = __int_as_float(len[r]);
         }
         fetch_balls(w, it);
