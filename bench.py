@@ -27,18 +27,16 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP64_VECTOR_PEAK_TFLOPS = 78.6  # MI355X FP64 vector
 
 KERNEL_OF_STAGE = {
-    "neighbours_count": "k_neighbours<0, 16, true>",
-    "neighbours_fill": "k_nbr_compact<16>",
-    "triangles_count": "k_triangles<0, true>",
-    "triangles_fill": "k_tri_compact",
-    "triangles_ac2_tetrahedra": "k_tet_candidates<0, true>",
-    "tetrahedra_fill": "k_tet_compact",
-    "tetrahedra_ac2": "k_tet_ac2",
+    "neighbours_count": "k_neighbours<16, 1, true>",
+    "neighbours_fill": "k_nbr_compact<16, 1, 256>",
+    "triangles_count": "k_triangles<false>",
+    "tetrahedra_ac2": "k_tet_ac2<false, 64>",
     "triangles_final": "k_tri_final",
     "edges_final": "k_edge_final",
-    "vertices_final": "k_vert_final",
+    "emit": "k_rows",
 }
 KERNEL_SOURCES = ["paper_1908_05944_amd/csrc/kernels.hpp", "paper_1908_05944_amd/csrc/predicates.hpp",
+                  "paper_1908_05944_amd/csrc/simplices.hpp",
                   "paper_1908_05944_amd/csrc/common.hpp", "paper_1908_05944_amd/csrc/radix.hpp",
                   "paper_1908_05944_amd/csrc/measure.hpp", "paper_1908_05944_amd/csrc/sweep.hpp",
                   "paper_1908_05944_amd/csrc/partition.hpp", "paper_1908_05944_amd/csrc/emit.hpp",
@@ -151,22 +149,18 @@ def algorithmic_work(n, C, E, F, Q, K, Nn, Pe):
     out = sum(K[d] * (4 * (d + 1) + 8) for d in range(4))
     B = 16 * n + 36 * n + 8 * C + 2 * (8 * E + 12 * F + 16 * Q) + out
     FL = 12 * Pe + 40 * F + 80 * Q + E * (30 + 12 * nbr) + F * (60 + 12 * nbr) + Q * (120 + 12 * nbr)
-    stage_bytes = {
+    stage_bytes = {  # the stages that are one kernel
         "neighbours_count": 16 * n + 8 * C + 8 * E,
         "neighbours_fill": 2 * 8 * E,
         "triangles_count": 16 * n + 8 * E + 12 * F,
-        "triangles_fill": 2 * 12 * F,
-        "triangles_ac2_tetrahedra": 16 * n + 12 * F + 16 * Q,
-        "tetrahedra_fill": 2 * 16 * Q,
         "tetrahedra_ac2": 16 * n + 16 * Q + 24 * K[3],
         "triangles_final": 12 * F + 20 * K[2],
         "edges_final": 8 * E + 16 * K[1],
-        "vertices_final": 16 * n + 12 * K[0],
+        "emit": 8 * E + 12 * F + 16 * K[3] + out - 12 * K[0],
     }
     stage_flops = {
         "neighbours_count": 12 * Pe + 12 * Nn,
-        "triangles_count": 40 * F + E * (30 + 12 * nbr),
-        "triangles_ac2_tetrahedra": 80 * Q + F * (60 + 12 * nbr),
+        "triangles_count": 40 * F,
         "tetrahedra_ac2": Q * (120 + 12 * nbr),
     }
     return B, FL, stage_bytes, stage_flops

@@ -98,11 +98,8 @@ template <int K> constexpr int ek_rows() { return K == 4 ? 512 : 2048; }
 // eight blocks per CU); the Size bits are read again from the bucket's
 // payload when the row is written, from cache, as the block has just read
 // them. Triangles and tetrahedra: the whole payload (20 bytes a row; a
-// triangle block, about 42 KB, leaves room for three per CU). The edge emit
-// ends the build, so it gains from the occupancy; the triangle emit runs on
-// the second stream beside the edge path, and slim triangle rows (six blocks
-// per CU) did not shorten the build (2.185 against 2.190 ms), so they keep
-// the payload and do not read it twice.
+// triangle block, about 42 KB, leaves room for three per CU): slim triangle
+// rows (six blocks per CU) read the payload twice and were no faster.
 template <int K> constexpr bool ek_slim() { return K == 2; }
 
 template <int K>
@@ -513,6 +510,11 @@ __global__ void __launch_bounds__(256) k_mol_rows(const int4 *__restrict__ base,
 // before the lane are counted in the wave's ballot, those of the run's first
 // ball before the run by a look back at their status (a block scan per round
 // would make every wave wait for the slowest of four scattered writes).
+// Bound by scattered requests to memory: balls are numbered in no spatial
+// order, so each ball's rows are segments of 15 to 45 bytes of their own (13M
+// write and 9M read requests at 3M atoms, 436 us, 50 requests a nanosecond); edges in a
+// launch apart from the rest, so that a launch's outputs fit the memory-side
+// cache, took 450 in all.
 // Kept candidates [first, x) of the ball that owns candidate x = c0 + lane
 // (first: the ball's first candidate), given the kept ballot of the run.
 __device__ __forceinline__ int rank_in_ball(unsigned long long kept, int lane, int first, int c0, int carry) {

@@ -610,8 +610,8 @@ __device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, const in
 // slab of BLOCK / LPB balls x SLOT entries, each ball's upper entries first;
 // k_nbr_compact puts the upper rows into place once the block totals are
 // scanned. Exact counts are kept unless a row outgrows its room; then
-// cnt->overflow is set, and the host counts with k_nbr_count and fills with
-// k_nbr_fill (same result).
+// cnt->overflow is set, and the host counts and fills with k_nbr_rows (same
+// result).
 // Slot sizes: 16 holds every row of the van der Waals workloads at alpha = 0
 // (largest degree 14); 32 serves grown radii up to about 2.6 A, 128 the
 // solvent-accessible ones up to 3.4 A (43 entries on average).

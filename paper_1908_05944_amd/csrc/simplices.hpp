@@ -399,7 +399,9 @@ __device__ __forceinline__ bool tet_ac2(const Cands &cd, const Tet &ts, const Pr
 // Candidate triangles (Sec. 4.3) of a group's edges. The balls of EDGE_CH
 // edges' other ends (and of the next EDGE_AHEAD, where a row goes on) are held
 // in LDS, so that the pair tests wait for no memory. COUNT: the groups' totals
-// only (the first pass of a counted build).
+// only (the first pass of a counted build). Bound by instruction issue (half of
+// the time) and the barriers between the tests: 195 us at 3M atoms and alpha = 0
+// with 512 edges at a time; with 256 208, with 1,024 240.
 constexpr int EDGE_PT = 2, EDGE_CH = EDGE_PT * BLOCK, EDGE_AHEAD = 64;
 template <bool COUNT>
 __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, long long *__restrict__ tri_min, Counters *cnt,
@@ -994,7 +996,8 @@ enum { VERT_OUT = 0, VERT_MAYBE = -1 };
 
 // Edges (Step 4): as triangles; a kept edge records itself on its ends that
 // fail AC2 (Step 5; vert_min by input id; cnt->vng: some ball does). A thread
-// per ball, over its few edges. Writes the balls' output records.
+// per ball, over its few edges. Writes the balls' output records: bound by that
+// scatter (a line each; 75 us at 3M balls).
 __global__ void __launch_bounds__(BLOCK) k_edge_final(Cands cd, PredParams pp, int shortcut,
                                                        unsigned char *__restrict__ egab,
                                                        const long long *__restrict__ edge_min,
