@@ -31,9 +31,9 @@ KERNEL_OF_STAGE = {
     "neighbours_fill": "k_nbr_compact<16, 1, 256>",
     "triangles_count": "k_triangles<false>",
     "tetrahedra_ac2": "k_tet_ac2<false, 64>",
-    "triangles_final": "k_tri_final",
+    "triangles_final": "k_tri_final<false>",
     "edges_final": "k_edge_final",
-    "emit": "k_rows",
+    "emit": "k_rows<false>",
 }
 KERNEL_SOURCES = ["paper_1908_05944_amd/csrc/kernels.hpp", "paper_1908_05944_amd/csrc/predicates.hpp",
                   "paper_1908_05944_amd/csrc/simplices.hpp",

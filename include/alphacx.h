@@ -128,7 +128,7 @@ ac_status ac_alpha_complex_device(const double *d_xyz, const double *d_radii, in
  * Errors as ac_alpha_complex_device, plus AC_E_CAPACITY when the build needs
  * more than the fixed scratch (n above AC_NOALLOC_SCRATCH_MIB MiB / 128 B is
  * refused before any device work; measured on synthetic molecules at alpha = 0:
- * 400,000 balls with van der Waals radii fit, and 20,000 but not 24,000 with
+ * 400,000 balls with van der Waals radii fit, and 18,000 but not 24,000 with
  * solvent-accessible radii, whose candidates per ball are about ten times as
  * many) or when an output buffer is
  * smaller than the result (nothing is written to the outputs then). The

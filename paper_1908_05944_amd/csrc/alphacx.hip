@@ -1211,8 +1211,14 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         if (n_alpha == 1) {
             int2 *ball_cnt = sc.get<int2>(n);
             dev_rows(res, 0, n);
+            int *tri_list = use_apex ? sc.get<int>(T1) : nullptr, *tri_kept = use_apex ? sc.get<int>(groups) : nullptr;
             auto prune = [&]() {
-                k_tri_final<<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, tri_min, egab, eng, edge_min, tt, ball_cnt, cnt, stop);
+                if (use_apex)
+                    k_tri_final<true><<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, tri_min, egab, eng, edge_min, tt, ball_cnt,
+                                                               tri_list, tri_kept, cnt, stop);
+                else
+                    k_tri_final<false><<<groups, BLOCK, 0, s>>>(cd, tgab, tsize, tri_min, egab, eng, edge_min, tt, ball_cnt,
+                                                                nullptr, nullptr, cnt, stop);
                 LAUNCH_CHECK();
                 tm.mark(ST_EDGE_FINAL);
                 k_edge_final<<<grid_for(n), BLOCK, 0, s>>>(cd, pp, o.vertex_shortcut, egab, edge_min, vgab, eng, vert_min,
@@ -1226,8 +1232,13 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 }
             };
             auto write_rows = [&]() {
-                k_rows<<<groups, BLOCK, 0, s>>>(cd, pp, rec, egab, edge_min, tgab, tsize, tri_min, tt, res->d_simp[1], res->d_size[1], res->d_simp[2],
-                                               res->d_size[2], res->d_simp[3], res->d_size[3], stop);
+                auto rows = [&](auto list) {
+                    k_rows<decltype(list)::value><<<groups, BLOCK, 0, s>>>(
+                        cd, pp, rec, egab, edge_min, tgab, tsize, tri_min, tt, ball_cnt, tri_list, tri_kept, res->d_simp[1],
+                        res->d_size[1], res->d_simp[2], res->d_size[2], res->d_simp[3], res->d_size[3], stop);
+                };
+                if (use_apex) rows(std::true_type{});
+                else rows(std::false_type{});
                 LAUNCH_CHECK();
             };
             tm.mark(ST_TRI_FINAL);

@@ -522,13 +522,17 @@ __device__ __forceinline__ int rank_in_ball(unsigned long long kept, int lane, i
     return first > c0 ? __popcll(before >> (first - c0)) : carry + __popcll(before);
 }
 
+// LIST: the kept triangles come from k_tri_final's list.
+template <bool LIST>
 __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const int4 *__restrict__ base,
                                                  const unsigned char *__restrict__ egab,
                                                  const long long *__restrict__ edge_min,
                                                  const unsigned char *__restrict__ tgab,
                                                  const double *__restrict__ tsize,
                                                  const long long *__restrict__ tri_min,
-                                                 Tets tt, int *__restrict__ out1, double *__restrict__ size1,
+                                                 Tets tt, const int2 *__restrict__ ball_cnt,
+                                                 const int *__restrict__ list, const int *__restrict__ list_cnt,
+                                                 int *__restrict__ out1, double *__restrict__ size1,
                                                  int *__restrict__ out2, double *__restrict__ size2,
                                                  int *__restrict__ out3, double *__restrict__ size3,
                                                  const int *__restrict__ stop) {
@@ -539,7 +543,12 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
     const int e0 = cd.up_start[b0], e1 = cd.up_start[b1];
     // the balls' input ids and first rows, gathered once (a ball's record lies
     // in a line of its own: read per row they would cost more than the rows)
-    __shared__ int ids[GROUP], row0[3][GROUP];
+    __shared__ int ids[GROUP], row0[3][GROUP], lfirst[LIST ? GROUP : 1];
+    if (LIST) {  // first list entry of each ball
+        int tot;
+        const int c = b0 + (int)threadIdx.x < b1 ? ball_cnt[b0 + threadIdx.x].x : 0;
+        lfirst[threadIdx.x] = block_exclusive_scan<BLOCK>(c, &tot);
+    }
     if (b0 + (int)threadIdx.x < b1) {
         const int u = cd.perm[b0 + threadIdx.x];
         const int4 r = base[u];
@@ -565,7 +574,26 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
         reinterpret_cast<int2 *>(out1)[p] = make_int2(u, cd.up_id[e]);
         size1[p] = sz / 1.0e6;  // mA^2 -> A^2
     }
-    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
+    // a kept triangle to its row
+    auto write = [&](int t, int e, int i, int st, int rank) {
+        const int u = ids[i - b0];
+        const long long p = row0[1][i - b0] + rank;
+        const double sz = st == FACE_GABRIEL ? tsize[t] : double_from_ordered(tri_min[t]);
+        out2[3 * p] = u;
+        out2[3 * p + 1] = cd.up_id[e];
+        out2[3 * p + 2] = cd.up_id[cd.tri_f[t]];
+        size2[p] = sz / 1.0e6;
+    };
+    const int t0 = cd.tri_base[g], t1 = t0 + (LIST ? 0 : cd.tri_cnt[g]);
+    if (LIST) {
+        const int m = list_cnt[g];
+        for (int x = threadIdx.x; x < m; x += BLOCK) {
+            const int t = list[t0 + x];
+            const int e = cd.tri_e[t];
+            const int i = cd.edge_i[e];
+            write(t, e, i, tgab[t], x - lfirst[i - b0]);
+        }
+    }
     for (int c0 = t0 + w * WAVE; c0 < t1; c0 += BLOCK) {
         const int t = c0 + lane;
         const int st = t < t1 ? tgab[t] : FACE_OUT;
@@ -587,14 +615,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
             carry += __popcll(__ballot(same && tgab[y] != FACE_OUT));
             if (x <= t0 || !__shfl((int)same, 0, WAVE)) break;
         }
-        if (st == FACE_OUT) continue;
-        const int u = ids[i - b0];
-        const long long p = row0[1][i - b0] + rank_in_ball(kept, lane, first, c0, carry);
-        const double sz = st == FACE_GABRIEL ? tsize[t] : double_from_ordered(tri_min[t]);
-        out2[3 * p] = u;
-        out2[3 * p + 1] = cd.up_id[e];
-        out2[3 * p + 2] = cd.up_id[cd.tri_f[t]];
-        size2[p] = sz / 1.0e6;
+        if (st != FACE_OUT) write(t, e, i, st, rank_in_ball(kept, lane, first, c0, carry));
     }
     const int qb = tt.base(g), qn = tt.kept[g];
     for (int x = threadIdx.x; x < qn; x += BLOCK) {
