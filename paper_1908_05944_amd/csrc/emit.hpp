@@ -423,7 +423,13 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
                                                           const int *__restrict__ tri_cnt,
                                                           const int *__restrict__ tet_cand, int groups, Counters *cnt,
                                                           int fixed, OutCap cap, int why, Mail *mail, unsigned seq) {
-    if (fixed && cnt->stop) return;
+    if (fixed) {
+        // read once for the block: the last block may set it (rec_totals) meanwhile
+        __shared__ int stopped;
+        if (threadIdx.x == 0) stopped = cnt->stop;
+        __syncthreads();
+        if (stopped) return;
+    }
     // a wave takes REC_IPT runs of WAVE consecutive records
     const int u0 = blockIdx.x * REC_TILE + (threadIdx.x / WAVE) * (WAVE * REC_IPT) + lane_id();
     int4 r[REC_IPT], c[REC_IPT], ex[REC_IPT], s = make_int4(0, 0, 0, 0);

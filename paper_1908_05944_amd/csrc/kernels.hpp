@@ -679,6 +679,7 @@ k_neighbours(const int4 *__restrict__ atom, const int2 *__restrict__ sball, cons
     }
     const bool lane_full = listed > FULL || cn > LSLOT;
     cn = min(cn, LSLOT);
+    if (cn < 32) mask &= (1u << cn) - 1u;
     // places in the slab: the ball's upper entries, then the others, each by lane
     const int cu = __popc(mask);
     int bn = cn, bu = cu, pu = 0, pl = 0;  // of the ball; before this lane: upper, others
