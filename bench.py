@@ -707,8 +707,8 @@ def main():
             acx.ac_alpha_complex(mol.xyz, mol.radii, args.alpha, options=opts).close()
             ts.append(time.perf_counter() - t0)
         h2h = {"ms": float(np.median(ts)) * 1e3, "atoms_per_s": n / float(np.median(ts)),
-               "note": "ac_alpha_complex from host arrays: inputs copied up, every result array copied back "
-                       "(pageable host memory), median of 3"}
+               "note": "ac_alpha_complex from host arrays: inputs copied up from pageable memory, every result "
+                       "array copied back into pinned memory, median of 3"}
         log(f"[bench] host-to-host: {h2h['ms']:.2f} ms per build")
 
     cpu = None
