@@ -36,7 +36,7 @@ KERNEL_OF_STAGE = {
     "emit": "k_rows<false>",
 }
 KERNEL_SOURCES = ["paper_1908_05944_amd/csrc/kernels.hpp", "paper_1908_05944_amd/csrc/predicates.hpp",
-                  "paper_1908_05944_amd/csrc/simplices.hpp",
+                  "paper_1908_05944_amd/csrc/simplices.hpp", "paper_1908_05944_amd/csrc/rules.hpp",
                   "paper_1908_05944_amd/csrc/common.hpp", "paper_1908_05944_amd/csrc/radix.hpp",
                   "paper_1908_05944_amd/csrc/measure.hpp", "paper_1908_05944_amd/csrc/sweep.hpp",
                   "paper_1908_05944_amd/csrc/partition.hpp", "paper_1908_05944_amd/csrc/emit.hpp",

@@ -916,10 +916,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned char *vgab = sc.get<unsigned char>(n);
         long long *vert_min = sc.get<long long>(n);
         const unsigned nbN = grid_for(n);
-        // slot per ball: wide for grown radii between 1.9 and 2.6 A (alpha > 0
-        // with van der Waals radii), where rows outgrow 16 entries, wider still
-        // up to 3.4 A (solvent-accessible radii); beyond, the counted fill
-        const int slot = pp.sgc <= 1900 ? NB_SLOT : pp.sgc <= 2600 ? NB_SLOT_WIDE : pp.sgc <= 3400 ? NB_SLOT_SAS : NB_SLOT;
+        const int slot = neighbour_slot(pp.sgc, n);
         // lanes per ball: the search of a few balls is a chain of dependent
         // loads; from 2^18 balls on one lane each fills the GPU. Rows of the
         // widest slot are always shared by four (a lane lists at most 32).

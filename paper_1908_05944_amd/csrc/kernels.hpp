@@ -12,6 +12,7 @@
 #include "common.hpp"
 #include "predicates.hpp"
 #include "radix.hpp"
+#include "rules.hpp"
 
 namespace acx {
 
@@ -612,12 +613,7 @@ __device__ __forceinline__ void scan_rows(const Grid &g, const int4 &a, const in
 // scanned. Exact counts are kept unless a row outgrows its room; then
 // cnt->overflow is set, and the host counts and fills with k_nbr_rows (same
 // result).
-// Slot sizes: 16 holds every row of the van der Waals workloads at alpha = 0
-// (largest degree 14); 32 serves grown radii up to about 2.6 A, 128 the
-// solvent-accessible ones up to 3.4 A (43 entries on average).
-constexpr int NB_SLOT = 16;
-constexpr int NB_SLOT_WIDE = 32;
-constexpr int NB_SLOT_SAS = 128;
+// Slot sizes: neighbour_slot.
 template <int SLOT, int LPB>
 constexpr int nb_waves() { return SLOT == NB_SLOT && LPB == 1 ? 8 : 4; }
 template <int SLOT, int LPB, bool SINGLE>

@@ -1,0 +1,27 @@
+// Sizes and kernel variants that the host chooses by arithmetic alone: plain
+// C++, so that every choice can be checked without a device.
+#pragma once
+
+namespace acx {
+
+constexpr long long INDEX_MAX = 0x7fffffffLL;  // the kernels' indices are int32
+
+// Slots of the one-pass neighbour search (entries a ball). 16 holds every row of
+// the van der Waals workloads at alpha = 0 (largest degree 14); 32 serves grown
+// radii up to about 2.6 A, 128 the solvent-accessible ones up to 3.4 A (43
+// entries on average). Larger grown radii have rows of every length: the least
+// slot, and the counted search where rows outgrow it.
+constexpr int NB_SLOT = 16;
+constexpr int NB_SLOT_WIDE = 32;
+constexpr int NB_SLOT_SAS = 128;
+
+// Slot for n balls of grown radii up to sgc (mA). A row starts at its ball's slot
+// at the latest, so a slot serves while n slots of it have int32 indices: 32
+// entries for every n below 2^26, 128 up to 2^24 - 1 balls. Past that the next
+// smaller one (the search counts and fills where rows outgrow it).
+inline int neighbour_slot(long long sgc, long long n) {
+    const int slot = sgc <= 1900 ? NB_SLOT : sgc <= 2600 ? NB_SLOT_WIDE : sgc <= 3400 ? NB_SLOT_SAS : NB_SLOT;
+    return slot == NB_SLOT_SAS && n * slot > INDEX_MAX ? NB_SLOT_WIDE : slot;
+}
+
+}  // namespace acx
