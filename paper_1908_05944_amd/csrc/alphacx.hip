@@ -1077,14 +1077,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         // Kept tetrahedra are those of the regular triangulation, about 6.8 a
         // ball at most where the radii are large, far fewer at alpha = 0 with
         // van der Waals radii; a group past its slab is counted and run again
-        // grown radii beyond the wide slots: some 170 candidate tetrahedra a
-        // ball, of which 6 are kept; each triangle's apex balls rule out the rest
-        const bool use_apex = pp.sgc > 2600;
+        const bool use_apex = pp.sgc > APEX_SGC;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
         Tets tt{};
-        // entries a ball: 2 to 3 times the candidates of dense parts at 0.05 atoms
-        // per A^3, and some more for the spread of small groups
-        tt.cap = ((pp.sgc <= 2000 ? 8 : pp.sgc <= 2350 || use_apex ? 16 : 48) << gshift) + (pp.sgc <= 2000 ? 64 : 320);
+        tt.cap = tet_slab(pp.sgc, gshift, groups);
         tt.num = sc.get<int>(groups);
         tt.kept = sc.get<int>(groups);
         tt.cand = sc.get<int>(groups);

@@ -24,4 +24,20 @@ inline int neighbour_slot(long long sgc, long long n) {
     return slot == NB_SLOT_SAS && n * slot > INDEX_MAX ? NB_SLOT_WIDE : slot;
 }
 
+// Grown radii (mA) beyond which a triangle's apex balls rule out most of its
+// candidate tetrahedra (some 170 a ball, of which 6 are kept).
+constexpr long long APEX_SGC = 2600;
+
+// Entries of a group's slab of candidate tetrahedra (2^gshift balls a group), for
+// grown radii up to sgc: a ball's share is 2 to 3 times the candidates of dense
+// parts at 0.05 atoms per A^3, with some more for the spread of small groups. A
+// group past its slab is counted and run again, so the slabs are as small as it
+// takes for all their entries to have int32 indices (12,608 entries a group of
+// 256 balls pass that at 43.6M balls).
+inline int tet_slab(long long sgc, int gshift, int groups) {
+    const int ball = sgc <= 2000 ? 8 : sgc <= 2350 || sgc > APEX_SGC ? 16 : 48;
+    const long long cap = ((long long)ball << gshift) + (sgc <= 2000 ? 64 : 320);
+    return (int)(cap * groups > INDEX_MAX ? INDEX_MAX / groups : cap);
+}
+
 }  // namespace acx

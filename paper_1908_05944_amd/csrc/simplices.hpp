@@ -703,7 +703,7 @@ __global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, i
 }
 
 // Tetrahedra of a build: group g's are at [base, base + num[g]) with base =
-// tet_base[g], or g * cap where tet_base is null. num: first the candidates
+// tet_base[g], or g * cap where tet_base is null (groups * cap < 2^31: tet_slab). num: first the candidates
 // left to test (k_tetrahedra; exact even where the slab is too small, which sets
 // Counters::overflow), and kept[g] of them, in order, once k_tet_ac2 has run.
 // A tetrahedron is (t, f): its triangle (i, j, k) and its edge (i, l).

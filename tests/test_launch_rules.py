@@ -16,6 +16,7 @@ WRAPPERS = """
 #include "rules.hpp"
 extern "C" {
 int neighbour_slot(long long sgc, long long n) { return acx::neighbour_slot(sgc, n); }
+int tet_slab(long long sgc, int gshift, int groups) { return acx::tet_slab(sgc, gshift, groups); }
 }
 """
 
@@ -45,3 +46,19 @@ def test_neighbour_rows_have_int32_indices(rules, n):
 def test_slots_where_they_fit(rules):
     for n in (1, 100000, (1 << 24) - 1):
         assert [rules.neighbour_slot(*_L(s, n)) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 128, 128, 16]
+
+
+@pytest.mark.parametrize("n", [1, 300, 1 << 18, 40000000, 43600000, 43700000, 1 << 25, 1 << 26])
+def test_tetrahedron_slabs_have_int32_indices(rules, n):
+    for gshift in range(9):
+        groups = ((n - 1) >> gshift) + 1
+        for sgc in RADII:
+            cap = rules.tet_slab(*_L(sgc), gshift, groups)
+            assert 1 <= cap and cap * groups <= INT_MAX, (gshift, sgc, cap)
+
+
+def test_slab_sizes_where_they_fit(rules):
+    want = {1900: 8, 2000: 8, 2001: 16, 2350: 16, 2351: 48, 2600: 48, 2601: 16, 5000: 16}
+    for sgc, ball in want.items():
+        for gshift, groups in ((4, 20), (8, 20000)):
+            assert rules.tet_slab(*_L(sgc), gshift, groups) == (ball << gshift) + (64 if sgc <= 2000 else 320)
