@@ -682,7 +682,7 @@ struct Fixed {
     std::vector<Grid> grids;       // per molecule: cell side, reach, order, balls
     std::vector<long long> cells;  // per molecule: grid cells
     PredParams pp{};
-    int wmax = 0, slot = 0;
+    int wmax = 0;
     long long E = 0, P = 0, T = 0, Q = 0;  // candidate edges, pairs, candidate triangles, kept tetrahedra
     bool two_pass = false;  // a stage needed a counted pass
     // given to a fixed run (device arrays uploaded before it)
@@ -916,12 +916,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned char *vgab = sc.get<unsigned char>(n);
         long long *vert_min = sc.get<long long>(n);
         const unsigned nbN = grid_for(n);
-        const int slot = neighbour_slot(pp.sgc, n);
+        const int slot = neighbour_slot(pp.sgc, n, fx != nullptr);
         // lanes per ball: the search of a few balls is a chain of dependent
         // loads; from 2^18 balls on one lane each fills the GPU. Rows of the
         // widest slot are always shared by four (a lane lists at most 32).
         const int lpb = slot == NB_SLOT_SAS ? 4 : n >= (1 << 18) ? 1 : n >= (1 << 13) ? 4 : 16;
-        if (fx && fx->learn) fx->slot = slot;
         const unsigned nbB = (unsigned)((n + BLOCK / lpb - 1) / (BLOCK / lpb));  // blocks of the search
         int *nslab = sc.get<int>((size_t)nbB * (BLOCK / lpb) * slot + NBR_PAD);
         const int nbs = (int)(nbB + 3) & ~3;
@@ -1000,8 +999,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         if (fx && fx->learn) {
             fx->E = E;
             fx->P = c0.P;
-            // (rows of the widest slot have no recorded build either)
-            fx->two_pass |= nbr_two_pass || counted || slot == NB_SLOT_SAS;
+            fx->two_pass |= nbr_two_pass || counted;
         }
         // neighbour rows: in the slabs after the one-pass search, else in CSR
         const size_t E1 = E > 0 ? E : 1;

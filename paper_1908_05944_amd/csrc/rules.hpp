@@ -18,9 +18,13 @@ constexpr int NB_SLOT_SAS = 128;
 // Slot for n balls of grown radii up to sgc (mA). A row starts at its ball's slot
 // at the latest, so a slot serves while n slots of it have int32 indices: 32
 // entries for every n below 2^26, 128 up to 2^24 - 1 balls. Past that the next
-// smaller one (the search counts and fills where rows outgrow it).
-inline int neighbour_slot(long long sgc, long long n) {
+// smaller one (the search counts and fills where rows outgrow it). A recorded
+// build has rows of at most 32 entries: of radii whose rows are usually far
+// longer it serves the sets with at most NB_SLOT (beads of 3 A some 4.7 A apart, or
+// a few ions among smaller atoms), and needs no slots of 512 bytes a ball for that.
+inline int neighbour_slot(long long sgc, long long n, bool recorded) {
     const int slot = sgc <= 1900 ? NB_SLOT : sgc <= 2600 ? NB_SLOT_WIDE : sgc <= 3400 ? NB_SLOT_SAS : NB_SLOT;
+    if (slot == NB_SLOT_SAS && recorded) return NB_SLOT;
     return slot == NB_SLOT_SAS && n * slot > INDEX_MAX ? NB_SLOT_WIDE : slot;
 }
 

@@ -114,3 +114,41 @@ def test_copies_of_a_molecule(acx, copies, grow_mA):
         for k in (0, 1, copies // 2, copies - 2, copies - 1):
             assert np.array_equal(s[rows[k]:rows[k + 1]] - off[k], want_s), (d, k)
             assert np.array_equal(z[rows[k]:rows[k + 1]], want_z), (d, k)
+
+
+def _same_as(got, want, what):
+    assert got.counts() == want.counts(), what
+    for d in range(4):
+        assert np.array_equal(got.simplices(d), want.simplices(d)), (what, d)
+        assert np.array_equal(got.sizes(d), want.sizes(d)), (what, d)
+
+
+def _replayed(acx, xyz, rad, alpha, label, headroom=1.25):
+    """A recorded build replayed on its own input: no stop, and the oracle's complex."""
+    print(f"[case] recorded {label} n={len(rad)} alpha={alpha}", flush=True)
+    X, R = _dev(xyz), _dev(rad)
+    plan = acx.Plan(X, R, np.array([0, len(rad)]), alpha, headroom=headroom)
+    for _ in range(2):
+        plan.launch()
+        got = plan.result()
+        assert plan.stopped() == 0 and plan.ordinary_builds() == 0
+        assert_same_complex(got, oracle.alpha_complex(xyz, rad, alpha), label)
+        got.close()
+    plan.close()
+
+
+@pytest.mark.parametrize("n", [300, 9001])
+@pytest.mark.parametrize("kind,spacing,radius", [("beads", 4.7, 3.0), ("beads", 8.0, 3.0), ("beads", 6.1, 3.8), ("ion", 0, 2.75)])
+def test_recorded_builds_of_large_radii(acx, n, kind, spacing, radius):
+    """Radii whose rows usually outgrow the slots, in sets whose rows do not:
+    coarse beads, far apart ones, and one ion among atoms."""
+    if kind == "ion":
+        m = synth.molecule(n, 21)
+        xyz, rad = m.xyz, m.radii.copy()
+        rad[n // 3] = radius
+    else:
+        rng = np.random.RandomState(n)
+        side = int(np.ceil(n ** (1.0 / 3.0)))
+        xyz = np.stack(np.meshgrid(*[np.arange(side) * spacing] * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
+        xyz, rad = xyz + rng.uniform(-0.3, 0.3, xyz.shape), np.full(n, radius)
+    _replayed(acx, xyz, rad, 0.0, kind)

@@ -15,7 +15,7 @@ RADII = [1, 1700, 1900, 1901, 2000, 2001, 2350, 2351, 2600, 2601, 3200, 3400, 34
 WRAPPERS = """
 #include "rules.hpp"
 extern "C" {
-int neighbour_slot(long long sgc, long long n) { return acx::neighbour_slot(sgc, n); }
+int neighbour_slot(long long sgc, long long n, int recorded) { return acx::neighbour_slot(sgc, n, recorded != 0); }
 int tet_slab(long long sgc, int gshift, int groups) { return acx::tet_slab(sgc, gshift, groups); }
 }
 """
@@ -38,14 +38,16 @@ def _L(*a):
 @pytest.mark.parametrize("n", [1, 300, 1 << 18, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, (1 << 25) + 77, N_MAX])
 def test_neighbour_rows_have_int32_indices(rules, n):
     for sgc in RADII:
-        slot = rules.neighbour_slot(*_L(sgc, n))
-        assert slot in (16, 32, 128)
-        assert n * slot <= INT_MAX, (sgc, slot)  # the end of the last ball's row
+        for recorded in (0, 1):
+            slot = rules.neighbour_slot(*_L(sgc, n), recorded)
+            assert slot in (16, 32, 128)
+            assert n * slot <= INT_MAX, (sgc, slot)  # the end of the last ball's row
 
 
 def test_slots_where_they_fit(rules):
     for n in (1, 100000, (1 << 24) - 1):
-        assert [rules.neighbour_slot(*_L(s, n)) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 128, 128, 16]
+        assert [rules.neighbour_slot(*_L(s, n), 0) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 128, 128, 16]
+        assert [rules.neighbour_slot(*_L(s, n), 1) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 16, 16, 16]
 
 
 @pytest.mark.parametrize("n", [1, 300, 1 << 18, 40000000, 43600000, 43700000, 1 << 25, 1 << 26])
