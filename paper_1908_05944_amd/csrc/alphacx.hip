@@ -684,6 +684,8 @@ struct Fixed {
     PredParams pp{};
     int wmax = 0;
     long long E = 0, P = 0, T = 0, Q = 0;  // candidate edges, pairs, candidate triangles, kept tetrahedra
+    long long tet_most = 0;  // candidate tetrahedra of the fullest group where one outgrew its slab, else 0
+    long long tet_limit = 0;  // most entries of a slab
     bool two_pass = false;  // a stage needed a counted pass
     // given to a fixed run (device arrays uploaded before it)
     long long ncell = 0;  // cells of all molecules' capacities
@@ -1078,7 +1080,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const bool use_apex = pp.sgc > APEX_SGC;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
         Tets tt{};
-        tt.cap = tet_slab(pp.sgc, gshift, groups);
+        tt.cap = tet_slab(pp.sgc, gshift, groups, fixed ? fx->tet_most : 0);
         tt.num = sc.get<int>(groups);
         tt.kept = sc.get<int>(groups);
         tt.cand = sc.get<int>(groups);
@@ -1120,7 +1122,12 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             tt.tet_base = base;
             tet_room((size_t)q);
             fill<int>(&cnt->overflow, 0, 1, s);
-            if (fx && fx->learn) fx->two_pass = true;
+            if (fx && fx->learn) {
+                std::vector<int> num(groups);
+                read_back(num.data(), tt.num, (size_t)groups, s);
+                fx->tet_most = *std::max_element(num.begin(), num.end());
+                fx->tet_limit = INDEX_MAX / groups;
+            }
             tetrahedra();
             tet_ac2();
         };
@@ -2170,6 +2177,8 @@ static ac_status plan_create(const double *d_xyz, const double *d_r, const Batch
         fx.P_cap = grow(fx.P);
         fx.T_cap = grow(fx.T);
         fx.Q_cap = grow(fx.Q);
+        if (fx.tet_most > 0) fx.tet_most = grow(fx.tet_most);
+        if (fx.tet_most > fx.tet_limit) throw HipError{AC_E_CAPACITY, "planned tetrahedron slabs beyond 2^31"};
         std::vector<long long> cap(n_mol);
         std::vector<Grid> tmpl = fx.grids;
         long long base = 0;

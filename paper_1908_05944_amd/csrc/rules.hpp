@@ -37,10 +37,12 @@ constexpr long long APEX_SGC = 2600;
 // parts at 0.05 atoms per A^3, with some more for the spread of small groups. A
 // group past its slab is counted and run again, so the slabs are as small as it
 // takes for all their entries to have int32 indices (12,608 entries a group of
-// 256 balls pass that at 43.6M balls).
-inline int tet_slab(long long sgc, int gshift, int groups) {
+// 256 balls pass that at 43.6M balls). most: what the fullest group is known to
+// need (a recorded build of an input that outgrew its slabs), else 0.
+inline int tet_slab(long long sgc, int gshift, int groups, long long most) {
     const int ball = sgc <= 2000 ? 8 : sgc <= 2350 || sgc > APEX_SGC ? 16 : 48;
-    const long long cap = ((long long)ball << gshift) + (sgc <= 2000 ? 64 : 320);
+    long long cap = ((long long)ball << gshift) + (sgc <= 2000 ? 64 : 320);
+    cap = cap > most ? cap : most;
     return (int)(cap * groups > INDEX_MAX ? INDEX_MAX / groups : cap);
 }
 

@@ -152,3 +152,15 @@ def test_recorded_builds_of_large_radii(acx, n, kind, spacing, radius):
         xyz = np.stack(np.meshgrid(*[np.arange(side) * spacing] * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
         xyz, rad = xyz + rng.uniform(-0.3, 0.3, xyz.shape), np.full(n, radius)
     _replayed(acx, xyz, rad, 0.0, kind)
+
+
+@pytest.mark.parametrize("a,radius", [(3.8, 1.95), (3.9, 1.98), (4.2, 2.2)])
+@pytest.mark.parametrize("headroom", [1.0, 2.0])
+def test_recorded_lattices(acx, a, radius, headroom):
+    """Close packings, about 14 candidate tetrahedra a ball: the groups' slabs of a
+    recorded build hold what the recorded input needs."""
+    g = np.stack(np.meshgrid(*[np.arange(10)] * 3, indexing="ij"), -1).reshape(-1, 1, 3).astype(float)
+    p = (g + np.array([[0, 0, 0], [0, .5, .5], [.5, 0, .5], [.5, .5, 0]])).reshape(-1, 3) * a
+    rng = np.random.RandomState(7)
+    p = rng.permutation(p + rng.uniform(-0.02, 0.02, p.shape))
+    _replayed(acx, p, np.full(len(p), radius), 0.0, f"lattice {a}", headroom)

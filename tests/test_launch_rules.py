@@ -16,7 +16,7 @@ WRAPPERS = """
 #include "rules.hpp"
 extern "C" {
 int neighbour_slot(long long sgc, long long n, int recorded) { return acx::neighbour_slot(sgc, n, recorded != 0); }
-int tet_slab(long long sgc, int gshift, int groups) { return acx::tet_slab(sgc, gshift, groups); }
+int tet_slab(long long sgc, int gshift, int groups, long long most) { return acx::tet_slab(sgc, gshift, groups, most); }
 }
 """
 
@@ -55,12 +55,15 @@ def test_tetrahedron_slabs_have_int32_indices(rules, n):
     for gshift in range(9):
         groups = ((n - 1) >> gshift) + 1
         for sgc in RADII:
-            cap = rules.tet_slab(*_L(sgc), gshift, groups)
-            assert 1 <= cap and cap * groups <= INT_MAX, (gshift, sgc, cap)
+            for most in (0, 1000000):
+                cap = rules.tet_slab(*_L(sgc), gshift, groups, *_L(most))
+                assert 1 <= cap and cap * groups <= INT_MAX, (gshift, sgc, cap)
 
 
 def test_slab_sizes_where_they_fit(rules):
     want = {1900: 8, 2000: 8, 2001: 16, 2350: 16, 2351: 48, 2600: 48, 2601: 16, 5000: 16}
     for sgc, ball in want.items():
         for gshift, groups in ((4, 20), (8, 20000)):
-            assert rules.tet_slab(*_L(sgc), gshift, groups) == (ball << gshift) + (64 if sgc <= 2000 else 320)
+            cap = (ball << gshift) + (64 if sgc <= 2000 else 320)
+            for most in (0, cap, cap + 1):
+                assert rules.tet_slab(*_L(sgc), gshift, groups, *_L(most)) == max(cap, most)
