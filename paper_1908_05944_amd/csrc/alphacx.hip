@@ -551,9 +551,6 @@ static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double
 // Bytes of the minima of the alphas that a sweep takes in one launch.
 constexpr size_t SWEEP_ROOM = 256u << 20;
 
-// Pairs of upper entries a build makes room for (25 bytes each); past it the
-// candidate triangles are counted first.
-constexpr long long PAIR_ROOM = 1LL << 28;
 // Bytes of output rows a build allocates for candidates that may not be kept
 // (see run_pipeline).
 constexpr long long OUT_ROOM = 64LL << 20;
@@ -689,7 +686,9 @@ struct Fixed {
     bool two_pass = false;  // a stage needed a counted pass
     // given to a fixed run (device arrays uploaded before it)
     long long ncell = 0;  // cells of all molecules' capacities
-    int E_cap = 1, P_cap = 1, T_cap = 1, Q_cap = 1;
+    int E_cap = 1, T_cap = 1, Q_cap = 1;
+    bool counted = false;  // the triangles are counted first (room for T_cap), else there is room for P_cap pairs
+    long long P_cap = 1;
     const int2 *d_tiles = nullptr;
     const int *d_tile_first = nullptr;
     const Grid *d_tmpl = nullptr;       // recorded grids with each molecule's first cell
@@ -972,7 +971,6 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             k_plan_guard<<<1, WAVE, 0, s>>>(cnt, fx->E_cap, fx->P_cap);
             LAUNCH_CHECK();
             c0.E = fx->E_cap;
-            c0.P = fx->P_cap;
         } else {
             c0 = mb ? mail_wait(*mb, nbr_seq, s).c : read_one(cnt, s);
         }
@@ -995,13 +993,13 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         check_total(c0.Nn, "neighbour entries");
         check_total(c0.E, "candidate edges");
         // room for every pair, or (too many pairs) the counted triangles
-        const bool counted = c0.P > PAIR_ROOM;
+        const bool counted = fixed ? fx->counted : counts_triangles(c0.P);
         const int E = (int)c0.E;
         const long long Nn = c0.Nn;
         if (fx && fx->learn) {
             fx->E = E;
             fx->P = c0.P;
-            fx->two_pass |= nbr_two_pass || counted;
+            fx->two_pass |= nbr_two_pass;
         }
         // neighbour rows: in the slabs after the one-pass search, else in CSR
         const size_t E1 = E > 0 ? E : 1;
@@ -1053,11 +1051,18 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         while ((slot << cd.sshift) > AC2_ROWS) cd.sshift--;
         cd.tri_sub = sc.get<int>(((size_t)(n - 1) >> cd.sshift) + 1);
         tm.mark(ST_TRI_COUNT);
-        long long room = c0.P;
+        long long room = fixed ? fx->P_cap : c0.P;
         if (counted) {
             k_triangles<true><<<groups, BLOCK, 0, s>>>(cd, pp, nullptr, cnt, stop);
             LAUNCH_CHECK();
-            room = total_i64(cd.tri_cnt, groups, s, sc);
+            if (fixed) {
+                sum_i64(cd.tri_cnt, groups, &cnt->T, s, sc);
+                k_plan_guard_triangles<<<1, WAVE, 0, s>>>(cnt, fx->T_cap);
+                LAUNCH_CHECK();
+                room = fx->T_cap;
+            } else {
+                room = total_i64(cd.tri_cnt, groups, s, sc);
+            }
             check_total(room, "candidate triangles");
             scan_i32(cd.tri_cnt, pair_base, groups, s, sc);
         }
@@ -2174,7 +2179,9 @@ static ac_status plan_create(const double *d_xyz, const double *d_r, const Batch
             return (int)c;
         };
         fx.E_cap = grow(fx.E);
-        fx.P_cap = grow(fx.P);
+        const long long pairs = (long long)std::ceil((double)fx.P * headroom) + 256;
+        fx.counted = counts_triangles(pairs);
+        fx.P_cap = fx.counted ? LLONG_MAX : pairs;
         fx.T_cap = grow(fx.T);
         fx.Q_cap = grow(fx.Q);
         if (fx.tet_most > 0) fx.tet_most = grow(fx.tet_most);

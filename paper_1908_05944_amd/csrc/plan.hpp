@@ -61,16 +61,21 @@ __global__ void __launch_bounds__(BLOCK) k_plan_grids(const Stats *__restrict__ 
 }
 
 // After the neighbour search: stops the build if a row outgrew its slot, two
-// centres are equal, or the candidate edges or pairs exceed their capacity.
+// centres are equal, or the candidate edges or pairs exceed their capacity
+// (k_plan_guard_triangles: the counted triangles theirs).
 // Every later kernel of the build returns at once when the build has stopped
 // (k_rec_prefix / k_rec_apply stop it for the output totals).
-__global__ void k_plan_guard(Counters *cnt, int E_cap, int P_cap) {
+__global__ void k_plan_guard(Counters *cnt, int E_cap, long long P_cap) {
     if (threadIdx.x != 0) return;
     int why = cnt->stop;
     if (cnt->overflow) why |= STOP_SLOT;
     if (cnt->dup) why |= STOP_DUP;
     if (cnt->E > E_cap || cnt->P > P_cap) why |= STOP_CAPACITY;
     cnt->stop = why;
+}
+__global__ void k_plan_guard_triangles(Counters *cnt, int T_cap) {
+    // a stopped build counted no triangles
+    if (threadIdx.x == 0 && !cnt->stop && cnt->T > T_cap) cnt->stop = STOP_CAPACITY;
 }
 
 }  // namespace acx

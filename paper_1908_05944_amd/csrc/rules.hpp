@@ -46,4 +46,10 @@ inline int tet_slab(long long sgc, int gshift, int groups, long long most) {
     return (int)(cap * groups > INDEX_MAX ? INDEX_MAX / groups : cap);
 }
 
+// Pairs of upper entries a build makes room for (25 bytes each); past it the
+// candidate triangles are counted first. A recorded build decides once, on the
+// pairs that its headroom asks for.
+constexpr long long PAIR_ROOM = 1LL << 28;
+inline bool counts_triangles(long long pairs) { return pairs > PAIR_ROOM; }
+
 }  // namespace acx

@@ -123,6 +123,19 @@ def _same_as(got, want, what):
         assert np.array_equal(got.sizes(d), want.sizes(d)), (what, d)
 
 
+def _on_device(c, d):
+    """The d-simplices and Sizes of a device result as torch tensors."""
+    import torch
+
+    class View:
+        def __init__(self, p, shape, kind):
+            self.__cuda_array_interface__ = {"shape": shape, "typestr": kind, "data": (p, False), "version": 2}
+
+    s, z = c.device_pointers(d)
+    return (torch.as_tensor(View(s, (c.count(d), d + 1), "<i4"), device="cuda:0"),
+            torch.as_tensor(View(z, (c.count(d),), "<f8"), device="cuda:0"))
+
+
 def _replayed(acx, xyz, rad, alpha, label, headroom=1.25):
     """A recorded build replayed on its own input: no stop, and the oracle's complex."""
     print(f"[case] recorded {label} n={len(rad)} alpha={alpha}", flush=True)
@@ -164,3 +177,34 @@ def test_recorded_lattices(acx, a, radius, headroom):
     rng = np.random.RandomState(7)
     p = rng.permutation(p + rng.uniform(-0.02, 0.02, p.shape))
     _replayed(acx, p, np.full(len(p), radius), 0.0, f"lattice {a}", headroom)
+
+
+@pytest.mark.parametrize("copies,headroom", [(9, 16.0), (130, 1.0)])
+def test_recorded_builds_with_counted_triangles(acx, copies, headroom):
+    """Recorded batches of copies of a molecule at alpha = 2 whose pairs of candidate
+    edges are more than a build makes room for: by the headroom alone, and by
+    themselves. Every copy has the molecule's own complex."""
+    import torch
+    m = synth.molecule(100003, 9)
+    X, R = _dev(m.xyz).repeat(copies, 1), _dev(m.radii).repeat(copies)
+    off = np.arange(copies + 1, dtype=np.int64) * m.n
+    single = acx.ac_alpha_complex_device(X[:m.n].clone(), R[:m.n].clone(), 2.0)
+    up = single.simplices(1)[:, 0]  # least ids of the kept edges: the pairs are at least theirs
+    c = np.bincount(up).astype(np.int64)
+    assert (c * (c - 1) // 2).sum() * copies * headroom > 1 << 28
+    print(f"[case] recorded batch of {copies} x {m.n}, headroom {headroom}", flush=True)
+    plan = acx.Plan(X, R, off, 2.0, headroom=headroom)
+    for _ in range(2):
+        plan.launch()
+        got = plan.result()
+        assert plan.stopped() == 0 and plan.ordinary_builds() == 0
+        torch.cuda.synchronize()
+        for d in range(4):
+            rows = got.molecule_rows(d)
+            assert np.array_equal(np.diff(rows), np.full(copies, single.count(d))), d
+            s, z = _on_device(got, d)
+            for k in (0, copies // 2, copies - 1):
+                assert np.array_equal(s[rows[k]:rows[k + 1]].cpu().numpy() - off[k], single.simplices(d)), (d, k)
+                assert np.array_equal(z[rows[k]:rows[k + 1]].cpu().numpy(), single.sizes(d)), (d, k)
+        got.close()
+    plan.close()

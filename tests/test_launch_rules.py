@@ -17,6 +17,7 @@ WRAPPERS = """
 extern "C" {
 int neighbour_slot(long long sgc, long long n, int recorded) { return acx::neighbour_slot(sgc, n, recorded != 0); }
 int tet_slab(long long sgc, int gshift, int groups, long long most) { return acx::tet_slab(sgc, gshift, groups, most); }
+int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
 }
 """
 
@@ -67,3 +68,7 @@ def test_slab_sizes_where_they_fit(rules):
             cap = (ball << gshift) + (64 if sgc <= 2000 else 320)
             for most in (0, cap, cap + 1):
                 assert rules.tet_slab(*_L(sgc), gshift, groups, *_L(most)) == max(cap, most)
+
+
+def test_pairs_past_their_room_are_counted(rules):
+    assert not rules.counts_triangles(*_L(1 << 28)) and rules.counts_triangles(*_L((1 << 28) + 1))
