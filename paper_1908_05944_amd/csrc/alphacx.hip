@@ -1957,10 +1957,8 @@ static void ensure_incidence(ac_complex *c, hipStream_t s) {
         start = static_cast<int32_t *>(dev_alloc((size_t)(n + 1) * sizeof(int32_t)));
         Scope sc;
         if (M > 0) {
-            // buckets of at most INC_KEYS balls, as small as the radix passes reach
-            const int bits = bits_for(n);
-            const int passes = std::max(1, (bits - INC_SHIFT + RS_BITS - 1) / RS_BITS);
-            const int shift = std::max(0, bits - RS_BITS * passes);
+            const IncBuckets ib = inc_buckets(n);
+            const int passes = ib.passes, shift = ib.shift;
             const int nb = ((n - 1) >> shift) + 1;
             const int tiles = (M + RS_TILE - 1) / RS_TILE;
             unsigned *kin = sc.get<unsigned>(M), *kout = sc.get<unsigned>(M);

@@ -24,6 +24,7 @@
 #pragma once
 #include "common.hpp"
 #include "radix.hpp"
+#include "rules.hpp"
 
 namespace acx {
 
@@ -359,8 +360,6 @@ __global__ void __launch_bounds__(RS_BLOCK) k_inc_hist(Simplices sx, int M, unsi
 // At 100,000 balls (196 buckets of some 7,000 rows) 18 us, with 256 threads a
 // block 44; three full radix passes and a search for every ball's start, which
 // this replaces, took 150.
-constexpr int INC_SHIFT = 9;
-constexpr int INC_KEYS = 1 << INC_SHIFT;
 constexpr int INC_BLOCK = 1024;
 __global__ void __launch_bounds__(INC_BLOCK) k_inc_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ pay,
                                                      const int *__restrict__ start, int M, int shift, int n,
@@ -372,7 +371,7 @@ __global__ void __launch_bounds__(INC_BLOCK) k_inc_finish(const unsigned *__rest
     const int s = start ? start[b] : key_start(key, M, shift, b);
     const int rows = (start ? start[b + 1] : key_start(key, M, shift, b + 1)) - s;
     const int k0 = b << shift, keys = min(1 << shift, n - k0);
-    for (int c = t; c < NW * INC_KEYS; c += INC_BLOCK) (&cnt[0][0])[c] = 0;
+    for (int c = t; c < NW << shift; c += INC_BLOCK) cnt[c >> shift][c & ((1 << shift) - 1)] = 0;
     __syncthreads();
     const int part = ((rows + NW - 1) / NW + WAVE - 1) / WAVE * WAVE;
     const int p0 = min(w * part, rows), p1 = min(p0 + part, rows);
@@ -390,11 +389,11 @@ __global__ void __launch_bounds__(INC_BLOCK) k_inc_finish(const unsigned *__rest
     __syncthreads();
     {
         int sum = 0, tot;
-        if (t < INC_KEYS)
+        if (t < keys)
             for (int v = 0; v < NW; v++) sum += cnt[v][t];
         int run = block_exclusive_scan<INC_BLOCK>(sum, &tot);
         if (t < keys) inc_start[k0 + t] = s + run;
-        if (t < INC_KEYS)
+        if (t < keys)
             for (int v = 0; v < NW; v++) {
                 const int c = cnt[v][t];
                 cnt[v][t] = run;

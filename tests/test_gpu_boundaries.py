@@ -208,3 +208,21 @@ def test_recorded_builds_with_counted_triangles(acx, copies, headroom):
                 assert np.array_equal(z[rows[k]:rows[k + 1]].cpu().numpy(), single.sizes(d)), (d, k)
         got.close()
     plan.close()
+
+
+@pytest.mark.parametrize("copies", [32, 33, 65])
+def test_gradients_of_copies(acx, copies):
+    """Corners sorted by ball on both sides of 2^17 and past 2^18 balls: in a batch of
+    copies every ball's gradient is that of the molecule's own complex, bit for bit."""
+    import torch
+    m = synth.molecule(4096, 13)
+    X, R = _dev(m.xyz), _dev(m.radii)
+    g = torch.tensor([0.7, -0.4], dtype=torch.float64, device="cuda:0")
+    one = acx.ac_alpha_complex_device(X, R, 0.0)
+    want_x, want_r = acx.ac_union_measure_backward(one, X, R, g)
+    print(f"[case] gradients of {copies} copies, {copies * m.n} balls", flush=True)
+    XX, RR = X.repeat(copies, 1), R.repeat(copies)
+    c = acx.ac_alpha_complex_batch(XX, RR, np.arange(copies + 1, dtype=np.int64) * m.n, 0.0)
+    dx, dr = acx.ac_union_measure_backward(c, XX, RR, g)
+    assert torch.equal(dx.view(copies, m.n, 3), want_x.expand(copies, m.n, 3))
+    assert torch.equal(dr.view(copies, m.n), want_r.expand(copies, m.n))

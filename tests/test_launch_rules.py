@@ -18,6 +18,8 @@ extern "C" {
 int neighbour_slot(long long sgc, long long n, int recorded) { return acx::neighbour_slot(sgc, n, recorded != 0); }
 int tet_slab(long long sgc, int gshift, int groups, long long most) { return acx::tet_slab(sgc, gshift, groups, most); }
 int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
+int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
+int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 }
 """
 
@@ -72,3 +74,15 @@ def test_slab_sizes_where_they_fit(rules):
 
 def test_pairs_past_their_room_are_counted(rules):
     assert not rules.counts_triangles(*_L(1 << 28)) and rules.counts_triangles(*_L((1 << 28) + 1))
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 511, 512, 513, 4001, 1 << 17, (1 << 17) + 1, 200000, 1 << 18,
+                               (1 << 18) + 1, 400000, 3000000, (1 << 25) + 1, N_MAX])
+def test_buckets_of_the_corner_sort(rules, n):
+    """Every ball id fits in the sorted bits, a bucket's balls in its counters, and
+    there are no more blocks than some hundreds or than whole buckets."""
+    passes, shift = rules.inc_passes(*_L(n)), rules.inc_shift(*_L(n))
+    assert 1 <= passes and 0 <= shift <= 9
+    assert (n - 1) >> (shift + 8 * passes) == 0
+    assert passes == 1 or (n - 1) >> (9 + 8 * (passes - 1)) > 0  # no pass too many
+    assert ((n - 1) >> shift) + 1 <= max(256, (n + 511) // 512)
