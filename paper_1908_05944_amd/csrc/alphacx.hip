@@ -2262,25 +2262,55 @@ static ac_status plan_create(const double *d_xyz, const double *d_r, const Batch
 
 static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
     const int n_mol = (int)p->bt.off.size() - 1;
+    const Fixed &fx = p->fx;
+    // Rows by capacity where that is little memory: their copies are enqueued
+    // behind the replay, and the wait for the counts is the wait for the rows. Else
+    // the counts come first. Either way the rows have left the plan's buffers and
+    // are complete for every stream when this returns: host copies, the next
+    // replay and ac_free order nothing.
+    const bool roomy = p->n * 12LL + fx.E_cap * 16LL + fx.T_cap * 20LL + fx.Q_cap * 24LL <= OUT_ROOM;
     Counters c{};
-    read_back(&c, p->fx.cnt, 1, s);
-    p->last_stop = c.stop;
-    if (c.stop) {
-        // the input did not fit the recording: an ordinary build of the same
-        // arguments (it also reports invalid input)
-        p->ordinary_builds++;
-        const ac_status st = run_pipeline(p->d_xyz, p->d_r, p->n, p->bt, &p->alpha, 1, p->o, s, out);
-        if (st == AC_OK) (*out)->batch = true;
-        return st;
-    }
-    if (c.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
+    if (!roomy) read_back(&c, fx.cnt, 1, s);
+    ac_complex *r = nullptr;
     std::vector<int64_t> rows;
-    if (n_mol > 1) {
-        rows.resize(4 * (size_t)(n_mol + 1));
-        read_back(rows.data(), (const int64_t *)p->fx.d_rows, rows.size(), s);
-    }
-    ac_complex *r = new ac_complex();
     try {
+        if (!c.stop) {
+            r = new ac_complex();
+            CopyList cl{};
+            const long long cap[4] = {p->n, fx.E_cap, fx.T_cap, fx.Q_cap};
+            const int m[4] = {c.m0, c.m1, c.m2, c.m3};
+            long long most = 0;
+            for (int d = 0; d < 4; d++) {
+                const long long k = std::max<long long>(roomy ? cap[d] : m[d], 1);
+                r->d_simp[d] = static_cast<int32_t *>(dev_alloc((size_t)k * (d + 1) * sizeof(int32_t)));
+                r->d_size[d] = static_cast<double *>(dev_alloc((size_t)k * sizeof(double)));
+                cl.src[2 * d] = p->out_simp[d];
+                cl.dst[2 * d] = r->d_simp[d];
+                cl.src[2 * d + 1] = reinterpret_cast<const int *>(p->out_size[d]);
+                cl.dst[2 * d + 1] = reinterpret_cast<int *>(r->d_size[d]);
+                most = std::max(most, k * std::max(2, d + 1));
+            }
+            k_copy_list<<<dim3((unsigned)std::min<long long>(most / 1024 + 1, roomy ? 256 : 2048), 8), 256, 0, s>>>(cl, fx.cnt);
+            LAUNCH_CHECK();
+        }
+        if (roomy) read_back(&c, fx.cnt, 1, s);
+        else HIP_TRY(hipStreamSynchronize(s));
+        p->last_stop = c.stop;
+        if (c.stop) {
+            // the input did not fit the recording: an ordinary build of the same
+            // arguments (it also reports invalid input)
+            free_complex(r);
+            r = nullptr;
+            p->ordinary_builds++;
+            const ac_status st = run_pipeline(p->d_xyz, p->d_r, p->n, p->bt, &p->alpha, 1, p->o, s, out);
+            if (st == AC_OK) (*out)->batch = true;
+            return st;
+        }
+        if (c.lookup) throw HipError{AC_E_DEVICE, "internal error: a facet of a kept simplex is not a candidate"};
+        if (n_mol > 1) {
+            rows.resize(4 * (size_t)(n_mol + 1));
+            read_back(rows.data(), (const int64_t *)fx.d_rows, rows.size(), s);
+        }
         for (double &x : r->stage_ms) x = -1.0;
         r->device = p->device;
         r->device_result = true;
@@ -2294,21 +2324,10 @@ static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
         r->cand[2] = c.T;
         r->cand[3] = c.Q;
         r->fallbacks = (int64_t)c.exact_fallbacks;
-        r->work[0] = p->fx.ncell;
+        r->work[0] = fx.ncell;
         r->work[1] = c.Nn;
-        CopyList cl{};
-        long long most = 0;
         for (int d = 0; d < 4; d++) {
             r->count[d] = m[d];
-            r->d_simp[d] = static_cast<int32_t *>(dev_alloc((size_t)(m[d] > 0 ? m[d] : 1) * (d + 1) * sizeof(int32_t)));
-            r->d_size[d] = static_cast<double *>(dev_alloc((size_t)(m[d] > 0 ? m[d] : 1) * sizeof(double)));
-            cl.src[2 * d] = p->out_simp[d];
-            cl.dst[2 * d] = r->d_simp[d];
-            cl.words[2 * d] = (long long)m[d] * (d + 1);
-            cl.src[2 * d + 1] = reinterpret_cast<const int *>(p->out_size[d]);
-            cl.dst[2 * d + 1] = reinterpret_cast<int *>(r->d_size[d]);
-            cl.words[2 * d + 1] = (long long)m[d] * 2;
-            most = std::max(most, std::max(cl.words[2 * d], cl.words[2 * d + 1]));
             if (n_mol > 1) {
                 const int64_t *b0 = rows.data() + (size_t)d * (n_mol + 1);
                 r->mol_rows[d].assign(b0, b0 + (n_mol + 1));
@@ -2316,8 +2335,6 @@ static ac_status plan_result(ac_plan *p, hipStream_t s, ac_complex **out) {
                 r->mol_rows[d] = {0, r->count[d]};
             }
         }
-        k_copy_list<<<dim3((unsigned)std::min<long long>(most / 1024 + 1, 2048), 8), 256, 0, s>>>(cl);
-        LAUNCH_CHECK();
     } catch (...) {
         (void)hipStreamSynchronize(s);
         free_complex(r);

@@ -478,16 +478,18 @@ __global__ void __launch_bounds__(REC_BLOCK) k_rec_apply(int4 *__restrict__ rec,
     }
 }
 
-// Up to eight arrays copied in one launch (blockIdx.y: the array; all 16-byte
-// aligned, sizes multiples of 4): a copy call each would cost a launch each.
+// The rows and Sizes of a finished recorded build in one launch (array
+// blockIdx.y = 2 d: rows of dimension d, 2 d + 1: their Sizes; all 16-byte
+// aligned): a copy call each would cost a launch each. The row counts are the
+// build's own, so the host need not know them; a stopped build has no rows.
 struct CopyList {
     const int *src[8];
     int *dst[8];
-    long long words[8];
 };
-__global__ void __launch_bounds__(256) k_copy_list(CopyList l) {
-    const int a = blockIdx.y;
-    const long long n = l.words[a], n4 = n / 4;
+__global__ void __launch_bounds__(256) k_copy_list(CopyList l, const Counters *__restrict__ cnt) {
+    const int a = blockIdx.y, d = a / 2;
+    const int m = cnt->stop ? 0 : d == 0 ? cnt->m0 : d == 1 ? cnt->m1 : d == 2 ? cnt->m2 : cnt->m3;
+    const long long n = (long long)m * (a & 1 ? 2 : d + 1), n4 = n / 4;
     const int4 *s4 = reinterpret_cast<const int4 *>(l.src[a]);
     int4 *d4 = reinterpret_cast<int4 *>(l.dst[a]);
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x, stride = (long long)gridDim.x * 256;

@@ -226,3 +226,30 @@ def test_gradients_of_copies(acx, copies):
     dx, dr = acx.ac_union_measure_backward(c, XX, RR, g)
     assert torch.equal(dx.view(copies, m.n, 3), want_x.expand(copies, m.n, 3))
     assert torch.equal(dr.view(copies, m.n), want_r.expand(copies, m.n))
+
+
+def test_replayed_rows_are_complete_on_return(acx):
+    """The result of a replay on a stream of its own: its rows are read through
+    another stream at once, and the next replay and its result come before the
+    first is looked at on the host."""
+    import torch
+    m = synth.molecule(200000, 5)
+    X, R = _dev(m.xyz), _dev(m.radii)
+    shifted = _dev(m.xyz + 3.0)
+    want = [acx.ac_alpha_complex_device(x, R, 0.0) for x in (X, shifted)]
+    src = X.clone()
+    plan = acx.Plan(src, R, np.array([0, m.n]), 0.0, headroom=1.5)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    print("[case] replays on two streams", flush=True)
+    for rep in range(3):
+        got = []
+        for k, (st, x) in enumerate(((a, X), (b, shifted))):
+            with torch.cuda.stream(st):
+                src.copy_(x)
+                plan.launch()
+                got.append(plan.result())
+            assert plan.stopped() == 0
+            if rep % 2 == k:  # at once
+                _same_as(got[k], want[k], (rep, k))
+        for k in (0, 1):
+            _same_as(got[k], want[k], (rep, k))
