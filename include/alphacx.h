@@ -111,9 +111,9 @@ ac_status ac_alpha_complex_device(const double *d_xyz, const double *d_radii, in
  *   d_xyz, d_radii, n, alpha, opt, stream  as ac_alpha_complex_device;
  *            opt->profile must be 0
  *   d_simp   host array of 4 device pointers: d_simp[d] has room for
- *            capacity[d] rows of d + 1 int32 (row-major)
+ *            capacity[d] rows of d + 1 int32 (row-major), aligned as int32
  *   d_size   host array of 4 device pointers: d_size[d] has room for
- *            capacity[d] float64
+ *            capacity[d] float64, aligned as float64
  *   capacity host array of 4 row capacities (>= 0; a pointer may be NULL
  *            when its capacity is 0)
  *   counts   host array of 4: receives the number of d-simplices of K_alpha

@@ -530,6 +530,12 @@ __device__ __forceinline__ int rank_in_ball(unsigned long long kept, int lane, i
     return first > c0 ? __popcll(before >> (first - c0)) : carry + __popcll(before);
 }
 
+// Rows of two and four ids as one store each. The arrays may be the caller's, so
+// no more than an int's alignment is taken for granted (one 8- or 16-byte store
+// all the same: the hardware asks for no more).
+typedef int row2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef int row4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // LIST: the kept triangles come from k_tri_final's list.
 template <bool LIST>
 __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const int4 *__restrict__ base,
@@ -579,7 +585,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
         const int u = ids[i - b0];
         const long long p = row0[0][i - b0] + rank_in_ball(kept, lane, first, c0, carry);
         const double sz = st == FACE_GABRIEL ? edge_size_canon(cd.atom[i], cd.atom[cd.up[e]]) : double_from_ordered(edge_min[e]);
-        reinterpret_cast<int2 *>(out1)[p] = make_int2(u, cd.up_id[e]);
+        reinterpret_cast<row2 *>(out1)[p] = row2{u, cd.up_id[e]};
         size1[p] = sz / 1.0e6;  // mA^2 -> A^2
     }
     // a kept triangle to its row
@@ -634,7 +640,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows(Cands cd, PredParams pp, const i
         while (rank < x && cd.edge_i[cd.tri_e[tt.t[qb + x - rank - 1]]] == i) rank++;
         const int u = ids[i - b0];
         const long long p = row0[2][i - b0] + rank;
-        reinterpret_cast<int4 *>(out3)[p] = make_int4(u, cd.up_id[e], cd.up_id[cd.tri_f[t]], cd.up_id[f2]);
+        reinterpret_cast<row4 *>(out3)[p] = row4{u, cd.up_id[e], cd.up_id[cd.tri_f[t]], cd.up_id[f2]};
         size3[p] = tt.size[qb + x] / 1.0e6;
     }
 }

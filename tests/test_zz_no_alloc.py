@@ -145,3 +145,28 @@ def test_input_beyond_the_scratch_is_refused(acx):
     simp, size = _buffers([len(ref[d][0]) for d in range(4)])
     counts = acx.ac_alpha_complex_noalloc(X, R, 0.0, simp, size)
     _check_same(counts, simp, size, ref, "after a scratch overflow")
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_outputs_aligned_as_their_elements_only(acx, shift):
+    """Output arrays that start `shift` int32 (one float64) past a 16-byte line, as
+    slices of one buffer do; what lies around the rows is not touched."""
+    import torch
+    m = synth.molecule(4000, 77)
+    X, R = _dev(m.xyz), _dev(m.radii)
+    ref = _reference(acx, X, R, 1.0, None)
+    simp, size, around = [], [], []
+    for d in range(4):
+        k = len(ref[d][0])
+        a = torch.full((k * (d + 1) + 8,), -7, dtype=torch.int32, device="cuda:0")
+        z = torch.full((k + 2,), -7.0, dtype=torch.float64, device="cuda:0")
+        simp.append(a[shift:shift + k * (d + 1)].view(k, d + 1))
+        size.append(z[1:1 + k])
+        around.append((a, z, shift + k * (d + 1)))
+        assert simp[d].data_ptr() % 16 == 4 * shift and size[d].data_ptr() % 16 == 8
+    print(f"[case] noalloc outputs {shift} int32 past a line", flush=True)
+    counts = acx.ac_alpha_complex_noalloc(X, R, 1.0, simp, size)
+    _check_same(counts, simp, size, ref, f"shift {shift}")
+    for a, z, end in around:
+        assert bool((a[:shift] == -7).all()) and bool((a[end:] == -7).all())
+        assert float(z[0]) == -7.0 and float(z[-1]) == -7.0
