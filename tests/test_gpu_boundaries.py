@@ -253,3 +253,33 @@ def test_replayed_rows_are_complete_on_return(acx):
                 _same_as(got[k], want[k], (rep, k))
         for k in (0, 1):
             _same_as(got[k], want[k], (rep, k))
+
+
+@pytest.mark.parametrize("n", [2049, 2304, 9001])
+@pytest.mark.parametrize("cell", [12000, 17000, 22000, 60000])
+def test_crowded_cells(acx, n, cell):
+    """Cells of some ten to all of the balls: buckets whose cells are ranked in LDS
+    and buckets that go in chunks."""
+    m = synth.molecule(n, 78)
+    _check(acx, m.xyz, m.radii, 0.0, f"cell {cell}", cell_mA=cell)
+
+
+@pytest.mark.parametrize("far", [400.0, 640.0])
+def test_dense_ball_in_a_large_box(acx, far):
+    """One atom far away makes most cells empty: buckets of ordinary cells with more
+    than 2,048 balls."""
+    m = synth.molecule(100003, 9)
+    xyz = np.vstack([m.xyz - m.xyz.mean(0) - [far / 2, 0.0, 0.0], [[far / 2, 0.0, 0.0]]])
+    _check(acx, xyz, np.append(m.radii, 1.5), 0.0, f"one atom {far} A away")
+
+
+@pytest.mark.parametrize("n,cell", [(3000, 60000), (30000, 60000), (30000, 3600)])
+@pytest.mark.parametrize("first,second", [(0, 1), (0, -1), (-2, -1), (1500, 2900)])
+def test_equal_centres_are_found(acx, n, cell, first, second):
+    m = synth.molecule(n, 79)
+    xyz = m.xyz.copy()
+    xyz[second] = xyz[first]
+    print(f"[case] equal centres n={n} cell={cell} {first} {second}", flush=True)
+    with pytest.raises(acx.AlphaCxError) as ei:
+        acx.ac_alpha_complex_device(_dev(xyz), _dev(m.radii), 0.0, options={"cell_mA": cell})
+    assert ei.value.status == 2
