@@ -679,7 +679,7 @@ struct Fixed {
     std::vector<Grid> grids;       // per molecule: cell side, reach, order, balls
     std::vector<long long> cells;  // per molecule: grid cells
     PredParams pp{};
-    int wmax = 0;
+    int wmax = 0, gshift = 0;
     long long E = 0, P = 0, T = 0, Q = 0;  // candidate edges, pairs, candidate triangles, kept tetrahedra
     long long tet_most = 0;  // candidate tetrahedra of the fullest group where one outgrew its slab, else 0
     long long tet_limit = 0;  // most entries of a slab
@@ -927,17 +927,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const int nbs = (int)(nbB + 3) & ~3;
         int *nbtot = sc.get<int>(3 * (size_t)nbs);
         int *uoff = sc.get<int>(nbB), *poff = sc.get<int>(nbB);
-        // balls of a group: enough groups to fill the GPU, else as many balls as
-        // a block's steps serve well (fewer waits per ball). Rows of the widest
-        // slot hold some ten times the triangles: smaller groups, more evenly
-        // spread (100,000 atoms with solvent-accessible radii: all kernels 2,304
-        // us with 16 balls a group, 2,354 with 32, 2,553 with 64; with van der
-        // Waals radii 188 with 32, 172 with 64, 182 with 128)
-        int gshift = 4;
-        while (gshift < 8 && (n >> gshift) >= (slot == NB_SLOT_SAS ? 8192 : 2048)) gshift++;
-        const int groups = ((n - 1) >> gshift) + 1;
         unsigned char *eng = sc.get<unsigned char>(n);
-        int *pair_base = sc.get<int>((size_t)groups + 1);
         const int *stop = fixed ? &cnt->stop : nullptr;  // kernels of a stopped recorded build return at once
         // f(SLOT, LPB) with the two as constants
         auto with_slot = [&](auto &&f) {
@@ -976,6 +966,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         }
         if (c0.dup) throw HipError{AC_E_DUPLICATE, "two balls have equal quantised centres"};
         const bool nbr_two_pass = c0.overflow != 0;
+        // (the search's edges: fewer than there are where rows outgrew their slots)
+        const int gshift = fixed ? fx->gshift : group_shift(n, slot, c0.E);
+        if (fx && fx->learn) fx->gshift = gshift;
+        const int groups = ((n - 1) >> gshift) + 1;
+        int *pair_base = sc.get<int>((size_t)groups + 1);
         int *pairs = nullptr;
         if (nbr_two_pass) {
             // exact counts and totals: neighbour entries, candidate edges, pairs

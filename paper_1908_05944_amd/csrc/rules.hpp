@@ -46,6 +46,24 @@ inline int tet_slab(long long sgc, int gshift, int groups, long long most) {
     return (int)(cap * groups > INDEX_MAX ? INDEX_MAX / groups : cap);
 }
 
+// Balls of a group (2^shift, at most 256): enough groups to fill the GPU, else as
+// many balls as a block's steps serve well (fewer waits per ball). Rows of the
+// widest slot hold some ten times the triangles: smaller groups, more evenly
+// spread (100,000 atoms with solvent-accessible radii: all kernels 2,304 us with 16
+// balls a group, 2,354 with 32, 2,553 with 64; with van der Waals radii 188 with
+// 32, 172 with 64, 182 with 128).
+// A group's work grows with the square of its balls' upper rows (edges: how many
+// there are at least), and one block does it all: where there are few groups and
+// their rows are long, fewer balls.
+constexpr long long GROUP_PAIRS = 4096;
+inline int group_shift(long long n, int slot, long long edges) {
+    int shift = 4;
+    while (shift < 8 && (n >> shift) >= (slot == NB_SLOT_SAS ? 8192 : 2048)) shift++;
+    const double row = (double)edges / (double)n;
+    while (shift > 0 && (n >> shift) < 4096 && row * row * (double)(1 << shift) > (double)GROUP_PAIRS) shift--;
+    return shift;
+}
+
 // Pairs of upper entries a build makes room for (25 bytes each); past it the
 // candidate triangles are counted first. A recorded build decides once, on the
 // pairs that its headroom asks for.

@@ -283,3 +283,11 @@ def test_equal_centres_are_found(acx, n, cell, first, second):
     with pytest.raises(acx.AlphaCxError) as ei:
         acx.ac_alpha_complex_device(_dev(xyz), _dev(m.radii), 0.0, options={"cell_mA": cell})
     assert ei.value.status == 2
+
+
+@pytest.mark.parametrize("n", [40, 300, 1500])
+@pytest.mark.parametrize("grow_mA,alpha", [(2000, 0.0), (3500, 0.0), (4500, -20.0)])
+def test_long_rows_in_few_balls(acx, n, grow_mA, alpha):
+    """Rows so long that a group is a few balls, or one."""
+    m = synth.molecule(n, 32).with_sas(grow_mA)
+    _check(acx, m.xyz, m.radii, alpha, f"grown by {grow_mA}")

@@ -20,6 +20,7 @@ int tet_slab(long long sgc, int gshift, int groups, long long most) { return acx
 int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
 int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
+int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
 }
 """
 
@@ -86,3 +87,13 @@ def test_buckets_of_the_corner_sort(rules, n):
     assert (n - 1) >> (shift + 8 * passes) == 0
     assert passes == 1 or (n - 1) >> (9 + 8 * (passes - 1)) > 0  # no pass too many
     assert ((n - 1) >> shift) + 1 <= max(256, (n + 511) // 512)
+
+
+def test_groups(rules):
+    """Ordinary builds keep their groups; long rows in few balls make them smaller."""
+    for n, slot, row, want in ((300, 16, 4, 4), (100000, 16, 4, 6), (100000, 128, 21, 4), (3000000, 16, 4, 8),
+                               (3000, 32, 10, 4), (300, 16, 60, 0), (3000, 16, 200, 0), (60000, 16, 200, 3),
+                               (70000, 16, 200, 4), (N_MAX, 32, 30, 8)):
+        got = rules.group_shift(*_L(n), slot, *_L(n * row))
+        assert got == want, (n, slot, row, got)
+    assert rules.group_shift(*_L(1), 16, *_L(0)) == 4
