@@ -1135,10 +1135,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const int parts = (int)((n - 1) >> cd.sshift) + 1;
         auto ac2 = [&](auto sl, int what) {
             constexpr int SLOT = decltype(sl)::value;
+            const dim3 blocks(parts, SLOT ? 1 : rows_split(parts));
             if (use_apex)
-                k_ac2<SLOT, true><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
+                k_ac2<SLOT, true><<<blocks, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
             else
-                k_ac2<SLOT, false><<<parts, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
+                k_ac2<SLOT, false><<<blocks, AC2_BLOCK, 0, s>>>(cd, pp, what, ao, cnt, stop);
             LAUNCH_CHECK();
         };
         auto ac2_of = [&](int what) {

@@ -64,6 +64,13 @@ inline int group_shift(long long n, int slot, long long edges) {
     return shift;
 }
 
+// Blocks that share a part of the balls in the AC2 test over rows in memory: some
+// 4,096 in all, and no more than 32 a part (most parts have no work for more).
+inline int rows_split(int parts) {
+    const int k = 4096 / parts;
+    return k < 1 ? 1 : k > 32 ? 32 : k;
+}
+
 // Pairs of upper entries a build makes room for (25 bytes each); past it the
 // candidate triangles are counted first. A recorded build decides once, on the
 // pairs that its headroom asks for.

@@ -21,6 +21,7 @@ int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
 int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
+int rows_split(int parts) { return acx::rows_split(parts); }
 }
 """
 
@@ -97,3 +98,8 @@ def test_groups(rules):
         got = rules.group_shift(*_L(n), slot, *_L(n * row))
         assert got == want, (n, slot, row, got)
     assert rules.group_shift(*_L(1), 16, *_L(0)) == 4
+
+
+@pytest.mark.parametrize("parts", [1, 17, 128, 129, 4095, 4096, 4097, N_MAX])
+def test_blocks_of_a_part(rules, parts):
+    assert rules.rows_split(parts) == min(32, max(1, 4096 // parts))
