@@ -29,7 +29,7 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # MI355X FP64 vector
 KERNEL_OF_STAGE = {
     "neighbours_count": "k_neighbours<16, 1, true>",
     "neighbours_fill": "k_nbr_compact<16, 1, 256>",
-    "triangles_count": "k_triangles<false>",
+    "triangles_count": "k_triangles<false, false>",
     "tetrahedra_ac2": "k_tet_ac2<false, 64>",
     "triangles_final": "k_tri_final<false>",
     "edges_final": "k_edge_final",

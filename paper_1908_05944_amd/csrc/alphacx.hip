@@ -1047,9 +1047,15 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         cd.tri_sub = sc.get<int>(((size_t)(n - 1) >> cd.sshift) + 1);
         tm.mark(ST_TRI_COUNT);
         long long room = fixed ? fx->P_cap : c0.P;
-        if (counted) {
-            k_triangles<true><<<groups, BLOCK, 0, s>>>(cd, pp, nullptr, cnt, stop);
+        auto triangles = [&](auto count, long long *mins) {
+            if (nbr_two_pass)
+                k_triangles<decltype(count)::value, true><<<groups, BLOCK, 0, s>>>(cd, pp, mins, cnt, stop);
+            else
+                k_triangles<decltype(count)::value, false><<<groups, BLOCK, 0, s>>>(cd, pp, mins, cnt, stop);
             LAUNCH_CHECK();
+        };
+        if (counted) {
+            triangles(std::true_type{}, nullptr);
             if (fixed) {
                 sum_i64(cd.tri_cnt, groups, &cnt->T, s, sc);
                 k_plan_guard_triangles<<<1, WAVE, 0, s>>>(cnt, fx->T_cap);
@@ -1068,8 +1074,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         long long *tri_min = sc.get<long long>(T1);
         unsigned char *tgab = sc.get<unsigned char>(T1);
         double *tsize = sc.get<double>(T1);
-        k_triangles<false><<<groups, BLOCK, 0, s>>>(cd, pp, tri_min, cnt, stop);
-        LAUNCH_CHECK();
+        triangles(std::false_type{}, tri_min);
         tm.mark(ST_TRI_SCAN);  // the triangles are in place: no scan, no fill
         tm.mark(ST_TRI_FILL);
 

@@ -402,15 +402,24 @@ __device__ __forceinline__ bool tet_ac2(const Cands &cd, const Tet &ts, const Pr
 // only (the first pass of a counted build). Bound by instruction issue (half of
 // the time) and the barriers between the tests: 195 us at 3M atoms and alpha = 0
 // with 512 edges at a time; with 256 208, with 1,024 240.
+// LONG (rows longer than the slots, after a counted neighbour search): the third
+// balls of (i, j) are also among the upper entries of j. Where more than LONG_ROW
+// edges come after (i, j) in its row and j has fewer, j's are the items, each
+// looked up in i's row: a large ball with thousands of small ones around it has a
+// few items an edge instead of thousands (7.9 A among 2,942 of 0.45 A: 65 ms with
+// all pairs, 0.33 as this). Looked for where the edges held have LONG_PAIRS pairs.
+// (In every build, the test of has_long costs 0.8 % at 3M atoms.)
 constexpr int EDGE_PT = 2, EDGE_CH = EDGE_PT * BLOCK, EDGE_AHEAD = 64;
-template <bool COUNT>
+constexpr int LONG_ROW = 64, LONG_PAIRS = 4 * PAIR_WIN;
+constexpr int LONG_EDGE = 0x80;  // in part_no: the items of the edge are j's upper entries
+template <bool COUNT, bool LONG>
 __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, long long *__restrict__ tri_min, Counters *cnt,
                                                       const int *__restrict__ stop) {
     if (stop && *stop) return;
     __shared__ int4 sat[EDGE_CH + EDGE_AHEAD];
     __shared__ unsigned short own[PAIR_WIN], hit[PAIR_WIN], res[PAIR_WIN];
     __shared__ int soff[EDGE_CH];
-    __shared__ unsigned char part_no[EDGE_CH];  // part of the group an edge belongs to
+    __shared__ unsigned char part_no[EDGE_CH];  // part of the group an edge belongs to (at most 64), LONG_EDGE
     __shared__ int wtot[2][NWAVE];
     const int g = xcd_block();
     const int b0 = g << cd.gshift, b1 = min(b0 + (1 << cd.gshift), cd.n);
@@ -431,20 +440,50 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
             part_no[threadIdx.x * EDGE_PT + u] = (unsigned char)((i - b0) >> cd.sshift);
         }
         int pairs;
-        const int off = pair_scan<EDGE_PT>(later, soff, &pairs);
+        int off = pair_scan<EDGE_PT>(later, soff, &pairs);
+        const bool has_long = LONG && pairs > LONG_PAIRS;
+        if (has_long) {
+#pragma unroll
+            for (int u = 0; u < EDGE_PT; u++) {
+                if (later[u] <= LONG_ROW) continue;
+                const int x = threadIdx.x * EDGE_PT + u, j = cd.up[c0 + x];
+                const int items = cd.up_start[j + 1] - cd.up_start[j];
+                if (items >= later[u]) continue;
+                later[u] = items;
+                part_no[x] |= LONG_EDGE;
+            }
+            off = pair_scan<EDGE_PT>(later, soff, &pairs);
+        }
         int prev = -1;  // edge (less c0) of the last triangle of the windows before
+        // edge (less c0) of i to the k-th upper entry of j, for edge c0 + o = (i, j); -1 if there is none
+        auto joint = [&](int o, int k) {
+            const int e = c0 + o, id = cd.up_id[cd.up_start[cd.up[e]] + k];
+            int lo = e + 1, hi = cd.up_start[cd.edge_i[e] + 1];
+            const int end = hi;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cd.up_id[mid] < id) lo = mid + 1; else hi = mid;
+            }
+            return lo < end && cd.up_id[lo] == id ? lo - c0 : -1;
+        };
+        auto part_of_edge = [&](int x) { return LONG ? part_no[x] & ~LONG_EDGE : part_no[x]; };
         // the ball at the far end of edge c0 + x
         auto far_ball = [&](int x) { return x < EDGE_CH + EDGE_AHEAD ? sat[x] : cd.atom[cd.up[c0 + x]]; };
         for (int w0 = 0; w0 < pairs; w0 += PAIR_WIN) {
             pair_owners<EDGE_PT>(w0, off, later, own);
             const int wn = min(PAIR_WIN, pairs - w0);
             // second edge of pair x of the window, less c0 (the first is own[x])
-            auto second = [&](int x) { const int o = own[x]; return o + 1 + (w0 + x - soff[o]); };
+            auto second = [&](int x) {
+                const int o = own[x], k = w0 + x - soff[o];
+                return has_long && (part_no[o] & LONG_EDGE) ? joint(o, k) : o + 1 + k;
+            };
             // pairs of the upper row whose spheres cross
             const int p1 = part_of(wn);
             const int h = wave_filter(wn, p1, hit, [&](int x, int &v) {
                 v = x;
-                return spheres_cross(far_ball(own[x]), far_ball(second(x)), pp);
+                const int y = second(x);
+                if (has_long && y < 0) return false;
+                return spheres_cross(far_ball(own[x]), far_ball(y), pp);
             });
             if (lane == 0) wtot[0][w] = h;
             __syncthreads();
@@ -474,13 +513,14 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
                     const int before = x > 0 ? own[res[rs.slot(x - 1)]] : prev;
                     if (before != o) {
                         cd.tri_first[c0 + o] = out + x;
-                        for (int k = x > 0 ? part_no[before] + 1 : last_part + 1; k <= part_no[o]; k++) sub[k] = out + x;
+                        for (int k = x > 0 ? part_of_edge(before) + 1 : last_part + 1; k <= part_of_edge(o); k++)
+                            sub[k] = out + x;
                     }
                 }
             }
             if (rs.total > 0) {
                 prev = own[res[rs.slot(rs.total - 1)]];
-                last_part = part_no[prev];
+                last_part = part_of_edge(prev);
             }
             out += rs.total;
             __syncthreads();

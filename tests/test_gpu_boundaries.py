@@ -291,3 +291,26 @@ def test_long_rows_in_few_balls(acx, n, grow_mA, alpha):
     """Rows so long that a group is a few balls, or one."""
     m = synth.molecule(n, 32).with_sas(grow_mA)
     _check(acx, m.xyz, m.radii, alpha, f"grown by {grow_mA}")
+
+
+def _hub(k, hub, ball):
+    """k balls spread over a sphere around a hub that their grown spheres cross."""
+    i = np.arange(k) + 0.5
+    phi, z = np.pi * (1 + 5 ** 0.5) * i, 1 - 2 * i / k
+    p = np.stack([np.cos(phi) * np.sqrt(1 - z * z), np.sin(phi) * np.sqrt(1 - z * z), z], -1) * (hub + ball * 2 / 3)
+    return np.vstack([[0, 0, 0], p + np.random.RandomState(k).uniform(-0.02, 0.02, p.shape)]), np.append(hub, np.full(k, ball))
+
+
+@pytest.mark.parametrize("k", [60, 66, 130, 700, 1500])
+@pytest.mark.parametrize("hub,ball", [(7.9, 0.45), (2.2, 0.15)])
+@pytest.mark.parametrize("place", [0, 1, -1])
+def test_hubs(acx, k, hub, ball, place):
+    """One ball with a long row, first, in the middle and last by input id, alone and
+    beside a molecule: its edges' items on both sides of what a row may hold."""
+    xyz, rad = _hub(k, hub, ball)
+    at = {0: 0, 1: k // 2, -1: k}[place]
+    order = np.concatenate([np.arange(1, at + 1), [0], np.arange(at + 1, k + 1)])
+    xyz, rad = xyz[order], rad[order]
+    _check(acx, xyz, rad, 0.0, f"hub of {k} at {at}")
+    m = synth.molecule(300, 33)
+    _check(acx, np.vstack([xyz, m.xyz - m.xyz.mean(0) + [30.0, 0, 0]]), np.append(rad, m.radii), 0.0, "hub and molecule")
