@@ -988,7 +988,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         check_total(c0.Nn, "neighbour entries");
         check_total(c0.E, "candidate edges");
         // room for every pair, or (too many pairs) the counted triangles
-        const bool counted = fixed ? fx->counted : counts_triangles(c0.P);
+        const int tet_cap = tet_slab(pp.sgc, gshift, groups, fixed ? fx->tet_most : 0);
+        const bool counted = fixed     ? fx->counted
+                             : t_arena ? counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn,
+                                                             groups, tet_cap)
+                                       : counts_triangles(c0.P);
         const int E = (int)c0.E;
         const long long Nn = c0.Nn;
         if (fx && fx->learn) {
@@ -1085,7 +1089,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         const bool use_apex = pp.sgc > APEX_SGC;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
         Tets tt{};
-        tt.cap = tet_slab(pp.sgc, gshift, groups, fixed ? fx->tet_most : 0);
+        tt.cap = tet_cap;
         tt.num = sc.get<int>(groups);
         tt.kept = sc.get<int>(groups);
         tt.cand = sc.get<int>(groups);

@@ -71,11 +71,22 @@ inline int rows_split(int parts) {
     return k < 1 ? 1 : k > 32 ? 32 : k;
 }
 
-// Pairs of upper entries a build makes room for (25 bytes each); past it the
+// Pairs of upper entries a build makes room for (PAIR_BYTES each); past it the
 // candidate triangles are counted first. A recorded build decides once, on the
 // pairs that its headroom asks for.
 constexpr long long PAIR_ROOM = 1LL << 28;
+constexpr int PAIR_BYTES = 37;  // edges, minimum, status, Size; apex balls and list where the radii are large
 inline bool counts_triangles(long long pairs) { return pairs > PAIR_ROOM; }
+
+// The same on fixed scratch, of which `left` bytes are left: room for every pair
+// where the rest of the build (n balls, E edges, Nn neighbour entries, slabs of cap
+// tetrahedra for each group) has its own beside it. (A ball with 4,000 small ones
+// around it has 8 million pairs, 285 MiB, and 12,000 triangles.)
+inline bool counts_triangles_in(long long left, long long pairs, long long n, long long E, long long Nn, long long groups,
+                                long long cap) {
+    const long long rest = 40 * n + 33 * E + 4 * Nn + (64 + 16 * cap) * groups + (1 << 20);
+    return pairs > (left - rest) / PAIR_BYTES || counts_triangles(pairs);
+}
 
 // Buckets of the corners sorted by ball: 2^shift balls of n each, after `passes`
 // radix passes of 8 bits over the ball ids above the bucket. As few passes as

@@ -17,6 +17,9 @@ WRAPPERS = """
 extern "C" {
 int neighbour_slot(long long sgc, long long n, int recorded) { return acx::neighbour_slot(sgc, n, recorded != 0); }
 int tet_slab(long long sgc, int gshift, int groups, long long most) { return acx::tet_slab(sgc, gshift, groups, most); }
+int counts_triangles_in(long long left, long long pairs, long long n, long long E, long long Nn, long long g, long long cap) {
+    return acx::counts_triangles_in(left, pairs, n, E, Nn, g, cap);
+}
 int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
 int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
@@ -103,3 +106,13 @@ def test_groups(rules):
 @pytest.mark.parametrize("parts", [1, 17, 128, 129, 4095, 4096, 4097, N_MAX])
 def test_blocks_of_a_part(rules, parts):
     assert rules.rows_split(parts) == min(32, max(1, 4096 // parts))
+
+
+def test_pairs_on_fixed_scratch(rules):
+    def counted(left, pairs, n=1000, E=4000, Nn=8000, groups=63, cap=192):
+        return bool(rules.counts_triangles_in(*_L(left, pairs, n, E, Nn, groups, cap)))
+
+    rest = 40 * 1000 + 33 * 4000 + 4 * 8000 + (64 + 16 * 192) * 63 + (1 << 20)
+    assert not counted(rest + 37 * 5000, 5000) and counted(rest + 37 * 5000 - 1, 5000)
+    assert counted(rest - 1, 1) and counted(0, 100)  # nothing left: the triangles need the least
+    assert counted(1 << 40, (1 << 28) + 1)

@@ -170,3 +170,23 @@ def test_outputs_aligned_as_their_elements_only(acx, shift):
     for a, z, end in around:
         assert bool((a[:shift] == -7).all()) and bool((a[end:] == -7).all())
         assert float(z[0]) == -7.0 and float(z[-1]) == -7.0
+
+
+@pytest.mark.parametrize("k", [500, 4000, 5000])
+def test_many_pairs_and_few_triangles(acx, k):
+    """A ball with thousands of small ones around it, the least and the last by id:
+    more pairs of its edges than the scratch has room for, and few triangles."""
+    i = np.arange(k) + 0.5
+    phi, z = np.pi * (1 + 5 ** 0.5) * i, 1 - 2 * i / k
+    p = np.stack([np.cos(phi) * np.sqrt(1 - z * z), np.sin(phi) * np.sqrt(1 - z * z), z], -1) * 8.2
+    p += np.random.RandomState(k).uniform(-0.02, 0.02, p.shape)
+    for last in (False, True):
+        xyz, rad = np.vstack([[0, 0, 0], p]), np.append(7.9, np.full(k, 0.33))
+        if last:
+            xyz, rad = xyz[::-1], rad[::-1]
+        X, R = _dev(xyz), _dev(rad)
+        ref = _reference(acx, X, R, 0.0, None)
+        simp, size = _buffers([len(ref[d][0]) for d in range(4)])
+        print(f"[case] noalloc hub of {k}, last={last}", flush=True)
+        counts = acx.ac_alpha_complex_noalloc(X, R, 0.0, simp, size)
+        _check_same(counts, simp, size, ref, f"hub {k}")
