@@ -1109,7 +1109,9 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             LAUNCH_CHECK();
         };
         auto tet_ac2 = [&]() {
-            const bool few = pp.sgc <= 2000;  // below one candidate a ball
+            // below one candidate a ball, and no balls with thousands (a ball of 1.6 A
+            // among 2,942 of 0.09 A: 12 ms by one wave)
+            const bool few = pp.sgc <= 2000 && !nbr_two_pass;
             if (n_alpha > 1 && few)
                 k_tet_ac2<true, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
             else if (n_alpha > 1)
@@ -1121,8 +1123,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             LAUNCH_CHECK();
         };
         // counted ranges for every group's tetrahedra, after an overflow: both
-        // kernels again (marks of the first run stand: minima, each of a kept
-        // tetrahedron)
+        // kernels again (k_tet_ac2 did nothing the first time)
         auto tet_counted = [&]() {
             const long long q = total_i64(tt.num, groups, s, sc);
             check_total(q, "candidate tetrahedra");

@@ -932,7 +932,8 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra_ac2(Cands cd, PredParam
 // wave where a group has some tens of candidates (four times as many groups in
 // flight: 139 against 191 us at 3M atoms and alpha = 0), else BLOCK, with half
 // the registers for twice the waves (212 against 257 us at 100,000 atoms with
-// solvent-accessible radii; the one-wave blocks fit all at once either way).
+// solvent-accessible radii; the one-wave blocks fit all at once either way). Where
+// a group outgrew its slab nothing is tested: all is run again over counted ranges.
 template <bool SWEEP, int NT>
 __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, PredParams pp, const unsigned char *__restrict__ tgab,
                                                        long long *__restrict__ tri_min, Tets tt, Counters *cnt,
@@ -940,6 +941,10 @@ __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, Pr
     if (stop && *stop) return;
     __shared__ int wtot[2][NT / WAVE];
     const int g = xcd_block();
+    if (cnt->overflow) {  // some group outgrew its slab: all run again, over counted ranges
+        if (threadIdx.x == 0) tt.kept[g] = 0;
+        return;
+    }
     const int qb = tt.base(g), num = min(tt.num[g], tt.room(g));
     const int w = wave_id(), lane = lane_id();
     int kept = 0;
