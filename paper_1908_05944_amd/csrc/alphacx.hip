@@ -429,8 +429,8 @@ static long long total_i64(const int *x, long long n, hipStream_t s, Scope &sc) 
 }
 
 static void check_total(long long t, const char *what) {
-    if (t >= (long long)INT_MAX)
-        throw HipError{AC_E_CAPACITY, std::string("more than 2^31 - 1 ") + what + " (32-bit indices)"};
+    if (!has_index(t))
+        throw HipError{AC_E_CAPACITY, "more than " + std::to_string(INDEX_LAST) + " " + what + " (32-bit indices)"};
 }
 
 static long long isqrt_ceil(long long v) {
@@ -1136,7 +1136,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 std::vector<int> num(groups);
                 read_back(num.data(), tt.num, (size_t)groups, s);
                 fx->tet_most = *std::max_element(num.begin(), num.end());
-                fx->tet_limit = INDEX_MAX / groups;
+                fx->tet_limit = INDEX_LAST / groups;
             }
             tetrahedra();
             tet_ac2();
@@ -1931,7 +1931,7 @@ static void check_measure_args(const ac_complex *c, const double *d_xyz, const d
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev != c->device) throw HipError{AC_E_INVALID, "the complex lives on another device"};
-    if (incidence_count(c) >= INT_MAX) throw HipError{AC_E_CAPACITY, "too many simplex corners"};
+    if (!has_index(incidence_count(c))) throw HipError{AC_E_CAPACITY, "too many simplex corners"};
 }
 
 static Simplices simplices_of(const ac_complex *c) {
@@ -2179,7 +2179,7 @@ static ac_status plan_create(const double *d_xyz, const double *d_r, const Batch
         // grid gets at least a cell per ball (a stopped molecule uses that)
         auto grow = [&](long long v) {
             const double c = std::ceil((double)v * headroom) + 256.0;
-            if (c >= (double)INT_MAX) throw HipError{AC_E_CAPACITY, "planned capacity beyond 2^31"};
+            if (c > (double)INDEX_LAST) throw HipError{AC_E_CAPACITY, "planned capacity beyond 2^31"};
             return (int)c;
         };
         fx.E_cap = grow(fx.E);

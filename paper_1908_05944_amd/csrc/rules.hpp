@@ -5,6 +5,10 @@
 namespace acx {
 
 constexpr long long INDEX_MAX = 0x7fffffffLL;  // the kernels' indices are int32
+// Totals end a few blocks before: the last block's threads, and loops that step by
+// a block, form indices past the end before they compare them with it.
+constexpr long long INDEX_LAST = INDEX_MAX - 4096;
+inline bool has_index(long long total) { return total <= INDEX_LAST; }
 
 // Slots of the one-pass neighbour search (entries a ball). 16 holds every row of
 // the van der Waals workloads at alpha = 0 (largest degree 14); 32 serves grown
@@ -43,7 +47,7 @@ inline int tet_slab(long long sgc, int gshift, int groups, long long most) {
     const int ball = sgc <= 2000 ? 8 : sgc <= 2350 || sgc > APEX_SGC ? 16 : 48;
     long long cap = ((long long)ball << gshift) + (sgc <= 2000 ? 64 : 320);
     cap = cap > most ? cap : most;
-    return (int)(cap * groups > INDEX_MAX ? INDEX_MAX / groups : cap);
+    return (int)(cap * groups > INDEX_LAST ? INDEX_LAST / groups : cap);
 }
 
 // Balls of a group (2^shift, at most 256): enough groups to fill the GPU, else as

@@ -21,6 +21,7 @@ int counts_triangles_in(long long left, long long pairs, long long n, long long 
     return acx::counts_triangles_in(left, pairs, n, E, Nn, g, cap);
 }
 int counts_triangles(long long pairs) { return acx::counts_triangles(pairs); }
+int has_index(long long total) { return acx::has_index(total); }
 int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
@@ -65,7 +66,8 @@ def test_tetrahedron_slabs_have_int32_indices(rules, n):
         for sgc in RADII:
             for most in (0, 1000000):
                 cap = rules.tet_slab(*_L(sgc), gshift, groups, *_L(most))
-                assert 1 <= cap and cap * groups <= INT_MAX, (gshift, sgc, cap)
+                # (loops over a group's tetrahedra step a block past its last)
+                assert 1 <= cap and cap * groups + 256 <= INT_MAX, (gshift, sgc, cap)
 
 
 def test_slab_sizes_where_they_fit(rules):
@@ -116,3 +118,11 @@ def test_pairs_on_fixed_scratch(rules):
     assert not counted(rest + 37 * 5000, 5000) and counted(rest + 37 * 5000 - 1, 5000)
     assert counted(rest - 1, 1) and counted(0, 100)  # nothing left: the triangles need the least
     assert counted(1 << 40, (1 << 28) + 1)
+
+
+def test_totals_leave_room_for_a_block(rules):
+    """The largest radix tile (2,048 items) and two blocks past an accepted total
+    are still int32 indices."""
+    assert not rules.has_index(*_L(INT_MAX)) and rules.has_index(*_L(INT_MAX - 4096))
+    for total in range(INT_MAX - 5000, INT_MAX):
+        assert not rules.has_index(*_L(total)) or total + 2048 + 512 <= INT_MAX
