@@ -680,6 +680,7 @@ struct Fixed {
     std::vector<long long> cells;  // per molecule: grid cells
     PredParams pp{};
     int wmax = 0, gshift = 0;
+    long long rule = 0;  // radius that chooses the kernels
     long long E = 0, P = 0, T = 0, Q = 0;  // candidate edges, pairs, candidate triangles, kept tetrahedra
     long long tet_most = 0;  // candidate tetrahedra of the fullest group where one outgrew its slab, else 0
     long long tet_limit = 0;  // most entries of a slab
@@ -757,13 +758,14 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         MailBox *mb = fixed || t_arena ? nullptr : &mail_box();
         Mail *const mail = mb ? mb->dev : nullptr;
         std::vector<Stats> hs(n_mol);
+        const int wlarge = (int)(LARGE_SGC * LARGE_SGC - aq);
         Stats *st = sc.get<Stats>(n_mol);
         if (n_mol == 1) {
             const int n_tiles = (n + QTILE - 1) / QTILE;
             Stats *part = sc.get<Stats>(n_tiles);
             const unsigned seq = mb ? ++mb->seq : 0;
             const bool one = n_tiles == 1;
-            k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, one ? st : part, cnt, one ? mail : nullptr, seq);
+            k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, wlarge, q, one ? st : part, cnt, one ? mail : nullptr, seq);
             if (!one) k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, mail, seq);
             LAUNCH_CHECK();
             if (mb) hs[0] = mail_wait(*mb, seq, s).st;
@@ -781,16 +783,18 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 HIP_TRY(hipMemcpyAsync(const_cast<int *>(d_tile_first), tile_first.data(), (n_mol + 1) * sizeof(int),
                                        hipMemcpyHostToDevice, s));
             }
-            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, n, q, part, cnt, nullptr, 0);
+            k_quantise<<<(unsigned)tiles.size(), BLOCK, 0, s>>>(d_xyz, d_r, d_tiles, n, wlarge, q, part, cnt, nullptr, 0);
             LAUNCH_CHECK();
             k_stats_reduce<<<(unsigned)n_mol, BLOCK, 0, s>>>(part, d_tile_first, 0, st, nullptr, 0);
             LAUNCH_CHECK();
             if (!fixed) read_back(hs.data(), st, (size_t)n_mol, s);
         }
         int flags = 0, wmax = 0;
+        long long large = 0;
         for (const Stats &x : hs) {
             flags |= x.flags;
             wmax = std::max(wmax, x.wmax);
+            large += x.large;
         }
         if (fixed) wmax = fx->wmax;  // the device checks that no radius exceeds it
         if (flags & 1) throw HipError{AC_E_INVALID, "non-finite coordinate, or radius not positive"};
@@ -917,16 +921,13 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned char *vgab = sc.get<unsigned char>(n);
         long long *vert_min = sc.get<long long>(n);
         const unsigned nbN = grid_for(n);
-        const int slot = neighbour_slot(pp.sgc, n, fx != nullptr);
-        // lanes per ball: the search of a few balls is a chain of dependent
-        // loads; from 2^18 balls on one lane each fills the GPU. Rows of the
-        // widest slot are always shared by four (a lane lists at most 32).
-        const int lpb = slot == NB_SLOT_SAS ? 4 : n >= (1 << 18) ? 1 : n >= (1 << 13) ? 4 : 16;
-        const unsigned nbB = (unsigned)((n + BLOCK / lpb - 1) / (BLOCK / lpb));  // blocks of the search
-        int *nslab = sc.get<int>((size_t)nbB * (BLOCK / lpb) * slot + NBR_PAD);
-        const int nbs = (int)(nbB + 3) & ~3;
-        int *nbtot = sc.get<int>(3 * (size_t)nbs);
-        int *uoff = sc.get<int>(nbB), *poff = sc.get<int>(nbB);
+        // the radius that chooses the kernels (on fixed scratch there is no room for a
+        // second search)
+        long long rule = fixed ? fx->rule : t_arena ? pp.sgc : kernel_radius(pp.sgc, large, n);
+        if (fx && fx->learn) fx->rule = rule;
+        int slot, lpb, nbs;
+        unsigned nbB;  // blocks of the search
+        int *nslab, *nbtot, *uoff, *poff;
         unsigned char *eng = sc.get<unsigned char>(n);
         const int *stop = fixed ? &cnt->stop : nullptr;  // kernels of a stopped recorded build return at once
         // f(SLOT, LPB) with the two as constants
@@ -941,28 +942,44 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             else if (slot == NB_SLOT_WIDE) lanes(integral_constant<int, NB_SLOT_WIDE>{});
             else lanes(integral_constant<int, NB_SLOT>{});
         };
-        tm.mark(ST_NBR_COUNT);
-        with_slot([&](auto sl, auto lp) {
-            constexpr int SLOT = decltype(sl)::value, LPB = decltype(lp)::value;
-            if (n_mol == 1)
-                k_neighbours<SLOT, LPB, true><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
-                                                                   deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
-            else
-                k_neighbours<SLOT, LPB, false><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
-                                                                    deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
-        });
-        LAUNCH_CHECK();
-        tm.mark(ST_NBR_SCAN);
-        const unsigned nbr_seq = mb ? ++mb->seq : 0;
-        k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbB, nbs, uoff, poff, cnt, mail, nbr_seq);
-        LAUNCH_CHECK();
         Counters c0{};
-        if (fixed) {
-            k_plan_guard<<<1, WAVE, 0, s>>>(cnt, fx->E_cap, fx->P_cap);
+        for (;;) {
+            slot = neighbour_slot(rule, n, fx != nullptr);
+            // lanes per ball: the search of a few balls is a chain of dependent
+            // loads; from 2^18 balls on one lane each fills the GPU. Rows of the
+            // widest slot are always shared by four (a lane lists at most 32).
+            lpb = slot == NB_SLOT_SAS ? 4 : n >= (1 << 18) ? 1 : n >= (1 << 13) ? 4 : 16;
+            nbB = (unsigned)((n + BLOCK / lpb - 1) / (BLOCK / lpb));
+            nslab = sc.get<int>((size_t)nbB * (BLOCK / lpb) * slot + NBR_PAD);
+            nbs = (int)(nbB + 3) & ~3;
+            nbtot = sc.get<int>(3 * (size_t)nbs);
+            uoff = sc.get<int>(nbB);
+            poff = sc.get<int>(nbB);
+            tm.mark(ST_NBR_COUNT);
+            with_slot([&](auto sl, auto lp) {
+                constexpr int SLOT = decltype(sl)::value, LPB = decltype(lp)::value;
+                if (n_mol == 1)
+                    k_neighbours<SLOT, LPB, true><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
+                                                                       deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
+                else
+                    k_neighbours<SLOT, LPB, false><<<nbB, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp,
+                                                                        deg_n, deg_up, nslab, nbtot, vgab, vert_min, cnt);
+            });
             LAUNCH_CHECK();
-            c0.E = fx->E_cap;
-        } else {
-            c0 = mb ? mail_wait(*mb, nbr_seq, s).c : read_one(cnt, s);
+            tm.mark(ST_NBR_SCAN);
+            const unsigned nbr_seq = mb ? ++mb->seq : 0;
+            k_nbr_scan<<<1, NBS_BLOCK, 0, s>>>(nbtot, (int)nbB, nbs, uoff, poff, cnt, mail, nbr_seq);
+            LAUNCH_CHECK();
+            if (fixed) {
+                k_plan_guard<<<1, WAVE, 0, s>>>(cnt, fx->E_cap, fx->P_cap);
+                LAUNCH_CHECK();
+                c0.E = fx->E_cap;
+            } else {
+                c0 = mb ? mail_wait(*mb, nbr_seq, s).c : read_one(cnt, s);
+            }
+            if (fx || !c0.overflow || rule == pp.sgc) break;
+            rule = pp.sgc;
+            fill<int>(&cnt->overflow, 0, 1, s);
         }
         if (c0.dup) throw HipError{AC_E_DUPLICATE, "two balls have equal quantised centres"};
         const bool nbr_two_pass = c0.overflow != 0;
@@ -988,7 +1005,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         check_total(c0.Nn, "neighbour entries");
         check_total(c0.E, "candidate edges");
         // room for every pair, or (too many pairs) the counted triangles
-        const int tet_cap = tet_slab(pp.sgc, gshift, groups, fixed ? fx->tet_most : 0);
+        const int tet_cap = tet_slab(rule, gshift, groups, fixed ? fx->tet_most : 0);
         const bool counted = fixed     ? fx->counted
                              : t_arena ? counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn,
                                                              groups, tet_cap)
@@ -1086,7 +1103,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         // Kept tetrahedra are those of the regular triangulation, about 6.8 a
         // ball at most where the radii are large, far fewer at alpha = 0 with
         // van der Waals radii; a group past its slab is counted and run again
-        const bool use_apex = pp.sgc > APEX_SGC;
+        const bool use_apex = rule > APEX_SGC;
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
         Tets tt{};
         tt.cap = tet_cap;
@@ -1111,7 +1128,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         auto tet_ac2 = [&]() {
             // below one candidate a ball, and no balls with thousands (a ball of 1.6 A
             // among 2,942 of 0.09 A: 12 ms by one wave)
-            const bool few = pp.sgc <= 2000 && !nbr_two_pass;
+            const bool few = rule <= 2000 && !nbr_two_pass;
             if (n_alpha > 1 && few)
                 k_tet_ac2<true, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
             else if (n_alpha > 1)
@@ -1555,7 +1572,7 @@ static ac_status run_partitioned(const double *d_xyz, const double *d_r, int64_t
         const int n_tiles = (n + QTILE - 1) / QTILE;
         Stats *part = sc.get<Stats>(n_tiles);
         Stats *st = sc.get<Stats>(1);
-        k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, q, part, nullptr, nullptr, 0);
+        k_quantise<<<n_tiles, BLOCK, 0, s>>>(d_xyz, d_r, nullptr, n, INT_MAX, q, part, nullptr, nullptr, 0);
         k_stats_reduce<<<1, BLOCK, 0, s>>>(part, nullptr, n_tiles, st, nullptr, 0);
         LAUNCH_CHECK();
         const Stats h = read_one(st, s);

@@ -19,6 +19,7 @@ namespace acx {
 struct Stats {
     int minx, miny, minz, maxx, maxy, maxz;
     int wmax, flags;  // flags: 1 invalid value, 2 out of range
+    int large;        // balls of a weight above what k_quantise was given
 };
 
 // Uniform grid (Sec. 4.2). Cells are numbered in row-major order (x fastest;
@@ -99,12 +100,12 @@ __device__ __forceinline__ void mail_post(Mail *mail, unsigned seq) {
 // thread is issued before the first conversion.
 constexpr int QTILE = 1024;  // balls per block
 __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ xyz, const double *__restrict__ r,
-                                                     const int2 *__restrict__ tiles, int n, int4 *__restrict__ q,
+                                                     const int2 *__restrict__ tiles, int n, int wlarge, int4 *__restrict__ q,
                                                      Stats *__restrict__ part, Counters *cnt, Mail *mail, unsigned seq) {
     static_assert(sizeof(Counters) % sizeof(int) == 0 && sizeof(Counters) / sizeof(int) <= BLOCK, "cleared as ints");
     if (cnt && blockIdx.x == 0 && threadIdx.x < sizeof(Counters) / sizeof(int)) reinterpret_cast<int *>(cnt)[threadIdx.x] = 0;
     constexpr int PT = QTILE / BLOCK;
-    int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN}, wmax = 0, flags = 0;
+    int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN}, wmax = 0, flags = 0, large = 0;
     const int2 tile = tiles ? tiles[blockIdx.x]
                             : make_int2((int)blockIdx.x * QTILE, min(((int)blockIdx.x + 1) * QTILE, n));
     double vx[PT][3], vr[PT];
@@ -148,6 +149,7 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
             }
         }
         wmax = max(wmax, W);
+        large += W > wlarge;
         q[i] = make_int4(c[0], c[1], c[2], W);
     }
 #pragma unroll
@@ -159,10 +161,11 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
         }
         wmax = max(wmax, __shfl_xor(wmax, off, WAVE));
         flags |= __shfl_xor(flags, off, WAVE);
+        large += __shfl_xor(large, off, WAVE);
     }
     __shared__ Stats ws[BLOCK / WAVE];
     const int w = threadIdx.x / WAVE;
-    if (lane_id() == 0) ws[w] = Stats{mn[0], mn[1], mn[2], mx[0], mx[1], mx[2], wmax, flags};
+    if (lane_id() == 0) ws[w] = Stats{mn[0], mn[1], mn[2], mx[0], mx[1], mx[2], wmax, flags, large};
     __syncthreads();
     if (threadIdx.x == 0) {
         Stats b = ws[0];
@@ -170,7 +173,7 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
             const Stats &o = ws[k];
             b.minx = min(b.minx, o.minx); b.miny = min(b.miny, o.miny); b.minz = min(b.minz, o.minz);
             b.maxx = max(b.maxx, o.maxx); b.maxy = max(b.maxy, o.maxy); b.maxz = max(b.maxz, o.maxz);
-            b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags;
+            b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags; b.large += o.large;
         }
         part[blockIdx.x] = b;
         if (mail) {
@@ -185,13 +188,13 @@ __global__ void __launch_bounds__(BLOCK) k_quantise(const double *__restrict__ x
 // nullptr), and mails a single molecule's.
 __global__ void __launch_bounds__(BLOCK) k_stats_reduce(const Stats *__restrict__ part, const int *__restrict__ tile_first,
                                                          int n_tiles, Stats *st, Mail *mail, unsigned seq) {
-    Stats b{INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN, 0, 0};
+    Stats b{INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN, 0, 0, 0};
     const int k0 = tile_first ? tile_first[blockIdx.x] : 0, k1 = tile_first ? tile_first[blockIdx.x + 1] : n_tiles;
     for (int k = k0 + threadIdx.x; k < k1; k += BLOCK) {
         const Stats &o = part[k];
         b.minx = min(b.minx, o.minx); b.miny = min(b.miny, o.miny); b.minz = min(b.minz, o.minz);
         b.maxx = max(b.maxx, o.maxx); b.maxy = max(b.maxy, o.maxy); b.maxz = max(b.maxz, o.maxz);
-        b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags;
+        b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags; b.large += o.large;
     }
 #pragma unroll
     for (int off = WAVE / 2; off > 0; off >>= 1) {
@@ -203,6 +206,7 @@ __global__ void __launch_bounds__(BLOCK) k_stats_reduce(const Stats *__restrict_
         b.maxz = max(b.maxz, __shfl_xor(b.maxz, off, WAVE));
         b.wmax = max(b.wmax, __shfl_xor(b.wmax, off, WAVE));
         b.flags |= __shfl_xor(b.flags, off, WAVE);
+        b.large += __shfl_xor(b.large, off, WAVE);
     }
     __shared__ Stats ws[BLOCK / WAVE];
     if (lane_id() == 0) ws[threadIdx.x / WAVE] = b;
@@ -212,7 +216,7 @@ __global__ void __launch_bounds__(BLOCK) k_stats_reduce(const Stats *__restrict_
             const Stats &o = ws[k];
             b.minx = min(b.minx, o.minx); b.miny = min(b.miny, o.miny); b.minz = min(b.minz, o.minz);
             b.maxx = max(b.maxx, o.maxx); b.maxy = max(b.maxy, o.maxy); b.maxz = max(b.maxz, o.maxz);
-            b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags;
+            b.wmax = max(b.wmax, o.wmax); b.flags |= o.flags; b.large += o.large;
         }
         st[blockIdx.x] = b;
         if (mail) {

@@ -19,6 +19,24 @@ constexpr int NB_SLOT = 16;
 constexpr int NB_SLOT_WIDE = 32;
 constexpr int NB_SLOT_SAS = 128;
 
+// Grown radii (mA) beyond which a triangle's apex balls rule out most of its
+// candidate tetrahedra (some 170 a ball, of which 6 are kept).
+constexpr long long APEX_SGC = 2600;
+
+// The radius (mA) that the slots and kernels are chosen by: the largest grown
+// radius sgc, but where that is between 2.6 and 3.4 A for a few of the n balls only
+// (beyond LARGE_SGC: ions among atoms), one whose slots of 32 entries hold their
+// rows and whose kernels suit the rest. 2 million atoms with one ball of 2.75 A: 1,313
+// us against 1,943 with slots of 128 entries (1,112 without that ball), with 10,000
+// such balls 1,388 against 2,017; 100,000 with one 215 against 277. Among atoms at 0.05
+// per A^3 rows have 18 entries at 3 A (26 at most in 50,000), 24 at 3.4 A (33), so past
+// 3 A fewer are few. Where a row outgrows its slot the search runs again with
+// those of sgc (10,000 of 3.3 A: 2,619 against 2,224).
+constexpr long long LARGE_SGC = 1900, SAS_SGC = 3400, FEW_SGC = 2350;
+inline long long kernel_radius(long long sgc, long long large, long long n) {
+    return sgc > APEX_SGC && sgc <= SAS_SGC && large <= n / (sgc <= 3000 ? 32 : 1024) ? FEW_SGC : sgc;
+}
+
 // Slot for n balls of grown radii up to sgc (mA). A row starts at its ball's slot
 // at the latest, so a slot serves while n slots of it have int32 indices: 32
 // entries for every n below 2^26, 128 up to 2^24 - 1 balls. Past that the next
@@ -27,14 +45,10 @@ constexpr int NB_SLOT_SAS = 128;
 // longer it serves the sets with at most NB_SLOT (beads of 3 A some 4.7 A apart, or
 // a few ions among smaller atoms), and needs no slots of 512 bytes a ball for that.
 inline int neighbour_slot(long long sgc, long long n, bool recorded) {
-    const int slot = sgc <= 1900 ? NB_SLOT : sgc <= 2600 ? NB_SLOT_WIDE : sgc <= 3400 ? NB_SLOT_SAS : NB_SLOT;
+    const int slot = sgc <= 1900 ? NB_SLOT : sgc <= 2600 ? NB_SLOT_WIDE : sgc <= SAS_SGC ? NB_SLOT_SAS : NB_SLOT;
     if (slot == NB_SLOT_SAS && recorded) return NB_SLOT;
     return slot == NB_SLOT_SAS && n * slot > INDEX_MAX ? NB_SLOT_WIDE : slot;
 }
-
-// Grown radii (mA) beyond which a triangle's apex balls rule out most of its
-// candidate tetrahedra (some 170 a ball, of which 6 are kept).
-constexpr long long APEX_SGC = 2600;
 
 // Entries of a group's slab of candidate tetrahedra (2^gshift balls a group), for
 // grown radii up to sgc: a ball's share is 2 to 3 times the candidates of dense

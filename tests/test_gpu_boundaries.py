@@ -314,3 +314,29 @@ def test_hubs(acx, k, hub, ball, place):
     _check(acx, xyz, rad, 0.0, f"hub of {k} at {at}")
     m = synth.molecule(300, 33)
     _check(acx, np.vstack([xyz, m.xyz - m.xyz.mean(0) + [30.0, 0, 0]]), np.append(rad, m.radii), 0.0, "hub and molecule")
+
+
+@pytest.mark.parametrize("n", [1025, 9001, 262145])
+@pytest.mark.parametrize("share,radius,alpha", [(0, 2.75, 0.0), (32, 2.75, 0.0), (31, 2.75, 0.0), (1024, 3.4, 0.0), (40, 3.4, 0.0), (40, 2.5, 1.0)])
+@pytest.mark.parametrize("clump", [False, True])
+def test_few_large_balls(acx, n, share, radius, alpha, clump):
+    """One ion, and one ball in 1,024, 40, 32 and 31, spread over a molecule or side by side
+    (rows longer than the slots of 32): as one call, of a batch and of a sweep."""
+    m = synth.molecule(n, 34)
+    k = n // share if share else 1
+    at = np.argsort(((m.xyz - m.xyz.mean(0)) ** 2).sum(1))[:k] if clump else np.arange(k) * (n // k)
+    rad = m.radii.copy()
+    rad[at] = radius
+    _check(acx, m.xyz, rad, alpha, f"{k} of {radius} A")
+    if n > 10000:
+        return
+    X, R = _dev(m.xyz), _dev(rad)
+    single = acx.ac_alpha_complex_device(X, R, alpha)
+    two = acx.ac_alpha_complex_batch(X.repeat(2, 1), R.repeat(2), np.array([0, n, 2 * n]), alpha)
+    for d in range(4):
+        rows, s = two.molecule_rows(d), two.simplices(d)
+        for c in (0, 1):
+            assert np.array_equal(s[rows[c]:rows[c + 1]] - c * n, single.simplices(d)), (c, d)
+    print(f"[case] sweep with {k} of {radius} A n={n}", flush=True)
+    swept = acx.ac_alpha_sweep_device(X, R, [alpha - 0.5, alpha])
+    _same_as(swept[1], single, "sweep")

@@ -25,6 +25,7 @@ int has_index(long long total) { return acx::has_index(total); }
 int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
+int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
 int rows_split(int parts) { return acx::rows_split(parts); }
 }
 """
@@ -57,6 +58,18 @@ def test_slots_where_they_fit(rules):
     for n in (1, 100000, (1 << 24) - 1):
         assert [rules.neighbour_slot(*_L(s, n), 0) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 128, 128, 16]
         assert [rules.neighbour_slot(*_L(s, n), 1) for s in (1900, 1901, 2600, 2601, 3400, 3401)] == [16, 32, 32, 16, 16, 16]
+
+
+def test_a_few_large_balls_do_not_choose_the_kernels(rules):
+    for n in (32, 1024, 100000, 2000000, N_MAX):
+        for sgc, part in ((1700, 0), (2350, 0), (2600, 0), (2601, 32), (3000, 32), (3001, 1024), (3400, 1024), (3401, 0), (8191, 0)):
+            for large in (1, n // 1024, n // 1024 + 1, n // 32, n // 32 + 1):
+                few = part > 0 and large <= n // part
+                got = rules.kernel_radius(*_L(sgc, large, n))
+                assert got == (2350 if few else sgc), (n, sgc, large)
+                if few:
+                    assert rules.neighbour_slot(*_L(got, n), 0) == rules.neighbour_slot(*_L(got, n), 1) == 32
+    assert rules.kernel_radius(*_L(2750, 1, 31)) == 2750
 
 
 @pytest.mark.parametrize("n", [1, 300, 1 << 18, 40000000, 43600000, 43700000, 1 << 25, 1 << 26])
