@@ -909,7 +909,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                 std::swap(pin, pout);
             }
             if (n > KS_SEARCH) key_starts(kin, n, shift, nb, start, s);
-            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, n > KS_SEARCH ? start : nullptr, n, shift, ncell, q, pout, cell_start, atom, sball,
+            k_bin_finish<<<nb, BIN_BLOCK, 0, s>>>(kin, pin, n > KS_SEARCH ? start : nullptr, n, shift, ncell, q, pout, kout, cell_start, atom, sball,
                                                    (int)aq, perm, cnt);
             LAUNCH_CHECK();
         }

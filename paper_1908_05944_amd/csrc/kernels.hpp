@@ -303,14 +303,16 @@ constexpr int BIN_CELLS = 1 << BIN_SHIFT;
 // Balls of a cell up to which its balls are compared with each other: both for
 // their order and for equal centres. A bucket with a fuller cell, or with more
 // than BIN_ROWS balls, goes in chunks with a counter per cell, and looks for equal
-// centres among balls of equal hashes.
+// centres among balls of equal hashes (of centre and cell: the bucket's cells may
+// be several molecules').
 constexpr int BIN_CROWD = 256;
 
-// Hash of a centre (coordinates below 2^20): Fibonacci hashing of the 63 bits.
-__device__ __forceinline__ int centre_hash(const int4 &a) {
+// Hash of a centre (coordinates below 2^20) and its cell: Fibonacci hashing of the
+// centre's 63 bits, turned by the cell's.
+__device__ __forceinline__ int centre_hash(const int4 &a, unsigned cell) {
     const unsigned long long k = ((unsigned long long)(a.x & 0x1fffff) << 42) | ((unsigned long long)(a.y & 0x1fffff) << 21) |
                                  (unsigned long long)(a.z & 0x1fffff);
-    return (int)((k * 0x9E3779B97F4A7C15ull) >> (64 - BIN_SHIFT));
+    return (int)((k * 0x9E3779B97F4A7C15ull) >> (64 - BIN_SHIFT)) ^ (int)((cell * 0x9E3779B9u) >> (32 - BIN_SHIFT));
 }
 
 // Exclusive scan of cnt[0..m) in place (m <= BIN_CELLS, all threads).
@@ -333,12 +335,13 @@ __device__ __forceinline__ void bin_scan(int *cnt, int m) {
 
 // start: first ball of every bucket (nb + 1 entries), or nullptr (searched for). Inside a cell the balls
 // keep input order (the radix passes are stable; the LDS places of a cell are
-// ranked). gidx: n entries of scratch, for a crowded bucket (BIN_CROWD). A build of
+// ranked). gidx, gcell: n entries of scratch each, for a crowded bucket (BIN_CROWD). A build of
 // 16,000 balls in one cell 3.9 ms, 146 when the block compared all with each other;
 // of 100,000 49 ms, 5,550.
 __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__restrict__ key, const unsigned *__restrict__ idx,
                                                            const int *__restrict__ start, int n, int shift, long long ncell,
                                                            const int4 *__restrict__ q, unsigned *__restrict__ gidx,
+                                                           unsigned *__restrict__ gcell,
                                                            int *__restrict__ cell_start, int4 *__restrict__ atom,
                                                            int2 *__restrict__ sball, int aq, int *__restrict__ perm,
                                                            Counters *cnt) {
@@ -429,27 +432,29 @@ __global__ void __launch_bounds__(BIN_BLOCK) k_bin_finish(const unsigned *__rest
             atom[s + at] = a;
             sball[s + at] = scan_ball(a, aq);
             perm[s + at] = (int)id;
+            gcell[s + at] = (unsigned)c;
         }
     }
-    // equal centres: the balls by hash, each compared with those of its own
+    // equal centres in a cell: the balls by hash, each compared with those of its own
     for (int c = t; c < BIN_CELLS; c += BIN_BLOCK) cc[c] = 0;
     __threadfence_block();
     __syncthreads();
-    for (int p = t; p < rows; p += BIN_BLOCK) atomicAdd(&cc[centre_hash(atom[s + p])], 1);
+    for (int p = t; p < rows; p += BIN_BLOCK) atomicAdd(&cc[centre_hash(atom[s + p], gcell[s + p])], 1);
     __syncthreads();
     bin_scan(cc, BIN_CELLS);
-    for (int p = t; p < rows; p += BIN_BLOCK) gidx[s + atomicAdd(&cc[centre_hash(atom[s + p])], 1)] = (unsigned)p;
+    for (int p = t; p < rows; p += BIN_BLOCK) gidx[s + atomicAdd(&cc[centre_hash(atom[s + p], gcell[s + p])], 1)] = (unsigned)p;
     __threadfence_block();
     __syncthreads();
     bool dup = false;
     for (int p = t; p < rows && !dup; p += BIN_BLOCK) {
         const int4 a = atom[s + p];
-        const int h = centre_hash(a);
+        const unsigned c = gcell[s + p];
+        const int h = centre_hash(a, c);
         for (int y = h > 0 ? cc[h - 1] : 0; y < cc[h] && !dup; y++) {
             const unsigned o = gidx[s + y];
             if ((int)o >= p) continue;
             const int4 v = atom[s + o];
-            dup = v.x == a.x && v.y == a.y && v.z == a.z;
+            dup = v.x == a.x && v.y == a.y && v.z == a.z && gcell[s + o] == c;
         }
     }
     if (dup) cnt->dup = 1;

@@ -285,6 +285,29 @@ def test_equal_centres_are_found(acx, n, cell, first, second):
     assert ei.value.status == 2
 
 
+@pytest.mark.parametrize("n,copies", [(300, 9), (300, 70), (2500, 3), (20, 2000)])
+@pytest.mark.parametrize("cell", [0, 60000])
+def test_equal_centres_of_molecules_in_crowded_buckets(acx, n, copies, cell):
+    """Copies of a molecule at the same place, whose cells share crowded buckets, are
+    no equal centres; two equal ones inside the last copy are."""
+    m = synth.molecule(n, 80)
+    X, R, off = _dev(m.xyz).repeat(copies, 1), _dev(m.radii).repeat(copies), np.arange(copies + 1, dtype=np.int64) * n
+    options = {"cell_mA": cell} if cell else None
+    print(f"[case] {copies} copies of {n} at one place, cell {cell}", flush=True)
+    got = acx.ac_alpha_complex_batch(X, R, off, 0.0, options=options)
+    single = acx.ac_alpha_complex_device(X[:n].clone(), R[:n].clone(), 0.0)
+    for d in range(4):
+        rows, s, z = got.molecule_rows(d), got.simplices(d), got.sizes(d)
+        assert np.array_equal(np.diff(rows), np.full(copies, single.count(d))), d
+        for k in (0, copies // 2, copies - 1):
+            assert np.array_equal(s[rows[k]:rows[k + 1]] - off[k], single.simplices(d)), (d, k)
+            assert np.array_equal(z[rows[k]:rows[k + 1]], single.sizes(d)), (d, k)
+    X[-1] = X[-n]
+    with pytest.raises(acx.AlphaCxError) as ei:
+        acx.ac_alpha_complex_batch(X, R, off, 0.0, options=options)
+    assert ei.value.status == 2
+
+
 @pytest.mark.parametrize("n", [40, 300, 1500])
 @pytest.mark.parametrize("grow_mA,alpha", [(2000, 0.0), (3500, 0.0), (4500, -20.0)])
 def test_long_rows_in_few_balls(acx, n, grow_mA, alpha):
