@@ -1005,6 +1005,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         check_total(c0.Nn, "neighbour entries");
         check_total(c0.E, "candidate edges");
         // room for every pair, or (too many pairs) the counted triangles
+        if (nbr_two_pass && rule < SAS_SGC && long_rows(c0.P, c0.E) &&
+            !(t_arena && counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn, groups,
+                                             tet_slab(SAS_SGC, gshift, groups, 0))))
+            rule = SAS_SGC;
         const int tet_cap = tet_slab(rule, gshift, groups, fixed ? fx->tet_most : 0);
         const bool counted = fixed     ? fx->counted
                              : t_arena ? counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn,

@@ -363,3 +363,28 @@ def test_few_large_balls(acx, n, share, radius, alpha, clump):
     print(f"[case] sweep with {k} of {radius} A n={n}", flush=True)
     swept = acx.ac_alpha_sweep_device(X, R, [alpha - 0.5, alpha])
     _same_as(swept[1], single, "sweep")
+
+
+@pytest.mark.parametrize("n,rows", [(40, 30), (150, 60), (150, 140), (700, 40), (700, 100)])
+@pytest.mark.parametrize("beside", [0, 9000])
+def test_small_balls_close_together(acx, n, rows, beside):
+    """Long rows of small radii, alone and beside a molecule (whose short rows keep
+    the kernels of small radii), also without allocation."""
+    import torch
+    rng = np.random.RandomState(n + rows)
+    side = (n * 4 / 3 * np.pi * 0.8 ** 3 / rows) ** (1 / 3)
+    xyz, rad = rng.uniform(-side / 2, side / 2, (n, 3)), rng.uniform(0.35, 0.45, n)
+    if beside:
+        m = synth.molecule(beside, 35)
+        xyz, rad = np.vstack([xyz, m.xyz - m.xyz.mean(0) + [90.0, 0, 0]]), np.append(rad, m.radii)
+    _check(acx, xyz, rad, 0.0, f"rows of {rows}")
+    X, R = _dev(xyz), _dev(rad)
+    single = acx.ac_alpha_complex_device(X, R, 0.0)
+    simp = [torch.empty((single.count(d), d + 1), dtype=torch.int32, device="cuda:0") for d in range(4)]
+    size = [torch.empty(single.count(d), dtype=torch.float64, device="cuda:0") for d in range(4)]
+    assert list(acx.ac_alpha_complex_noalloc(X, R, 0.0, simp, size)) == list(single.counts())
+    torch.cuda.synchronize()
+    for d in range(4):
+        assert np.array_equal(simp[d].cpu().numpy(), single.simplices(d)), d
+        assert np.array_equal(size[d].cpu().numpy(), single.sizes(d)), d
+    _same_as(acx.ac_alpha_sweep_device(X, R, [0.0, -0.05])[0], single, "sweep")

@@ -26,6 +26,7 @@ int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
 int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
+int long_rows(long long pairs, long long edges) { return acx::long_rows(pairs, edges); }
 int rows_split(int parts) { return acx::rows_split(parts); }
 }
 """
@@ -139,3 +140,9 @@ def test_totals_leave_room_for_a_block(rules):
     assert not rules.has_index(*_L(INT_MAX)) and rules.has_index(*_L(INT_MAX - 4096))
     for total in range(INT_MAX - 5000, INT_MAX):
         assert not rules.has_index(*_L(total)) or total + 2048 + 512 <= INT_MAX
+
+
+def test_long_rows(rules):
+    """On both sides of 16 later entries a row, and at the largest totals."""
+    for edges in (0, 1, 100, 35525, INT_MAX - 4096):
+        assert not rules.long_rows(*_L(8 * edges, edges)) and rules.long_rows(*_L(8 * edges + 1, edges))
