@@ -921,9 +921,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         unsigned char *vgab = sc.get<unsigned char>(n);
         long long *vert_min = sc.get<long long>(n);
         const unsigned nbN = grid_for(n);
-        // the radius that chooses the kernels (on fixed scratch there is no room for a
-        // second search)
-        long long rule = fixed ? fx->rule : t_arena ? pp.sgc : kernel_radius(pp.sgc, large, n);
+        // the radius that chooses the kernels
+        long long rule = fixed ? fx->rule : kernel_radius(pp.sgc, large, n);
         if (fx && fx->learn) fx->rule = rule;
         int slot, lpb, nbs;
         unsigned nbB;  // blocks of the search
@@ -977,7 +976,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             } else {
                 c0 = mb ? mail_wait(*mb, nbr_seq, s).c : read_one(cnt, s);
             }
-            if (fx || !c0.overflow || rule == pp.sgc) break;
+            // (fixed scratch has no room for the wide slots too: the counted search)
+            if (fx || t_arena || !c0.overflow || rule == pp.sgc) break;
             rule = pp.sgc;
             fill<int>(&cnt->overflow, 0, 1, s);
         }
@@ -1041,7 +1041,9 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             scan_i32(deg_n, nbr_start, n, s, sc);
             scan_i32(deg_up, up_start, n, s, sc);
             if (!counted) scan_i32(pairs, pair_base, groups, s, sc);
-            int *up_scan = sc.get<int>(E1), *id_scan = sc.get<int>(E1);
+            // the search's slabs are free again
+            const bool in_slab = 2 * E1 <= (size_t)nbB * (BLOCK / lpb) * slot;
+            int *up_scan = in_slab ? nslab : sc.get<int>(E1), *id_scan = in_slab ? nslab + E1 : sc.get<int>(E1);
             k_nbr_rows<true><<<nbN, BLOCK, 0, s>>>(atom, sball, perm, n, d_grids, n_mol, g0, cell_start, pp, nullptr, nullptr,
                                                   nullptr, nbr_start, up_start, nbr, up_scan, edge_i, vert_min, cnt);
             k_up_ids<<<grid_for(E), BLOCK, 0, s>>>(up_scan, E, perm, id_scan);

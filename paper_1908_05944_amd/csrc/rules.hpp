@@ -26,13 +26,13 @@ constexpr long long APEX_SGC = 2600;
 // The radius (mA) that the slots and kernels are chosen by: the largest grown
 // radius sgc, but where that is between 2.6 and 3.4 A for a few of the n balls only
 // (beyond LARGE_SGC: ions among atoms), one whose slots of 32 entries hold their
-// rows and whose kernels suit the rest. 2 million atoms with one ball of 2.75 A: 1,313
+// rows and whose kernels suit the rest. 2 million atoms with one ball of 2.75 A: 1,289
 // us against 1,943 with slots of 128 entries (1,112 without that ball), with 10,000
-// such balls 1,388 against 2,017; 100,000 with one 215 against 277. Among atoms at 0.05
+// such balls 1,365 against 2,017; 100,000 with one 196 against 277. Among atoms at 0.05
 // per A^3 rows have 18 entries at 3 A (26 at most in 50,000), 24 at 3.4 A (33), so past
 // 3 A fewer are few. Where a row outgrows its slot the search runs again with
-// those of sgc (10,000 of 3.3 A: 2,619 against 2,224).
-constexpr long long LARGE_SGC = 1900, SAS_SGC = 3400, FEW_SGC = 2350;
+// those of sgc (10,000 of 3.3 A: 2,619 against 2,224), on fixed scratch the counted one.
+constexpr long long LARGE_SGC = 1900, SAS_SGC = 3400, FEW_SGC = 2000;
 inline long long kernel_radius(long long sgc, long long large, long long n) {
     return sgc > APEX_SGC && sgc <= SAS_SGC && large <= n / (sgc <= 3000 ? 32 : 1024) ? FEW_SGC : sgc;
 }

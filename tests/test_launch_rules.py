@@ -67,7 +67,7 @@ def test_a_few_large_balls_do_not_choose_the_kernels(rules):
             for large in (1, n // 1024, n // 1024 + 1, n // 32, n // 32 + 1):
                 few = part > 0 and large <= n // part
                 got = rules.kernel_radius(*_L(sgc, large, n))
-                assert got == (2350 if few else sgc), (n, sgc, large)
+                assert got == (2000 if few else sgc), (n, sgc, large)
                 if few:
                     assert rules.neighbour_slot(*_L(got, n), 0) == rules.neighbour_slot(*_L(got, n), 1) == 32
     assert rules.kernel_radius(*_L(2750, 1, 31)) == 2750

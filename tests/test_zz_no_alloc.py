@@ -190,3 +190,18 @@ def test_many_pairs_and_few_triangles(acx, k):
         print(f"[case] noalloc hub of {k}, last={last}", flush=True)
         counts = acx.ac_alpha_complex_noalloc(X, R, 0.0, simp, size)
         _check_same(counts, simp, size, ref, f"hub {k}")
+
+
+@pytest.mark.parametrize("n,large,radius", [(416000, 1, 2.75), (416000, 1, 5.0), (9001, 200, 2.75), (9001, 8, 3.4)])
+def test_few_large_balls(acx, n, large, radius):
+    """One large ball does not take the scratch of many atoms; some side by side whose
+    rows outgrow their slots."""
+    m = synth.molecule(n, 36)
+    rad = m.radii.copy()
+    rad[np.argsort(((m.xyz - m.xyz.mean(0)) ** 2).sum(1))[:large]] = radius
+    X, R = _dev(m.xyz), _dev(rad)
+    ref = _reference(acx, X, R, 0.0, None)
+    simp, size = _buffers([len(ref[d][0]) for d in range(4)])
+    print(f"[case] noalloc {n} with {large} of {radius} A", flush=True)
+    counts = acx.ac_alpha_complex_noalloc(X, R, 0.0, simp, size)
+    _check_same(counts, simp, size, ref, f"{large} of {radius}")
