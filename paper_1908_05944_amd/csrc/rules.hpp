@@ -82,6 +82,16 @@ inline int group_shift(long long n, int slot, long long edges) {
     return shift;
 }
 
+// Later entries of an edge's row as the sum over the edges that a block of
+// k_triangles holds takes them, when it asks whether that is more than PAIRS_LONG
+// (then shorter rows take their place where there are any): the sum stays an int32 also
+// for rows of millions.
+constexpr int EDGES_HELD = 512, PAIRS_LONG = 8192;
+constexpr int later_counted(int later) {
+    constexpr int most = (int)(INDEX_MAX / EDGES_HELD);
+    return later < most ? later : most;
+}
+
 // Blocks that share a part of the balls in the AC2 test over rows in memory: some
 // 4,096 in all, and no more than 32 a part (most parts have no work for more).
 inline int rows_split(int parts) {

@@ -411,6 +411,7 @@ __device__ __forceinline__ bool tet_ac2(const Cands &cd, const Tet &ts, const Pr
 // (In every build, the test of has_long costs 0.8 % at 3M atoms.)
 constexpr int EDGE_PT = 2, EDGE_CH = EDGE_PT * BLOCK, EDGE_AHEAD = 64;
 constexpr int LONG_ROW = 64, LONG_PAIRS = 4 * PAIR_WIN;
+static_assert(EDGE_CH == EDGES_HELD && LONG_PAIRS == PAIRS_LONG, "later_counted");
 constexpr int LONG_EDGE = 0x80;  // in part_no: the items of the edge are j's upper entries
 template <bool COUNT, bool LONG>
 __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, long long *__restrict__ tri_min, Counters *cnt,
@@ -439,8 +440,10 @@ __global__ void __launch_bounds__(BLOCK) k_triangles(Cands cd, PredParams pp, lo
             later[u] = e < e1 ? cd.up_start[i + 1] - e - 1 : 0;
             part_no[threadIdx.x * EDGE_PT + u] = (unsigned char)((i - b0) >> cd.sshift);
         }
-        int pairs;
-        int off = pair_scan<EDGE_PT>(later, soff, &pairs);
+        int pairs, some[EDGE_PT];
+#pragma unroll
+        for (int u = 0; u < EDGE_PT; u++) some[u] = LONG ? later_counted(later[u]) : later[u];
+        int off = pair_scan<EDGE_PT>(some, soff, &pairs);
         const bool has_long = LONG && pairs > LONG_PAIRS;
         if (has_long) {
 #pragma unroll

@@ -26,6 +26,7 @@ int inc_passes(long long n) { return acx::inc_buckets(n).passes; }
 int inc_shift(long long n) { return acx::inc_buckets(n).shift; }
 int group_shift(long long n, int slot, long long edges) { return acx::group_shift(n, slot, edges); }
 int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
+int later_counted(int later) { return acx::later_counted(later); }
 int long_rows(long long pairs, long long edges) { return acx::long_rows(pairs, edges); }
 int rows_split(int parts) { return acx::rows_split(parts); }
 }
@@ -146,3 +147,10 @@ def test_long_rows(rules):
     """On both sides of 16 later entries a row, and at the largest totals."""
     for edges in (0, 1, 100, 35525, INT_MAX - 4096):
         assert not rules.long_rows(*_L(8 * edges, edges)) and rules.long_rows(*_L(8 * edges + 1, edges))
+
+
+def test_later_entries_of_the_edges_held(rules):
+    """Their sum is an int32 for rows of any length, and still says which are long."""
+    for later in (0, 1, 64, 8192, 8193, (1 << 22) - 1, 1 << 22, 5000000, N_MAX):
+        got = rules.later_counted(later)
+        assert 512 * got <= INT_MAX and (got == later or later > got > 8192)
