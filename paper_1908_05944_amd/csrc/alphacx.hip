@@ -1132,18 +1132,21 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             LAUNCH_CHECK();
         };
         auto tet_ac2 = [&]() {
-            // below one candidate a ball, and no balls with thousands (a ball of 1.6 A
-            // among 2,942 of 0.09 A: 12 ms by one wave)
-            const bool few = rule <= 2000 && !nbr_two_pass;
-            if (n_alpha > 1 && few)
-                k_tet_ac2<true, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
-            else if (n_alpha > 1)
-                k_tet_ac2<true, BLOCK><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
-            else if (few)
-                k_tet_ac2<false, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
-            else
-                k_tet_ac2<false, BLOCK><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
-            LAUNCH_CHECK();
+            const bool few = rule <= 2000;  // below one candidate a ball
+            auto run = [&](auto sweep) {
+                constexpr bool SW = decltype(sweep)::value;
+                if (nbr_two_pass) {
+                    k_tet_test<<<dim3(groups, tests_split(groups)), BLOCK, 0, s>>>(cd, pp, tt, cnt);
+                    k_tet_ac2<SW, BLOCK, true><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+                } else if (few) {
+                    k_tet_ac2<SW, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+                } else {
+                    k_tet_ac2<SW, BLOCK><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
+                }
+                LAUNCH_CHECK();
+            };
+            if (n_alpha > 1) run(std::true_type{});
+            else run(std::false_type{});
         };
         // counted ranges for every group's tetrahedra, after an overflow: both
         // kernels again (k_tet_ac2 did nothing the first time)

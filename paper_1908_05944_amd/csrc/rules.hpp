@@ -99,6 +99,13 @@ inline int rows_split(int parts) {
     return k < 1 ? 1 : k > 32 ? 32 : k;
 }
 
+// Blocks that share a group's tetrahedra in the same: eight at least, since one ball of
+// a large molecule may have nearly all.
+inline int tests_split(int groups) {
+    const int k = rows_split(groups);
+    return k < 8 ? 8 : k;
+}
+
 // Pairs of upper entries a build makes room for (PAIR_BYTES each); past it the
 // candidate triangles are counted first. A recorded build decides once, on the
 // pairs that its headroom asks for.

@@ -951,7 +951,23 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra_ac2(Cands cd, PredParam
 // the registers for twice the waves (212 against 257 us at 100,000 atoms with
 // solvent-accessible radii; the one-wave blocks fit all at once either way). Where
 // a group outgrew its slab nothing is tested: all is run again over counted ranges.
-template <bool SWEEP, int NT>
+// TESTED: after a counted neighbour search k_tet_test has done the walks, with several
+// blocks a group: a ball with thousands of neighbours has thousands of candidates,
+// each with the walk along its row (1,334 small balls around one, all grown: a build
+// 20.4 ms by the one block of its group, 6.7 as this).
+__global__ void __launch_bounds__(BLOCK, 8) k_tet_test(Cands cd, PredParams pp, Tets tt, Counters *cnt) {
+    const int g = xcd_block();
+    if (cnt->overflow) return;
+    const int qb = tt.base(g), num = min(tt.num[g], tt.room(g));
+    for (int x = (int)blockIdx.y * BLOCK + (int)threadIdx.x; x < num; x += (int)gridDim.y * BLOCK) {
+        const int t = tt.t[qb + x], t2 = tt.t2[qb + x];
+        const int e = cd.tri_e[t];
+        const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[cd.tri_f[t]], l = cd.up[cd.tri_f[t2]];
+        if (!tet_ac2(cd, tet_setup(cd.atom[i], cd.atom[j], cd.atom[k], cd.atom[l], pp), pp, i, j, k, l, cnt))
+            tt.t2[qb + x] = ~t2;
+    }
+}
+template <bool SWEEP, int NT, bool TESTED = false>
 __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, PredParams pp, const unsigned char *__restrict__ tgab,
                                                        long long *__restrict__ tri_min, Tets tt, Counters *cnt,
                                                        const int *__restrict__ stop) {
@@ -972,11 +988,16 @@ __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, Pr
         if (x < num) {
             t = tt.t[qb + x];
             t2 = tt.t2[qb + x];
-            f2 = cd.tri_f[t2];
-            const int e = cd.tri_e[t];
-            const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[cd.tri_f[t]], l = cd.up[f2];
-            const int4 vi = cd.atom[i], vj = cd.atom[j], vk = cd.atom[k], vl = cd.atom[l];
-            keep = tet_ac2(cd, tet_setup(vi, vj, vk, vl, pp), pp, i, j, k, l, cnt);
+            if constexpr (TESTED) {
+                keep = t2 >= 0;
+                f2 = cd.tri_f[keep ? t2 : ~t2];
+            } else {
+                f2 = cd.tri_f[t2];
+                const int e = cd.tri_e[t];
+                const int i = cd.edge_i[e], j = cd.up[e], k = cd.up[cd.tri_f[t]], l = cd.up[f2];
+                const int4 vi = cd.atom[i], vj = cd.atom[j], vk = cd.atom[k], vl = cd.atom[l];
+                keep = tet_ac2(cd, tet_setup(vi, vj, vk, vl, pp), pp, i, j, k, l, cnt);
+            }
         }
         const unsigned long long mask = __ballot(keep);
         if (lane == 0) wtot[turn][w] = __popcll(mask);

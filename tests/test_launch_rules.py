@@ -28,6 +28,7 @@ int group_shift(long long n, int slot, long long edges) { return acx::group_shif
 int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
 int later_counted(int later) { return acx::later_counted(later); }
 int long_rows(long long pairs, long long edges) { return acx::long_rows(pairs, edges); }
+int tests_split(int groups) { return acx::tests_split(groups); }
 int rows_split(int parts) { return acx::rows_split(parts); }
 }
 """
@@ -123,6 +124,7 @@ def test_groups(rules):
 @pytest.mark.parametrize("parts", [1, 17, 128, 129, 4095, 4096, 4097, N_MAX])
 def test_blocks_of_a_part(rules, parts):
     assert rules.rows_split(parts) == min(32, max(1, 4096 // parts))
+    assert rules.tests_split(parts) == min(32, max(8, 4096 // parts))
 
 
 def test_pairs_on_fixed_scratch(rules):
