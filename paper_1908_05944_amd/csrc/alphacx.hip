@@ -471,11 +471,6 @@ static void radix_sort(unsigned *&key, P *&pay, int n, int lo, int hi, hipStream
     if (spare_pay) *spare_pay = pout;
 }
 
-template <class P>
-static void radix_sort(unsigned *&key, P *&pay, int n, int bits, hipStream_t s, Scope &sc) {
-    radix_sort<P>(key, pay, n, 0, bits, s, sc);
-}
-
 static int bits_for(long long n) {
     int b = 1;
     while ((1LL << b) < n) b++;
@@ -486,12 +481,10 @@ static int bits_for(long long n) {
 // their least input id (< n); a bucket is 2^shift ids, at most EK_KEYS, at
 // least 256 buckets where n allows (so that small inputs still spread over
 // many blocks), and small enough that the expected largest bucket, 2^shift K
-// M / n rows, stays within 95% of what a block orders in LDS; `drop` is the
-// first key of the bucket after those of every id, and keys up to it fit in
-// `bits` bits. The radix sort orders bits [shift, bits).
+// M / n rows, stays within 95% of what a block orders in LDS; nb buckets hold
+// every id, and keys fit in `bits` bits. The radix sort orders bits [shift, bits).
 struct EmitKeys {
-    int bits, shift;
-    unsigned drop;
+    int bits, shift, nb;
 };
 template <int K>
 static EmitKeys emit_keys(int n, long long M) {
@@ -500,8 +493,8 @@ static EmitKeys emit_keys(int n, long long M) {
     while (k.shift > 0 && ((n >> k.shift) < 256 ||
                            (double)(1LL << k.shift) * K * (double)M > 0.95 * ek_rows<K>() * (double)n))
         k.shift--;
-    k.drop = (unsigned)((((long long)n >> k.shift) + 1) << k.shift);
-    k.bits = bits_for((long long)k.drop + 1);
+    k.nb = ((n - 1) >> k.shift) + 1;
+    k.bits = bits_for(n);
     return k;
 }
 
@@ -531,7 +524,7 @@ static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double
     if (n <= EK_KEYS && M <= ek_rows<K>()) {
         // a few hundred balls: one block orders every row, no radix sort
         k_emit_block<K><<<1, EK_BLOCK, 0, s>>>(key, pay, nullptr, EK_SHIFT, 1, nullptr, nullptr, size_in,
-                                              res->d_simp[d], res->d_size[d], m_out, n, M);
+                                              res->d_simp[d], res->d_size[d], m_out, M);
         LAUNCH_CHECK();
         return;
     }
@@ -539,7 +532,7 @@ static void emit_dim(unsigned *key, typename EmitPay<K>::type *pay, const double
     unsigned *gkey = nullptr;
     P *gpay = nullptr;
     radix_sort<P>(key, pay, M, ek.shift, ek.bits, s, sc, &gkey, &gpay);
-    const int nb = (int)(ek.drop >> ek.shift);
+    const int nb = ek.nb;
     int *start = sc.get<int>((size_t)nb + 1);
     key_starts(key, M, ek.shift, nb, start, s);
     LAUNCH_CHECK();

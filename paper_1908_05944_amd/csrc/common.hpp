@@ -56,20 +56,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
     return v;
 }
 
-// Append one item per lane where pred holds; returns the slot (or -1). Must be
-// reached by every active lane of the wave together.
-__device__ __forceinline__ int wave_append(int *counter, bool pred) {
-    const unsigned long long mask = __ballot(pred);
-    if (mask == 0) return -1;
-    const int lane = lane_id();
-    const int leader = __ffsll((long long)mask) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(counter, __popcll(mask));
-    base = __shfl(base, leader, WAVE);
-    const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-    return pred ? base + rank : -1;
-}
-
 // Exclusive prefix sum over a block of nthreads (a multiple of 64) threads;
 // every thread of the block must call it. *total receives the block's sum.
 template <int NT>

@@ -119,18 +119,14 @@ __device__ __forceinline__ bool ids_less(const unsigned (&v)[3], const unsigned 
     return v[0] != r[0] ? v[0] < r[0] : (v[1] != r[1] ? v[1] < r[1] : v[2] < r[2]);
 }
 
-// Block b finishes bucket b (b < nb, the drop key's bucket): its rows
-// [start[b], start[b + 1]) of key / pay are written, in order, to out /
-// out_size at the same places (every row before the bucket belongs to smaller
-// ids). Block 0 writes the kept count start[nb] to *m_out. gkey / gpay (m
-// entries) are scratch for a bucket with more than ek_rows<K>() rows. Sizes are
-// converted from mA^2 to A^2 when to_A2 is set (emit of a build), else copied
-// (merge of rows that are already output).
-// single > 0: one block takes every row unsorted (at most ek_rows<K>(), ids
-// below single <= EK_KEYS, shift EK_SHIFT): the rows whose key is single or
-// more are dropped ones and skipped, and the block writes the kept count.
-// `start` is then unused and the row count is rows_in. A few hundred balls
-// then need no radix sort.
+// Block b finishes bucket b (b < nb): its rows [start[b], start[b + 1]) of key /
+// pay are written, in order, to out / out_size at the same places (every row
+// before the bucket belongs to smaller ids), with their Sizes as they are. Block 0
+// writes the row count start[nb] to *m_out. gkey / gpay (m entries) are scratch
+// for a bucket with more than ek_rows<K>() rows.
+// start = nullptr: one block takes every row unsorted (rows_in, at most
+// ek_rows<K>(); ids below EK_KEYS, shift EK_SHIFT). A few hundred balls then need
+// no radix sort.
 template <int K>
 __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restrict__ key,
                                                           const typename EmitPay<K>::type *__restrict__ pay,
@@ -139,7 +135,7 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
                                                           typename EmitPay<K>::type *__restrict__ gpay,
                                                           const double *__restrict__ size_in,
                                                           int *__restrict__ out, double *__restrict__ out_size,
-                                                          int *__restrict__ m_out, int single = 0, int rows_in = 0) {
+                                                          int *__restrict__ m_out, int rows_in = 0) {
     constexpr int NI = K - 1;  // ids after the least
     constexpr bool SLIM = ek_slim<K>();
     constexpr int NW = SLIM ? NI : (K == 2 ? 3 : 4);  // payload words held in LDS
@@ -149,15 +145,14 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
     __shared__ unsigned short sord[ROWS];   // load positions in id order
     // rows per id; then each id's first place; after the ordering, where each
     // id's group ends (= the next id's first place)
-    __shared__ int cnt[EK_KEYS + 1];
+    __shared__ int cnt[EK_KEYS];
     __shared__ int wsum[EK_BLOCK / WAVE];
-    constexpr unsigned short DROPPED = 0xFFFF;  // skey of a skipped row (single block)
     const int b = blockIdx.x, t = threadIdx.x;
-    const bool one = single > 0;
-    if (!one && b == 0 && t == 0) *m_out = start[nb];
+    const bool one = start == nullptr;
+    if (b == 0 && t == 0) *m_out = one ? rows_in : start[nb];
     const int bs = one ? 0 : start[b], rows = one ? rows_in : start[b + 1] - bs;
     const unsigned k0 = (unsigned)b << shift;  // the bucket's ids: [k0, k0 + 2^shift), 2^shift <= EK_KEYS
-    for (int k = t; k <= EK_KEYS; k += EK_BLOCK) cnt[k] = 0;
+    for (int k = t; k < EK_KEYS; k += EK_BLOCK) cnt[k] = 0;
     __syncthreads();
     const bool lds = rows <= ROWS;
     // counts per id (and, in LDS, the rows' ids); four rows per thread loaded
@@ -175,10 +170,9 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
         for (int u = 0; u < 4; u++) {
             const int p = p0 + u * EK_BLOCK;
             if (p >= rows) continue;
-            const bool drop = one && kk[u] >= (unsigned)single;  // k0 = 0 in a single block
-            if (!drop) atomicAdd(&cnt[kk[u]], 1);
+            atomicAdd(&cnt[kk[u]], 1);
             if (lds) {
-                skey[p] = drop ? DROPPED : (unsigned short)kk[u];
+                skey[p] = (unsigned short)kk[u];
                 sid[0][p] = q[u].x;
                 if constexpr (NW >= 2) sid[1][p] = q[u].y;
                 if constexpr (NW >= 3) sid[2][p] = q[u].z;
@@ -207,20 +201,14 @@ __global__ void __launch_bounds__(EK_BLOCK) k_emit_block(const unsigned *__restr
             cnt[t * PT + u] = run;
             run += c[u];
         }
-        if (t == EK_BLOCK - 1) {
-            cnt[EK_KEYS] = run;
-            if (one) *m_out = run;  // the kept rows
-        }
     }
     __syncthreads();
     if (lds) {
         // order the rows by id (within an id in atomics' order), then rank
         // each row in its id's group by the remaining ids
-        for (int p = t; p < rows; p += EK_BLOCK)
-            if (skey[p] != DROPPED) sord[atomicAdd(&cnt[skey[p]], 1)] = (unsigned short)p;
+        for (int p = t; p < rows; p += EK_BLOCK) sord[atomicAdd(&cnt[skey[p]], 1)] = (unsigned short)p;
         __syncthreads();
-        const int kept = one ? cnt[EK_KEYS] : rows;
-        for (int s = t; s < kept; s += EK_BLOCK) {
+        for (int s = t; s < rows; s += EK_BLOCK) {
             const int p = sord[s];
             uint4 me;  // Size bits or candidate index
             if constexpr (SLIM) {

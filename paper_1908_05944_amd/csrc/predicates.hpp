@@ -69,7 +69,6 @@ struct Counters {
 };
 
 __device__ __forceinline__ int sgn128(i128 v) { return (v > 0) - (v < 0); }
-__device__ __forceinline__ int sgn64(i64 v) { return (v > 0) - (v < 0); }
 
 // First non-zero partial in input-index order.
 template <int K>
@@ -208,8 +207,6 @@ __device__ __forceinline__ Tri tri_setup(int4 v0, int4 v1, int4 v2, const PredPa
     t.eP = 16.0 * ACX_U * ((double)t.den * pp.gmax + pp.bmax * Mabs);
     return t;
 }
-
-__device__ __forceinline__ bool tri_degenerate(const Tri &t) { return t.nx == 0 && t.ny == 0 && t.nz == 0; }
 
 // Candidate test of a triangle (Step 1): not collinear, and AC3 in Gram form,
 // beta^T adj(G) beta <= 4 det(G) (W0 + alpha) with G the Gram matrix of
