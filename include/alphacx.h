@@ -128,9 +128,9 @@ ac_status ac_alpha_complex_device(const double *d_xyz, const double *d_radii, in
  * Errors as ac_alpha_complex_device, plus AC_E_CAPACITY when the build needs
  * more than the fixed scratch (n above AC_NOALLOC_SCRATCH_MIB MiB / 128 B is
  * refused before any device work; measured on synthetic molecules at alpha = 0:
- * 400,000 balls with van der Waals radii fit, and 18,000 but not 24,000 with
- * solvent-accessible radii, whose candidates per ball are about ten times as
- * many) or when an output buffer is
+ * 576,000 balls with van der Waals radii fit, 429,000 where one of them is of
+ * 5 A, and 45,000 with solvent-accessible radii, whose candidates per ball are
+ * about ten times as many) or when an output buffer is
  * smaller than the result (nothing is written to the outputs then). The
  * pointers of d_simp / d_size are not written on any error. */
 #define AC_NOALLOC_SCRATCH_MIB 256
@@ -240,9 +240,11 @@ ac_status ac_alpha_complex_batch(const double *d_xyz, const double *d_radii, con
  * own. Arguments as ac_alpha_complex_batch; opt->profile must be 0;
  * 1 <= headroom <= 16. d_xyz / d_radii are recorded: every replay reads the
  * coordinates and radii found at those addresses when it runs, so they must
- * stay allocated until ac_plan_free. Synchronises `stream`. AC_E_CAPACITY if a
- * stage of the input needs the counted fill (rows longer than the single-pass
- * slots, e.g. solvent-accessible radii), which a recorded build does not have.
+ * stay allocated until ac_plan_free. Synchronises `stream`. AC_E_CAPACITY if
+ * the input needs the counted neighbour search (a ball with more than 16
+ * neighbours, or 32 where the largest grown radius is between 1.9 and 2.6 A or
+ * few balls are larger; e.g. solvent-accessible radii), which a recorded build
+ * does not have, or if a planned size passes 2^31.
  *
  * ac_plan_launch enqueues one replay on `stream` (may be captured or ordered
  * like any kernel launch). ac_plan_result then synchronises `stream` and

@@ -94,7 +94,7 @@ __device__ __forceinline__ void mail_post(Mail *mail, unsigned seq) {
 // Quantise: x -> rint(1000 x) (round half to even), W = R^2. Block b handles
 // the balls [tiles[b].x, tiles[b].y) (at most QTILE, all of one molecule; of a
 // single molecule of n balls the b-th QTILE, tiles = nullptr) and writes their
-// bounding box and flags; k_stats_reduce folds each molecule's tiles (of a
+// bounding box, flags and number of weights above wlarge; k_stats_reduce folds each molecule's tiles (of a
 // single tile there is nothing to fold: it is mailed from here). Block 0 also
 // clears the counters of the build, whose first kernel this is. Every load of a
 // thread is issued before the first conversion.
