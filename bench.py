@@ -30,7 +30,7 @@ KERNEL_OF_STAGE = {
     "neighbours_count": "k_neighbours<16, 1, true>",
     "neighbours_fill": "k_nbr_compact<16, 1, 256>",
     "triangles_count": "k_triangles<false, false>",
-    "tetrahedra_ac2": "k_tet_ac2<false, 64>",
+    "tetrahedra_ac2": "k_tet_ac2<false, 64, false>",
     "triangles_final": "k_tri_final<false>",
     "edges_final": "k_edge_final",
     "emit": "k_rows<false>",
