@@ -1002,7 +1002,8 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             !(t_arena && counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn, groups,
                                              tet_slab(SAS_SGC, gshift, groups, 0))))
             rule = SAS_SGC;
-        const int tet_cap = tet_slab(rule, gshift, groups, fixed ? fx->tet_most : 0);
+        const int cut = nbr_two_pass && !t_arena && rule > APEX_SGC ? tet_split(groups) : 0, slices = groups << cut;
+        const int tet_cap = tet_slab(rule, gshift, slices, fixed ? fx->tet_most : 0);
         const bool counted = fixed     ? fx->counted
                              : t_arena ? counts_triangles_in((long long)(t_arena->cap - t_arena->used), c0.P, n, c0.E, c0.Nn,
                                                              groups, tet_cap)
@@ -1106,9 +1107,11 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         int2 *apex = use_apex ? sc.get<int2>(T1) : nullptr;
         Tets tt{};
         tt.cap = tet_cap;
-        tt.num = sc.get<int>(groups);
+        tt.split = cut;
+        tt.num = sc.get<int>(slices);
         tt.kept = sc.get<int>(groups);
         tt.cand = sc.get<int>(groups);
+        tt.slice_cand = cut > 0 ? sc.get<int>(slices) : tt.cand;
         auto tet_room = [&](size_t rows) {
             if (rows < 1) rows = 1;
             tt.t = sc.get<int>(rows);
@@ -1116,10 +1119,10 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             tt.size = sc.get<double>(rows);
             if (n_alpha > 1) tt.face = sc.get<int4>(rows);
         };
-        tet_room((size_t)groups * tt.cap);
+        tet_room((size_t)slices * tt.cap);
         auto tetrahedra = [&]() {
             if (use_apex)
-                k_tetrahedra<true><<<groups, BLOCK, 0, s>>>(cd, pp, apex, tt, cnt, stop);
+                k_tetrahedra<true><<<slices, BLOCK, 0, s>>>(cd, pp, apex, tt, cnt, stop);
             else
                 k_tetrahedra<false><<<groups, BLOCK, 0, s>>>(cd, pp, apex, tt, cnt, stop);
             LAUNCH_CHECK();
@@ -1129,7 +1132,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             auto run = [&](auto sweep) {
                 constexpr bool SW = decltype(sweep)::value;
                 if (nbr_two_pass) {
-                    k_tet_test<<<dim3(groups, tests_split(groups)), BLOCK, 0, s>>>(cd, pp, tt, cnt);
+                    k_tet_test<<<dim3(slices, std::max(1, tests_split(groups) >> cut)), BLOCK, 0, s>>>(cd, pp, tt, cnt);
                     k_tet_ac2<SW, BLOCK, true><<<groups, BLOCK, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
                 } else if (few) {
                     k_tet_ac2<SW, WAVE><<<groups, WAVE, 0, s>>>(cd, pp, tgab, tri_min, tt, cnt, stop);
@@ -1144,18 +1147,18 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
         // counted ranges for every group's tetrahedra, after an overflow: both
         // kernels again (k_tet_ac2 did nothing the first time)
         auto tet_counted = [&]() {
-            const long long q = total_i64(tt.num, groups, s, sc);
+            const long long q = total_i64(tt.num, slices, s, sc);
             check_total(q, "candidate tetrahedra");
-            int *base = sc.get<int>((size_t)groups + 1);
-            scan_i32(tt.num, base, groups, s, sc);
+            int *base = sc.get<int>((size_t)slices + 1);
+            scan_i32(tt.num, base, slices, s, sc);
             tt.tet_base = base;
             tet_room((size_t)q);
             fill<int>(&cnt->overflow, 0, 1, s);
             if (fx && fx->learn) {
-                std::vector<int> num(groups);
-                read_back(num.data(), tt.num, (size_t)groups, s);
+                std::vector<int> num(slices);
+                read_back(num.data(), tt.num, (size_t)slices, s);
                 fx->tet_most = *std::max_element(num.begin(), num.end());
-                fx->tet_limit = INDEX_LAST / groups;
+                fx->tet_limit = INDEX_LAST / slices;
             }
             tetrahedra();
             tet_ac2();
@@ -1274,7 +1277,7 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
             // Outputs sized for every candidate where that is little memory: the
             // rows are then written before the counts are read, one wait in
             // all. Else the counts are read first.
-            const long long q_room = (long long)groups * tt.cap;
+            const long long q_room = (long long)slices * tt.cap;
             const bool roomy = fixed || !ext && E * 16LL + room * 20LL + q_room * 24LL <= OUT_ROOM;
             if (roomy) {
                 dev_rows(res, 1, fixed ? fx->E_cap : E);

@@ -106,6 +106,15 @@ inline int tests_split(int groups) {
     return k < 8 ? 8 : k;
 }
 
+// Slices (2^this) of a group's triangles whose tetrahedra are a block's work each,
+// where rows are long: up to 4,096 in all, and 32 a group. The least of some hundred
+// balls that all meet owns most of the tetrahedra.
+inline int tet_split(int groups) {
+    int split = 0;
+    while (split < 5 && ((long long)groups << (split + 1)) <= 4096) split++;
+    return split;
+}
+
 // Pairs of upper entries a build makes room for (PAIR_BYTES each); past it the
 // candidate triangles are counted first. A recorded build decides once, on the
 // pairs that its headroom asks for.
@@ -127,8 +136,9 @@ inline bool counts_triangles_in(long long left, long long pairs, long long n, lo
 // together; known after a counted search): over its edges a row has more than 16
 // entries after the first on average. Such builds take the kernels of large radii: apex
 // balls rule out most of their candidate tetrahedra too (300 balls with 160
-// neighbours each 4,630 us without, 1,000 with 100 2,659). Van der Waals radii at
-// alpha = 0 have 2.5 pairs an edge, radii grown to 2.6 A 8, solvent-accessible ones 14.
+// neighbours each 896 us with slices of their groups, 4,630 without either; 1,000 with
+// 100 893 and 2,659). Van der Waals radii at alpha = 0 have 2.5 pairs an edge, radii
+// grown to 2.6 A 8, solvent-accessible ones 14.
 inline bool long_rows(long long pairs, long long edges) { return pairs > 8 * edges; }
 
 // Buckets of the corners sorted by ball: 2^shift balls of n each, after `passes`

@@ -766,20 +766,25 @@ __global__ void __launch_bounds__(AC2_BLOCK, 8) k_ac2(Cands cd, PredParams pp, i
     ac2_part<SLOT, APEX>(cd, pp, xcd_block(), what, o, cnt, rows);
 }
 
-// Tetrahedra of a build: group g's are at [base, base + num[g]) with base =
-// tet_base[g], or g * cap where tet_base is null (groups * cap < 2^31: tet_slab). num: first the candidates
-// left to test (k_tetrahedra; exact even where the slab is too small, which sets
-// Counters::overflow), and kept[g] of them, in order, once k_tet_ac2 has run.
-// A tetrahedron is (t, f): its triangle (i, j, k) and its edge (i, l).
+// Tetrahedra of a build. A group's triangles are cut into 2^split slices (one, but
+// where few groups have long rows: tet_split); slice v, of group v >> split, has its
+// tetrahedra at [at(v), at(v) + num[v]) with at(v) = tet_base[v], or v * cap where
+// tet_base is null (slices * cap < 2^31: tet_slab). num: the candidates left to test
+// (k_tetrahedra; exact even where the slab is too small, which sets
+// Counters::overflow). Once k_tet_ac2 has run, kept[g] of them, in order, are at
+// [base(g), base(g) + kept[g]). A tetrahedron is (t, f): its triangle (i, j, k) and its
+// edge (i, l).
+constexpr int MOST_SLICES = 32;
 struct Tets {
     const int *tet_base;
-    int cap;
+    int cap, split;
     int *t, *t2;  // candidates: triangles (i, j, k) and (i, j, l); t2 becomes f
     double *size;
     int4 *face;   // the facets (sweep only)
-    int *num, *kept, *cand;  // cand: candidates in Sigma_ortho^3
-    __device__ __forceinline__ int base(int g) const { return tet_base ? tet_base[g] : g * cap; }
-    __device__ __forceinline__ int room(int g) const { return tet_base ? tet_base[g + 1] - tet_base[g] : cap; }
+    int *num, *kept, *cand, *slice_cand;  // cand: candidates in Sigma_ortho^3 (slice_cand is cand with one slice)
+    __device__ __forceinline__ int at(int v) const { return tet_base ? tet_base[v] : v * cap; }
+    __device__ __forceinline__ int room(int v) const { return tet_base ? tet_base[v + 1] - tet_base[v] : cap; }
+    __device__ __forceinline__ int base(int g) const { return at(g << split); }
 };
 
 // A group's candidate tetrahedra: all six edges in Sigma_ortho^1, not flat,
@@ -792,6 +797,9 @@ struct Tets {
 // at a time, 26 KB of LDS and five blocks a CU, 101 us at 3M atoms and alpha = 0
 // and 663 at 100,000 with solvent-accessible radii; with 768 triangles, 32 KB and
 // four blocks 116 and 779; with 256 113 and 710.
+// APEX: a block takes a slice of the group's triangles (Tets), with the later ones of
+// their edges as seconds (100 atoms grown by 4 A a build of 480 us, 1,184 with a block
+// a group; 289 balls that all meet 4,120, 13,240).
 constexpr int TRI_PT = 2, TRI_CH = TRI_PT * BLOCK, TRI_AHEAD = 64;
 struct TetLds {
     int4 sk[TRI_CH + TRI_AHEAD];
@@ -801,7 +809,7 @@ struct TetLds {
     int wtot[2][NWAVE], cands[NWAVE];
 };
 template <bool APEX>
-__device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredParams &pp, int g,
+__device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredParams &pp, int v,
                                                  const int2 *__restrict__ apex, const Tets &tt, Counters *cnt, TetLds &l) {
     auto &sk = l.sk;
     auto &se = l.se;
@@ -811,12 +819,16 @@ __device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredPara
     auto &soff = l.soff;
     auto &wtot = l.wtot;
     auto &cands = l.cands;
-    const int t0 = cd.tri_base[g], t1 = t0 + cd.tri_cnt[g];
+    // the slice's triangles [t0, te); their pairs' second ones reach to t1
+    const int split = APEX ? tt.split : 0, g = v >> split, part = v & ((1 << split) - 1);
+    const long long tris = cd.tri_cnt[g];
+    const int t1 = cd.tri_base[g] + (int)tris;
+    const int t0 = cd.tri_base[g] + (int)(tris * part >> split), te = cd.tri_base[g] + (int)(tris * (part + 1) >> split);
     const int w = wave_id(), lane = lane_id();
     const int4 *const atom = cd.atom;
-    const int qb = tt.base(g), qcap = tt.room(g);
+    const int qb = tt.at(v), qcap = tt.room(v);
     int num = 0, nc = 0;
-    for (int c0 = t0; c0 < t1; c0 += TRI_CH) {
+    for (int c0 = t0; c0 < te; c0 += TRI_CH) {
         const int held = min(TRI_CH + TRI_AHEAD, t1 - c0);
 #pragma unroll 1
         for (int x = threadIdx.x; x < held; x += BLOCK) {
@@ -830,7 +842,7 @@ __device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredPara
         for (int u = 0; u < TRI_PT; u++) {
             const int x = threadIdx.x * TRI_PT + u;
             later[u] = 0;
-            if (c0 + x < t1) {
+            if (c0 + x < te) {
                 const int e = se[x];
                 int y = x + 1;
 #pragma unroll 1
@@ -907,10 +919,10 @@ __device__ __forceinline__ void tetrahedra_group(const Cands &cd, const PredPara
     if (lane == 0) cands[w] = nc;
     __syncthreads();
     if (threadIdx.x == 0) {
-        tt.num[g] = num;
+        tt.num[v] = num;
         int s = 0;
         for (int k = 0; k < NWAVE; k++) s += cands[k];
-        tt.cand[g] = s;
+        tt.slice_cand[v] = s;
     }
 }
 template <bool APEX>
@@ -952,13 +964,13 @@ __global__ void __launch_bounds__(BLOCK, 4) k_tetrahedra_ac2(Cands cd, PredParam
 // solvent-accessible radii; the one-wave blocks fit all at once either way). Where
 // a group outgrew its slab nothing is tested: all is run again over counted ranges.
 // TESTED: after a counted neighbour search k_tet_test has done the walks, with several
-// blocks a group: a ball with thousands of neighbours has thousands of candidates,
-// each with the walk along its row (1,334 small balls around one, all grown: a build
+// blocks a group (or slice), and here a group's slices come together: a ball with
+// thousands of neighbours has thousands of candidates, each with the walk along its row (1,334 small balls around one, all grown: a build
 // 20.4 ms by the one block of its group, 6.7 as this).
 __global__ void __launch_bounds__(BLOCK, 8) k_tet_test(Cands cd, PredParams pp, Tets tt, Counters *cnt) {
-    const int g = xcd_block();
+    const int v = xcd_block();  // a slice
     if (cnt->overflow) return;
-    const int qb = tt.base(g), num = min(tt.num[g], tt.room(g));
+    const int qb = tt.at(v), num = min(tt.num[v], tt.room(v));
     for (int x = (int)blockIdx.y * BLOCK + (int)threadIdx.x; x < num; x += (int)gridDim.y * BLOCK) {
         const int t = tt.t[qb + x], t2 = tt.t2[qb + x];
         const int e = cd.tri_e[t];
@@ -978,16 +990,42 @@ __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, Pr
         if (threadIdx.x == 0) tt.kept[g] = 0;
         return;
     }
-    const int qb = tt.base(g), num = min(tt.num[g], tt.room(g));
+    const int split = TESTED ? tt.split : 0, v0 = g << split;
+    const int qb = tt.at(v0);
     const int w = wave_id(), lane = lane_id();
+    // the slices' candidates as one list (a loop over slices of a few candidates each
+    // would be a chain of 32 rounds)
+    __shared__ int first[TESTED ? MOST_SLICES + 1 : 1];
+    int num = 0;
+    if constexpr (TESTED) {
+        const int m = lane < 1 << split ? min(tt.num[v0 + lane], tt.room(v0 + lane)) : 0;
+        const int incl = wave_inclusive_scan(m);
+        if (threadIdx.x < MOST_SLICES) first[threadIdx.x + 1] = incl;
+        if (threadIdx.x == 0) first[0] = 0;
+        if (split > 0) {
+            const int c = wave_inclusive_scan(lane < 1 << split ? tt.slice_cand[v0 + lane] : 0);
+            if (threadIdx.x == WAVE - 1) tt.cand[g] = c;
+        }
+        __syncthreads();
+        num = first[1 << split];
+    } else {
+        num = min(tt.num[g], tt.room(g));
+    }
+    auto place = [&](int x) {
+        if (!TESTED) return qb + x;
+        int v = 0;
+        for (int step = 1 << split >> 1; step > 0; step >>= 1) v += first[v + step] <= x ? step : 0;
+        return tt.at(v0 + v) + x - first[v];
+    };
     int kept = 0;
     for (int c0 = 0, turn = 0; c0 < num; c0 += NT, turn ^= 1) {
         const int x = c0 + threadIdx.x;
         bool keep = false;
         int t = 0, t2 = 0, f2 = 0;
         if (x < num) {
-            t = tt.t[qb + x];
-            t2 = tt.t2[qb + x];
+            const int at = place(x);
+            t = tt.t[at];
+            t2 = tt.t2[at];
             if constexpr (TESTED) {
                 keep = t2 >= 0;
                 f2 = cd.tri_f[keep ? t2 : ~t2];
@@ -1004,9 +1042,9 @@ __global__ void __launch_bounds__(NT, NT == WAVE ? 4 : 8) k_tet_ac2(Cands cd, Pr
         __syncthreads();  // also: every candidate of the round is read before a kept one is written over it
         int at = kept + __popcll(mask & ((1ull << lane) - 1ull));
 #pragma unroll
-        for (int v = 0; v < NT / WAVE; v++) {
-            if (v < w) at += wtot[turn][v];
-            kept += wtot[turn][v];
+        for (int u = 0; u < NT / WAVE; u++) {
+            if (u < w) at += wtot[turn][u];
+            kept += wtot[turn][u];
         }
         if (keep) {
             tt.t[qb + at] = t;

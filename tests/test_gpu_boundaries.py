@@ -365,7 +365,7 @@ def test_few_large_balls(acx, n, share, radius, alpha, clump):
     _same_as(swept[1], single, "sweep")
 
 
-@pytest.mark.parametrize("n,rows", [(40, 30), (150, 60), (150, 140), (700, 40), (700, 100)])
+@pytest.mark.parametrize("n,rows", [(40, 30), (150, 60), (150, 140), (700, 40), (700, 100), (2100, 40)])
 @pytest.mark.parametrize("beside", [0, 9000])
 def test_small_balls_close_together(acx, n, rows, beside):
     """Long rows of small radii, alone and beside a molecule (whose short rows keep
@@ -388,3 +388,6 @@ def test_small_balls_close_together(acx, n, rows, beside):
         assert np.array_equal(simp[d].cpu().numpy(), single.simplices(d)), d
         assert np.array_equal(size[d].cpu().numpy(), single.sizes(d)), d
     _same_as(acx.ac_alpha_sweep_device(X, R, [0.0, -0.05])[0], single, "sweep")
+    # no apex balls: the candidate tetrahedra outgrow the slabs of a group's slices
+    _same_as(acx.ac_alpha_complex_device(X, R, 0.0, options={"force_exact": 1}), single, "exact")
+    _same_as(acx.ac_alpha_sweep_device(X, R, [0.0, -0.05], options={"force_exact": 1})[0], single, "exact sweep")

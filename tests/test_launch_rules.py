@@ -28,6 +28,7 @@ int group_shift(long long n, int slot, long long edges) { return acx::group_shif
 int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
 int later_counted(int later) { return acx::later_counted(later); }
 int long_rows(long long pairs, long long edges) { return acx::long_rows(pairs, edges); }
+int tet_split(int groups) { return acx::tet_split(groups); }
 int tests_split(int groups) { return acx::tests_split(groups); }
 int rows_split(int parts) { return acx::rows_split(parts); }
 }
@@ -156,3 +157,10 @@ def test_later_entries_of_the_edges_held(rules):
     for later in (0, 1, 64, 8192, 8193, (1 << 22) - 1, 1 << 22, 5000000, N_MAX):
         got = rules.later_counted(later)
         assert 512 * got <= INT_MAX and (got == later or later > got > 8192)
+
+
+def test_slices_of_a_group(rules):
+    for groups, want in ((1, 5), (128, 5), (129, 4), (1000, 2), (2048, 1), (2049, 0), (4097, 0), (N_MAX, 0)):
+        assert rules.tet_split(groups) == want, groups
+        for sgc in RADII:
+            assert rules.tet_slab(*_L(sgc), 0, groups << want, *_L(0)) * (groups << want) <= INT_MAX
