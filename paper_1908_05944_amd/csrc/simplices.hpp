@@ -198,6 +198,7 @@ enum { FACE_OUT = 0, FACE_GABRIEL = 1, FACE_ATTACHED = 2, FACE_UNSURE = 3 };
 struct RowLds {
     const float4 *row;  // filled up with zeros to a multiple of AC2_GROUP
     int len;
+    __device__ __forceinline__ unsigned places() const { return 255u; }  // mask of a place in the row
     __device__ __forceinline__ void begin() {}
     __device__ __forceinline__ void load(int k, float4 (&r)[AC2_GROUP]) {
 #pragma unroll
@@ -212,6 +213,7 @@ struct RowMem {
     int nx[AC2_GROUP];  // the next group's indices, one 16-byte load while this group is tested
     __device__ __forceinline__ RowMem(const Cands &cd, int i_)
         : atom(cd.atom), row(cd.nbr + cd.nbr_start[i_]), i(i_), len(cd.nbr_cnt[i_]) {}
+    __device__ __forceinline__ unsigned places() const { return len <= 256 ? 255u : 8191u; }
     __device__ __forceinline__ void begin() {
         me = atom[i];
         __builtin_memcpy(nx, row, sizeof nx);  // in bounds: NBR_PAD
@@ -339,9 +341,10 @@ __device__ __forceinline__ double tet_size_canon(int4 a, int4 b, int4 c, int4 d,
 // iff P_q - s D < 0, so on its side of the plane the ball of least P / D (where
 // D > 0; of the largest where D < 0) violates every tetrahedron of another
 // apex there. The two are found in float32, their places in the row in the low
-// 8 bits of the quotient (past 256 neighbours another one of the row): they are
-// only the first neighbours that a candidate is tested against, with the exact
-// predicate.
+// 8 bits of the quotient, 13 of rows past 256 neighbours (past 8,192 another one of
+// the row; with 8 bits for all, 2,598 grown balls around one took 38 ms, 20 in the
+// walks of the candidates that were left): they are only the first neighbours that
+// a candidate is tested against, with the exact predicate.
 template <bool APEX, class R>
 __device__ __forceinline__ int tri_ac2(const PredParams &pp, R row, const int4 &vi, const int4 &vj, const int4 &vk,
                                        double &size, int2 &apex) {
@@ -357,17 +360,18 @@ __device__ __forceinline__ int tri_ac2(const PredParams &pp, R row, const int4 &
     const Power32 pw = power32(den, Mx, My, Mz, ts.eP, pp);
     const float nx = (float)ts.nx, ny = (float)ts.ny, nz = (float)ts.nz;
     float lo = INFINITY, hi = -INFINITY;
+    const unsigned place = row.places();
     const int res = walk_row<false>(row, pw, 2, [&](const float4 &r, float P, int at) {
         if (APEX) {
             const float D = fmaf(nx, r.x, fmaf(ny, r.y, nz * r.z));
-            const float s = __uint_as_float((__float_as_uint(P * __builtin_amdgcn_rcpf(D)) & ~255u) | (at & 255u));
+            const float s = __uint_as_float((__float_as_uint(P * __builtin_amdgcn_rcpf(D)) & ~place) | (at & place));
             const bool other = fabsf(P) > pw.e;
             lo = fminf(lo, other & (D > 0.0f) ? s : INFINITY);
             hi = fmaxf(hi, other & (D < 0.0f) ? s : -INFINITY);
         }
     });
-    if (lo < INFINITY) apex.x = __float_as_uint(lo) & 255u;
-    if (hi > -INFINITY) apex.y = __float_as_uint(hi) & 255u;
+    if (lo < INFINITY) apex.x = __float_as_uint(lo) & place;
+    if (hi > -INFINITY) apex.y = __float_as_uint(hi) & place;
     return res;
 }
 __device__ __forceinline__ bool tri_violated(const Cands &cd, const PredParams &pp, int i, int j, int k, Counters *cnt) {
