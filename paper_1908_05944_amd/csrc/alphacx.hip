@@ -868,15 +868,16 @@ static ac_status run_pipeline(const double *d_xyz, const double *d_r, int64_t n6
                                                  (int)aq, perm, cnt);
             LAUNCH_CHECK();
         } else {
-            // bucket: at most BIN_CELLS cells, and a bucket of full cells (2.5
-            // times the mean: molecules fill a third to a half of their box)
-            // within BIN_ROWS balls; as few radix passes as that allows, and of
-            // the shifts these passes reach the least that leaves a bucket 128
-            // balls on average
+            // bucket: at most BIN_CELLS cells, and a bucket of full cells within
+            // BIN_ROWS balls; as few radix passes as that allows, and of the shifts
+            // these passes reach the least that leaves a bucket 128 balls on average
+            int side = 0;
+            for (const Grid &g : fixed ? fx->grids : grids) side = std::max(side, g.s);
+            const double full = full_cell(n, ncell, side);
             const int bits = bits_for(ncell);
             int most = 0;
             while (most < BIN_SHIFT && most < bits - 1 &&
-                   (double)(2LL << most) * 2.5 * (double)n <= (double)BIN_ROWS * (double)ncell)
+                   (double)(2LL << most) * full <= (double)BIN_ROWS)
                 most++;
             int shift = std::max(0, bits - RS_BITS * ((bits - most + RS_BITS - 1) / RS_BITS));
             while (shift < most && (double)(1LL << shift) * (double)n < 128.0 * (double)ncell) shift++;

@@ -28,6 +28,7 @@ int group_shift(long long n, int slot, long long edges) { return acx::group_shif
 int kernel_radius(long long sgc, long long large, long long n) { return (int)acx::kernel_radius(sgc, large, n); }
 int later_counted(int later) { return acx::later_counted(later); }
 int long_rows(long long pairs, long long edges) { return acx::long_rows(pairs, edges); }
+double full_cell(long long n, long long ncell, int side) { return acx::full_cell(n, ncell, side); }
 int tet_split(int groups) { return acx::tet_split(groups); }
 int tests_split(int groups) { return acx::tests_split(groups); }
 int rows_split(int parts) { return acx::rows_split(parts); }
@@ -164,3 +165,12 @@ def test_slices_of_a_group(rules):
         assert rules.tet_split(groups) == want, groups
         for sgc in RADII:
             assert rules.tet_slab(*_L(sgc), 0, groups << want, *_L(0)) * (groups << want) <= INT_MAX
+
+
+def test_full_cells(rules):
+    """2.5 times the mean in a molecule's own box; the density where most cells are empty."""
+    rules.full_cell.restype = ctypes.c_double
+    assert rules.full_cell(*_L(3000000, 3800000), 1800) == pytest.approx(2.5 * 3 / 3.8)
+    assert rules.full_cell(*_L(159284, 262144), 9000) == pytest.approx(0.06 * 729)
+    for side in (1, 700, 1800, 9000, 60000, 1 << 20):
+        assert rules.full_cell(*_L(1, 1 << 30), side) > 0
